@@ -160,7 +160,7 @@ constexpr int kMaxL2 = 16;         // level 2 (target <= 10)
 //   w = D^-1 t per child; y = forward substitution, z = backward substitution
 //   out = z (mode 0) or out = u + z (mode 1)
 // One thread per row (child, slot) with the children in hyperplane order, so
-// the rows of plane s are threads [off[s] LP, off[s+1] LP).  Each thread keeps
+// the rows of plane s are threads [off[s] W, off[s+1] W).  Each thread keeps
 // the rows of its lower and upper couplings G in registers; only y lives in
 // LDS.  A plane step is one LDS read per coupling entry, the products, a store
 // and a barrier.  Missing neighbours read the thread's own child with weight 0.
@@ -172,16 +172,20 @@ __global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, co
                                                       int npar) {
     if (check_done && sc->done) return;
     __shared__ T sY[kMaxChildren * LP];
+    // row width: LP, except in the widest instantiation, which serves every
+    // width above kNarrow (entries b >= W are neither read nor written)
+    constexpr bool RT = LP == kMaxLc;
+    const int W = RT ? g.L : LP;
     const int agg = g.agg, nc = agg * agg * agg, sh = log2_agg(agg);
     const int nplanes = 3 * (agg - 1) + 1;
     // npar parents per workgroup (several when a parent has few rows, so
-    // that the wavefronts are full), each with its own nc * LP rows of sY
-    const int per = nc * LP;
+    // that the wavefronts are full), each with its own nc * W rows of sY
+    const int per = nc * W;
     const int t = threadIdx.x, qp = t / per, tt = t - qp * per;
     const int E = blockIdx.x * npar + qp;
     const bool row_ok = qp < npar && E < g.M;
     const int base = row_ok ? qp * per : 0;
-    const int k = row_ok ? tt / LP : 0, a = tt % LP;
+    const int k = row_ok ? tt / W : 0, a = tt % W;
     const int p = agg == 4 ? kCP.pos4[k] : kCP.pos2[k];
     const int q[3] = {p & (agg - 1), (p >> sh) & (agg - 1), p >> (2 * sh)};
     const int plane = q[0] + q[1] + q[2];
@@ -195,20 +199,21 @@ __global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, co
         const bool in = (d & 1) ? (q[ax] < agg - 1) : (q[ax] > 0);
         const int step = 1 << (sh * ax);
         const int pn = in ? ((d & 1) ? p + step : p - step) : p;
-        nb[d] = base + (agg == 4 ? kCP.rank4[pn] : kCP.rank2[pn]) * LP;
+        nb[d] = base + (agg == 4 ? kCP.rank4[pn] : kCP.rank2[pn]) * W;
         wgt[d] = in ? T(1) : T(0);
     }
     // slots beyond the child's kept count are zero rows of every block: their
     // threads load nothing and carry zeros
     const bool live = row_ok && (g.nkeep == nullptr || a < g.nkeep[c]);
     // right-hand side t = r (- A_l u): all loads of the row first
-    const size_t row = (size_t)c * LP + a;
+    const size_t row = (size_t)c * W + a;
     T tv = live ? r[row] : T(0);
     if (mode && live) {
         const int cx = c % g.mx, cy = (c / g.mx) % g.my, cz = c / (g.mx * g.my);
         T acc = T(0);
 #pragma unroll
-        for (int b = 0; b < LP; ++b) acc += Ad[row * LP + b] * u[(size_t)c * LP + b];
+        for (int b = 0; b < LP; ++b)
+            if (!RT || b < W) acc += Ad[row * W + b] * u[(size_t)c * W + b];
         // one direction at a time keeps the loads in flight to 4 LP values
 #pragma unroll 1
         for (int ax = 0; ax < 3; ++ax) {
@@ -222,8 +227,9 @@ __global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, co
 #pragma unroll
             for (int b = 0; b < LP; ++b) {
                 // A(c, c+e) = Aoff[c][ax]; A(c, c-e) = Aoff[c-e][ax]^T
-                sp += Aoff[(((size_t)c * 3 + ax) * LP + a) * LP + b] * u[(size_t)cp * LP + b];
-                sm += Aoff[(((size_t)cm * 3 + ax) * LP + b) * LP + a] * u[(size_t)cm * LP + b];
+                if (RT && b >= W) continue;
+                sp += Aoff[(((size_t)c * 3 + ax) * W + a) * W + b] * u[(size_t)cp * W + b];
+                sm += Aoff[(((size_t)cm * 3 + ax) * W + b) * W + a] * u[(size_t)cm * W + b];
             }
             acc += wp * sp + wm * sm;
         }
@@ -247,25 +253,25 @@ __global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, co
         const bool in = live && (A2 || lo);
         const int d = (A2 && !lo) ? 2 * ax + 1 : 2 * ax;
 #pragma unroll
-        for (int b = 0; b < LP; ++b) gl[ax][b] = in ? G[(((size_t)c * 6 + d) * LP + a) * LP + b] : T(0);
+        for (int b = 0; b < LP; ++b) gl[ax][b] = in && (!RT || b < W) ? G[(((size_t)c * 6 + d) * W + a) * W + b] : T(0);
     }
 #pragma unroll
-    for (int b = 0; b < LP; ++b) dv[b] = live ? Dinv[row * LP + b] : T(0);
+    for (int b = 0; b < LP; ++b) dv[b] = live && (!RT || b < W) ? Dinv[row * W + b] : T(0);
     if (kUpperEarly) {
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
             const bool in = live && wgt[2 * ax + 1] != T(0);
 #pragma unroll
             for (int b = 0; b < LP; ++b)
-                gu[ax][b] = in ? G[(((size_t)c * 6 + 2 * ax + 1) * LP + a) * LP + b] : T(0);
+                gu[ax][b] = in && (!RT || b < W) ? G[(((size_t)c * 6 + 2 * ax + 1) * W + a) * W + b] : T(0);
         }
     }
     __syncthreads();
     T w = T(0);
     {
-        const T* ty = sY + base + k * LP;
+        const T* ty = sY + base + k * W;
 #pragma unroll
-        for (int b = 0; b < LP; ++b) w += dv[b] * ty[b];
+        for (int b = 0; b < LP; ++b) w += (!RT || b < W) ? dv[b] * ty[b] : T(0);
     }
     __syncthreads();
     // forward: y = w - sum_lower G y
@@ -275,6 +281,7 @@ __global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, co
             T s0 = T(0), s1 = T(0), s2 = T(0);
 #pragma unroll
             for (int b = 0; b < LP; ++b) {
+                if (RT && b >= W) continue;
                 s0 += gl[0][b] * sY[nb[0] + b];
                 s1 += gl[1][b] * sY[nb[2] + b];
                 s2 += gl[2][b] * sY[nb[4] + b];
@@ -296,7 +303,7 @@ __global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, co
             const bool in = live && wgt[2 * ax + 1] != T(0);
 #pragma unroll
             for (int b = 0; b < LP; ++b)
-                gu[ax][b] = in ? G[(((size_t)c * 6 + 2 * ax + 1) * LP + a) * LP + b] : T(0);
+                gu[ax][b] = in && (!RT || b < W) ? G[(((size_t)c * 6 + 2 * ax + 1) * W + a) * W + b] : T(0);
         }
     }
     T z = T(0);
@@ -306,6 +313,7 @@ __global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, co
             if constexpr (A2) {
 #pragma unroll
                 for (int b = 0; b < LP; ++b) {
+                    if (RT && b >= W) continue;
                     s0 += gl[0][b] * sY[nb[1] + b];
                     s1 += gl[1][b] * sY[nb[3] + b];
                     s2 += gl[2][b] * sY[nb[5] + b];
@@ -316,6 +324,7 @@ __global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, co
             } else {
 #pragma unroll
                 for (int b = 0; b < LP; ++b) {
+                    if (RT && b >= W) continue;
                     s0 += gu[0][b] * sY[nb[1] + b];
                     s1 += gu[1][b] * sY[nb[3] + b];
                     s2 += gu[2][b] * sY[nb[5] + b];
