@@ -15,252 +15,9 @@
 // (twice) and performs Rayleigh-Ritz with a one-wavefront parallel cyclic
 // Jacobi eigensolver.  Only operator applications and M x M reductions are
 // needed, so the whole solve stays in registers and LDS.
-#include "common.hpp"
+#include "eig_common.hpp"
 
 namespace specmg {
-
-constexpr int kDeg = 20;          // Chebyshev degree per cycle of a relaxed, warm-started solve
-constexpr int kDegExact = 40;     // ... of an exact solve (fewer cycles, so fewer orthonormalisations
-                                  //     and Rayleigh-Ritz steps per filtered vector)
-constexpr int kMaxCycles = 300;
-constexpr int kMaxEigWaves = 12;   // workgroups of at most 768 threads
-constexpr int kWarmCycles = 4;     // cycles a learned start gets to reach the relaxed residual
-
-
-__device__ __forceinline__ double hash_noise(unsigned a, unsigned b, unsigned c) {
-    unsigned h = a * 0x9E3779B1u ^ (b + 0x7F4A7C15u) * 0x85EBCA77u ^ (c + 0x165667B1u) * 0xC2B2AE3Du;
-    h ^= h >> 15;
-    h *= 0x2C1B3C6Du;
-    h ^= h >> 12;
-    h *= 0x297A2D39u;
-    h ^= h >> 15;
-    return (double)(h & 0xFFFFFF) / 8388608.0 - 1.0;   // [-1, 1)
-}
-
-// low-frequency cosine modes (p, q, r) by increasing p^2+q^2+r^2
-__constant__ unsigned char kModes[16][3] = {
-    {0, 0, 0}, {1, 0, 0}, {0, 1, 0}, {0, 0, 1}, {1, 1, 0}, {1, 0, 1}, {0, 1, 1}, {1, 1, 1},
-    {2, 0, 0}, {0, 2, 0}, {0, 0, 2}, {2, 1, 0}, {1, 2, 0}, {2, 0, 1}, {0, 2, 1}, {1, 0, 2}};
-
-template <typename T>
-__device__ __forceinline__ T harm_e(T a, T b) {
-    const T s = a + b;
-    return s > T(0) ? (T(2) * a * b) / s : T(0);
-}
-
-// ---------------------------------------------------------------------------
-// small dense helpers on LDS, run by one thread or one wavefront
-
-// Circle-method round robin on M players (M even): in round r player M-1
-// meets player r and every other pair (i, j) has i + j = 2r modulo M-1.
-template <int M>
-__device__ __forceinline__ int jac_partner(int i, int r) {
-    constexpr int K = M - 1;
-    if (i == K) return r;
-    if (i == r) return K;
-    int j = 2 * r - i;
-    j = j < 0 ? j + K : (j >= K ? j - K : j);
-    return j;
-}
-
-// Rotation (c, s) that annihilates H[p][q] (p < q): the rotated rows are
-// p' = c p - s q and q' = s p + c q.
-__device__ __forceinline__ void jac_rot(const double* H, int M, int p, int q, double& c, double& s) {
-    const double hpp = H[p * M + p], hqq = H[q * M + q], hpq = H[p * M + q];
-    c = 1.0;
-    s = 0.0;
-    if (hpq != 0.0) {
-        const double tt = (hqq - hpp) / (2.0 * hpq);
-        const double t = (tt >= 0.0 ? 1.0 : -1.0) / (fabs(tt) + sqrt(tt * tt + 1.0));
-        c = 1.0 / sqrt(t * t + 1.0);
-        s = t * c;
-    }
-}
-
-// Symmetric eigendecomposition H = Q diag(th) Q^T, eigenvalues ascending,
-// by parallel cyclic Jacobi in wavefront 0: each round applies M/2 disjoint
-// rotations at once; lanes 0..M-1 derive the round's rotations (scr holds
-// the cosines and sines), then every lane applies them to its own elements:
-// a round is one rotation phase, one read phase and one write phase.  Stops
-// when the largest off-diagonal entry is below 1e-15 times the largest
-// diagonal entry.  H (M*M) is destroyed; Q (M*M)
-// receives the eigenvectors as columns.  Must be called by all threads.
-template <int M>
-__device__ __forceinline__ void jacobi_eig(double* H, double* Q, double* th, double* scr, int* iscr) {
-    static_assert(M % 2 == 0 && M <= 26, "Jacobi block size");
-    constexpr int MM = M * M;
-    constexpr int PER = (MM + 63) / 64;
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        int ei[PER], ej[PER];
-        bool ev[PER];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int t = lane + 64 * u;
-            ev[u] = t < MM;
-            ei[u] = ev[u] ? t / M : 0;
-            ej[u] = ev[u] ? t % M : 0;
-            if (ev[u]) Q[t] = (ei[u] == ej[u]) ? 1.0 : 0.0;
-        }
-        wave_sync();
-#pragma unroll 1
-        for (int sweep = 0; sweep < 30; ++sweep) {
-            double off = 0.0, dg = 0.0;
-#pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const double h = ev[u] ? fabs(H[ei[u] * M + ej[u]]) : 0.0;
-                if (ei[u] != ej[u]) off = fmax(off, h);
-                else dg = fmax(dg, h);
-            }
-            off = wave_max(off);
-            dg = wave_max(dg);
-            if (off <= 1e-15 * dg || off == 0.0) break;
-#pragma unroll 1
-            for (int r = 0; r < M - 1; ++r) {
-                // the round's M/2 rotations, once each: lane i < M stores the
-                // rotation of its pair (both members hold the same one)
-                if (lane < M) {
-                    const int pl = jac_partner<M>(lane, r);
-                    double cl, sl;
-                    jac_rot(H, M, lane < pl ? lane : pl, lane < pl ? pl : lane, cl, sl);
-                    scr[lane] = cl;
-                    scr[M + lane] = sl;
-                }
-                wave_sync();
-                double nh[PER], nq[PER];
-#pragma unroll
-                for (int u = 0; u < PER; ++u) {
-                    const int i = ei[u], j = ej[u];
-                    const int pi = jac_partner<M>(i, r), pj = jac_partner<M>(j, r);
-                    const int ai = i < pi ? i : pi, bi = i < pi ? pi : i;
-                    const int aj = j < pj ? j : pj, bj = j < pj ? pj : j;
-                    const double ci = scr[i], si = scr[M + i], cj = scr[j], sj = scr[M + j];
-                    const double wra = (i == ai) ? ci : si, wrb = (i == ai) ? -si : ci;
-                    const double wca = (j == aj) ? cj : sj, wcb = (j == aj) ? -sj : cj;
-                    nh[u] = wra * (wca * H[ai * M + aj] + wcb * H[ai * M + bj]) +
-                            wrb * (wca * H[bi * M + aj] + wcb * H[bi * M + bj]);
-                    // the annihilated entry of a rotated pair is zero exactly
-                    if (ai == aj && bi == bj && i != j) nh[u] = 0.0;
-                    nq[u] = wca * Q[i * M + aj] + wcb * Q[i * M + bj];
-                }
-                wave_sync();
-#pragma unroll
-                for (int u = 0; u < PER; ++u) {
-                    if (ev[u]) {
-                        H[ei[u] * M + ej[u]] = nh[u];
-                        Q[ei[u] * M + ej[u]] = nq[u];
-                    }
-                }
-                wave_sync();
-            }
-        }
-        // ascending order: lane k < M finds the rank of H[k][k]
-        if (lane < M) {
-            const double hk = H[lane * M + lane];
-            int rank = 0;
-#pragma unroll
-            for (int l = 0; l < M; ++l) {
-                const double hl = H[l * M + l];
-                rank += (hl < hk || (hl == hk && l < lane)) ? 1 : 0;
-            }
-            iscr[rank] = lane;
-            th[rank] = hk;
-        }
-        wave_sync();
-        double nq[PER];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) nq[u] = ev[u] ? Q[ei[u] * M + iscr[ej[u]]] : 0.0;
-        wave_sync();
-#pragma unroll
-        for (int u = 0; u < PER; ++u)
-            if (ev[u]) Q[ei[u] * M + ej[u]] = nq[u];
-    }
-    __syncthreads();
-}
-
-// Cholesky G = R^T R of the SPD M x M matrix G (R upper triangular, stored
-// in Rm; dinv[j] = 1 / R[j][j]) by wavefront 0, one column per step with a
-// lane-parallel trailing update.  G is left intact.  Returns false (in every
-// thread) when G is not numerically positive definite.
-template <int M>
-__device__ __forceinline__ bool chol_wave(const double* G, double* Rm, double* dinv, int* flag) {
-    constexpr int MM = M * M;
-    constexpr int PER = (MM + 63) / 64;
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        int ei[PER], ej[PER];
-        bool ev[PER];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int t = lane + 64 * u;
-            ev[u] = t < MM;
-            ei[u] = ev[u] ? t / M : 0;
-            ej[u] = ev[u] ? t % M : 0;
-            if (ev[u]) Rm[t] = ei[u] <= ej[u] ? G[t] : 0.0;
-        }
-        wave_sync();
-        int ok = 1;
-#pragma unroll 1
-        for (int j = 0; j < M; ++j) {
-            double d = Rm[j * M + j];
-            if (!(d > 0.0)) {
-                ok = 0;
-                d = 1.0;
-            }
-            const double inv_d = 1.0 / d;
-            // trailing update of the upper triangle with the unscaled row j
-#pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const int i = ei[u], l = ej[u];
-                if (ev[u] && i > j && l >= i) Rm[i * M + l] -= Rm[j * M + i] * Rm[j * M + l] * inv_d;
-            }
-            wave_sync();
-            const double rjj = sqrt(d), ir = 1.0 / rjj;
-            if (lane > j && lane < M) Rm[j * M + lane] *= ir;
-            if (lane == j) {
-                Rm[j * M + j] = rjj;
-                dinv[j] = ir;
-            }
-            wave_sync();
-        }
-        if (lane == 0) *flag = ok;
-    }
-    __syncthreads();
-    const bool ok = *flag != 0;
-    __syncthreads();
-    return ok;
-}
-
-// Cluster rule on ascending values th[0..n-1] (n >= target+4 or all values):
-// keep `target`, grow to the end of a cluster of equal values up to
-// target+3, or shrink before the cluster when it runs past that cap.
-__device__ int cluster_cut_dev(const double* th, int n, int target, double rtol, double thr) {
-    if (thr > 0.0) {
-        // threshold rule (strategy 2 of Section 5): the eigenvalues below
-        // thr, at least one and at most target, then the cluster rule
-        int below = 0;
-        for (int j = 0; j < n; ++j) below += th[j] < thr ? 1 : 0;
-        target = below < 1 ? 1 : (below < target ? below : target);
-    }
-    if (target >= n) return n;
-    auto same = [&](int k) { return th[k] - th[k - 1] <= rtol * fmax(fabs(th[k]), 1e-12); };
-    int k = target;
-    const int cap = target + 3 < n ? target + 3 : n;
-    while (k < cap && same(k)) ++k;
-    if (k == cap && k < n && same(k)) {
-        k = target;
-        while (k > 1 && same(k)) --k;
-    }
-    return k;
-}
-
-// Empty asm statements that take v as an operand: the arithmetic producing v
-// runs before them, and no memory access moves across pin().  Used after
-// every few columns of an operator apply, so that the compiler cannot hoist
-// all of its LDS loads ahead of the arithmetic (a register per loaded value,
-// which halves the waves per SIMD).
-__device__ __forceinline__ void pin(double& v) { asm volatile("" : "+v"(v)::"memory"); }
-__device__ __forceinline__ void pin_value(double& v) { asm volatile("" : "+v"(v)); }
 
 // ---------------------------------------------------------------------------
 // Block storage: the current block lives in LDS as Y[j * ld + row] (ld odd,
@@ -390,25 +147,6 @@ __device__ __forceinline__ void load_block(const double* Y, int ld, int n, doubl
     }
 }
 
-// Inverse of the upper triangular factor (Rm, dinv from chol_wave) into
-// Ri, by wavefront 0: rows from the bottom up, lane l owning column l.
-template <int M>
-__device__ __forceinline__ void trtri_wave(const double* Rm, const double* dinv, double* Ri) {
-    if (threadIdx.x < 64) {
-        const int l = threadIdx.x;
-#pragma unroll 1
-        for (int i = M - 1; i >= 0; --i) {
-            if (l < M) {
-                double v = (l == i) ? 1.0 : 0.0;
-                for (int k = i + 1; k <= l; ++k) v -= Rm[i * M + k] * Ri[k * M + l];
-                Ri[i * M + l] = l >= i ? v * dinv[i] : 0.0;
-            }
-            wave_sync();
-        }
-    }
-    __syncthreads();
-}
-
 // Orthonormalise the LDS block (Cholesky-QR, twice): Y <- Y R^-1 with
 // Y^T Y = R^T R.
 template <int M, int R>
@@ -438,29 +176,6 @@ __device__ __forceinline__ void orthonormalise(double* Y, int ld, int n, EigShar
 
 // ---------------------------------------------------------------------------
 // operators: out = A * (block in LDS), rows of this thread
-
-// Level 2: A~ = S^-1/2 A_K S^-1/2 on one 8^3 element, thread = cell.
-struct Op2 {
-    double diag;
-    double off[6];
-    int nb[6];
-    template <int M>
-    __device__ __forceinline__ void apply(const double* Y, int ld, double (&out)[1][M]) const {
-        const int c = threadIdx.x;
-#pragma unroll
-        for (int j = 0; j < M; ++j) {
-            double s = diag * Y[j * ld + c];
-#pragma unroll
-            for (int d = 0; d < 6; ++d) s -= off[d] * Y[j * ld + nb[d]];
-            out[0][j] = s;
-            if (j % 3 == 2) {
-                pin_value(out[0][j - 2]);
-                pin_value(out[0][j - 1]);
-                pin(out[0][j]);
-            }
-        }
-    }
-};
 
 // Levels >= 3: block 7-point H_E on the agg^3 children of E, lp slots per
 // child (the padded width of the lower level, at most kMaxLP); row =
@@ -639,17 +354,7 @@ __device__ int chefsi(const OP& op, double* Y, int ld, int n, double (&X)[R][M],
                 for (int j = 0; j < M; ++j) Rs[r][j] = AX[r][j] - sh.th[j] * X[r][j];
             colnorm2<M, R>(Rs, sh.nrm, sh.red);
         }
-        const int nk = cluster_cut_dev(sh.th, M, target, crtol, thr);
-        bool ok = true;
-        for (int j = 0; j < need; ++j) {
-            const double rj = sqrt(sh.nrm[j]);
-            // under the threshold rule the 5 % separation counts only after
-            // a filter cycle: an eigenvalue below the threshold that the start
-            // block misses has not been amplified yet and would change the count
-            const bool sep = (thr <= 0.0 || cyc > 0) && j >= nk && nk > 0 &&
-                             sh.th[j] - sh.th[nk - 1] > 0.05 * fabs(sh.th[j]);
-            ok = ok && (rj <= (j < nk ? tol : sqrt(tol)) * bnd || sep);
-        }
+        const bool ok = chefsi_done(sh.th, sh.nrm, M, need, tol, bnd, target, crtol, thr, cyc);
         if (ok) return cyc;
         if (cyc >= max_cycles) return -1;
         const double a = fmin(sh.th[M - 1], 0.5 * bnd);
@@ -692,125 +397,6 @@ __device__ void column_sums(const double (&A)[R][M], double* dst, int cnt, int n
         dst[threadIdx.x] = ((int)threadIdx.x < nk) ? s : 0.0;
     }
     __syncthreads();
-}
-
-// ---------------------------------------------------------------------------
-// level 2 kernel: one 512-thread workgroup per 8^3 element
-// Learned start (warm != null): the first kw columns of the start block are
-// the predicted cell vectors warm[blockIdx.x][0..kw-1][512] (row pitch kp),
-// the rest the next cosine modes.  From that block the eigensolve runs to
-// the relaxed residual ws_tol (times the spectral bound) within
-// kWarmCycles cycles; an element that does not get there falls back to the
-// exact solve (tolerance tol) from the cold start, and ws_fb[e] = 1.
-// status[e] counts the cycles of both attempts.
-// At most 128 VGPRs (four waves per SIMD): with about 68 KB of LDS per
-// workgroup, two elements then share a CU, and one element's serial phases
-// (Jacobi, Cholesky) overlap the other's filter.
-template <int M>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_eig2(
-    FineGeom g, const double* __restrict__ kt, int target, int L, double tol, double crtol,
-    double* __restrict__ phi, double* __restrict__ lam, int* __restrict__ nkeep, double* __restrict__ Aint,
-    double* __restrict__ zc, int* __restrict__ status, int e0, const float* __restrict__ warm, int kp, int kw,
-    double ws_tol, int* __restrict__ ws_fb, double thr) {
-    constexpr int LD = 513;
-    __shared__ double sY[M * LD];
-    __shared__ EigShared<M> sh;
-    const int e = e0 + blockIdx.x;
-    const int ex = e % g.mx, ey = (e / g.mx) % g.my, ez = e / (g.mx * g.my);
-    const int c = threadIdx.x;
-    const int i = c & 7, j = (c >> 3) & 7, k = c >> 6;
-    auto gid = [&](int x, int y, int z) { return eidx(g, x, y, z); };
-    // kappa~ per face direction: one array (isotropic) or three (orthotropic)
-    const size_t N = g.ortho ? g.ncell() : 0;
-    const size_t gc = gid(ex * 8 + i, ey * 8 + j, ez * 8 + k);
-    const double kc[3] = {kt[gc], kt[N + gc], kt[2 * N + gc]};
-    // weight tr K~: kappa~ (1 + cy + cz) with the y and z faces carrying cy
-    // and cz, or the sum of the three components
-    const double wsum = 1.0 + g.cy + g.cz;
-    auto weight = [&](size_t q) { return g.ortho ? kt[q] + kt[N + q] + kt[2 * N + q] : wsum * kt[q]; };
-    const double S = weight(gc);
-    const double sq = sqrt(S);
-    Op2 op;
-    double diag = 0.0, rowsum = 0.0;
-#pragma unroll
-    for (int d = 0; d < 6; ++d) {
-        const int ii = i + (d == 0 ? -1 : (d == 1 ? 1 : 0));
-        const int jj = j + (d == 2 ? -1 : (d == 3 ? 1 : 0));
-        const int kk = k + (d == 4 ? -1 : (d == 5 ? 1 : 0));
-        op.off[d] = 0.0;
-        op.nb[d] = c;
-        if (ii >= 0 && ii < 8 && jj >= 0 && jj < 8 && kk >= 0 && kk < 8) {
-            const int ax = d >> 1;
-            const size_t gn = gid(ex * 8 + ii, ey * 8 + jj, ez * 8 + kk);
-            const double T = harm_e(kc[ax], kt[ax * N + gn]) * (ax == 0 ? 1.0 : (ax == 1 ? g.cy : g.cz));
-            diag += T;
-            op.off[d] = T / (sq * sqrt(weight(gn)));
-            op.nb[d] = ii + 8 * (jj + 8 * kk);
-            rowsum += op.off[d];
-        }
-    }
-    op.diag = diag / S;
-    const double bnd = block_max(op.diag + rowsum, sh.misc);
-
-    double X[1][M], AX[1][M];
-    const double pi8 = 3.14159265358979323846 / 8.0;
-    const int nw = warm ? kw : 0;
-#pragma unroll
-    for (int jj = 0; jj < M; ++jj) {
-        const double md = cos(pi8 * kModes[jj][0] * (i + 0.5)) * cos(pi8 * kModes[jj][1] * (j + 0.5)) *
-                          cos(pi8 * kModes[jj][2] * (k + 0.5));
-        const double cold = sq * (md + 0.05 * hash_noise((unsigned)e, (unsigned)jj, (unsigned)c));
-        X[0][jj] = jj < nw ? sq * (double)warm[((size_t)blockIdx.x * kp + jj) * 512 + c] : cold;
-    }
-    const int need = (target + 4 < M - 2) ? target + 4 : M - 2;
-    int cyc = -1, spent = 0;
-    if (warm) {
-        cyc = chefsi<M, 1>(op, sY, LD, 512, X, AX, bnd, need, ws_tol, target, crtol, thr, sh, kWarmCycles, kDeg);
-        const bool fb = cyc < 0;
-        if (fb) {
-            spent = kWarmCycles + 1;
-#pragma unroll
-            for (int jj = 0; jj < M; ++jj) {
-                const double md = cos(pi8 * kModes[jj][0] * (i + 0.5)) * cos(pi8 * kModes[jj][1] * (j + 0.5)) *
-                                  cos(pi8 * kModes[jj][2] * (k + 0.5));
-                X[0][jj] = sq * (md + 0.05 * hash_noise((unsigned)e, (unsigned)jj, (unsigned)c));
-            }
-        }
-        if (c == 0) ws_fb[e] = fb ? 1 : 0;
-        __syncthreads();
-    }
-    if (cyc < 0) {
-        cyc = chefsi<M, 1>(op, sY, LD, 512, X, AX, bnd, need, tol, target, crtol, thr, sh);
-        if (cyc >= 0) cyc += spent;
-    }
-
-    if (threadIdx.x == 0) {
-        const int nk = cluster_cut_dev(sh.th, M, target, crtol, thr);
-        sh.flag = nk;
-        nkeep[e] = nk;
-        status[e] = cyc;
-        for (int a = 0; a < L; ++a) lam[(size_t)e * L + a] = sh.th[a];
-    }
-    __syncthreads();
-    const int nk = sh.flag;
-    __syncthreads();
-    // interior block X^T A~ X on the kept vectors (= Phi^T A_K Phi)
-    store_block<M, 1>(sY, LD, 512, X);
-    __syncthreads();
-    gram_lds_reg<M, 1>(sY, LD, 512, AX, sh.G, sh.red);
-    for (int t = threadIdx.x; t < L * L; t += blockDim.x) {
-        const int a = t / L, b = t % L;
-        Aint[(size_t)e * L * L + t] = (a < nk && b < nk) ? sh.G[a * M + b] : 0.0;
-    }
-    // coefficients of the constant function: Phi^T S 1 = X^T S^1/2 1
-    double zv[1][M];
-#pragma unroll
-    for (int jj = 0; jj < M; ++jj) zv[0][jj] = X[0][jj] * sq;
-    column_sums<M, 1>(zv, zc + (size_t)e * L, L, nk, sh.red);
-#pragma unroll
-    for (int jj = 0; jj < M; ++jj) {
-        if (jj < L) phi[((size_t)e * L + jj) * 512 + phi_pos(c)] = (jj < nk) ? X[0][jj] / sq : 0.0;
-    }
 }
 
 // Hd[c] = Aint[c] + sum of D[c][d] over the faces of c interior to its parent
@@ -960,31 +546,6 @@ __global__ __launch_bounds__(768) void k_eig_up(CoarseGeom lo, CoarseGeom up, co
 
 // ---------------------------------------------------------------------------
 // launchers
-
-#define SPECMG_M_DISPATCH(MV, ...)                   \
-    switch (MV) {                                    \
-        case 10: {                                   \
-            constexpr int M = 10;                    \
-            __VA_ARGS__;                             \
-        } break;                                     \
-        case 12: {                                   \
-            constexpr int M = 12;                    \
-            __VA_ARGS__;                             \
-        } break;                                     \
-        default: {                                   \
-            constexpr int M = 14;                    \
-            __VA_ARGS__;                             \
-        } break;                                     \
-    }
-
-void launch_eig2(const FineGeom& g, const double* kt, int target, int nvec, double tol, double crtol,
-                 double* phi, double* lam, int* nkeep, double* Aint, int* status, double* zc, int e0, int count,
-                 const float* warm, int kp, int kw, double ws_tol, int* ws_fb, double thr, hipStream_t s) {
-    const int L = target + 3;
-    SPECMG_M_DISPATCH(nvec, hipLaunchKernelGGL((k_eig2<M>), dim3(count), dim3(512), 0, s, g, kt, target, L, tol,
-                                               crtol, phi, lam, nkeep, Aint, zc, status, e0, warm, kp, kw, ws_tol,
-                                               ws_fb, thr));
-}
 
 void launch_eig_up(const CoarseGeom& lo, const CoarseGeom& up, const double* Aint_lo, const double* Dlo,
                    const double* Aofflo, const int* nkeep_lo, const double* zlo, double* Hd_work,
