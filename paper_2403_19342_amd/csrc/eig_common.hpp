@@ -8,10 +8,7 @@
 namespace specmg {
 
 constexpr int kDeg = 20;          // Chebyshev degree per cycle of a relaxed, warm-started solve
-constexpr int kDegExact = 40;     // ... of an exact solve (fewer cycles, so fewer orthonormalisations
-                                  //     and Rayleigh-Ritz steps per filtered vector)
 constexpr int kMaxCycles = 300;
-constexpr int kMaxEigWaves = 12;   // workgroups of at most 768 threads
 constexpr int kWarmCycles = 4;     // cycles a learned start gets to reach the relaxed residual
 
 
@@ -210,14 +207,6 @@ __device__ __forceinline__ void jacobi_wave(lds_double* H, lds_double* Q, lds_do
     wave_sync();
 }
 
-// the same by wavefront 0 of a workgroup; called by all threads
-template <int M>
-__device__ __forceinline__ void jacobi_eig(double* H, double* Q, double* th, double* scr, int* iscr) {
-    if (threadIdx.x < 64)
-        jacobi_wave<M>((lds_double*)H, (lds_double*)Q, (lds_double*)th, (lds_double*)scr, (lds_int*)iscr);
-    __syncthreads();
-}
-
 // Generalised Rayleigh-Ritz of a block Y from G = Y^T Y and H = Y^T A Y, by
 // one wavefront: C (into Q) with (Y C)^T (Y C) = I and (Y C)^T A (Y C) =
 // diag(th).  G is scaled to a unit diagonal and factored G = R^T R with lane l
@@ -226,20 +215,29 @@ __device__ __forceinline__ void jacobi_eig(double* H, double* Q, double* th, dou
 // (D R^-1)^T H (D R^-1).  Returns the smallest pivot of the scaled G; pivots
 // below 1e-12 are raised to that.  When it is below min_ritz the eigenproblem
 // is left out and C = D R^-1 (a Cholesky-QR step).  G and H are destroyed (H
-// keeps D R^-1 while the eigenproblem runs); scr holds M values.
+// keeps D R^-1 while the eigenproblem runs); scr holds M values.  With nval < M
+// the columns nval.. of Y are zero and the others orthonormal: C is the
+// eigenvectors' matrix, pad (above the spectrum) the values of the empty
+// columns, which sort last.
 // A call of its own: inlined, the caller's live registers (the couplings of
 // its operator) push this routine's arrays to scratch.
 template <int M>
 __device__ __attribute__((noinline)) double ritz_wave(lds_double* G, lds_double* H, lds_double* Q, lds_double* scr,
-                                                      lds_double* th, lds_int* iscr, double min_ritz, double rtol) {
+                                                      lds_double* th, lds_int* iscr, double min_ritz, double rtol,
+                                                      int nval = M, double pad = 0.0) {
     const int lane = threadIdx.x & 63, l = lane < M ? lane : M - 1;
-    double g[M], x[M];
+    double x[M];
+    double low = 1.0;
+    if (nval < M) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) x[i] = i == l ? 1.0 : 0.0;
+    } else {
+    double g[M];
     const double gll = G[l * M + l];
     const double dl = gll > 1e-300 ? rsqrt_f64(gll) : 0.0;
 #pragma unroll
     for (int i = 0; i < M; ++i) g[i] = G[i * M + l] * dl * read_lane(dl, i);
     double ir[M];
-    double low = 1.0;
 #pragma unroll
     for (int j = 0; j < M; ++j) {
         double p = read_lane(g[j], j);
@@ -262,6 +260,7 @@ __device__ __attribute__((noinline)) double ritz_wave(lds_double* G, lds_double*
     }
 #pragma unroll
     for (int i = 0; i < M; ++i) x[i] = i <= l ? x[i] * read_lane(dl, i) : 0.0;
+    }
     if (low < min_ritz) {
         if (lane < M) {
 #pragma unroll
@@ -296,7 +295,7 @@ __device__ __attribute__((noinline)) double ritz_wave(lds_double* G, lds_double*
     }
     if (lane < M) {
 #pragma unroll
-        for (int m = 0; m < M; ++m) G[m * M + lane] = t[m];
+        for (int m = 0; m < M; ++m) G[m * M + lane] = m == lane && m >= nval ? pad : t[m];
     }
     wave_sync();
     jacobi_wave<M>(G, Q, th, scr, iscr, rtol);
@@ -322,59 +321,6 @@ __device__ __attribute__((noinline)) double ritz_wave(lds_double* G, lds_double*
     return low;
 }
 
-// Cholesky G = R^T R of the SPD M x M matrix G (R upper triangular, stored
-// in Rm; dinv[j] = 1 / R[j][j]) by wavefront 0, one column per step with a
-// lane-parallel trailing update.  G is left intact.  Returns false (in every
-// thread) when G is not numerically positive definite.
-template <int M>
-__device__ __forceinline__ bool chol_wave(const double* G, double* Rm, double* dinv, int* flag) {
-    constexpr int MM = M * M;
-    constexpr int PER = (MM + 63) / 64;
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        int ei[PER], ej[PER];
-        bool ev[PER];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int t = lane + 64 * u;
-            ev[u] = t < MM;
-            ei[u] = ev[u] ? t / M : 0;
-            ej[u] = ev[u] ? t % M : 0;
-            if (ev[u]) Rm[t] = ei[u] <= ej[u] ? G[t] : 0.0;
-        }
-        wave_sync();
-        int ok = 1;
-#pragma unroll 1
-        for (int j = 0; j < M; ++j) {
-            double d = Rm[j * M + j];
-            if (!(d > 0.0)) {
-                ok = 0;
-                d = 1.0;
-            }
-            const double inv_d = 1.0 / d;
-            // trailing update of the upper triangle with the unscaled row j
-#pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const int i = ei[u], l = ej[u];
-                if (ev[u] && i > j && l >= i) Rm[i * M + l] -= Rm[j * M + i] * Rm[j * M + l] * inv_d;
-            }
-            wave_sync();
-            const double rjj = sqrt(d), ir = 1.0 / rjj;
-            if (lane > j && lane < M) Rm[j * M + lane] *= ir;
-            if (lane == j) {
-                Rm[j * M + j] = rjj;
-                dinv[j] = ir;
-            }
-            wave_sync();
-        }
-        if (lane == 0) *flag = ok;
-    }
-    __syncthreads();
-    const bool ok = *flag != 0;
-    __syncthreads();
-    return ok;
-}
-
 // Cluster rule on ascending values th[0..n-1] (n >= target+4 or all values):
 // keep `target`, grow to the end of a cluster of equal values up to
 // target+3, or shrink before the cluster when it runs past that cap.
@@ -396,25 +342,6 @@ __device__ inline int cluster_cut_dev(const double* th, int n, int target, doubl
         while (k > 1 && same(k)) --k;
     }
     return k;
-}
-
-// Inverse of the upper triangular factor (Rm, dinv from chol_wave) into
-// Ri, by wavefront 0: rows from the bottom up, lane l owning column l.
-template <int M>
-__device__ __forceinline__ void trtri_wave(const double* Rm, const double* dinv, double* Ri) {
-    if (threadIdx.x < 64) {
-        const int l = threadIdx.x;
-#pragma unroll 1
-        for (int i = M - 1; i >= 0; --i) {
-            if (l < M) {
-                double v = (l == i) ? 1.0 : 0.0;
-                for (int k = i + 1; k <= l; ++k) v -= Rm[i * M + k] * Ri[k * M + l];
-                Ri[i * M + l] = l >= i ? v * dinv[i] : 0.0;
-            }
-            wave_sync();
-        }
-    }
-    __syncthreads();
 }
 
 // whether every vector that decides the kept space has converged (see chefsi)

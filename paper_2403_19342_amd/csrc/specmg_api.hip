@@ -495,7 +495,9 @@ static int do_setup(specmg_ctx* c, const double* perm, hipStream_t s) {
         launch_galerkin2(fg, c->kt, lv.basis, lv.nkeep, L, lv.D, lv.Aoff, s);
         launch_assemble_diag(lv.g, lv.Aint, lv.D, lv.Ad, s);
     }
-    // ---- levels 3..levels
+    // ---- levels 3..levels (the eigensolves' workspaces are kept until the
+    // stream has been waited for below)
+    std::vector<std::unique_ptr<DevBuf>> eig_ws;
     for (int li = 1; li < levels - 1; ++li) {
         Level& lo = c->lev[li - 1];
         Level& up = c->lev[li];
@@ -526,7 +528,8 @@ static int do_setup(specmg_ctx* c, const double* perm, hipStream_t s) {
         up.Ad = c->alloc<double>((size_t)m * Lu * Lu);
         up.z = c->alloc<double>((size_t)m * Lu);
         double* hd = c->alloc<double>((size_t)lo.g.m * lo.L * lo.L);
-        launch_eig_up(lo.g, up.g, lo.Aint, lo.D, lo.Aoff, lo.nkeep, lo.z, hd, c->target_cc, c->nvec_cc, tol, crtol,
+        eig_ws.emplace_back(new DevBuf(c->al, eig_up_work_doubles(lo.g, up.g, c->nvec_cc) * sizeof(double)));
+        launch_eig_up(lo.g, up.g, lo.Aint, lo.D, lo.Aoff, lo.nkeep, lo.z, hd, (double*)eig_ws.back()->p, c->target_cc, c->nvec_cc, tol, crtol,
                       c->thr_cc, up.basis, up.lam, up.nkeep, up.Aint, up.z, up.status, s);
         launch_galerkin_up(lo.g, up.g, lo.D, lo.Aoff, up.basis, up.nkeep, up.D, up.Aoff, s);
         launch_assemble_diag(up.g, up.Aint, up.D, up.Ad, s);
@@ -550,6 +553,7 @@ static int do_setup(specmg_ctx* c, const double* perm, hipStream_t s) {
         for (int k : lv.nkeep_h) lv.dim += k;
         for (int v : st) unconv += (v < 0);
     }
+    eig_ws.clear();
     coarse_traffic(c);
     // ---- coarsest: A_L^+ = (A_L + alpha z z^T)^{-1} - z z^T / alpha
     {
