@@ -70,18 +70,20 @@ __device__ __forceinline__ double rcp_f64(double x) {
 }
 
 // In-place inverse of the symmetric positive definite m x m matrix at T (leading
-// dimension ld) by symmetric sweeps, the matrix in the registers of the NT
-// threads (thread (ty, tx) of a TY x TX grid owns elements (ty + TY a,
-// tx + TX b)).  A sweep publishes its pivot row (by symmetry also the column)
-// through one of two LDS rows in turn, so it costs one barrier.  Entries
-// beyond m come out zero.  rows: 2 x 192 doubles.
+// dimension ld) by symmetric sweeps over pairs of pivots, the matrix in the
+// registers of the NT threads (thread (ty, tx) of a TY x TX grid owns elements
+// (ty + TY a, tx + TX b)).  A sweep publishes its two pivot rows (by symmetry
+// also the columns) through one of two LDS buffers in turn, so a pair costs one
+// barrier; the latency of that exchange and of the pivots' reciprocals is what
+// bounds it.  Entries beyond m come out zero.  rows: 4 x 192 doubles.
+constexpr int kSweepRow = 192;
 template <int NT, int A, int B>
 __device__ __attribute__((noinline)) void sweep_inverse(gl_double* Tv, int mv, int ldv, lds_double* rowsv) {
     gl_double* const T = (gl_double*)uniform64((unsigned long long)Tv);
     lds_double* const rows = (lds_double*)uniform32((unsigned)(size_t)rowsv);
     const int m = (int)uniform32((unsigned)mv), ld = (int)uniform32((unsigned)ldv);
     constexpr int TY = 16, TX = NT / TY;
-    static_assert(TX == TY || TX == 2 * TY, "pivot column in a static register");
+    static_assert(TX == TY || TX == 2 * TY, "pivot columns in a static register");
     const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
     double v[A][B];
 #pragma unroll
@@ -94,35 +96,51 @@ __device__ __attribute__((noinline)) void sweep_inverse(gl_double* Tv, int mv, i
 #pragma unroll
     for (int a = 0; a < A; ++a) {
         constexpr int step = TX / TY;
-        const int bk = a / step;   // register column of the pivot
+        const int bk = a / step;   // register column of the pivots
 #pragma unroll 1
-        for (int s = 0; s < TY; ++s) {
+        for (int s = 0; s < TY; s += 2) {
             const int k = TY * a + s;
             if (k >= m) break;
-            lds_double* r = rows + 192 * (k & 1);
-            if (ty == s) {
+            lds_double* r0 = rows + 2 * kSweepRow * ((k >> 1) & 1);
+            lds_double* r1 = r0 + kSweepRow;
+            if ((ty & ~1) == s) {
+                lds_double* r = ty == s ? r0 : r1;
 #pragma unroll
                 for (int b = 0; b < B; ++b) r[tx + TX * b] = v[a][b];
             }
             __syncthreads();
-            const double rd = rcp_f64(r[k]);
-            double c[B], w[A];
+            // inverse of the pivot block; a row k + 1 beyond m is zero
+            const bool two = k + 1 < m;
+            const double a00 = r0[k], a01 = r0[k + 1], a11 = r1[k + 1];
+            const double i0 = rcp_f64(a00), l = a01 * i0;
+            const double i1 = rcp_f64(two ? a11 - l * a01 : 1.0);
+            const double p01 = -l * i1, p00 = i0 - l * p01, p11 = two ? i1 : 0.0;
+            double c0[B], c1[B], w0[A], w1[A];
 #pragma unroll
-            for (int b = 0; b < B; ++b) c[b] = r[tx + TX * b] * rd;
+            for (int b = 0; b < B; ++b) {
+                const double x = r0[tx + TX * b], y = r1[tx + TX * b];
+                c0[b] = p00 * x + p01 * y;
+                c1[b] = p01 * x + p11 * y;
+            }
 #pragma unroll
-            for (int i = 0; i < A; ++i) w[i] = r[ty + TY * i];
+            for (int i = 0; i < A; ++i) {
+                w0[i] = r0[ty + TY * i];
+                w1[i] = r1[ty + TY * i];
+            }
 #pragma unroll
             for (int i = 0; i < A; ++i)
 #pragma unroll
-                for (int b = 0; b < B; ++b) v[i][b] -= w[i] * c[b];
-            if (ty == s) {
+                for (int b = 0; b < B; ++b) v[i][b] -= w0[i] * c0[b] + w1[i] * c1[b];
+            const bool row0 = ty == s, row1 = ty == s + 1, col0 = tx == k % TX, col1 = tx == k % TX + 1;
+            if (row0 || row1) {
 #pragma unroll
-                for (int b = 0; b < B; ++b) v[a][b] = c[b];
+                for (int b = 0; b < B; ++b) v[a][b] = row0 ? c0[b] : c1[b];
             }
-            if (tx == k % TX) {
+            if (col0 || col1) {
 #pragma unroll
-                for (int i = 0; i < A; ++i) v[i][bk] = w[i] * rd;
-                if (ty == s) v[a][bk] = -rd;
+                for (int i = 0; i < A; ++i) v[i][bk] = col0 ? p00 * w0[i] + p01 * w1[i] : p01 * w0[i] + p11 * w1[i];
+                if (row0) v[a][bk] = col0 ? -p00 : -p01;
+                if (row1) v[a][bk] = col0 ? -p01 : -p11;
             }
         }
     }
@@ -157,7 +175,7 @@ struct UpShared {
     double Q[M * M];
     double th[M], nrm[M], scr[M];
     double red[NT];
-    double rows[2 * 192];
+    double rows[4 * kSweepRow];
     double misc[NT / 64];
     double ct[3 * 4];
     double low;
@@ -200,13 +218,37 @@ struct UpProblem {
         return up ? Aoff[(((size_t)ci * 3 + ax) * LP + ai) * LP + bj] : Aoff[(((size_t)cj * 3 + ax) * LP + bj) * LP + ai];
     }
 
+    // coordinates of child p (agg is 2 or 4: shifts)
+    __device__ __forceinline__ int lg() const { return agg == 4 ? 2 : 1; }
+    __device__ __forceinline__ int child_x(int p) const { return p & (agg - 1); }
+    __device__ __forceinline__ int child_y(int p) const { return (p >> lg()) & (agg - 1); }
+    __device__ __forceinline__ int child_z(int p) const { return p >> (2 * lg()); }
+
+    // sum_k c[k cs] x[k xs], k < kn (kn >= 1): eight of each in flight (beyond kn
+    // the last one again, with weight zero, so that no load is conditional)
+    template <class PC, class PX>
+    static __device__ __forceinline__ double coupled(PC c, int cs, PX x, int xs, int kn) {
+        double s = 0.0;
+#pragma unroll 1
+        for (int k0 = 0; k0 < kn; k0 += 8) {
+            double h[8], y[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) h[u] = c[min(k0 + u, kn - 1) * cs];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) y[u] = x[min(k0 + u, kn - 1) * xs];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += (k0 + u < kn ? h[u] : 0.0) * y[u];
+        }
+        return s;
+    }
+
     // AYg = H_E Y, one row per thread
     __device__ __forceinline__ void apply() const {
         const int a2 = agg * agg;
 #pragma unroll 1
         for (int r = threadIdx.x; r < n; r += NT) {
             const int p = row[r] >> 8, a = row[r] & 255;
-            const int qx = p % agg, qy = (p / agg) % agg, qz = p / a2;
+            const int qx = child_x(p), qy = child_y(p), qz = child_z(p);
             const int c = sh->elem[p];
             double acc[M];
 #pragma unroll
@@ -374,38 +416,86 @@ struct UpProblem {
             gl_double* Tp = T + (size_t)p * mpmax * mpmax;
             const int q0 = p ? plane_row(p - 1) : 0, mq = r0 - q0, ldq = ceil16(mq);
             const gl_double* Tq = T + (size_t)(p - 1) * mpmax * mpmax;
+            const int c0 = planes == 1 ? 0 : p * a2, nch = planes == 1 ? a2 * agg : a2;
             if (p) {
-                // Wk = T_{p-1} C_{p-1}: row i of the plane below, column j of this one
+                // Wk[j][i] = (T_{p-1} C_{p-1})[i][j]: a wavefront takes a child of this
+                // plane, a lane a row i of the plane below; the child's couplings are
+                // the same for every lane
 #pragma unroll 1
-                for (int i = w; i < mq; i += NW) {
-                    for (int j = lane; j < m; j += 64) {
-                        const int pj = row[r0 + j] >> 8, bj = row[r0 + j] & 255, pb = pj - a2;
-                        const int k0 = sh->koff[pb], kn = sh->koff[pb + 1] - k0, cb = sh->elem[pb];
-                        double s = 0.0;
-                        for (int k = 0; k < kn; ++k)
-                            s += Tq[(size_t)(k0 - q0 + k) * ldq + i] * Aoff[(((size_t)cb * 3 + 2) * LP + k) * LP + bj];
-                        Wk[(size_t)i * ld + j] = s;
+                for (int q = w; q < nch; q += NW) {
+                    const int pj = (int)uniform32((unsigned)(c0 + q)), pb = pj - a2;
+                    const int kb = (int)uniform32((unsigned)sh->koff[pb]), kn = (int)uniform32((unsigned)sh->koff[pb + 1]) - kb;
+                    const int jb = (int)uniform32((unsigned)sh->koff[pj]), jn = (int)uniform32((unsigned)sh->koff[pj + 1]) - jb;
+                    const gl_double* C = Aoff + ((size_t)uniform32((unsigned)sh->elem[pb]) * 3 + 2) * LP * LP;
+                    for (int i = lane; i < mq; i += 64) {
+                        const gl_double* t = Tq + (size_t)(kb - q0) * ldq + i;
+#pragma unroll 1
+                        for (int k0 = 0; k0 < kn; k0 += 8) {
+                            double x[8];
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) x[u] = t[min(k0 + u, kn - 1) * ldq];
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) x[u] = k0 + u < kn ? x[u] : 0.0;
+#pragma unroll 2
+                            for (int b = 0; b < jn; ++b) {
+                                gl_double* o = Wk + (size_t)(jb - r0 + b) * mpmax + i;
+                                double v = k0 ? *o : 0.0;
+#pragma unroll
+                                for (int u = 0; u < 8; ++u) v += x[u] * C[min(k0 + u, kn - 1) * LP + b];
+                                *o = v;
+                            }
+                        }
                     }
                 }
                 __syncthreads();
             }
+            // S_p row by row of a child: a lane takes a column j
 #pragma unroll 1
-            for (int i = w; i < m; i += NW) {
-                const int pi = row[r0 + i] >> 8, ai = row[r0 + i] & 255, ci = sh->elem[pi];
-                const int xi = pi % agg, yi = (pi / agg) % agg, zi = pi / a2;
+            for (int q = w; q < nch; q += NW) {
+                const int pi = (int)uniform32((unsigned)(c0 + q)), ci = (int)uniform32((unsigned)sh->elem[pi]);
+                const int ib = (int)uniform32((unsigned)sh->koff[pi]), in = (int)uniform32((unsigned)sh->koff[pi + 1]) - ib;
+                const int xi = child_x(pi), yi = child_y(pi), zi = child_z(pi);
+                const int pb = p ? pi - a2 : pi;
+                const int kb = (int)uniform32((unsigned)sh->koff[pb]), kn = p ? (int)uniform32((unsigned)sh->koff[pb + 1]) - kb : 0;
+                const gl_double* C = Aoff + ((size_t)uniform32((unsigned)sh->elem[pb]) * 3 + 2) * LP * LP;
                 for (int j = lane; j < m; j += 64) {
                     const int pj = row[r0 + j] >> 8, bj = row[r0 + j] & 255, cj = sh->elem[pj];
-                    const int dx = pj % agg - xi, dy = (pj / agg) % agg - yi, dz = pj / a2 - zi;
-                    double s = i == j ? sigma : 0.0;
+                    const int dx = child_x(pj) - xi, dy = child_y(pj) - yi, dz = child_z(pj) - zi;
                     const int dist = abs(dx) + abs(dy) + abs(dz);
-                    if (dist == 0) s += entry(ci, ai, cj, bj, -1, false);
-                    else if (dist == 1) s += entry(ci, ai, cj, bj, dx ? 0 : (dy ? 1 : 2), dx + dy + dz > 0);
-                    if (p) {
-                        const int pb = pi - a2, k0 = sh->koff[pb] - q0, kn = sh->koff[pb + 1] - sh->koff[pb], cb = sh->elem[pb];
-                        for (int k = 0; k < kn; ++k)
-                            s -= Aoff[(((size_t)cb * 3 + 2) * LP + k) * LP + ai] * Wk[(size_t)(k0 + k) * ld + j];
+                    const bool up = dx + dy + dz > 0;
+                    const int ax = dx ? 0 : (dy ? 1 : 2);
+                    // entries of the lane's column: e[a es]
+                    const gl_double* e = dist == 0 ? Hd + (size_t)ci * LP * LP + bj
+                                                   : Aoff + ((size_t)(up ? ci : cj) * 3 + ax) * LP * LP + (up ? bj : bj * LP);
+                    const int es = dist == 0 || up ? LP : 1;
+                    const double we = dist <= 1 ? 1.0 : 0.0;
+                    if (dist > 1) e = Hd;   // any valid entry, weight zero
+                    const gl_double* x0 = Wk + (size_t)j * mpmax + (p ? kb - q0 : 0);
+#pragma unroll 1
+                    for (int a0 = 0; a0 < in; a0 += 4) {
+                        double v[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) v[u] = e[dist <= 1 ? min(a0 + u, in - 1) * es : 0];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            v[u] = we * v[u] + (dist == 0 && a0 + u == bj ? sigma : 0.0);
+#pragma unroll 1
+                        for (int k0 = 0; k0 < kn; k0 += 8) {
+                            double x[8];
+#pragma unroll
+                            for (int k = 0; k < 8; ++k) x[k] = x0[min(k0 + k, kn - 1)];
+#pragma unroll
+                            for (int k = 0; k < 8; ++k) x[k] = k0 + k < kn ? x[k] : 0.0;
+#pragma unroll
+                            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                                for (int k = 0; k < 8; ++k)
+                                    v[u] -= C[min(k0 + k, kn - 1) * LP + min(a0 + u, in - 1)] * x[k];
+                        }
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            if (a0 + u < in) Tp[(size_t)(ib - r0 + a0 + u) * ld + j] = v[u];
                     }
-                    Tp[(size_t)i * ld + j] = s;
                 }
             }
             __syncthreads();
@@ -415,37 +505,59 @@ struct UpProblem {
 
     // acc = T_p U on the rows of the plane: V rows = acc (sub: V -= acc).  The
     // symmetric T_p is read by its columns, 128 contiguous bytes per 16 lanes,
-    // eight k-steps in flight while the previous eight are multiplied.
-    __device__ __forceinline__ void product(int p, bool sub) const {
-        const int r0 = plane_row(p), m = plane_end(p) - r0, ld = ceil16(m), nk = ld / 4;
-        const gl_double* Tp = T + (size_t)p * mpmax * mpmax;
+    // in groups of four k-steps, three groups in flight (the last group again
+    // past the end, so that no load is conditional); the first ones are
+    // loaded by the caller ahead of U's barrier.  Columns of U beyond M only reach
+    // columns of the result that are not stored.
+    struct Ahead {
+        double a[3][4];
+    };
+    __device__ __forceinline__ void load_group(const gl_double* tc, int ld, int g, double (&a)[4]) const {
+        const gl_double* t = tc + (size_t)(16 * min(g, ld / 16 - 1)) * ld;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a[u] = t[(size_t)(4 * u) * ld];
+    }
+    __device__ __forceinline__ const gl_double* tile_column(int p, int ld, int t0) const {
+        return T + (size_t)p * mpmax * mpmax + (size_t)(lane >> 4) * ld + min(t0, ld - 16) + (lane & 15);
+    }
+    __device__ __forceinline__ void product_first(int p, Ahead& f) const {
+        const int ld = ceil16(plane_end(p) - plane_row(p));
+        const gl_double* tc = tile_column(p, ld, 16 * w);
+#pragma unroll
+        for (int g = 0; g < 3; ++g) load_group(tc, ld, g, f.a[g]);
+    }
+    __device__ __forceinline__ void product(int p, bool sub, Ahead& f) const {
+        const int r0 = plane_row(p), m = plane_end(p) - r0, ld = ceil16(m), ng = ld / 16;
         const int li = lane & 15, lk = lane >> 4;
 #pragma unroll 1
         for (int t0 = 16 * w; t0 < ld; t0 += 16 * NW) {
             v4d acc[NCT];
 #pragma unroll
             for (int b = 0; b < NCT; ++b) acc[b] = v4d{0.0, 0.0, 0.0, 0.0};
-            const gl_double* tc = Tp + (size_t)lk * ld + t0 + li;
-            double a[8], an[8];
+            const gl_double* tc = tile_column(p, ld, t0);
+            if (t0 != 16 * w) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a[u] = u < nk ? tc[(size_t)(4 * u) * ld] : 0.0;
+                for (int g = 0; g < 3; ++g) load_group(tc, ld, g, f.a[g]);
+            }
 #pragma unroll 1
-            for (int k0 = 0; k0 < nk; k0 += 8) {
+            for (int g0 = 0; g0 < ng; g0 += 3) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) an[u] = k0 + 8 + u < nk ? tc[(size_t)(4 * (k0 + 8 + u)) * ld] : 0.0;
+                for (int g = 0; g < 3; ++g) {
+                    if (g0 + g < ng) {
+                        double x[NCT][4];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    if (k0 + u < nk) {
+                        for (int u = 0; u < 4; ++u)
 #pragma unroll
-                        for (int b = 0; b < NCT; ++b) {
-                            const int j = 16 * b + li;
-                            const double x = j < M ? U[(4 * (k0 + u) + lk) * PT + j] : 0.0;
-                            acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], x, acc[b], 0, 0, 0);
-                        }
+                            for (int b = 0; b < NCT; ++b)
+                                x[b][u] = U[(16 * (g0 + g) + 4 * u + lk) * PT + min(16 * b + li, PT - 1)];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+#pragma unroll
+                            for (int b = 0; b < NCT; ++b)
+                                acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[g][u], x[b][u], acc[b], 0, 0, 0);
+                        load_group(tc, ld, g0 + g + 3, f.a[g]);
                     }
                 }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) a[u] = an[u];
             }
 #pragma unroll
             for (int b = 0; b < NCT; ++b)
@@ -468,28 +580,26 @@ struct UpProblem {
             const bool back = s >= planes;
             const int p = back ? 2 * planes - 2 - s : s;
             const int r0 = plane_row(p), m = plane_end(p) - r0, ld = ceil16(m);
+            Ahead first;
+            product_first(p, first);
+            const int j = min((int)threadIdx.x % PG, M - 1);
 #pragma unroll 1
-            for (int t = threadIdx.x; t < ld * PG; t += NT) {
-                const int i = t / PG, j = t % PG;
-                if (j >= M) continue;
-                double v = 0.0;
-                if (i < m) {
-                    if (!back) v = Yg[(size_t)(r0 + i) * PG + j];
-                    if (s) {
-                        // the coupled child: below on the way up, above on the way down
-                        const int pi = row[r0 + i] >> 8, ai = row[r0 + i] & 255;
-                        const int pn = back ? pi + a2 : pi - a2, k0 = sh->koff[pn], kn = sh->koff[pn + 1] - k0;
-                        const int c = sh->elem[pi], cn = sh->elem[pn];
-                        double q = 0.0;
-#pragma unroll 4
-                        for (int k = 0; k < kn; ++k) q += entry(c, ai, cn, k, 2, back) * Y[(k0 + k) * PT + j];
-                        v = back ? q : v - q;
-                    }
+            for (int i = threadIdx.x / PG; i < ld; i += NT / PG) {
+                const int r = r0 + min(i, m - 1);
+                double v = back ? 0.0 : Yg[(size_t)r * PG + j];
+                if (s) {
+                    // the coupled child: below on the way up, above on the way down
+                    const int pi = row[r] >> 8, ai = row[r] & 255;
+                    const int pn = back ? pi + a2 : pi - a2, k0 = sh->koff[pn], kn = sh->koff[pn + 1] - k0;
+                    const gl_double* h =
+                        Aoff + ((size_t)sh->elem[back ? pi : pn] * 3 + 2) * LP * LP + (back ? ai * LP : ai);
+                    const double q = coupled(h, back ? 1 : LP, Y + k0 * PT + j, PT, kn);
+                    v = back ? q : v - q;
                 }
-                U[i * PT + j] = v;
+                if (threadIdx.x % PG < M) U[i * PT + j] = i < m ? v : 0.0;
             }
             __syncthreads();
-            product(p, back);
+            product(p, back, first);
             __syncthreads();
         }
     }
@@ -587,7 +697,7 @@ static size_t up_slot_doubles(int agg, int lp, int M) {
 }
 
 template <int M, int NT>
-__global__ __launch_bounds__(NT) void k_eig_up(CoarseGeom lo, CoarseGeom up, const double* __restrict__ Hd,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_eig_up(CoarseGeom lo, CoarseGeom up, const double* __restrict__ Hd,
                                                const double* __restrict__ Aoff, const int* __restrict__ nkeep_lo,
                                                const double* __restrict__ zlo, int target, double tol, double crtol,
                                                double thr, double* __restrict__ V, double* __restrict__ lam,
@@ -648,7 +758,7 @@ __global__ __launch_bounds__(NT) void k_eig_up(CoarseGeom lo, CoarseGeom up, con
         double rs = 0.0, az = 0.0;
         for (int r = threadIdx.x; r < nval; r += NT) {
             const int p = pr.row[r] >> 8, a = pr.row[r] & 255, c = sh.elem[p];
-            const int q[3] = {p % agg, (p / agg) % agg, p / (agg * agg)}, st[3] = {1, agg, agg * agg};
+            const int q[3] = {pr.child_x(p), pr.child_y(p), pr.child_z(p)}, st[3] = {1, agg, agg * agg};
             double s = 0.0;
             for (int b = 0; b < sh.koff[p + 1] - sh.koff[p]; ++b) s += fabs(pr.entry(c, a, c, b, -1, false));
 #pragma unroll
@@ -693,8 +803,8 @@ __global__ __launch_bounds__(NT) void k_eig_up(CoarseGeom lo, CoarseGeom up, con
                 if (j == 0) v = z;
                 else if (a == 0) {
                     const unsigned char* md = kModes[j & 15];
-                    v += z * sh.ct[4 * md[0] + p % agg] * sh.ct[4 * md[1] + (p / agg) % agg] *
-                         sh.ct[4 * md[2] + p / (agg * agg)];
+                    v += z * sh.ct[4 * md[0] + pr.child_x(p)] * sh.ct[4 * md[1] + pr.child_y(p)] *
+                         sh.ct[4 * md[2] + pr.child_z(p)];
                 }
             }
             pr.Y[r * PT + j] = v;
