@@ -587,7 +587,7 @@ static int do_setup(specmg_ctx* c, const double* perm, hipStream_t s) {
         } else {
             c->Pinv = c->alloc<double>((size_t)np * np);
         }
-        DevBuf work_buf(c->al, (size_t)np * np * sizeof(double));
+        DevBuf work_buf(c->al, dense_spd_inverse_work_doubles(np) * sizeof(double));
         DevBuf tbuf(c->al, dense_spd_inverse_tbuf_doubles(np) * sizeof(double));
         double* work = (double*)work_buf.p;
         HIPCHK(hipMemsetAsync(c->Pinv, 0, (size_t)np * np * sizeof(double), s));
