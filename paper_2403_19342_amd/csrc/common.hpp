@@ -321,8 +321,11 @@ void launch_pcg_init(Scalars* sc, double thresh2, int flexible, hipStream_t s);
 
 // coarse levels (k_coarse.hip)
 template <typename T>
-void launch_coarse_smooth(const CoarseGeom& g, const T* Dinv, const T* G, const T* r, T* u,
-                          const Scalars* sc, int check_done, hipStream_t s);
+void launch_coarse_smooth(const CoarseGeom& g, const T* SM, T* r, int nparts, T* u, const Scalars* sc, int check_done,
+                          hipStream_t s);
+// parts in which launch_coarse_resid_restrict writes r_up, g.M Lup words apart;
+// the first kernel to read r_up adds them
+int coarse_restrict_parts(const CoarseGeom& g);
 template <typename T>
 void launch_coarse_resid_restrict(const CoarseGeom& g, const T* Ad, const T* Aoff, const T* r,
                                   const T* u, const T* V, const int* nkeep_up, int Lup, T* rup,
@@ -331,12 +334,13 @@ template <typename T>
 void launch_coarse_prolong(const CoarseGeom& g, T* u, const T* V, const int* nkeep_up, int Lup,
                            const T* eup, const Scalars* sc, int check_done, hipStream_t s);
 template <typename T>
-void launch_coarse_resid_smooth(const CoarseGeom& g, const T* Ad, const T* Dinv, const T* Aoff,
-                                const T* G, const T* r, const T* u, T* e, const Scalars* sc,
-                                int check_done, hipStream_t s);
+void launch_coarse_resid_smooth(const CoarseGeom& g, const T* Ad, const T* Aoff, const T* SM, const T* r,
+                                const T* u, T* e, const Scalars* sc, int check_done, hipStream_t s);
+// words of the sweep's matrices SM (g.m elements of level l)
+size_t coarse_sweep_doubles(const CoarseGeom& g);
 template <typename T>
-void launch_coarsest(int n, int np, const double* Pinv, const int* cmap, const T* r, T* e, double* rc,
-                     const Scalars* sc, int check_done, hipStream_t s);
+void launch_coarsest(int n, int np, const double* Pinv, const int* cmap, const T* r, int nparts, int64_t pstride, T* e,
+                     double* rc, const Scalars* sc, int check_done, hipStream_t s);
 // values of the coarsest right-hand side staged in LDS at a time; wider
 // coarsest spaces use the symmetric product below
 constexpr int kCoarsestChunk = 8192;
@@ -347,7 +351,7 @@ size_t coarsest_sym_packed_doubles(int np);
 std::vector<int2> coarsest_sym_chunks(int np, int* maxc);
 void launch_pack_lower_tiles(const double* dense, int np, double* packed, hipStream_t s);
 void launch_coarsest_sym(int n, int np, const double* packed, const int2* chunks, int nchunks, int maxc,
-                         const int* cmap, const double* r, double* e, double* rc, double* P, double* Q,
+                         const int* cmap, const double* r, int nparts, int64_t pstride, double* e, double* rc, double* P, double* Q,
                          const Scalars* sc, int check_done, hipStream_t s);
 
 // set-up (k_coarse.hip)
@@ -359,7 +363,7 @@ void launch_galerkin_up(const CoarseGeom& lo, const CoarseGeom& up, const double
 void launch_assemble_diag(const CoarseGeom& g, const double* Aint, const double* D, double* Ad,
                           hipStream_t s);
 void launch_blockic_setup(const CoarseGeom& g, const double* Ad, const double* Aoff, const int* nkeep,
-                          double* Dinv, double* G, int* bad, hipStream_t s);
+                          double* Dinv, double* SM, int* bad, hipStream_t s);
 void launch_build_coarsest(const CoarseGeom& g, const double* Ad, const double* Aoff,
                            const int* cmap_inv, int np, double* dense, hipStream_t s);
 template <typename S, typename T>

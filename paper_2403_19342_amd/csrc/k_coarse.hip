@@ -74,86 +74,185 @@ __device__ void build_planes(int agg, int* pos, int* off) {
 constexpr int kMaxLc = 23;   // padded widths up to target 20 + 3 (levels >= 3)
 constexpr int kNarrow = 13;  // widths up to target 10 + 3 get their own instantiations
 
-// y_c = (A_l u)_c for row a of child element c.  Blocks up to 9 wide: the
-// diagonal block, then one axis at a time both coupling blocks, every load
-// of an axis issued before its products (at the domain boundary from valid
-// stand-in rows of the element itself, whose sums a select then drops), so
-// a row waits for memory four times.  Wider blocks (register budget): the
-// diagonal block, then each coupling block inside the domain in turn.
-template <typename T, int LP = kMaxLc>
+// y_c = (A_l u)_c for row a of child element c: the diagonal block (symmetric:
+// its column, which neighbouring rows read side by side), then both coupling
+// blocks of each axis (at the domain boundary from valid stand-in rows of the
+// element itself, whose sums a select then drops).  ALL: every load of the row
+// is in flight at once, one wait for memory, for launches that leave the chip
+// idle; otherwise one axis at a time, four waits but half the registers.
+template <typename T, int LP, bool ALL>
 __device__ __forceinline__ T block_row_apply(const CoarseGeom& g, const T* __restrict__ Ad,
                                              const T* __restrict__ Aoff, const T* __restrict__ u, int c,
                                              int a) {
-    const int L = g.L;
+    constexpr bool RT = LP == kMaxLc;   // the widest serves every width above kNarrow
+    const int W = RT ? g.L : LP;
     const int cx = c % g.mx, cy = (c / g.mx) % g.my, cz = c / (g.mx * g.my);
-    const int cc[3] = {cx, cy, cz};
-    const int ext[3] = {g.mx, g.my, g.mz};
-    const int stride[3] = {1, g.mx, g.mx * g.my};
     T acc = T(0);
     {
-        const T* ad = Ad + ((size_t)c * L + a) * L;
-        const T* uc = u + (size_t)c * L;
+        const T* ad = Ad + (size_t)c * W * W + a;
+        const T* uc = u + (size_t)c * W;
+#pragma unroll
+        for (int b = 0; b < LP; ++b)
+            if (!RT || b < W) acc += ad[b * W] * uc[b];
+    }
+    auto axis = [&](int ax) {
+        const int cca = ax == 0 ? cx : (ax == 1 ? cy : cz);
+        const int exa = ax == 0 ? g.mx : (ax == 1 ? g.my : g.mz);
+        const int sta = ax == 0 ? 1 : (ax == 1 ? g.mx : g.mx * g.my);
+        const bool hp = cca + 1 < exa, hm = cca > 0;
+        const int cp = hp ? c + sta : c, cm = hm ? c - sta : c;
+        // A(c, c+e) = Aoff[c][ax]; A(c, c-e) = Aoff[c-e][ax]^T
+        const T* op = Aoff + (((size_t)c * 3 + ax) * W + a) * W;
+        const T* om = Aoff + ((size_t)cm * 3 + ax) * W * W + a;
+        const T* up = u + (size_t)cp * W;
+        const T* um = u + (size_t)cm * W;
+        T sp = T(0), sm = T(0);
 #pragma unroll
         for (int b = 0; b < LP; ++b) {
-            const int bb = b < L ? b : L - 1;
-            acc += (b < L ? ad[bb] : T(0)) * uc[bb];
+            if (RT && b >= W) continue;
+            sp += op[b] * up[b];
+            sm += om[b * W] * um[b];
         }
-    }
-    if constexpr (LP <= 9) {
-#pragma unroll 1
-        for (int ax = 0; ax < 3; ++ax) {
-            const int cca = ax == 0 ? cx : (ax == 1 ? cy : cz);
-            const int exa = ax == 0 ? g.mx : (ax == 1 ? g.my : g.mz);
-            const int sta = ax == 0 ? 1 : (ax == 1 ? g.mx : g.mx * g.my);
-            const bool hp = cca + 1 < exa, hm = cca > 0;
-            const int cp = hp ? c + sta : c, cm = hm ? c - sta : c;
-            // A(c, c+e) = Aoff[c][ax]; A(c, c-e) = Aoff[c-e][ax]^T
-            const T* op = Aoff + (((size_t)c * 3 + ax) * L + a) * L;
-            const T* om = Aoff + ((size_t)cm * 3 + ax) * L * L + a;
-            const T* up = u + (size_t)cp * L;
-            const T* um = u + (size_t)cm * L;
-            T sp = T(0), sm = T(0);
+        acc += hp ? sp : T(0);
+        acc += hm ? sm : T(0);
+    };
+    if constexpr (ALL && !RT) {
 #pragma unroll
-            for (int b = 0; b < LP; ++b) {
-                const int bb = b < L ? b : L - 1;
-                sp += (b < L ? op[bb] : T(0)) * up[bb];
-                sm += (b < L ? om[(size_t)bb * L] : T(0)) * um[bb];
-            }
-            acc += hp ? sp : T(0);
-            acc += hm ? sm : T(0);
-        }
+        for (int ax = 0; ax < 3; ++ax) axis(ax);
     } else {
-#pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            if (cc[ax] + 1 < ext[ax]) {
-                const int cn = c + stride[ax];
-                const T* o = Aoff + (((size_t)c * 3 + ax) * L + a) * L;
-                const T* un = u + (size_t)cn * L;
-#pragma unroll
-                for (int b = 0; b < LP; ++b) {
-                    const int bb = b < L ? b : L - 1;
-                    acc += (b < L ? o[bb] : T(0)) * un[bb];
-                }
-            }
-            if (cc[ax] > 0) {
-                const int cn = c - stride[ax];
-                const T* o = Aoff + ((size_t)cn * 3 + ax) * L * L;
-                const T* un = u + (size_t)cn * L;
-#pragma unroll
-                for (int b = 0; b < LP; ++b) {
-                    const int bb = b < L ? b : L - 1;
-                    acc += (b < L ? o[bb * L + a] : T(0)) * un[bb];
-                }
-            }
-        }
+#pragma unroll 1
+        for (int ax = 0; ax < 3; ++ax) axis(ax);
     }
     return acc;
 }
 
 constexpr int kCoarseThreads = 1024;   // upper bound; launches use agg^3 L rounded to waves
 constexpr int kMaxChildren = 64;   // agg <= 4
+constexpr int kRestrictParts4 = 4;   // parts of a parent's restricted residual (agg 4)
 constexpr int kMaxL = kMaxLc;      // set-up arrays of the levels >= 3
 constexpr int kMaxL2 = 16;         // level 2 (target <= 10)
+
+// ---- the residual's row, u staged in LDS ------------------------------------
+// The sweep's workgroup (agg 4) keeps u of its parent's children and of the
+// children across the parent's faces in LDS: 64 blocks in hyperplane order (as
+// the rows of the sweep), then face d = 2 ax (below) or 2 ax + 1 (above), 16
+// blocks each; beyond the domain zeros, so the products need no test.  The
+// rows of A are then the only loads of a row from memory.
+constexpr int kHaloBlocks = 160;
+
+template <typename T, int LP>
+__device__ __forceinline__ void stage_u(const CoarseGeom& g, const T* __restrict__ u, int E, T* sU) {
+    const int x0 = E % g.px * 4, y0 = E / g.px % g.py * 4, z0 = E / (g.px * g.py) * 4;
+    for (int t = threadIdx.x; t < kHaloBlocks * LP; t += blockDim.x) {
+        const int h = t / LP, b = t - h * LP;
+        int x, y, z;
+        if (h < 64) {
+            const int p = kCP.pos4[h];
+            x = x0 + (p & 3);
+            y = y0 + ((p >> 2) & 3);
+            z = z0 + (p >> 4);
+        } else {
+            const int d = (h - 64) >> 4, ax = d >> 1, i = h & 3, j = (h >> 2) & 3, o = (d & 1) ? 4 : -1;
+            x = x0 + (ax == 0 ? o : i);
+            y = y0 + (ax == 1 ? o : (ax == 0 ? i : j));
+            z = z0 + (ax == 2 ? o : j);
+        }
+        const bool in = x >= 0 && x < g.mx && y >= 0 && y < g.my && z >= 0 && z < g.mz;
+        sU[t] = in ? u[(size_t)(x + g.mx * (y + g.my * z)) * LP + b] : T(0);
+    }
+}
+
+// Row a of child c at hyperplane rank k, position pos of its parent: the loads
+// of A, then (after the barrier that publishes sU) the products.  The diagonal
+// block and FIRST axes are loaded at once, as many as the registers of a
+// workgroup hold (up to width 8 it has 256 a thread, wider ones 168), the
+// other axes in turn.
+template <typename T, int LP, int FIRST = LP <= 8 ? 3 : 1>
+struct ResidRow {
+    T ad[LP], op[FIRST][LP], om[FIRST][LP];
+
+    struct Place {
+        int c, a, k, qx, qy, qz, cx, cy, cz;
+    };
+
+    __device__ static __forceinline__ Place place(const CoarseGeom& g, int c, int a, int k, int pos) {
+        return {c, a, k, pos & 3, (pos >> 2) & 3, pos >> 4, c % g.mx, (c / g.mx) % g.my, c / (g.mx * g.my)};
+    }
+    // A(c, c) is symmetric, so its column a, which neighbouring rows read side
+    // by side, stands for its row; A(c, c+e) = Aoff[c][ax], A(c, c-e) = Aoff[c-e][ax]^T,
+    // beyond the domain any block of the array, against zeros
+    __device__ static __forceinline__ const T* above_row(const Place& p, const T* Aoff, int ax) {
+        return Aoff + (((size_t)p.c * 3 + ax) * LP + p.a) * LP;
+    }
+    __device__ static __forceinline__ const T* below_col(const CoarseGeom& g, const Place& p, const T* Aoff, int ax) {
+        const int st = ax == 0 ? 1 : (ax == 1 ? g.mx : g.mx * g.my);
+        const int x = ax == 0 ? p.cx : (ax == 1 ? p.cy : p.cz);
+        return Aoff + ((size_t)(x > 0 ? p.c - st : p.c) * 3 + ax) * LP * LP + p.a;
+    }
+    // block of sU next to p, above (up) or below along ax
+    __device__ static __forceinline__ int block(const Place& p, int ax, bool up) {
+        const int x = ax == 0 ? p.qx : (ax == 1 ? p.qy : p.qz);
+        const bool in = up ? x < 3 : x > 0;
+        const int pos = p.qx | (p.qy << 2) | (p.qz << 4), st = 1 << (2 * ax);
+        const int i = ax == 0 ? p.qy : p.qx, j = ax == 2 ? p.qy : p.qz;
+        return in ? kCP.rank4[up ? pos + st : pos - st] : 64 + ((2 * ax + (up ? 1 : 0)) << 4) + i + (j << 2);
+    }
+    __device__ __forceinline__ void load(const CoarseGeom& g, const Place& p, const T* __restrict__ Ad,
+                                         const T* __restrict__ Aoff) {
+#pragma unroll
+        for (int b = 0; b < LP; ++b) ad[b] = Ad[((size_t)p.c * LP + b) * LP + p.a];
+#pragma unroll
+        for (int ax = 0; ax < FIRST; ++ax) {
+            const T* po = above_row(p, Aoff, ax);
+            const T* pm = below_col(g, p, Aoff, ax);
+#pragma unroll
+            for (int b = 0; b < LP; ++b) {
+                op[ax][b] = po[b];
+                om[ax][b] = pm[b * LP];
+            }
+        }
+    }
+    __device__ __forceinline__ T apply(const CoarseGeom& g, const Place& p, const T* __restrict__ Aoff,
+                                       const T* sU) const {
+        T acc = T(0);
+#pragma unroll
+        for (int b = 0; b < LP; ++b) acc += ad[b] * sU[p.k * LP + b];
+#pragma unroll
+        for (int ax = 0; ax < FIRST; ++ax) {
+            const T* up = sU + block(p, ax, true) * LP;
+            const T* um = sU + block(p, ax, false) * LP;
+            T sp = T(0), sm = T(0);
+#pragma unroll
+            for (int b = 0; b < LP; ++b) {
+                sp += op[ax][b] * up[b];
+                sm += om[ax][b] * um[b];
+            }
+            acc += sp + sm;
+        }
+        if constexpr (FIRST < 3) __builtin_amdgcn_sched_barrier(0);   // the rest's loads stay behind: registers
+#pragma unroll 1
+        for (int ax = FIRST; ax < 3; ++ax) {
+            const T* po = above_row(p, Aoff, ax);
+            const T* pm = below_col(g, p, Aoff, ax);
+            const T* up = sU + block(p, ax, true) * LP;
+            const T* um = sU + block(p, ax, false) * LP;
+            T sp = T(0), sm = T(0);
+#pragma unroll
+            for (int b = 0; b < LP; ++b) {
+                sp += po[b] * up[b];
+                sm += pm[b * LP] * um[b];
+            }
+            acc += sp + sm;
+        }
+        return acc;
+    }
+};
+
+// parents of one sweep workgroup: with 2x aggregation as many as fill about 512
+// threads (a parent has 8 W rows), otherwise one
+constexpr int sweep_parents(int agg, int W) {
+    return agg != 2 ? 1 : (512 / (8 * W) < 1 ? 1 : (512 / (8 * W) > kMaxChildren / 8 ? kMaxChildren / 8 : 512 / (8 * W)));
+}
 
 // Level-l smoother on parent E, both substitutions in one kernel:
 //   t = r (mode 0) or t = r - A_l u (mode 1)
@@ -164,20 +263,30 @@ constexpr int kMaxL2 = 16;         // level 2 (target <= 10)
 // the rows of its lower and upper couplings G in registers; only y lives in
 // LDS.  A plane step is one LDS read per coupling entry, the products, a store
 // and a barrier.  Missing neighbours read the thread's own child with weight 0.
-template <typename T, int LP, bool A2>
-__global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, const T* __restrict__ Ad,
-                                                      const T* __restrict__ Aoff, const T* __restrict__ Dinv,
-                                                      const T* __restrict__ G, const T* __restrict__ r,
-                                                      const T* u, T* out, const Scalars* sc, int check_done,
-                                                      int npar) {
+// SM holds D^-1 and the couplings as the threads read them: per parent the
+// matrices d (0: D^-1; agg 4: 1 + 2 ax below, 2 + 2 ax above; agg 2, where a
+// child has one sibling along an axis: 1 + ax), each column b of all the rows
+// side by side.
+// With few parents the time of a workgroup is a chain: at 64 parents of 64 x 9
+// rows the rows' arrival (0.3 MB a CU at 20 to 30 bytes a clock) takes 14k
+// clocks of 32k, the 20 plane steps 11.5k (LDS reads), in mode 1 the residual
+// 15k more.  With rows read from row-major blocks, one axis at a time, mode 0
+// took 16.2 us and mode 1 19.1; now 12.9 and 17.7 (64 parents of 64 x 9) and
+// 9.8 / 13.4 -> 9.1 / 13.2 (27 of 64 x 7).
+template <typename T, int LP, bool A2, int MODE>
+__global__ __launch_bounds__(A2 ? 512 : 64 * LP) void k_coarse_sweep(
+    CoarseGeom g, const T* __restrict__ Ad, const T* __restrict__ Aoff, const T* __restrict__ SM,
+    T* __restrict__ r, const T* u, T* out, const Scalars* sc, int check_done, int npar, int nparts) {
     if (check_done && sc->done) return;
-    __shared__ T sY[kMaxChildren * LP];
     // row width: LP, except in the widest instantiation, which serves every
     // width above kNarrow (entries b >= W are neither read nor written)
     constexpr bool RT = LP == kMaxLc;
+    constexpr int MAXP = sweep_parents(A2 ? 2 : 4, RT ? kNarrow + 1 : LP);
+    __shared__ T sY[MAXP * (A2 ? 8 : 64) * LP];
+    __shared__ T sU[MODE && !A2 ? kHaloBlocks * LP : 1];
     const int W = RT ? g.L : LP;
-    const int agg = g.agg, nc = agg * agg * agg, sh = log2_agg(agg);
-    const int nplanes = 3 * (agg - 1) + 1;
+    constexpr int agg = A2 ? 2 : 4, nc = agg * agg * agg, sh = A2 ? 1 : 2;
+    constexpr int nplanes = 3 * (agg - 1) + 1;
     // npar parents per workgroup (several when a parent has few rows, so
     // that the wavefronts are full), each with its own nc * W rows of sY
     const int per = nc * W;
@@ -186,10 +295,10 @@ __global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, co
     const bool row_ok = qp < npar && E < g.M;
     const int base = row_ok ? qp * per : 0;
     const int k = row_ok ? tt / W : 0, a = tt % W;
-    const int p = agg == 4 ? kCP.pos4[k] : kCP.pos2[k];
+    const int p = A2 ? kCP.pos2[k] : kCP.pos4[k];
     const int q[3] = {p & (agg - 1), (p >> sh) & (agg - 1), p >> (2 * sh)};
     const int plane = q[0] + q[1] + q[2];
-    const int c = child_of(g, E, p);
+    const int c = child_of(g, row_ok ? E : 0, p);
     // neighbour rows in LDS and weights per direction (lower: 2 ax, upper: 2 ax + 1)
     int nb[6];
     T wgt[6];
@@ -199,7 +308,7 @@ __global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, co
         const bool in = (d & 1) ? (q[ax] < agg - 1) : (q[ax] > 0);
         const int step = 1 << (sh * ax);
         const int pn = in ? ((d & 1) ? p + step : p - step) : p;
-        nb[d] = base + (agg == 4 ? kCP.rank4[pn] : kCP.rank2[pn]) * W;
+        nb[d] = base + (A2 ? kCP.rank2[pn] : kCP.rank4[pn]) * W;
         wgt[d] = in ? T(1) : T(0);
     }
     // slots beyond the child's kept count are zero rows of every block: their
@@ -207,64 +316,51 @@ __global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, co
     const bool live = row_ok && (g.nkeep == nullptr || a < g.nkeep[c]);
     // right-hand side t = r (- A_l u): all loads of the row first
     const size_t row = (size_t)c * W + a;
-    T tv = live ? r[row] : T(0);
-    if (mode && live) {
-        const int cx = c % g.mx, cy = (c / g.mx) % g.my, cz = c / (g.mx * g.my);
-        T acc = T(0);
-#pragma unroll
-        for (int b = 0; b < LP; ++b)
-            if (!RT || b < W) acc += Ad[row * W + b] * u[(size_t)c * W + b];
-        // one direction at a time keeps the loads in flight to 4 LP values
-#pragma unroll 1
-        for (int ax = 0; ax < 3; ++ax) {
-            const int cca = ax == 0 ? cx : (ax == 1 ? cy : cz);
-            const int exa = ax == 0 ? g.mx : (ax == 1 ? g.my : g.mz);
-            const int sta = ax == 0 ? 1 : (ax == 1 ? g.mx : g.mx * g.my);
-            const bool hp = cca + 1 < exa, hm = cca > 0;
-            const int cp = hp ? c + sta : c, cm = hm ? c - sta : c;
-            const T wp = hp ? T(1) : T(0), wm = hm ? T(1) : T(0);
-            T sp = T(0), sm = T(0);
-#pragma unroll
-            for (int b = 0; b < LP; ++b) {
-                // A(c, c+e) = Aoff[c][ax]; A(c, c-e) = Aoff[c-e][ax]^T
-                if (RT && b >= W) continue;
-                sp += Aoff[(((size_t)c * 3 + ax) * W + a) * W + b] * u[(size_t)cp * W + b];
-                sm += Aoff[(((size_t)cm * 3 + ax) * W + b) * W + a] * u[(size_t)cm * W + b];
-            }
-            acc += wp * sp + wm * sm;
+    T tv = T(0), own = T(0);
+    if (live) {
+        tv = r[row];
+        // the restriction's partial sums, in order; their sum is kept in r
+        for (int i = 1; MODE == 0 && i < nparts; ++i) tv += r[row + (size_t)i * g.m * W];
+    }
+    if (MODE == 0 && nparts > 1 && live) r[row] = tv;
+    if constexpr (MODE && A2) {
+        if (live) {
+            own = u[row];
+            tv -= block_row_apply<T, LP, false>(g, Ad, Aoff, u, c, a);
         }
-        tv -= acc;
+    } else if constexpr (MODE) {
+        using Row = ResidRow<T, LP>;
+        const auto at = Row::place(g, c, a, k, p);
+        Row rr;
+        if (live) rr.load(g, at, Ad, Aoff);
+        stage_u<T, LP>(g, u, blockIdx.x, sU);
+        __syncthreads();
+        if (live) {
+            tv -= rr.apply(g, at, Aoff, sU);
+            own = sU[k * W + a];
+        }
     }
     if (row_ok) sY[t] = tv;
-    // lower coupling rows G[c][2 ax][a][0..LP-1] and the pivot row, loaded
-    // while the block synchronises; at widths up to 8 the upper rows too
-    // (one memory round less), wider ones follow the forward sweep so that
-    // the two sets are never live together
-    // A2 (agg = 2): along each axis a child couples to exactly one sibling,
-    // below or above it, so gl[ax] holds that one coupling row, all loaded
-    // here, and the sweeps weight it by direction (gu unused)
-    constexpr bool kUpperEarly = LP <= 8 && !A2;
-    // couplings to children outside the parent are never loaded (with
-    // agg = 2 half of them)
+    // The rows of D^-1 and of the couplings, loaded while the block
+    // synchronises: up to width 9 all at once, wider ones (register budget)
+    // load the upper couplings after the forward sweep.  A2 (agg = 2): along
+    // each axis a child couples to exactly one sibling, below or above it, so
+    // gl[ax] holds that one row, and the sweeps weight it by direction (gu
+    // unused).  Couplings to children outside the parent are never loaded.
+    constexpr bool kUpperEarly = LP <= 9 && !A2;
+    constexpr int ND = A2 ? 4 : 7;
     T gl[3][LP], gu[3][LP], dv[LP];
+    const T* sm = SM + (size_t)(row_ok ? E : 0) * ND * W * per + (row_ok ? tt : 0);
+    auto load_row = [&](int d, bool in, T* dst) {
 #pragma unroll
-    for (int ax = 0; ax < 3; ++ax) {
-        const bool lo = wgt[2 * ax] != T(0);
-        const bool in = live && (A2 || lo);
-        const int d = (A2 && !lo) ? 2 * ax + 1 : 2 * ax;
+        for (int b = 0; b < LP; ++b) dst[b] = in && (!RT || b < W) ? sm[((size_t)d * W + b) * per] : T(0);
+    };
+    load_row(0, live, dv);
 #pragma unroll
-        for (int b = 0; b < LP; ++b) gl[ax][b] = in && (!RT || b < W) ? G[(((size_t)c * 6 + d) * W + a) * W + b] : T(0);
-    }
-#pragma unroll
-    for (int b = 0; b < LP; ++b) dv[b] = live && (!RT || b < W) ? Dinv[row * W + b] : T(0);
+    for (int ax = 0; ax < 3; ++ax) load_row(A2 ? 1 + ax : 1 + 2 * ax, live && (A2 || wgt[2 * ax] != T(0)), gl[ax]);
     if (kUpperEarly) {
 #pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            const bool in = live && wgt[2 * ax + 1] != T(0);
-#pragma unroll
-            for (int b = 0; b < LP; ++b)
-                gu[ax][b] = in && (!RT || b < W) ? G[(((size_t)c * 6 + 2 * ax + 1) * W + a) * W + b] : T(0);
-        }
+        for (int ax = 0; ax < 3; ++ax) load_row(2 + 2 * ax, live && wgt[2 * ax + 1] != T(0), gu[ax]);
     }
     __syncthreads();
     T w = T(0);
@@ -299,12 +395,7 @@ __global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, co
     // backward: z = y - sum_upper G z
     if (!kUpperEarly && !A2) {
 #pragma unroll
-        for (int ax = 0; ax < 3; ++ax) {
-            const bool in = live && wgt[2 * ax + 1] != T(0);
-#pragma unroll
-            for (int b = 0; b < LP; ++b)
-                gu[ax][b] = in && (!RT || b < W) ? G[(((size_t)c * 6 + 2 * ax + 1) * W + a) * W + b] : T(0);
-        }
+        for (int ax = 0; ax < 3; ++ax) load_row(2 + 2 * ax, live && wgt[2 * ax + 1] != T(0), gu[ax]);
     }
     T z = T(0);
     for (int s = nplanes - 1; s >= 0; --s) {
@@ -335,53 +426,48 @@ __global__ __launch_bounds__(768) void k_coarse_sweep(CoarseGeom g, int mode, co
         }
         __syncthreads();
     }
-    if (row_ok) out[row] = mode ? u[row] + z : z;
+    if (row_ok) out[row] = MODE ? own + z : z;
 }
 
-// s = r - A_l u on the children of E, then r_up[E] = V_E^T s
-template <typename T, int LP, int LU>
-__global__ __launch_bounds__(kCoarseThreads) void k_coarse_resid_restrict(
+// s = r - A_l u on the children of parent E, then r_up[E] = V_E^T s, one row a
+// thread.  With agg 4 a workgroup takes one z plane of a parent's children and
+// writes its part of the sum (part p at r_up + p M Lup; the kernel that reads
+// r_up next adds the parts in order): a parent is a small task for 16 W rows
+// of latency, and levels of 27 to 64 parents left most of the chip idle.
+template <typename T, int LP, int LU, bool A2>
+__global__ __launch_bounds__(((A2 ? 8 : 16) * LP + 63) / 64 * 64) __attribute__((amdgpu_waves_per_eu(A2 ? 4 : 2))) void k_coarse_resid_restrict(
     CoarseGeom g, const T* __restrict__ Ad, const T* __restrict__ Aoff, const T* __restrict__ r,
     const T* __restrict__ u, const T* __restrict__ V, const int* __restrict__ nkeep_up, int Lup,
     T* __restrict__ rup, const Scalars* sc, int check_done) {
     if (check_done && sc->done) return;
-    __shared__ T sS[kMaxChildren * kMaxL];
-    __shared__ double sred[kCoarseThreads / 64];
-    const int E = blockIdx.x;
-    const int L = g.L, nc = g.agg * g.agg * g.agg, n = nc * L;
-    for (int t = threadIdx.x; t < n; t += blockDim.x) {
-        const int p = t / L, a = t % L;
-        const int c = child_of(g, E, p);
-        const bool live = g.nkeep == nullptr || a < g.nkeep[c];   // zero rows beyond the kept slots
-        sS[t] = live ? r[(size_t)c * L + a] - block_row_apply<T, LP>(g, Ad, Aoff, u, c, a) : T(0);
-    }
-    __syncthreads();
+    constexpr bool RT = LP == kMaxLc;
+    constexpr int PARTS = A2 ? 1 : kRestrictParts4, NC = A2 ? 8 : 64;
+    __shared__ double sacc[(16 * LP + 63) / 64][LU];
+    const int E = blockIdx.x / PARTS, part = blockIdx.x % PARTS;
+    const int W = RT ? g.L : LP, n = NC * W, rows = n / PARTS;
     const int nk = nkeep_up[E];
-    double acc[LU];
+    const int t = threadIdx.x, tr = t < rows ? t : 0;
+    const int p = part * (NC / PARTS) + tr / W, a = tr % W;
+    const int c = child_of(g, E, p);
+    const bool live = t < rows && (g.nkeep == nullptr || a < g.nkeep[c]);   // zero rows beyond the kept slots
+    const T* v = V + (size_t)E * Lup * n + (size_t)p * W + a;
+    T vv[LU];
 #pragma unroll
-    for (int j = 0; j < LU; ++j) acc[j] = 0.0;
-    for (int t = threadIdx.x; t < n; t += blockDim.x) {
-        const double sv = (double)sS[t];
-#pragma unroll
-        for (int j = 0; j < LU; ++j) {
-            const int jj = j < nk ? j : nk - 1;
-            acc[j] += (j < nk ? (double)V[((size_t)E * Lup + jj) * n + t] : 0.0) * sv;
-        }
-    }
-    __shared__ double sacc[kCoarseThreads / 64][LU];
+    for (int j = 0; j < LU; ++j) vv[j] = live ? v[(size_t)(j < nk ? j : nk - 1) * n] : T(0);
+    double sv = 0.0;
+    if (live) sv = (double)(r[(size_t)c * W + a] - block_row_apply<T, LP, !A2>(g, Ad, Aoff, u, c, a));
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
     for (int j = 0; j < LU; ++j) {
-        const double v = wave_sum(acc[j]);
-        if (lane == 0) sacc[w][j] = v;
+        const double x = wave_sum((double)vv[j] * sv);
+        if (lane == 0) sacc[w][j] = x;
     }
     __syncthreads();
     if ((int)threadIdx.x < Lup) {
-        double t = 0.0;
-        for (int ww = 0; ww < (int)(blockDim.x >> 6); ++ww) t += sacc[ww][threadIdx.x];
-        rup[(size_t)E * Lup + threadIdx.x] = (int)threadIdx.x < nk ? (T)t : T(0);
+        double x = 0.0;
+        for (int ww = 0; ww < (int)(blockDim.x >> 6); ++ww) x += sacc[ww][threadIdx.x];
+        rup[((size_t)part * g.M + E) * Lup + threadIdx.x] = (int)threadIdx.x < nk ? (T)x : T(0);
     }
-    (void)sred;
 }
 
 // u += V_E e_up[E] on the children of E
@@ -418,11 +504,26 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_prolong(CoarseGeom g,
 // rows a full row apart share few HBM channels and ran at 2.2 TB/s).
 constexpr int kCoarsestRows = 16;
 
+// value of a level vector that arrives in nparts parts, pstride apart
 template <typename T>
-__global__ void k_gather_compact(int n, const int* __restrict__ cmap, const T* __restrict__ r,
+__device__ __forceinline__ T gather_parts(const T* r, int nparts, int64_t pstride) {
+    T v = r[0];
+    if (nparts == kRestrictParts4) {
+        T w[kRestrictParts4 - 1];
+#pragma unroll
+        for (int i = 1; i < kRestrictParts4; ++i) w[i - 1] = r[i * pstride];
+#pragma unroll
+        for (int i = 1; i < kRestrictParts4; ++i) v += w[i - 1];
+    }
+    return v;
+}
+
+template <typename T>
+__global__ void k_gather_compact(int n, const int* __restrict__ cmap, const T* __restrict__ r, int nparts, int64_t pstride,
                                  double* __restrict__ rc, const Scalars* sc, int check_done) {
     if (check_done && sc->done) return;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) rc[i] = (double)r[cmap[i]];
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
+        rc[i] = (double)gather_parts(r + cmap[i], nparts, pstride);
 }
 
 template <typename T>
@@ -470,8 +571,9 @@ __global__ __launch_bounds__(256) void k_coarsest_rows(int n, int np, const doub
 // itself from the level vector r through cmap, so no separate gather launch)
 template <typename T, int RW>
 __global__ __launch_bounds__(256) void k_coarsest(int n, int np, const double* __restrict__ Pinv,
-                                                   const int* __restrict__ cmap, const T* __restrict__ r,
-                                                   T* __restrict__ e, const Scalars* sc, int check_done) {
+                                                   const int* __restrict__ cmap, const T* __restrict__ r, int nparts,
+                                                   int64_t pstride, T* __restrict__ e, const Scalars* sc,
+                                                   int check_done) {
     if (check_done && sc->done) return;
     extern __shared__ double srz[];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -482,7 +584,7 @@ __global__ __launch_bounds__(256) void k_coarsest(int n, int np, const double* _
     for (int c0 = 0; c0 < n; c0 += kCoarsestChunk) {
         const int cn = min(kCoarsestChunk, n - c0);
         if (c0) __syncthreads();
-        for (int j = threadIdx.x; j < cn; j += blockDim.x) srz[j] = (double)r[cmap[c0 + j]];
+        for (int j = threadIdx.x; j < cn; j += blockDim.x) srz[j] = (double)gather_parts(r + cmap[c0 + j], nparts, pstride);
         __syncthreads();
         for (int j = lane; j < cn; j += 64) {
             const double v = srz[j];
@@ -910,32 +1012,42 @@ __global__ __launch_bounds__(64 * kMaxPlane) void k_blockic_setup(CoarseGeom g, 
     }
 }
 
-// G[c][2ax] = Dinv_c A(c, c - e_ax), G[c][2ax+1] = Dinv_c A(c, c + e_ax) for
-// neighbours inside the same parent (zero otherwise)
+// the sweep's matrices: Dinv_c, and Dinv_c A(c, c -+ e_ax) for neighbours
+// inside the same parent (zero otherwise), in the layout of k_coarse_sweep
 __global__ __launch_bounds__(256) void k_blockic_couple(CoarseGeom g, const double* __restrict__ Aoff,
-                                                         const double* __restrict__ Dinv, double* __restrict__ G) {
+                                                         const double* __restrict__ Dinv, double* __restrict__ SM) {
     const int c = blockIdx.x;
-    const int L = g.L, LL = L * L, agg = g.agg;
+    const int L = g.L, LL = L * L, agg = g.agg, nc = agg * agg * agg;
     const int cx = c % g.mx, cy = (c / g.mx) % g.my, cz = c / (g.mx * g.my);
     const int q[3] = {cx % agg, cy % agg, cz % agg};
     const int stride[3] = {1, g.mx, g.mx * g.my};
+    const int E = cx / agg + g.px * (cy / agg + g.py * (cz / agg)), pos = q[0] + agg * (q[1] + agg * q[2]);
+    const int k = agg == 4 ? kCP.rank4[pos] : kCP.rank2[pos], nd = agg == 4 ? 7 : 4, rows = nc * L;
     const double* Di = Dinv + (size_t)c * LL;
-    for (int t = threadIdx.x; t < 6 * LL; t += blockDim.x) {
-        const int d = t / LL, a = (t % LL) / L, b = t % L;
-        const int ax = d >> 1;
-        const bool upper = d & 1;
+    for (int t = threadIdx.x; t < nd * LL; t += blockDim.x) {
+        const int d = t / LL, b = (t % LL) / L, a = t % L;
         double v = 0.0;
-        if (upper ? (q[ax] < agg - 1) : (q[ax] > 0)) {
-            for (int k = 0; k < L; ++k) {
-                // A(c, c - e) = Aoff[c - e][ax]^T ; A(c, c + e) = Aoff[c][ax]
-                const double A = upper ? Aoff[(((size_t)c * 3 + ax) * L + k) * L + b]
-                                       : Aoff[(((size_t)(c - stride[ax]) * 3 + ax) * L + b) * L + k];
-                v += Di[a * L + k] * A;
+        if (d == 0) {
+            v = Di[a * L + b];
+        } else {
+            const int ax = agg == 4 ? (d - 1) >> 1 : d - 1;
+            const bool upper = agg == 4 ? (d - 1) & 1 : q[ax] == 0;
+            if (upper ? (q[ax] < agg - 1) : (q[ax] > 0)) {
+                for (int i = 0; i < L; ++i) {
+                    // A(c, c - e) = Aoff[c - e][ax]^T ; A(c, c + e) = Aoff[c][ax]
+                    const double A = upper ? Aoff[(((size_t)c * 3 + ax) * L + i) * L + b]
+                                           : Aoff[(((size_t)(c - stride[ax]) * 3 + ax) * L + b) * L + i];
+                    v += Di[a * L + i] * A;
+                }
             }
         }
-        G[((size_t)c * 6 + d) * LL + a * L + b] = v;
+        SM[(((size_t)E * nd + d) * L + b) * rows + (size_t)k * L + a] = v;
     }
 }
+
+int coarse_restrict_parts(const CoarseGeom& g) { return g.agg == 4 ? kRestrictParts4 : 1; }
+
+size_t coarse_sweep_doubles(const CoarseGeom& g) { return (size_t)g.m * (g.agg == 4 ? 7 : 4) * g.L * g.L; }
 
 // coarsest dense matrix over the compact unknowns (cinv: padded -> compact
 // or -1); the matrix must be zeroed beforehand
@@ -976,18 +1088,50 @@ __global__ void k_convert(const S* __restrict__ src, T* __restrict__ dst, int64_
 // ---------------------------------------------------------------------------
 // launchers
 
-#define SPECMG_LP_DISPATCH(LV, ...)                           \
-    switch (LV) {                                             \
-        case 4: { constexpr int LP = 4; __VA_ARGS__; } break;     \
-        case 5: { constexpr int LP = 5; __VA_ARGS__; } break;     \
-        case 6: { constexpr int LP = 6; __VA_ARGS__; } break;     \
-        case 7: { constexpr int LP = 7; __VA_ARGS__; } break;     \
-        case 8: { constexpr int LP = 8; __VA_ARGS__; } break;     \
-        case 9: { constexpr int LP = 9; __VA_ARGS__; } break;     \
-        case 10: { constexpr int LP = 10; __VA_ARGS__; } break;   \
-        case 11: { constexpr int LP = 11; __VA_ARGS__; } break;   \
-        case 12: { constexpr int LP = 12; __VA_ARGS__; } break;   \
-        case 13: { constexpr int LP = 13; __VA_ARGS__; } break;   \
+#define SPECMG_LP_DISPATCH_NARROW(LV, ...) \
+    switch (LV) { \
+        case 4: { constexpr int LP = 4; __VA_ARGS__; } break; \
+        case 5: { constexpr int LP = 5; __VA_ARGS__; } break; \
+        case 6: { constexpr int LP = 6; __VA_ARGS__; } break; \
+        case 7: { constexpr int LP = 7; __VA_ARGS__; } break; \
+        case 8: { constexpr int LP = 8; __VA_ARGS__; } break; \
+        case 9: { constexpr int LP = 9; __VA_ARGS__; } break; \
+    }
+
+#define SPECMG_LP_DISPATCH_SWEEP4(LV, ...) \
+    switch (LV) { \
+        case 4: { constexpr int LP = 4; __VA_ARGS__; } break; \
+        case 5: { constexpr int LP = 5; __VA_ARGS__; } break; \
+        case 6: { constexpr int LP = 6; __VA_ARGS__; } break; \
+        case 7: { constexpr int LP = 7; __VA_ARGS__; } break; \
+        case 8: { constexpr int LP = 8; __VA_ARGS__; } break; \
+        case 9: { constexpr int LP = 9; __VA_ARGS__; } break; \
+        case 10: { constexpr int LP = 10; __VA_ARGS__; } break; \
+        case 11: { constexpr int LP = 11; __VA_ARGS__; } break; \
+        case 12: { constexpr int LP = 12; __VA_ARGS__; } break; \
+    }
+
+#define SPECMG_LP_DISPATCH_WIDE(LV, ...) \
+    switch (LV) { \
+        case 10: { constexpr int LP = 10; __VA_ARGS__; } break; \
+        case 11: { constexpr int LP = 11; __VA_ARGS__; } break; \
+        case 12: { constexpr int LP = 12; __VA_ARGS__; } break; \
+        case 13: { constexpr int LP = 13; __VA_ARGS__; } break; \
+        default: { constexpr int LP = kMaxLc; __VA_ARGS__; } break; \
+    }
+
+#define SPECMG_LP_DISPATCH(LV, ...) \
+    switch (LV) { \
+        case 4: { constexpr int LP = 4; __VA_ARGS__; } break; \
+        case 5: { constexpr int LP = 5; __VA_ARGS__; } break; \
+        case 6: { constexpr int LP = 6; __VA_ARGS__; } break; \
+        case 7: { constexpr int LP = 7; __VA_ARGS__; } break; \
+        case 8: { constexpr int LP = 8; __VA_ARGS__; } break; \
+        case 9: { constexpr int LP = 9; __VA_ARGS__; } break; \
+        case 10: { constexpr int LP = 10; __VA_ARGS__; } break; \
+        case 11: { constexpr int LP = 11; __VA_ARGS__; } break; \
+        case 12: { constexpr int LP = 12; __VA_ARGS__; } break; \
+        case 13: { constexpr int LP = 13; __VA_ARGS__; } break; \
         default: { constexpr int LP = kMaxLc; __VA_ARGS__; } break; \
     }
 
@@ -1024,7 +1168,7 @@ __global__ __launch_bounds__(256) void k_coarse_resid_restrict_w(
             for (int q = 1; q < 8; ++q) p += qr >= pre[q] ? 1 : 0;
             const int a = qr - pre[p];
             const int c = child_of(g, E, p);
-            const double sv = (double)(r[(size_t)c * L + a] - block_row_apply<T, LP>(g, Ad, Aoff, u, c, a));
+            const double sv = (double)(r[(size_t)c * L + a] - block_row_apply<T, LP, false>(g, Ad, Aoff, u, c, a));
             const T* vc = V + (size_t)E * Lup * n + (size_t)p * L + a;
 #pragma unroll
             for (int j = 0; j < LU; ++j)
@@ -1041,11 +1185,13 @@ __global__ __launch_bounds__(256) void k_coarse_resid_restrict_w(
 }
 
 template <typename T>
-void launch_coarse_resid_restrict(const CoarseGeom& g, const T* Ad, const T* Aoff, const T* r, const T* u,
+void launch_coarse_resid_restrict(const CoarseGeom& g0, const T* Ad, const T* Aoff, const T* r, const T* u,
                                   const T* V, const int* nkeep_up, int Lup, T* rup, const Scalars* sc,
                                   int check_done, hipStream_t s) {
-    const int rows = g.agg * g.agg * g.agg * g.L;
-    const int th = std::min(kCoarseThreads, (rows + 63) / 64 * 64);
+    CoarseGeom g = g0;
+    if (g.agg == 4 && g.M * kRestrictParts4 <= 256) g.nkeep = nullptr;   // as the sweeps
+    const int parts = coarse_restrict_parts(g), rows = g.agg * g.agg * g.agg * g.L / parts;
+    const int th = (rows + 63) / 64 * 64;
     if (g.L < 4 || g.L > kMaxLc) throw HipError{hipErrorInvalidValue, "coarse residual width"};
     if (Lup > kMaxLc) throw HipError{hipErrorInvalidValue, "coarse residual upper width"};
     // wider blocks keep about 8 L > 64 rows per parent, two passes of the
@@ -1053,20 +1199,27 @@ void launch_coarse_resid_restrict(const CoarseGeom& g, const T* Ad, const T* Aof
     if (g.agg == 2 && g.L <= 9) {
         const int nb = (g.M + 3) / 4;
         if (Lup <= kNarrow) {
-            SPECMG_LP_DISPATCH(g.L, hipLaunchKernelGGL((k_coarse_resid_restrict_w<T, LP, kNarrow>), dim3(nb),
+            SPECMG_LP_DISPATCH_NARROW(g.L, hipLaunchKernelGGL((k_coarse_resid_restrict_w<T, LP, kNarrow>), dim3(nb),
                                                        dim3(256), 0, s, g, Ad, Aoff, r, u, V, nkeep_up, Lup, rup, sc,
                                                        check_done));
         } else {
-            SPECMG_LP_DISPATCH(g.L, hipLaunchKernelGGL((k_coarse_resid_restrict_w<T, LP, kMaxLc>), dim3(nb),
+            SPECMG_LP_DISPATCH_NARROW(g.L, hipLaunchKernelGGL((k_coarse_resid_restrict_w<T, LP, kMaxLc>), dim3(nb),
                                                        dim3(256), 0, s, g, Ad, Aoff, r, u, V, nkeep_up, Lup, rup, sc,
                                                        check_done));
         }
-    } else if (Lup <= kNarrow) {
-        SPECMG_LP_DISPATCH(g.L, hipLaunchKernelGGL((k_coarse_resid_restrict<T, LP, kNarrow>), dim3(g.M), dim3(th), 0,
-                                                   s, g, Ad, Aoff, r, u, V, nkeep_up, Lup, rup, sc, check_done));
+    } else if (g.agg == 2) {
+        SPECMG_LP_DISPATCH_WIDE(g.L, if (Lup <= kNarrow)
+            hipLaunchKernelGGL((k_coarse_resid_restrict<T, LP, kNarrow, true>), dim3(g.M), dim3(th), 0, s, g, Ad, Aoff, r,
+                               u, V, nkeep_up, Lup, rup, sc, check_done);
+            else hipLaunchKernelGGL((k_coarse_resid_restrict<T, LP, kMaxLc, true>), dim3(g.M), dim3(th), 0, s, g, Ad, Aoff,
+                                    r, u, V, nkeep_up, Lup, rup, sc, check_done));
     } else {
-        SPECMG_LP_DISPATCH(g.L, hipLaunchKernelGGL((k_coarse_resid_restrict<T, LP, kMaxLc>), dim3(g.M), dim3(th), 0,
-                                                   s, g, Ad, Aoff, r, u, V, nkeep_up, Lup, rup, sc, check_done));
+        const dim3 nb(g.M * parts);
+        SPECMG_LP_DISPATCH(g.L, if (Lup <= kNarrow)
+            hipLaunchKernelGGL((k_coarse_resid_restrict<T, LP, kNarrow, false>), nb, dim3(th), 0, s, g, Ad, Aoff, r, u, V,
+                               nkeep_up, Lup, rup, sc, check_done);
+            else hipLaunchKernelGGL((k_coarse_resid_restrict<T, LP, kMaxLc, false>), nb, dim3(th), 0, s, g, Ad, Aoff, r, u,
+                                    V, nkeep_up, Lup, rup, sc, check_done));
     }
 }
 
@@ -1084,15 +1237,7 @@ void launch_coarse_prolong(const CoarseGeom& g, T* u, const T* V, const int* nke
                            check_done);
 }
 
-// dynamic LDS of the sweep kernels; couplings are staged when they fit
-// parents per sweep workgroup: with 2x aggregation as many as fill about
-// 512 threads (a parent has 8 L rows), otherwise one
-static int sweep_parents(const CoarseGeom& g) {
-    const int rows = g.agg * g.agg * g.agg * g.L;
-    if (g.agg != 2) return 1;
-    const int p = 512 / rows;
-    return p < 1 ? 1 : (p > kMaxChildren / 8 ? kMaxChildren / 8 : p);
-}
+static int sweep_parents(const CoarseGeom& g) { return sweep_parents(g.agg, g.L); }
 static int sweep_threads(const CoarseGeom& g) {
     const int rows = sweep_parents(g) * g.agg * g.agg * g.agg * g.L;
     return (rows + 63) / 64 * 64;
@@ -1102,34 +1247,38 @@ static int sweep_blocks(const CoarseGeom& g) {
     return (g.M + np - 1) / np;
 }
 
-// u = M_l^{-1} r
-template <typename T>
-void launch_coarse_smooth(const CoarseGeom& g, const T* Dinv, const T* G, const T* r, T* u, const Scalars* sc,
-                          int check_done, hipStream_t s) {
+template <typename T, int MODE>
+static void launch_sweep(const CoarseGeom& g0, const T* Ad, const T* Aoff, const T* SM, T* r, const T* u, T* out,
+                         const Scalars* sc, int check_done, int nparts, hipStream_t s) {
+    CoarseGeom g = g0;
     if (g.L < 4 || g.L > kMaxLc || sweep_threads(g) > 768) throw HipError{hipErrorInvalidValue, "coarse sweep shape"};
+    const dim3 nb(sweep_blocks(g)), th(sweep_threads(g));
+    const int npar = sweep_parents(g);
+    // launches of at most one workgroup a CU wait for latency, not for bandwidth:
+    // they take the padded rows too (zeros) instead of waiting for the kept counts
+    // (27 parents of 64 x 7 rows: 9.8 -> 9.1 us; 64 of 64 x 9: no difference)
+    if (sweep_blocks(g) <= 256) g.nkeep = nullptr;
     if (g.agg == 2) {
-        SPECMG_LP_DISPATCH(g.L, hipLaunchKernelGGL((k_coarse_sweep<T, LP, true>), dim3(sweep_blocks(g)), dim3(sweep_threads(g)), 0,
-                                                   s, g, 0, (const T*)nullptr, (const T*)nullptr, Dinv, G, r,
-                                                   (const T*)nullptr, u, sc, check_done, sweep_parents(g)));
+        SPECMG_LP_DISPATCH(g.L, hipLaunchKernelGGL((k_coarse_sweep<T, LP, true, MODE>), nb, th, 0, s, g, Ad, Aoff, SM, r, u,
+                                                   out, sc, check_done, npar, nparts));
     } else {
-        SPECMG_LP_DISPATCH(g.L, hipLaunchKernelGGL((k_coarse_sweep<T, LP, false>), dim3(sweep_blocks(g)), dim3(sweep_threads(g)), 0,
-                                                   s, g, 0, (const T*)nullptr, (const T*)nullptr, Dinv, G, r,
-                                                   (const T*)nullptr, u, sc, check_done, sweep_parents(g)));
+        SPECMG_LP_DISPATCH_SWEEP4(g.L, hipLaunchKernelGGL((k_coarse_sweep<T, LP, false, MODE>), nb, th, 0, s, g, Ad, Aoff,
+                                                          SM, r, u, out, sc, check_done, npar, nparts));
     }
+}
+
+// u = M_l^{-1} r; r arrives in nparts parts and is left summed
+template <typename T>
+void launch_coarse_smooth(const CoarseGeom& g, const T* SM, T* r, int nparts, T* u, const Scalars* sc, int check_done,
+                          hipStream_t s) {
+    launch_sweep<T, 0>(g, nullptr, nullptr, SM, r, nullptr, u, sc, check_done, nparts, s);
 }
 
 // e = u + M_l^{-1} (r - A_l u)
 template <typename T>
-void launch_coarse_resid_smooth(const CoarseGeom& g, const T* Ad, const T* Dinv, const T* Aoff, const T* G,
-                                const T* r, const T* u, T* e, const Scalars* sc, int check_done, hipStream_t s) {
-    if (g.L < 4 || g.L > kMaxLc || sweep_threads(g) > 768) throw HipError{hipErrorInvalidValue, "coarse sweep shape"};
-    if (g.agg == 2) {
-        SPECMG_LP_DISPATCH(g.L, hipLaunchKernelGGL((k_coarse_sweep<T, LP, true>), dim3(sweep_blocks(g)), dim3(sweep_threads(g)), 0,
-                                                   s, g, 1, Ad, Aoff, Dinv, G, r, u, e, sc, check_done, sweep_parents(g)));
-    } else {
-        SPECMG_LP_DISPATCH(g.L, hipLaunchKernelGGL((k_coarse_sweep<T, LP, false>), dim3(sweep_blocks(g)), dim3(sweep_threads(g)), 0,
-                                                   s, g, 1, Ad, Aoff, Dinv, G, r, u, e, sc, check_done, sweep_parents(g)));
-    }
+void launch_coarse_resid_smooth(const CoarseGeom& g, const T* Ad, const T* Aoff, const T* SM, const T* r, const T* u, T* e,
+                                const Scalars* sc, int check_done, hipStream_t s) {
+    launch_sweep<T, 1>(g, Ad, Aoff, SM, const_cast<T*>(r), u, e, sc, check_done, 1, s);
 }
 
 int coarsest_sym_tile() { return kSymT; }
@@ -1155,11 +1304,11 @@ void launch_pack_lower_tiles(const double* dense, int np, double* packed, hipStr
 }
 
 void launch_coarsest_sym(int n, int np, const double* packed, const int2* chunks, int nchunks, int maxc,
-                         const int* cmap, const double* r, double* e, double* rc, double* P, double* Q,
+                         const int* cmap, const double* r, int nparts, int64_t pstride, double* e, double* rc, double* P, double* Q,
                          const Scalars* sc, int check_done, hipStream_t s) {
     const int nT = np / kSymT;
     hipLaunchKernelGGL((k_gather_compact<double>), dim3(std::min((n + 255) / 256, 1024)), dim3(256), 0, s, n, cmap,
-                       r, rc, sc, check_done);
+                       r, nparts, pstride, rc, sc, check_done);
     SPECMG_TIMED_LAUNCH(k_coarsest_sym, dim3(nchunks), dim3(64 * kSymWaves), 0, s, nT, chunks, packed, rc, P, Q,
                         maxc, sc, check_done);
     hipLaunchKernelGGL((k_coarsest_sym_reduce<double>), dim3(nT), dim3(kSymT * kSymRedGroups), 0, s, nT, n, P, Q, maxc, cmap, e, sc,
@@ -1167,15 +1316,16 @@ void launch_coarsest_sym(int n, int np, const double* packed, const int2* chunks
 }
 
 template <typename T>
-void launch_coarsest(int n, int np, const double* Pinv, const int* cmap, const T* r, T* e, double* rc,
+void launch_coarsest(int n, int np, const double* Pinv, const int* cmap, const T* r, int nparts, int64_t pstride, T* e,
+                     double* rc,
                      const Scalars* sc, int check_done, hipStream_t s) {
     const size_t lds = (size_t)std::min(n, kCoarsestChunk) * sizeof(double);
     if (n <= kCoarsestChunk) {
-        SPECMG_TIMED_LAUNCH((k_coarsest<T, 1>), dim3((n + 3) / 4), dim3(256), lds, s, n, np, Pinv, cmap, r, e, sc,
-                            check_done);
+        SPECMG_TIMED_LAUNCH((k_coarsest<T, 1>), dim3((n + 3) / 4), dim3(256), lds, s, n, np, Pinv, cmap, r, nparts,
+                            pstride, e, sc, check_done);
     } else {
         hipLaunchKernelGGL((k_gather_compact<T>), dim3(std::min((n + 255) / 256, 1024)), dim3(256), 0, s, n, cmap, r,
-                           rc, sc, check_done);
+                           nparts, pstride, rc, sc, check_done);
         SPECMG_TIMED_LAUNCH((k_coarsest_rows<T>), dim3((n + kCoarsestRows - 1) / kCoarsestRows), dim3(256), lds, s,
                             n, np, Pinv, cmap, rc, e, sc, check_done);
     }
@@ -1196,13 +1346,13 @@ void launch_assemble_diag(const CoarseGeom& g, const double* Aint, const double*
 }
 
 void launch_blockic_setup(const CoarseGeom& g, const double* Ad, const double* Aoff, const int* nkeep,
-                          double* Dinv, double* G, int* bad, hipStream_t s) {
+                          double* Dinv, double* SM, int* bad, hipStream_t s) {
     // widest hyperplane of the parent's children: 3 (agg 2) or 12 (agg 4)
     const int wmax = g.agg == 2 ? 3 : kMaxPlane;
     const size_t shmem = (size_t)wmax * 3 * g.L * g.L * sizeof(double);
     if (g.L > kMaxL || shmem > 64 * 1024) throw HipError{hipErrorInvalidValue, "block-IC set-up shape"};
     hipLaunchKernelGGL(k_blockic_setup, dim3(g.M), dim3(64 * kMaxPlane), shmem, s, g, Ad, Aoff, nkeep, Dinv, bad);
-    hipLaunchKernelGGL(k_blockic_couple, dim3(g.m), dim3(256), 0, s, g, Aoff, Dinv, G);
+    hipLaunchKernelGGL(k_blockic_couple, dim3(g.m), dim3(256), 0, s, g, Aoff, Dinv, SM);
 }
 
 void launch_build_coarsest(const CoarseGeom& g, const double* Ad, const double* Aoff, const int* cinv, int np,
@@ -1218,10 +1368,8 @@ void launch_convert(const S* src, T* dst, int64_t n, hipStream_t s, const Scalar
     hipLaunchKernelGGL((k_convert<S, T>), dim3((int)b), dim3(256), 0, s, src, dst, n, sc);
 }
 
-template void launch_coarse_smooth<double>(const CoarseGeom&, const double*, const double*, const double*, double*,
-                                           const Scalars*, int, hipStream_t);
-template void launch_coarse_smooth<float>(const CoarseGeom&, const float*, const float*, const float*, float*,
-                                          const Scalars*, int, hipStream_t);
+template void launch_coarse_smooth<double>(const CoarseGeom&, const double*, double*, int, double*, const Scalars*, int, hipStream_t);
+template void launch_coarse_smooth<float>(const CoarseGeom&, const float*, float*, int, float*, const Scalars*, int, hipStream_t);
 template void launch_coarse_resid_restrict<double>(const CoarseGeom&, const double*, const double*, const double*,
                                                    const double*, const double*, const int*, int, double*,
                                                    const Scalars*, int, hipStream_t);
@@ -1232,15 +1380,13 @@ template void launch_coarse_prolong<double>(const CoarseGeom&, double*, const do
                                             const double*, const Scalars*, int, hipStream_t);
 template void launch_coarse_prolong<float>(const CoarseGeom&, float*, const float*, const int*, int, const float*,
                                            const Scalars*, int, hipStream_t);
-template void launch_coarse_resid_smooth<double>(const CoarseGeom&, const double*, const double*, const double*,
-                                                 const double*, const double*, const double*, double*,
-                                                 const Scalars*, int, hipStream_t);
-template void launch_coarse_resid_smooth<float>(const CoarseGeom&, const float*, const float*, const float*,
-                                                const float*, const float*, const float*, float*, const Scalars*,
-                                                int, hipStream_t);
-template void launch_coarsest<double>(int, int, const double*, const int*, const double*, double*, double*,
+template void launch_coarse_resid_smooth<double>(const CoarseGeom&, const double*, const double*, const double*, const double*,
+                                                 const double*, double*, const Scalars*, int, hipStream_t);
+template void launch_coarse_resid_smooth<float>(const CoarseGeom&, const float*, const float*, const float*, const float*,
+                                                 const float*, float*, const Scalars*, int, hipStream_t);
+template void launch_coarsest<double>(int, int, const double*, const int*, const double*, int, int64_t, double*, double*,
                                       const Scalars*, int, hipStream_t);
-template void launch_coarsest<float>(int, int, const double*, const int*, const float*, float*, double*,
+template void launch_coarsest<float>(int, int, const double*, const int*, const float*, int, int64_t, float*, double*,
                                      const Scalars*, int, hipStream_t);
 template void launch_convert<double, float>(const double*, float*, int64_t, hipStream_t, const Scalars*);
 template void launch_convert<float, double>(const float*, double*, int64_t, hipStream_t, const Scalars*);

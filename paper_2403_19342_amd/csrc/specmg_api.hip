@@ -54,8 +54,7 @@ struct Level {
     double* D = nullptr;
     double* Aoff = nullptr;
     double* Ad = nullptr;
-    double* Dinv = nullptr;
-    double* G = nullptr;       // D_c^{-1} A(c, neighbour) for the smoother
+    double* SM = nullptr;      // D_c^{-1} and D_c^{-1} A(c, neighbour), laid out for the smoother
     double* z = nullptr;
     float* basis32 = nullptr;  // level 2, the mixed modes: float32 copy of the basis
     double *r = nullptr, *u = nullptr, *e = nullptr;
@@ -232,36 +231,34 @@ void coarse_cycle(specmg_ctx* c, size_t li, int check, hipStream_t s) {
     Level& lv = c->lev[li];
     double* r = lv.r;
     double* e = lv.e;
+    const int parts = li > 0 ? coarse_restrict_parts(c->lev[li - 1].g) : 1;
+    const int64_t pstride = (int64_t)lv.g.m * lv.L;
     if (li + 1 == c->lev.size()) {
         const size_t ev = prof_begin(c, s);
         if (c->Psym)
-            launch_coarsest_sym(c->nL, c->npL, c->Psym, c->sym_chunks, c->sym_nchunks, c->sym_maxc, c->cmap, r, e,
+            launch_coarsest_sym(c->nL, c->npL, c->Psym, c->sym_chunks, c->sym_nchunks, c->sym_maxc, c->cmap, r, parts, pstride, e,
                                 c->rc, c->sym_P, c->sym_Q, c->sc, check, s);
         else
-            launch_coarsest<double>(c->nL, c->npL, c->Pinv, c->cmap, r, e, c->rc, c->sc, check, s);
+            launch_coarsest<double>(c->nL, c->npL, c->Pinv, c->cmap, r, parts, pstride, e, c->rc, c->sc, check, s);
         prof_end(c, ev, PC_COARSEST, s);
         return;
     }
     Level& up = c->lev[li + 1];
-    double* u = lv.u;
-    // a repeated sweep u += M^-1 (r - A u) reads neighbouring blocks' u, so
-    // it writes e (free until the last sweep) and copies back
-    const int64_t nrow = (int64_t)lv.g.m * lv.g.L;
-    launch_coarse_smooth<double>(lv.g, lv.Dinv, lv.G, r, u, c->sc, check, s);
-    const Scalars* gate = check ? c->sc : nullptr;
-    for (int it = 1; it < c->nu_c; ++it) {
-        launch_coarse_resid_smooth<double>(lv.g, lv.Ad, lv.Dinv, lv.Aoff, lv.G, r, u, e, c->sc, check, s);
-        launch_copy(u, e, nrow, s, gate);
-    }
-    launch_coarse_resid_restrict<double>(lv.g, lv.Ad, lv.Aoff, r, u, up.basis, up.nkeep, up.L, up.r, c->sc, check,
+    // a sweep u += M^-1 (r - A u) reads neighbouring blocks' u, so repeated ones
+    // alternate between the level's two vectors; after each half of the cycle the
+    // iterate is in x, from where the nu_c sweeps of the second half end in e
+    double* const buf[2] = {lv.u, e};
+    const int x = c->nu_c % 2 ? 0 : 1;
+    int at = (x + c->nu_c - 1) % 2;
+    launch_coarse_smooth<double>(lv.g, lv.SM, r, parts, buf[at], c->sc, check, s);
+    for (int it = 1; it < c->nu_c; ++it, at ^= 1)
+        launch_coarse_resid_smooth<double>(lv.g, lv.Ad, lv.Aoff, lv.SM, r, buf[at], buf[at ^ 1], c->sc, check, s);
+    launch_coarse_resid_restrict<double>(lv.g, lv.Ad, lv.Aoff, r, buf[x], up.basis, up.nkeep, up.L, up.r, c->sc, check,
                                          s);
     coarse_cycle(c, li + 1, check, s);
-    launch_coarse_prolong<double>(lv.g, u, up.basis, up.nkeep, up.L, up.e, c->sc, check, s);
-    for (int it = 1; it < c->nu_c; ++it) {
-        launch_coarse_resid_smooth<double>(lv.g, lv.Ad, lv.Dinv, lv.Aoff, lv.G, r, u, e, c->sc, check, s);
-        launch_copy(u, e, nrow, s, gate);
-    }
-    launch_coarse_resid_smooth<double>(lv.g, lv.Ad, lv.Dinv, lv.Aoff, lv.G, r, u, e, c->sc, check, s);
+    launch_coarse_prolong<double>(lv.g, buf[x], up.basis, up.nkeep, up.L, up.e, c->sc, check, s);
+    for (int it = 0; it < c->nu_c; ++it, at ^= 1)
+        launch_coarse_resid_smooth<double>(lv.g, lv.Ad, lv.Aoff, lv.SM, r, buf[at], buf[at ^ 1], c->sc, check, s);
 }
 
 // One repeated fine sweep u1 += M^-1 (r - A u1): the residual, the sweep
@@ -495,9 +492,9 @@ static int do_setup(specmg_ctx* c, const double* perm, hipStream_t s) {
         launch_galerkin2(fg, c->kt, lv.basis, lv.nkeep, L, lv.D, lv.Aoff, s);
         launch_assemble_diag(lv.g, lv.Aint, lv.D, lv.Ad, s);
     }
-    // ---- levels 3..levels (the eigensolves' workspaces are kept until the
-    // stream has been waited for below)
-    std::vector<std::unique_ptr<DevBuf>> eig_ws;
+    // ---- levels 3..levels (set-up workspaces are kept until the stream has been
+    // waited for below)
+    std::vector<std::unique_ptr<DevBuf>> setup_ws;
     for (int li = 1; li < levels - 1; ++li) {
         Level& lo = c->lev[li - 1];
         Level& up = c->lev[li];
@@ -528,8 +525,8 @@ static int do_setup(specmg_ctx* c, const double* perm, hipStream_t s) {
         up.Ad = c->alloc<double>((size_t)m * Lu * Lu);
         up.z = c->alloc<double>((size_t)m * Lu);
         double* hd = c->alloc<double>((size_t)lo.g.m * lo.L * lo.L);
-        eig_ws.emplace_back(new DevBuf(c->al, eig_up_work_doubles(lo.g, up.g, c->nvec_cc) * sizeof(double)));
-        launch_eig_up(lo.g, up.g, lo.Aint, lo.D, lo.Aoff, lo.nkeep, lo.z, hd, (double*)eig_ws.back()->p, c->target_cc, c->nvec_cc, tol, crtol,
+        setup_ws.emplace_back(new DevBuf(c->al, eig_up_work_doubles(lo.g, up.g, c->nvec_cc) * sizeof(double)));
+        launch_eig_up(lo.g, up.g, lo.Aint, lo.D, lo.Aoff, lo.nkeep, lo.z, hd, (double*)setup_ws.back()->p, c->target_cc, c->nvec_cc, tol, crtol,
                       c->thr_cc, up.basis, up.lam, up.nkeep, up.Aint, up.z, up.status, s);
         launch_galerkin_up(lo.g, up.g, lo.D, lo.Aoff, up.basis, up.nkeep, up.D, up.Aoff, s);
         launch_assemble_diag(up.g, up.Aint, up.D, up.Ad, s);
@@ -537,9 +534,9 @@ static int do_setup(specmg_ctx* c, const double* perm, hipStream_t s) {
     // ---- smoothers of the non-coarsest coarse levels
     for (int li = 0; li < levels - 2; ++li) {
         Level& lv = c->lev[li];
-        lv.Dinv = c->alloc<double>((size_t)lv.g.m * lv.L * lv.L);
-        lv.G = c->alloc<double>((size_t)lv.g.m * 6 * lv.L * lv.L);
-        launch_blockic_setup(lv.g, lv.Ad, lv.Aoff, lv.nkeep, lv.Dinv, lv.G, c->dflag + 2, s);
+        lv.SM = c->alloc<double>(coarse_sweep_doubles(lv.g));
+        setup_ws.emplace_back(new DevBuf(c->al, (size_t)lv.g.m * lv.L * lv.L * sizeof(double)));   // D^-1 by element
+        launch_blockic_setup(lv.g, lv.Ad, lv.Aoff, lv.nkeep, (double*)setup_ws.back()->p, lv.SM, c->dflag + 2, s);
     }
     // ---- host copies of the kept counts, unconverged eigensolves
     int unconv = 0;
@@ -553,7 +550,7 @@ static int do_setup(specmg_ctx* c, const double* perm, hipStream_t s) {
         for (int k : lv.nkeep_h) lv.dim += k;
         for (int v : st) unconv += (v < 0);
     }
-    eig_ws.clear();
+    setup_ws.clear();
     coarse_traffic(c);
     // ---- coarsest: A_L^+ = (A_L + alpha z z^T)^{-1} - z z^T / alpha
     {
@@ -644,12 +641,14 @@ static int do_setup(specmg_ctx* c, const double* perm, hipStream_t s) {
         launch_convert<double, float>(lv.basis, lv.basis32, (int64_t)nb, s);
     }
     // ---- vectors
-    for (auto& lv : c->lev) {
+    for (size_t li = 0; li < c->lev.size(); ++li) {
+        Level& lv = c->lev[li];
         const size_t nv = (size_t)lv.g.m * lv.L;
-        lv.r = c->alloc<double>(nv);
+        const size_t nr = nv * (li > 0 ? coarse_restrict_parts(c->lev[li - 1].g) : 1);
+        lv.r = c->alloc<double>(nr);
         lv.u = c->alloc<double>(nv);
         lv.e = c->alloc<double>(nv);
-        HIPCHK(hipMemsetAsync(lv.r, 0, nv * sizeof(double), s));
+        HIPCHK(hipMemsetAsync(lv.r, 0, nr * sizeof(double), s));
         HIPCHK(hipMemsetAsync(lv.u, 0, nv * sizeof(double), s));
         HIPCHK(hipMemsetAsync(lv.e, 0, nv * sizeof(double), s));
         if (c->fp32 && &lv == &c->lev[0]) {
