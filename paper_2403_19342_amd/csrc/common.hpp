@@ -297,12 +297,16 @@ void launch_sub_mean(double* x, int64_t n, const double* sum, hipStream_t s);
 
 // flexible GMRES (k_krylov.hip): device state of one restart cycle
 constexpr int kMaxRestart = 64;
+struct GmresTail {   // what the host reads after a step
+    double res, beta;
+    int done;   // 1: converged or invariant space, 2: singular Hessenberg column
+};
 struct GmresState {
     double H[(kMaxRestart + 1) * kMaxRestart];   // column j at H + j (kMaxRestart + 1)
     double cs[kMaxRestart], sn[kMaxRestart], y[kMaxRestart];
     double g[kMaxRestart + 1], h[kMaxRestart + 1], h2[kMaxRestart + 1];
-    double nrm2, inv, res, beta;
-    int done;   // 1: converged or invariant space, 2: singular Hessenberg column
+    double nrm2, inv;
+    GmresTail tail;
 };
 size_t mdot_part_doubles();
 void launch_mdot(const double* V, int64_t pitch, int cnt, const double* w, int64_t n, double* part, double* out,
@@ -311,7 +315,8 @@ void launch_maxpy(const double* V, int64_t pitch, int cnt, const double* coef, d
                   hipStream_t s);
 void launch_scale_dev(double* dst, const double* src, const double* factor, int64_t n, hipStream_t s);
 void launch_gmres_begin(GmresState* st, double thr, hipStream_t s);
-void launch_gmres_step(GmresState* st, int j, double thr, hipStream_t s);
+void launch_gmres_orthogonalise(const double* V, int64_t n, int j, double* w, double* part, GmresState* st, double thr,
+                                hipStream_t s);
 void launch_gmres_lsq(GmresState* st, int k, hipStream_t s);
 // copy / convert a vector; with sc non-null nothing is done once the solve
 // has converged (sc->done), as in the V-cycle kernels

@@ -120,6 +120,7 @@ struct specmg_ctx {
     double* gm_buf = nullptr;
     int gm_restart = 0;
     GmresState* gm_state = nullptr;
+    GmresTail* gm_tail = nullptr;   // pinned
     RedBuf rb{};
     specmg_solve_info setup_info{};
     // per-kernel-class event timing of pcg_solve (see specmg_set_profiling)
@@ -149,6 +150,7 @@ struct specmg_ctx {
         al.put(gm_buf);
         al.put(gm_state);
         if (sc_host) (void)hipHostFree(sc_host);
+        if (gm_tail) (void)hipHostFree(gm_tail);
     }
 };
 
@@ -1013,23 +1015,26 @@ static int do_gmres(specmg_ctx* c, const double* b_nat, double* x_nat, int use_x
         c->gm_restart = restart;
     }
     if (!c->gm_state) c->gm_state = (GmresState*)c->al.get(sizeof(GmresState));
+    if (!c->gm_tail) HIPCHK(hipHostMalloc((void**)&c->gm_tail, sizeof(GmresTail), hipHostMallocDefault));
     double* V = c->gm_buf;                          // restart + 1 vectors
     double* Z = V + (size_t)(restart + 1) * n;      // restart vectors
     double* w = Z + (size_t)restart * n;
     double* part = w + n;
     GmresState* st = c->gm_state;
     const double thr = tol * nb;
-    struct Host {
-        double res, beta;
-        int done;
-    } hs{};
+    const GmresTail& hs = *c->gm_tail;
     auto read_state = [&]() {
-        HIPCHK(hipMemcpyAsync(&hs.res, &st->res, sizeof(double), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipMemcpyAsync(&hs.beta, &st->beta, sizeof(double), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipMemcpyAsync(&hs.done, &st->done, sizeof(int), hipMemcpyDeviceToHost, s));
+        HIPCHK(hipMemcpyAsync(c->gm_tail, &st->tail, sizeof(GmresTail), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         HIPCHK(hipGetLastError());
     };
+    struct Event {
+        hipEvent_t e = nullptr;
+        ~Event() {
+            if (e) (void)hipEventDestroy(e);
+        }
+    } read;
+    HIPCHK(hipEventCreateWithFlags(&read.e, hipEventDisableTiming));
     // the solve runs in element order
     const double* b = c->b_e;
     double* x = c->x_e;
@@ -1050,22 +1055,27 @@ static int do_gmres(specmg_ctx* c, const double* b_nat, double* x_nat, int use_x
     while (!converged && it < max_iter) {
         launch_scale_dev(V, V, &st->inv, n, s);
         int k = 0;
-        for (int j = 0; j < restart && it < max_iter; ++j) {
-            double* vj = V + (size_t)j * n;
-            double* zj = Z + (size_t)j * n;
-            run_vcycle(c, vj, zj, nullptr, 0, 0, 0, s);
-            launch_apply_A(c->fg, c->kt, zj, nullptr, w, 0, s);
-            launch_mdot(V, n, j + 1, w, n, part, st->h, s);
-            launch_maxpy(V, n, j + 1, st->h, -1.0, w, n, s);
-            launch_mdot(V, n, j + 1, w, n, part, st->h2, s);
-            launch_maxpy(V, n, j + 1, st->h2, -1.0, w, n, s);
-            launch_mdot(w, n, 1, w, n, part, &st->nrm2, s);
-            launch_gmres_step(st, j, thr, s);
-            launch_scale_dev(V + (size_t)(j + 1) * n, w, &st->inv, n, s);
+        // z_j = P^{-1} v_j, w = A z_j
+        auto directions = [&](int j) {
+            run_vcycle(c, V + (size_t)j * n, Z + (size_t)j * n, nullptr, 0, 0, 0, s);
+            launch_apply_A(c->fg, c->kt, Z + (size_t)j * n, nullptr, w, 0, s);
+        };
+        directions(0);
+        while (true) {
+            launch_mdot(V, n, k + 1, w, n, part, st->h, s);
+            launch_gmres_orthogonalise(V, n, k, w, part, st, thr, s);
+            launch_scale_dev(V + (size_t)(k + 1) * n, w, &st->inv, n, s);
+            HIPCHK(hipMemcpyAsync(c->gm_tail, &st->tail, sizeof(GmresTail), hipMemcpyDeviceToHost, s));
+            HIPCHK(hipEventRecord(read.e, s));
             ++it;
-            k = j + 1;
-            read_state();
-            if (hs.done) break;
+            ++k;
+            // the next direction is on its way while the host reads the flag
+            // (unused, and harmless, after the step that converges)
+            const bool more = k < restart && it < max_iter;
+            if (more) directions(k);
+            HIPCHK(hipEventSynchronize(read.e));
+            HIPCHK(hipGetLastError());
+            if (hs.done || !more) break;
         }
         if (hs.done == 2) {
             rc = fail(SPECMG_EBREAKDOWN, "GMRES breakdown: singular Hessenberg column");
