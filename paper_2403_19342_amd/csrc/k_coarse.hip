@@ -567,30 +567,39 @@ __global__ __launch_bounds__(256) void k_coarsest_rows(int n, int np, const doub
     if (t < kCoarsestRows && i0 + t < n) e[cmap[i0 + t]] = (T)((red[0][t] + red[1][t]) + (red[2][t] + red[3][t]));
 }
 
-// (spaces of one LDS chunk: each block gathers the compact right-hand side
-// itself from the level vector r through cmap, so no separate gather launch)
-template <typename T, int RW>
-__global__ __launch_bounds__(256) void k_coarsest(int n, int np, const double* __restrict__ Pinv,
+// Spaces of one LDS chunk: each block gathers the compact right-hand side
+// itself from the level vector r through cmap, so no separate gather launch; a
+// wavefront takes RW rows, as many as leave a block a CU, since what a block
+// stages (n values, with their indices) is then a small part of what its rows
+// read.  One row a wavefront, the only form before, took 46 us at n = 4096
+// (2.7 TB/s) and 104 at 5120; eight wavefronts of two rows take 34 and 46.
+template <typename T, int RW, int NW>
+__global__ __launch_bounds__(64 * NW) void k_coarsest(int n, int np, const double* __restrict__ Pinv,
                                                    const int* __restrict__ cmap, const T* __restrict__ r, int nparts,
                                                    int64_t pstride, T* __restrict__ e, const Scalars* sc,
                                                    int check_done) {
     if (check_done && sc->done) return;
     extern __shared__ double srz[];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int i0 = blockIdx.x * 4 * RW + w * RW;
+    const int i0 = blockIdx.x * NW * RW + w * RW;
+    for (int j = threadIdx.x; j < n; j += blockDim.x) srz[j] = (double)gather_parts(r + cmap[j], nparts, pstride);
+    if ((n & 1) && threadIdx.x == 0) srz[n] = 0.0;
+    __syncthreads();
     double acc[RW];
+    const double* row[RW];
 #pragma unroll
-    for (int qq = 0; qq < RW; ++qq) acc[qq] = 0.0;
-    for (int c0 = 0; c0 < n; c0 += kCoarsestChunk) {
-        const int cn = min(kCoarsestChunk, n - c0);
-        if (c0) __syncthreads();
-        for (int j = threadIdx.x; j < cn; j += blockDim.x) srz[j] = (double)gather_parts(r + cmap[c0 + j], nparts, pstride);
-        __syncthreads();
-        for (int j = lane; j < cn; j += 64) {
-            const double v = srz[j];
+    for (int q = 0; q < RW; ++q) {
+        acc[q] = 0.0;
+        row[q] = Pinv + (size_t)min(i0 + q, n - 1) * np;
+    }
+    // pairs of columns (np is a multiple of 32, so the last pair exists)
+#pragma unroll 4
+    for (int j = 2 * lane; j < n; j += 128) {
+        const double2 v = *reinterpret_cast<const double2*>(srz + j);
 #pragma unroll
-            for (int q = 0; q < RW; ++q)
-                if (i0 + q < n) acc[q] += Pinv[(size_t)(i0 + q) * np + c0 + j] * v;
+        for (int q = 0; q < RW; ++q) {
+            const double2 m = *reinterpret_cast<const double2*>(row[q] + j);
+            acc[q] += m.x * v.x + m.y * v.y;
         }
     }
 #pragma unroll
@@ -728,60 +737,77 @@ __global__ __launch_bounds__(kSymT * kSymRedGroups) void k_coarsest_sym_reduce(
 //   D[e][d] = sum_{tau on face d} T_f phi(tau) phi(tau)^T       (d = -x,+x,-y,+y,-z,+z)
 //   Aoff[e][ax] = -sum_{tau on face +ax} T_f phi_e(tau) phi_{e+ax}(tau')^T
 // (the terms of eq. discrete varia for faces between elements)
+// Bound by the basis: the face cells of a column lie in every one of its lines,
+// so the whole of it is fetched, and half of it again for the neighbours.  One sum of 64
+// products a thread, from LDS, took 1.90 ms at 256^3 with 11 columns; nine 16 x 16 products of depth 64 on the matrix cores,
+// all rows loaded at once, take 0.52 (0.20 -> 0.067 ms at 128^3).
 __global__ __launch_bounds__(256) void k_galerkin2(FineGeom g, const double* __restrict__ kt,
                                                    const double* __restrict__ phi, const int* __restrict__ nkeep,
                                                    int L, double* __restrict__ D, double* __restrict__ Aoff) {
+    constexpr int LD = 66;                     // rows of 64 face cells, padded against bank conflicts
     __shared__ double sT[6][64];
-    __shared__ double sP[6][kMaxL2][64];    // own face rows
-    __shared__ double sN[3][kMaxL2][64];    // neighbour face rows (+ faces)
+    __shared__ double sP[9][kMaxL2 * LD];      // own faces 2 ax (-), 2 ax + 1 (+); 6 + ax: across the + face
     const int e = blockIdx.x;
     const int ex = e % g.mx, ey = (e / g.mx) % g.my, ez = e / (g.mx * g.my);
-    auto gid = [&](int x, int y, int z) { return eidx(g, x, y, z); };
-    for (int t = threadIdx.x; t < 6 * 64; t += blockDim.x) {
-        const int d = t / 64, f = t % 64;
-        const int ax = d >> 1;
-        const bool plus = d & 1;
-        const int u = f & 7, v = f >> 3;     // in-face coordinates
-        int i, j, k;
-        if (ax == 0) { i = plus ? 7 : 0; j = u; k = v; }
-        else if (ax == 1) { i = u; j = plus ? 7 : 0; k = v; }
-        else { i = u; j = v; k = plus ? 7 : 0; }
-        const int gx = ex * 8 + i, gy = ey * 8 + j, gz = ez * 8 + k;
-        const int nx_ = gx + (ax == 0 ? (plus ? 1 : -1) : 0);
-        const int ny_ = gy + (ax == 1 ? (plus ? 1 : -1) : 0);
-        const int nz_ = gz + (ax == 2 ? (plus ? 1 : -1) : 0);
-        const bool inside = nx_ >= 0 && nx_ < g.nx && ny_ >= 0 && ny_ < g.ny && nz_ >= 0 && nz_ < g.nz;
-        double T = 0.0;
-        if (inside) {
-            // kappa~ of this face's direction (three arrays for orthotropic K)
-            const size_t off = g.ortho ? (size_t)ax * g.ncell() : 0;
-            const double a = kt[off + gid(gx, gy, gz)], b = kt[off + gid(nx_, ny_, nz_)];
-            T = 2.0 * a * b / (a + b) * (ax == 0 ? 1.0 : (ax == 1 ? g.cy : g.cz));
-        }
-        sT[d][f] = T;
-        const int c = i + 8 * (j + 8 * k);
-        for (int jj = 0; jj < L; ++jj) sP[d][jj][f] = phi[((size_t)e * L + jj) * 512 + phi_pos(c)];
-        if (plus) {
-            const int en = e + (ax == 0 ? 1 : (ax == 1 ? g.mx : g.mx * g.my));
-            const int ci = ax == 0 ? 0 : i, cj = ax == 1 ? 0 : j, ck = ax == 2 ? 0 : k;
-            const int cn = ci + 8 * (cj + 8 * ck);
-            for (int jj = 0; jj < L; ++jj)
-                sN[ax][jj][f] = inside ? phi[((size_t)en * L + jj) * 512 + phi_pos(cn)] : 0.0;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int fu = lane & 7, fv = lane >> 3;   // in-face coordinates
+    auto across = [&](int ax) {                // the element across the + face, or -1
+        const bool in = ax == 0 ? ex + 1 < g.mx : (ax == 1 ? ey + 1 < g.my : ez + 1 < g.mz);
+        return in ? e + (ax == 0 ? 1 : (ax == 1 ? g.mx : g.mx * g.my)) : -1;
+    };
+    // face rows: wavefront w takes columns w, w + 4, ..., all loads in flight
+    double v[9][kMaxL2 / 4];
+#pragma unroll
+    for (int d = 0; d < 9; ++d) {
+        const int ax = d < 6 ? d >> 1 : d - 6;
+        const int en = d < 6 ? e : across(ax);
+        const int at = d < 6 && (d & 1) ? 7 : 0;
+        const int pos = phi_pos(ax == 0 ? at + 8 * (fu + 8 * fv) : (ax == 1 ? fu + 8 * (at + 8 * fv) : fu + 8 * (fv + 8 * at)));
+#pragma unroll
+        for (int m = 0; m < kMaxL2 / 4; ++m) {
+            const int jj = w + 4 * m;
+            v[d][m] = jj < L && en >= 0 ? phi[((size_t)en * L + jj) * 512 + pos] : 0.0;
         }
     }
+    // face transmissibilities
+    for (int d = w; d < 6; d += 4) {
+        const int ax = d >> 1, at = (d & 1) ? 7 : 0, o = (d & 1) ? 1 : -1;
+        const int gx = ex * 8 + (ax == 0 ? at : fu), gy = ey * 8 + (ax == 0 ? fu : (ax == 1 ? at : fv));
+        const int gz = ez * 8 + (ax == 2 ? at : fv);
+        const int hx = gx + (ax == 0 ? o : 0), hy = gy + (ax == 1 ? o : 0), hz = gz + (ax == 2 ? o : 0);
+        double T = 0.0;
+        if (hx >= 0 && hx < g.nx && hy >= 0 && hy < g.ny && hz >= 0 && hz < g.nz) {
+            // kappa~ of this face's direction (three arrays for orthotropic K)
+            const size_t off = g.ortho ? (size_t)ax * g.ncell() : 0;
+            const double a = kt[off + eidx(g, gx, gy, gz)], b = kt[off + eidx(g, hx, hy, hz)];
+            T = 2.0 * a * b / (a + b) * (ax == 0 ? 1.0 : (ax == 1 ? g.cy : g.cz));
+        }
+        sT[d][lane] = T;
+    }
+#pragma unroll
+    for (int d = 0; d < 9; ++d)
+#pragma unroll
+        for (int m = 0; m < kMaxL2 / 4; ++m) sP[d][(w + 4 * m) * LD + lane] = v[d][m];
     __syncthreads();
-    const int LL = L * L;
-    for (int t = threadIdx.x; t < 9 * LL; t += blockDim.x) {
-        const int blk = t / LL, a = (t % LL) / L, b = t % L;
-        double s = 0.0;
-        if (blk < 6) {
-            for (int f = 0; f < 64; ++f) s += sT[blk][f] * sP[blk][a][f] * sP[blk][b][f];
-            D[((size_t)e * 6 + blk) * LL + a * L + b] = s;
-        } else {
-            const int ax = blk - 6;
-            const int d = 2 * ax + 1;
-            for (int f = 0; f < 64; ++f) s += sT[d][f] * sP[d][a][f] * sN[ax][b][f];
-            Aoff[((size_t)e * 3 + ax) * LL + a * L + b] = -s;
+    // block blk = P^T diag(T) Q over the 64 cells of a face, one 16 x 16
+    // product of depth 64 on the matrix cores
+    const int li = lane & 15, lk = lane >> 4, LL = L * L;
+    typedef double dbl4 __attribute__((ext_vector_type(4)));
+    for (int blk = w; blk < 9; blk += 4) {
+        const int ax = blk - 6, d = blk < 6 ? blk : 2 * ax + 1;
+        dbl4 c{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int kk = 0; kk < 16; ++kk) {
+            const int f = 4 * kk + lk;
+            c = __builtin_amdgcn_mfma_f64_16x16x4f64(sT[d][f] * sP[d][li * LD + f], sP[blk < 6 ? d : blk][li * LD + f], c,
+                                                     0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int a = lk + 4 * r;
+            if (a >= L || li >= L) continue;
+            if (blk < 6) D[((size_t)e * 6 + blk) * LL + a * L + li] = c[r];
+            else Aoff[((size_t)e * 3 + ax) * LL + a * L + li] = -c[r];
         }
     }
 }
@@ -876,139 +902,153 @@ __global__ void k_assemble_diag(CoarseGeom g, const double* __restrict__ Aint, c
     }
 }
 
-// In-place inverse of an SPD n x n matrix (n <= kMaxL) by one wavefront:
-// lane 0 factors A = L L^T (Lw, lower), then lane k < n solves
-// L L^T x = e_k for column k.  Padded slots (index >= nk) get identity.
-// Returns false (in every lane) if A is not numerically SPD.
-__device__ bool small_spd_inverse_wave(double* A, int n, int nk, double* Lw, int* flag) {
-    const int lane = threadIdx.x & 63;
-    for (int t = lane; t < n * n; t += 64) {
-        const int i = t / n, j = t % n;
-        if (i >= nk || j >= nk) A[t] = (i == j) ? 1.0 : 0.0;
-    }
-    wave_sync();
-    if (lane == 0) {
-        int ok = 1;
-        for (int j = 0; j < n; ++j) {
-            double d = A[j * n + j];
-            for (int k = 0; k < j; ++k) d -= Lw[j * n + k] * Lw[j * n + k];
-            if (!(d > 0.0)) {
-                ok = 0;
-                d = 1.0;
-            }
-            const double ljj = sqrt(d);
-            Lw[j * n + j] = ljj;
-            for (int i = j + 1; i < n; ++i) {
-                double v = A[i * n + j];
-                for (int k = 0; k < j; ++k) v -= Lw[i * n + k] * Lw[j * n + k];
-                Lw[i * n + j] = v / ljj;
-            }
-            for (int i = 0; i < j; ++i) Lw[i * n + j] = 0.0;
-        }
-        *flag = ok;
-    }
-    wave_sync();
-    if (lane < n) {
-        const int kcol = lane;
-        double y[kMaxL];
-#pragma unroll
-        for (int i = 0; i < kMaxL; ++i) {
-            if (i < n) {
-                double v = (i == kcol) ? 1.0 : 0.0;
-#pragma unroll
-                for (int k = 0; k < kMaxL; ++k)
-                    if (k < i) v -= Lw[i * n + k] * y[k];
-                y[i] = v / Lw[i * n + i];
-            }
-        }
-#pragma unroll
-        for (int i = kMaxL - 1; i >= 0; --i) {
-            if (i < n) {
-                double v = y[i];
-#pragma unroll
-                for (int k = 0; k < kMaxL; ++k)
-                    if (k > i && k < n) v -= Lw[k * n + i] * y[k];
-                y[i] = v / Lw[i * n + i];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < kMaxL; ++i)
-            if (i < n) A[i * n + kcol] = y[i];
-    }
-    wave_sync();
-    return *flag != 0;
-}
-
-// Block IC(0) pivots of the level-l smoother, one workgroup per parent:
-// the children of one hyperplane (at most 12) are factored in parallel,
-// one wavefront each, with the Schur updates of the lower neighbours'
-// couplings lane-parallel over the L x L entries.
+// Block IC(0) pivots of the level-l smoother, one workgroup per parent: the
+// children of one hyperplane (at most 12, 3 with agg 2) are factored in
+// parallel, one wavefront each.  Entry t = lane + 64 u of an L x L block is
+// lane's u-th register, U of them; LDS passes blocks and pivot rows around
+// the wavefront.  The inverse is that of the Cholesky factor, A = L L^T,
+// W = L^{-1} by eliminating [A | I] row by row (column k of I takes the place
+// that column k of A leaves), then W^T W; padded slots (index >= nkeep) are
+// rows of the identity.
+// A chain: per plane one memory round trip, three Schur updates, L pivots of
+// one LDS round trip each.  With lane 0 alone factoring and lane k solving for
+// column k, from LDS, and the couplings read where they are used, it took 433 us for
+// 64 parents of 64 x 9 (128^3), 2.2 ms for 512 of 64 x 11, 46 ms for the 32768 of
+// 8 x 9 and 4096 of 8 x 13 at 512^3; now 85 us, 0.20 ms and 1.2 ms.
 constexpr int kMaxPlane = 12;   // children per hyperplane of a 4^3 parent
+template <int U>
 __global__ __launch_bounds__(64 * kMaxPlane) void k_blockic_setup(CoarseGeom g, const double* __restrict__ Ad,
                                                                    const double* __restrict__ Aoff,
                                                                    const int* __restrict__ nkeep, double* Dinv,
                                                                    int* bad) {
     __shared__ int pos[kMaxChildren], off[12];
     extern __shared__ double work_lds[];   // [children of the widest plane][3][L * L]
-    __shared__ int flags[kMaxPlane];
     const int E = blockIdx.x;
     const int L = g.L, agg = g.agg, LL = L * L;
     build_planes(agg, pos, off);
     const int nplanes = 3 * (agg - 1) + 1;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double* sA = work_lds + (size_t)(3 * w) * LL;
+    double* sB = sA + LL;
+    double* sR = sB + LL;
+    int row[U], col[U];
+    bool in[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int t = lane + 64 * u;
+        in[u] = t < LL;
+        row[u] = in[u] ? t / L : 0;
+        col[u] = in[u] ? t - row[u] * L : 0;
+    }
     for (int s = 0; s < nplanes; ++s) {
         const int cnt = off[s + 1] - off[s];
         if (w < cnt) {
             const int p = pos[off[s] + w];
             const int c = child_of(g, E, p);
-            double* P = work_lds + (size_t)(3 * w) * LL;
-            double* T = P + LL;
-            double* Lw = T + LL;
-            for (int t = lane; t < LL; t += 64) P[t] = Ad[(size_t)c * LL + t];
             const int q[3] = {p % agg, (p / agg) % agg, p / (agg * agg)};
             const int cstep[3] = {1, g.mx, g.mx * g.my};
-            wave_sync();
+            const int nk = nkeep[c];
+            constexpr bool ONCE = U <= 2;   // all couplings loaded at once, if the registers hold them
+            double P[U], O[ONCE ? 3 : 1][U], Di[ONCE ? 3 : 1][U];
+            auto load = [&](int ax, double (&o)[U], double (&di)[U]) {
+                const size_t cn = q[ax] > 0 ? c - cstep[ax] : c;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool ld = in[u] && q[ax] > 0;
+                    o[u] = ld ? Aoff[(cn * 3 + ax) * LL + lane + 64 * u] : 0.0;   // A(cn, c)
+                    di[u] = ld ? Dinv[cn * LL + lane + 64 * u] : 0.0;
+                }
+            };
+#pragma unroll
+            for (int u = 0; u < U; ++u) P[u] = in[u] ? Ad[(size_t)c * LL + lane + 64 * u] : 0.0;
+            if constexpr (ONCE)
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax) load(ax, O[ax], Di[ax]);
+            // P -= O^T (Dinv_cn O)
+#pragma unroll
             for (int ax = 0; ax < 3; ++ax) {
                 if (q[ax] == 0) continue;
-                const int cn = c - cstep[ax];
-                const double* O = Aoff + ((size_t)cn * 3 + ax) * LL;   // A(cn, c)
-                const double* Di = Dinv + (size_t)cn * LL;
-                // T = Dinv_cn O ; P -= O^T T
-                for (int t = lane; t < LL; t += 64) {
-                    const int i = t / L, j = t % L;
-                    double v = 0.0;
-                    for (int b = 0; b < L; ++b) v += Di[i * L + b] * O[b * L + j];
-                    T[t] = v;
-                }
-                wave_sync();
-                for (int t = lane; t < LL; t += 64) {
-                    const int i = t / L, j = t % L;
-                    double v = 0.0;
-                    for (int b = 0; b < L; ++b) v += O[b * L + i] * T[b * L + j];
-                    P[t] -= v;
-                }
-                wave_sync();
-            }
-            // symmetrise (all reads before the writes), invert
-            double sym[(kMaxL * kMaxL + 63) / 64];
+                if constexpr (!ONCE) load(ax, O[0], Di[0]);
 #pragma unroll
-            for (int u = 0; u < (kMaxL * kMaxL + 63) / 64; ++u) {
-                const int t = lane + 64 * u;
-                sym[u] = t < LL ? 0.5 * (P[t] + P[(t % L) * L + t / L]) : 0.0;
+                for (int u = 0; u < U; ++u)
+                    if (in[u]) {
+                        sA[lane + 64 * u] = Di[ONCE ? ax : 0][u];
+                        sB[lane + 64 * u] = O[ONCE ? ax : 0][u];
+                    }
+                wave_sync();
+                double T[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) T[u] = 0.0;
+                for (int b = 0; b < L; ++b)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) T[u] += sA[row[u] * L + b] * sB[b * L + col[u]];
+                wave_sync();
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (in[u]) sA[lane + 64 * u] = T[u];
+                wave_sync();
+#pragma unroll
+                for (int u = 0; u < U; ++u) T[u] = 0.0;
+                for (int b = 0; b < L; ++b)
+#pragma unroll
+                    for (int u = 0; u < U; ++u) T[u] += sB[b * L + row[u]] * sA[b * L + col[u]];
+#pragma unroll
+                for (int u = 0; u < U; ++u) P[u] -= T[u];
+                wave_sync();
             }
+            // symmetrise, padded slots
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (in[u]) sA[lane + 64 * u] = P[u];
             wave_sync();
 #pragma unroll
-            for (int u = 0; u < (kMaxL * kMaxL + 63) / 64; ++u) {
-                const int t = lane + 64 * u;
-                if (t < LL) P[t] = sym[u];
+            for (int u = 0; u < U; ++u) {
+                P[u] = 0.5 * (P[u] + sA[col[u] * L + row[u]]);
+                if (row[u] >= nk || col[u] >= nk) P[u] = row[u] == col[u] ? 1.0 : 0.0;
             }
+            // W, its rows scaled at the end by the root of their pivots
+            double piv[U];
+            bool ok = true;
+#pragma unroll
+            for (int u = 0; u < U; ++u) piv[u] = 1.0;
+            for (int k = 0; k < L; ++k) {
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (in[u] && row[u] == k) sR[col[u]] = P[u];
+                wave_sync();
+                double d = sR[k];
+                if (!(d > 0.0)) {
+                    ok = false;
+                    d = 1.0;
+                }
+                const double rd = 1.0 / d;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const double l = sR[row[u]] * rd, f = sR[col[u]];
+                    if (row[u] > k) P[u] = col[u] == k ? -l : P[u] - l * f;
+                    if (row[u] == k) {
+                        piv[u] = d;
+                        if (col[u] == k) P[u] = 1.0;
+                    }
+                }
+                wave_sync();
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (in[u]) sA[lane + 64 * u] = col[u] <= row[u] ? P[u] / sqrt(piv[u]) : 0.0;
             wave_sync();
-            if (!small_spd_inverse_wave(P, L, nkeep[c], Lw, &flags[w]) && lane == 0) atomicOr(bad, 2);
-            for (int t = lane; t < LL; t += 64) Dinv[(size_t)c * LL + t] = P[t];
+#pragma unroll
+            for (int u = 0; u < U; ++u) P[u] = 0.0;
+            for (int b = 0; b < L; ++b)
+#pragma unroll
+                for (int u = 0; u < U; ++u) P[u] += sA[b * L + row[u]] * sA[b * L + col[u]];
+            wave_sync();
+            if (!ok && lane == 0) atomicOr(bad, 2);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (in[u]) Dinv[(size_t)c * LL + lane + 64 * u] = P[u];
         }
-        __threadfence();
-        __syncthreads();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __syncthreads();   // the plane's pivots are read by this workgroup alone
     }
 }
 
@@ -1319,9 +1359,15 @@ template <typename T>
 void launch_coarsest(int n, int np, const double* Pinv, const int* cmap, const T* r, int nparts, int64_t pstride, T* e,
                      double* rc,
                      const Scalars* sc, int check_done, hipStream_t s) {
-    const size_t lds = (size_t)std::min(n, kCoarsestChunk) * sizeof(double);
-    if (n <= kCoarsestChunk) {
-        SPECMG_TIMED_LAUNCH((k_coarsest<T, 1>), dim3((n + 3) / 4), dim3(256), lds, s, n, np, Pinv, cmap, r, nparts,
+    const size_t lds = (size_t)(std::min(n, kCoarsestChunk) + 1) * sizeof(double);
+    if (n <= 1024) {
+        SPECMG_TIMED_LAUNCH((k_coarsest<T, 1, 4>), dim3((n + 3) / 4), dim3(256), lds, s, n, np, Pinv, cmap, r, nparts,
+                            pstride, e, sc, check_done);
+    } else if (n <= 2048) {
+        SPECMG_TIMED_LAUNCH((k_coarsest<T, 1, 8>), dim3((n + 7) / 8), dim3(512), lds, s, n, np, Pinv, cmap, r, nparts,
+                            pstride, e, sc, check_done);
+    } else if (n <= kCoarsestChunk) {
+        SPECMG_TIMED_LAUNCH((k_coarsest<T, 2, 8>), dim3((n + 15) / 16), dim3(512), lds, s, n, np, Pinv, cmap, r, nparts,
                             pstride, e, sc, check_done);
     } else {
         hipLaunchKernelGGL((k_gather_compact<T>), dim3(std::min((n + 255) / 256, 1024)), dim3(256), 0, s, n, cmap, r,
@@ -1351,7 +1397,11 @@ void launch_blockic_setup(const CoarseGeom& g, const double* Ad, const double* A
     const int wmax = g.agg == 2 ? 3 : kMaxPlane;
     const size_t shmem = (size_t)wmax * 3 * g.L * g.L * sizeof(double);
     if (g.L > kMaxL || shmem > 64 * 1024) throw HipError{hipErrorInvalidValue, "block-IC set-up shape"};
-    hipLaunchKernelGGL(k_blockic_setup, dim3(g.M), dim3(64 * kMaxPlane), shmem, s, g, Ad, Aoff, nkeep, Dinv, bad);
+    const dim3 nb(g.M), th(64 * wmax);
+    const int entries = (g.L * g.L + 63) / 64;
+    if (entries <= 2) hipLaunchKernelGGL(k_blockic_setup<2>, nb, th, shmem, s, g, Ad, Aoff, nkeep, Dinv, bad);
+    else if (entries <= 4) hipLaunchKernelGGL(k_blockic_setup<4>, nb, th, shmem, s, g, Ad, Aoff, nkeep, Dinv, bad);
+    else hipLaunchKernelGGL(k_blockic_setup<9>, nb, th, shmem, s, g, Ad, Aoff, nkeep, Dinv, bad);
     hipLaunchKernelGGL(k_blockic_couple, dim3(g.m), dim3(256), 0, s, g, Aoff, Dinv, SM);
 }
 
