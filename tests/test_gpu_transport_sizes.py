@@ -1,0 +1,33 @@
+"""Saturation sub-steps at sizes on both sides of every cells-a-thread rule (1 up
+to 524288 cells, then 2, 3, 4, and several passes beyond 2 million), with
+extents below, at and beyond the 512 cells between a thread's own, against the
+oracle; S within 1e-12 absolute and the summed step within 1e-12 relative, the
+bars of the smaller cases.
+"""
+import numpy as np
+import pytest
+
+from oracle import impes as im
+from synth.fields import random_saturation
+from tests.gpu_util import to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shape", [(2, 3, 511), (3, 512, 1), (513, 2, 3), (1, 70000, 1), (64, 64, 128), (64, 64, 129),
+                                   (85, 220, 60), (131, 111, 109), (128, 128, 129), (9, 701, 700)])
+def test_sizes(shape):
+    import torch
+    from paper_2403_19342_amd.specmg import transport
+    rng = np.random.default_rng(shape[0])
+    s0 = random_saturation(shape, 3)
+    phi = rng.uniform(0.05, 0.35, shape)
+    q = rng.standard_normal(shape) * (rng.random(shape) < 0.1)
+    v = [rng.standard_normal(shape) * (rng.random(shape) < 0.9) for _ in range(3)]
+    ref, tref = im.transport(phi, q, *v, s0, (0.1, 0.05, 0.01), 3, 1e-2)
+    s = to_dev(s0)
+    work = torch.empty(2 * s0.size + 2048, dtype=torch.float64, device="cuda")
+    t = torch.empty(1, dtype=torch.float64, device="cuda")
+    transport(to_dev(phi), to_dev(q), *(to_dev(a) for a in v), s, (0.1, 0.05, 0.01), 3, 1e-2, work, t)
+    assert np.max(np.abs(to_host(s) - ref)) <= 1e-12
+    assert abs(float(t) - tref) <= 1e-12 * tref
