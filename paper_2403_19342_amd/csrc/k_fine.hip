@@ -47,20 +47,20 @@ constexpr int kMaxCols = 12;   // padded basis width (target <= 8, plus 3)
 template <typename T>
 __device__ __forceinline__ T harm(T a, T b) {
     // harmonic mean 2ab/(a+b); zero when a neighbour is outside the domain
-    // (a + b = 0).  1/(a+b) by Newton's iteration r <- r (2 - s r) from the
-    // hardware reciprocal: two steps in float64, one in float32; no branch
-    const T s = a + b;
-    T r;
+    // (b = 0; the bound below keeps a = b = 0 from giving 0 * infinity).
+    // 1/(a+b) from the hardware reciprocal r: r + r (e + e^2), e = 1 - s r, in
+    // float64, one Newton step in float32
     if constexpr (sizeof(T) == 8) {
-        r = __builtin_amdgcn_rcp(s);
-        r = fma(fma(-s, r, 1.0), r, r);
-        r = fma(fma(-s, r, 1.0), r, r);
+        const double s = fmax(a + b, 2.2250738585072014e-308);
+        const double r = __builtin_amdgcn_rcp(s);
+        const double e = fma(-s, r, 1.0);
+        return (2.0 * a * b) * fma(r, fma(e, e, e), r);
     } else {
-        r = __builtin_amdgcn_rcpf(s);
+        const float s = fmaxf(a + b, 1.17549435e-38f);
+        float r = __builtin_amdgcn_rcpf(s);
         r = fmaf(fmaf(-s, r, 1.0f), r, r);
+        return (2.0f * a * b) * r;
     }
-    const T v = (T(2) * a * b) * r;
-    return s > T(0) ? v : T(0);
 }
 
 // LDS layouts use odd row pitches so that cells of one hyperplane spread
@@ -348,8 +348,10 @@ __device__ __forceinline__ void load_faces(const FineGeom& g, const T* __restric
 // mode bit1: return at once when the solve is finished
 // T: stored word of kappa~, 1/d and u; C: arithmetic (T, or float64 with
 // float32 storage); O: three kappa~ arrays (orthotropic K)
+// Held to 128 registers (130 otherwise): the 4096 wavefronts of 128^3 are then
+// all resident, 25.5 -> 23.6 us; 256^3 145 us either way.
 template <int EX, typename T, typename C, bool O>
-__global__ __launch_bounds__(64 * EX) void k_pre_smooth(FineGeom g, const T* __restrict__ kt,
+__global__ __launch_bounds__(64 * EX) __attribute__((amdgpu_waves_per_eu(O ? 1 : 4))) void k_pre_smooth(FineGeom g, const T* __restrict__ kt,
                                                         const T* __restrict__ invd, double* r,
                                                         const double* __restrict__ q, T* __restrict__ u,
                                                         Scalars* sc, RedBuf rb, int mode) {
@@ -414,31 +416,52 @@ __device__ __forceinline__ void load_col(const TB* __restrict__ col, int lane, C
 }
 
 
-// The cells beyond the element's four y and z faces (-y, +y, -z, +z): the
-// vector value val(i) (i an element-order index) and kappa~ (the face's own
-// component for orthotropic K), zero outside the domain.  All 64 lanes load
-// them together, one cell per face and array (lane = (x, row) of the face),
-// and stage them in the wavefront's LDS area fu[4][64], fk[4][64] for the
-// lanes on those faces.
-template <bool O, typename T, typename C, typename VF>
-__device__ __forceinline__ void stage_faces_yz(const FineGeom& g, const T* __restrict__ kt, VF val, int x0, int y0,
-                                               int z0, int lane, C* fu, C* fk) {
+// The cells beyond the element's four y and z faces and the fluxes through its
+// plus faces, in the wavefront's LDS area ff[8][64].  All 64 lanes load the cells
+// beyond together, one per face and array (lane = (x, row) of the face; zero
+// outside the domain; the face's own component for orthotropic K).  Those beyond
+// the minus faces are staged as they are, u in ff[0] (y) and ff[2] (z), kappa~
+// in ff[1] and ff[3], for the lanes whose neighbours they are.  Beyond the plus
+// faces (their lanes hand their neighbours nothing) the flux T (u_in - u_out) is
+// formed here, one face cell a lane, with the row inside passed through LDS: ff[4]
+// and ff[6].
+template <bool O, typename T, typename C>
+__device__ __forceinline__ void stage_faces_yz(const FineGeom& g, const T* __restrict__ kt, const T* __restrict__ u,
+                                               int x0, int y0, int z0, int lane, const C (&uc)[8], const C (&ky)[8],
+                                               const C (&kz)[8], C* ff) {
     const int fx = lane & 7, fr = lane >> 3;
     const size_t N = O ? g.ncell() : 0;
     C vu[4], vk[4];
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
-        const int yy = f < 2 ? (f == 0 ? y0 - 1 : y0 + 8) : y0 + fr;
-        const int zz = f < 2 ? z0 + fr : (f == 2 ? z0 - 1 : z0 + 8);
+    for (int f = 0; f < 4; ++f) {   // -y, -z, +y, +z
+        const int o = f < 2 ? -1 : 8;
+        const int yy = f % 2 == 0 ? y0 + o : y0 + fr, zz = f % 2 == 0 ? z0 + fr : z0 + o;
         const bool in = yy >= 0 && yy < g.ny && zz >= 0 && zz < g.nz;
         const size_t gi = in ? eidx(g, x0 + fx, yy, zz) : 0;
-        vu[f] = in ? (C)val(gi) : C(0);
-        vk[f] = in ? (C)kt[(f < 2 ? N : 2 * N) + gi] : C(0);
+        vu[f] = in ? (C)u[gi] : C(0);
+        vk[f] = in ? (C)kt[(f % 2 == 0 ? N : 2 * N) + gi] : C(0);
     }
+    if ((lane & 7) == 7) {
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
-        fu[f * 64 + lane] = vu[f];
-        fk[f * 64 + lane] = vk[f];
+        for (int x = 0; x < 8; ++x) {
+            ff[4 * 64 + (lane & ~7) + x] = uc[x];
+            ff[5 * 64 + (lane & ~7) + x] = ky[x];
+        }
+    }
+    if (lane >= 56) {
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            ff[6 * 64 + 8 * (lane & 7) + x] = uc[x];
+            ff[7 * 64 + 8 * (lane & 7) + x] = kz[x];
+        }
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+        const C ui = ff[(4 + 2 * f) * 64 + lane], ki = ff[(5 + 2 * f) * 64 + lane];
+        ff[2 * f * 64 + lane] = vu[f];
+        ff[(2 * f + 1) * 64 + lane] = vk[f];
+        ff[(4 + 2 * f) * 64 + lane] = harm(ki, vk[2 + f]) * (C)(f == 0 ? g.cy : g.cz) * (ui - vu[2 + f]);
     }
     wave_lds_sync();
 }
@@ -447,16 +470,16 @@ __device__ __forceinline__ void stage_faces_yz(const FineGeom& g, const T* __res
 // inside the pencil: uc, kc the row's u and kappa~ (kappa~_x for orthotropic
 // K; ky, kz its y and z components), um, km and up, kp u and kappa~ of the
 // cells before and after the pencil in x (used when xlo, xhi: inside the
-// domain), fu, fk the staged y and z face cells (stage_faces_yz).  y and z
-// neighbours inside the element come from the lanes -+1 and -+8: through the
-// LDS crossbar (bpermute), or with DY the y neighbours by DPP row shifts,
+// domain), ff the staged y and z faces (stage_faces_yz).  A lane forms the
+// fluxes through its minus faces and hands them to its neighbours, whose plus
+// faces they are; neighbours inside the element are the lanes -+1 and -+8:
+// through the LDS crossbar (bpermute), or with DY those in y by DPP row shifts,
 // which take VALU issue slots and registers instead (the better trade where
-// the crossbar also carries an IC(0) sweep).
+// the crossbar also carries an IC(0) sweep). 
 template <bool O, bool DY, typename C>
-__device__ __forceinline__ void pencil_apply(const FineGeom& g, int lane, int j, int k, const C (&uc)[8],
+__device__ __forceinline__ void pencil_apply(const FineGeom& g, int j, int k, const C (&uc)[8],
                                              const C (&kc)[8], const C (&ky)[8], const C (&kz)[8], C um, C km,
-                                             C up, C kp, bool xlo, bool xhi, const C* fu, const C* fk,
-                                             C (&s)[8]) {
+                                             C up, C kp, bool xlo, bool xhi, const C* ff, C (&s)[8]) {
     // x faces: inside the pencil, then the two ends
 #pragma unroll
     for (int x = 0; x < 7; ++x) {
@@ -467,52 +490,29 @@ __device__ __forceinline__ void pencil_apply(const FineGeom& g, int lane, int j,
     if (xlo) s[0] -= harm(kc[0], km) * (uc[0] - um);
     if (xhi) s[7] -= harm(kc[7], kp) * (uc[7] - up);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (DY) {
-        // -y, +y: the face lanes (j = 0, j = 7) take the staged cells.  The
-        // shifts run on every lane before the select: a DPP source lane that
-        // is switched off in EXEC reads as out of range, so a shift inside
-        // the branch would zero the neighbours of lanes j = 1 and j = 6.
-        const C cf = (C)g.cy;
-        const int fo0 = 8 * k, fo1 = 64 + 8 * k;
+    // y and z faces.  The shifts run on every lane before the selects: a DPP
+    // source lane that is switched off in EXEC reads as out of range.
+    const C* fy = ff + 8 * k;
+    const C* fz = ff + 128 + 8 * j;
 #pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            const C ko = O ? ky[x] : kc[x];
-            const C pu = lane_prev<true>(uc[x]), pk = lane_prev<true>(ko);
-            const C nu = j == 0 ? fu[fo0 + x] : pu;
-            const C nk = j == 0 ? fk[fo0 + x] : pk;
-            s[x] -= harm(ko, nk) * cf * (uc[x] - nu);
-            if (x % 2 == 1) __builtin_amdgcn_sched_barrier(0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            const C ko = O ? ky[x] : kc[x];
-            const C pu = lane_next<true>(uc[x]), pk = lane_next<true>(ko);
-            const C nu = j == 7 ? fu[fo1 + x] : pu;
-            const C nk = j == 7 ? fk[fo1 + x] : pk;
-            s[x] -= harm(ko, nk) * cf * (uc[x] - nu);
-            if (x % 2 == 1) __builtin_amdgcn_sched_barrier(0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    for (int x = 0; x < 8; ++x) {
+        const C ko = O ? ky[x] : kc[x];
+        const C pu = lane_prev<DY>(uc[x]), pk = lane_prev<DY>(ko);
+        const C ou = fy[x], ok = fy[64 + x], hi = fy[256 + x];
+        const C f = harm(ko, j == 0 ? ok : pk) * (C)g.cy * (uc[x] - (j == 0 ? ou : pu));
+        const C nf = lane_next<DY>(f);
+        s[x] -= f - (j == 7 ? -hi : nf);
+        if (x % 2 == 1) __builtin_amdgcn_sched_barrier(0);
     }
-    // the remaining faces one direction at a time (-y, +y,) -z, +z
-    // (orthotropic: the y and z faces take the y and z arrays, own pencil
-    // included)
-#pragma unroll 1
-    for (int d = DY ? 2 : 0; d < 4; ++d) {
-        const int src = (lane + (d == 0 ? -1 : (d == 1 ? 1 : (d == 2 ? -8 : 8)))) & 63;
-        const bool mem = d == 0 ? j == 0 : (d == 1 ? j == 7 : (d == 2 ? k == 0 : k == 7));
-        const int fo = d * 64 + 8 * (d < 2 ? k : j);
-        const C cf = (C)(d < 2 ? g.cy : g.cz);
 #pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            const C ko = O ? (d < 2 ? ky[x] : kz[x]) : kc[x];
-            const C su = __shfl(uc[x], src, 64), sk = __shfl(ko, src, 64);
-            const C nu = mem ? fu[fo + x] : su;
-            const C nk = mem ? fk[fo + x] : sk;
-            s[x] -= harm(ko, nk) * cf * (uc[x] - nu);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+    for (int x = 0; x < 8; ++x) {
+        const C ko = O ? kz[x] : kc[x];
+        const C pu = __shfl_up(uc[x], 8, 64), pk = __shfl_up(ko, 8, 64);
+        const C ou = fz[x], ok = fz[64 + x], hi = fz[256 + x];
+        const C f = harm(ko, k == 0 ? ok : pk) * (C)g.cz * (uc[x] - (k == 0 ? ou : pu));
+        const C nf = __shfl_down(f, 8, 64);
+        s[x] -= f - (k == 7 ? -hi : nf);
+        if (x % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -524,11 +524,11 @@ __device__ __forceinline__ void pencil_apply(const FineGeom& g, int lane, int j,
 template <bool O, bool DY, typename T, typename C>
 __device__ __forceinline__ void pencil_residual(const FineGeom& g, const T* __restrict__ kt, const T* __restrict__ u,
                                                 size_t row, int x0, int y0, int z0, int lane, int j, int k,
-                                                C* fu, C* fk, C (&s)[8], C (&uc)[8], C (&kc)[8]) {
+                                                C* ff, C (&s)[8], C (&uc)[8], C (&kc)[8]) {
     const size_t N = O ? g.ncell() : 0;   // offsets of the y and z arrays
+    C ky[8], kz[8];
     load8(u + row, uc);
     load8(kt + row, kc);
-    C ky[8], kz[8];
     if constexpr (O) {
         load8(kt + N + row, ky);
         load8(kt + 2 * N + row, kz);
@@ -538,8 +538,8 @@ __device__ __forceinline__ void pencil_residual(const FineGeom& g, const T* __re
     const size_t ip = xhi ? eidx(g, x0 + 8, y0 + j, z0 + k) : row;
     const C um = xlo ? (C)u[im] : C(0), km = xlo ? (C)kt[im] : C(0);
     const C up = xhi ? (C)u[ip] : C(0), kp = xhi ? (C)kt[ip] : C(0);
-    stage_faces_yz<O>(g, kt, [&](size_t i) { return u[i]; }, x0, y0, z0, lane, fu, fk);
-    pencil_apply<O, DY>(g, lane, j, k, uc, kc, ky, kz, um, km, up, kp, xlo, xhi, fu, fk, s);
+    stage_faces_yz<O>(g, kt, u, x0, y0, z0, lane, uc, O ? ky : kc, O ? kz : kc, ff);
+    pencil_apply<O, DY>(g, j, k, uc, kc, ky, kz, um, km, up, kp, xlo, xhi, ff, s);
 }
 
 // T: stored word of kappa~ and u; TB: stored word of the basis; C: the
@@ -551,7 +551,7 @@ __global__ __launch_bounds__(256) void k_resid_restrict(FineGeom g, const T* __r
                                                        int L, C* __restrict__ r2, const Scalars* sc,
                                                        int check_done) {
     if (check_done && sc->done) return;
-    __shared__ C sfu[4][256], sfk[4][256];
+    __shared__ C sff[4][512];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int m = g.mx * g.my * g.mz;
     const int nb = gridDim.x;
@@ -567,7 +567,7 @@ __global__ __launch_bounds__(256) void k_resid_restrict(FineGeom g, const T* __r
     {
         load8(r + row, s);
         C uc[8], kc[8];
-        pencil_residual<O, false>(g, kt, u, row, x0, ey * 8, ez * 8, lane, j, k, sfu[w], sfk[w], s, uc, kc);
+        pencil_residual<O, false>(g, kt, u, row, x0, ey * 8, ez * 8, lane, j, k, sff[w], s, uc, kc);
     }
     // restriction onto the element's kept basis vectors
     const int nkp = nkeep[e];
@@ -638,7 +638,7 @@ __global__ __launch_bounds__(64 * EX) void k_post_fused(FineGeom g, const T* __r
                                                         double* __restrict__ z, Scalars* sc, RedBuf rb, int mode) {
     if ((mode & 2) && sc->done) return;
     __shared__ double sred[EX];
-    __shared__ C sa[EX][512];        // y/z faces (fu, fk), then the row's u
+    __shared__ C sa[EX][512];        // y and z faces, then the row's u
     __shared__ double srr[EX][512];  // the row's r
     int x0, y0, z0;
     tile_origin(g, x0, y0, z0);
@@ -656,7 +656,7 @@ __global__ __launch_bounds__(64 * EX) void k_post_fused(FineGeom g, const T* __r
             srr[w][x * 64 + lane] = rv[x];
         }
     }
-    pencil_residual<O, true>(g, kt, u, row, ex0, y0, z0, lane, j, k, sa[w], sa[w] + 256, s, uc, kc);
+    pencil_residual<O, true>(g, kt, u, row, ex0, y0, z0, lane, j, k, sa[w], s, uc, kc);
     wave_lds_sync();
 #pragma unroll
     for (int x = 0; x < 8; ++x) sa[w][x * 64 + lane] = uc[x];
@@ -727,7 +727,7 @@ __global__ __launch_bounds__(256) void k_spmv_pcg(FineGeom g, const double* __re
                                                   const double* __restrict__ p, double* __restrict__ q,
                                                   Scalars* sc, RedBuf rb, int pbuf) {
     if (sc->done) return;
-    __shared__ double sfu[4][256], sfk[4][256];
+    __shared__ double sff[4][512];
     __shared__ double sred[4];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int e = block_element4();
@@ -739,7 +739,7 @@ __global__ __launch_bounds__(256) void k_spmv_pcg(FineGeom g, const double* __re
         double s[8], pc[8], kc[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) s[i] = 0.0;
-        pencil_residual<O, false>(g, kt, p, row, ex * 8, ey * 8, ez * 8, lane, j, k, sfu[w], sfk[w], s, pc, kc);
+        pencil_residual<O, false>(g, kt, p, row, ex * 8, ey * 8, ez * 8, lane, j, k, sff[w], s, pc, kc);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             s[i] = -s[i];
@@ -758,7 +758,7 @@ template <bool O>
 __global__ __launch_bounds__(256) void k_apply_A(FineGeom g, const double* __restrict__ kt,
                                                  const double* __restrict__ xv, const double* __restrict__ b,
                                                  double* __restrict__ y, int resid) {
-    __shared__ double sfu[4][256], sfk[4][256];
+    __shared__ double sff[4][512];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int e = block_element4();
     if (e >= g.mx * g.my * g.mz) return;   // whole wavefront; no block barriers
@@ -772,7 +772,7 @@ __global__ __launch_bounds__(256) void k_apply_A(FineGeom g, const double* __res
 #pragma unroll
         for (int i = 0; i < 8; ++i) s[i] = 0.0;
     }
-    pencil_residual<O, false>(g, kt, xv, row, ex * 8, ey * 8, ez * 8, lane, j, k, sfu[w], sfk[w], s, uc, kc);
+    pencil_residual<O, false>(g, kt, xv, row, ex * 8, ey * 8, ez * 8, lane, j, k, sff[w], s, uc, kc);
     if (!resid) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) s[i] = -s[i];
