@@ -65,7 +65,6 @@ __global__ __launch_bounds__(256) void k_total_mobility(int64_t n, const double*
 }
 
 constexpr int kMaxRateBlocks = 2048;   // slots of the per-block maxima in the workspace
-constexpr int kRateBlocks = 1024;      // used: every update block re-reads every slot
 constexpr int kRateThreads = 512;
 constexpr int kUpdateBlocks = 1280;    // about five workgroups of four wavefronts a CU
 
@@ -94,6 +93,8 @@ __device__ __forceinline__ void cell_xyz(int64_t i, int nx, int ny, int64_t n, i
 // Workgroups go to the 8 XCDs in turn; numbered like this, each XCD works on
 // one contiguous eighth of the cells, so that the neighbours of a cell, and what
 // the previous pass wrote of it, are in its own L2 (grids of a multiple of 8).
+// Both passes, in turn / like this: 23.0 / 21.4 us for 0.88 million cells, 25.4 /
+// 24.6 for 1.12, 40.4 / 38.6 for 2.1, 71.4 / 70.4 for 4.1, 169 / 176 for 8.4.
 __device__ __forceinline__ int64_t block_in_order() {
     const int b = blockIdx.x, nb = gridDim.x;
     return nb & 7 ? b : (b & 7) * (nb >> 3) + (b >> 3);
@@ -109,7 +110,9 @@ struct CellStep {
 // (from the cell itself at the boundary): all 15 values of all K cells are
 // then in flight at once, one wait for memory, where loads behind the tests
 // took two and a cell at a time as many again: 20.0 -> 14.8 us for 1.12 million
-// cells (54 MB in, 9 MB out), three cells a thread.
+// cells (54 MB in, 9 MB out), three cells a thread.  Both passes of a sub-step,
+// before and after, at 0.26, 0.88, 1.12, 2.1, 4.1 and 8.4 million cells: 11.1,
+// 25.6, 31.2, 44.6, 79.4, 200 -> 10.4, 21.4, 24.6, 38.6, 70.4, 176 us.
 template <int K>
 __global__ __launch_bounds__(kRateThreads) void k_sat_rate(int nx, int ny, int nz, double hx, double hy, double hz,
                                                            CellStep step, const double* __restrict__ phi,
@@ -215,7 +218,7 @@ __global__ __launch_bounds__(256) void k_sat_update(int64_t n, const double* __r
     load(first);
     double m = 0.0;
 #pragma unroll
-    for (int u = 0; u < kRateBlocks / 256; ++u) {
+    for (int u = 0; u < kMaxRateBlocks / 256; ++u) {
         const int k = threadIdx.x + 256 * u;
         if (k < nmax) m = fmax(m, block_max[k]);
     }
@@ -270,19 +273,19 @@ static int run_transport(const specmg_grid* grid, const double* phi_dev, const d
     double* rate = work_dev;
     double* fw = work_dev + n;
     double* block_max = work_dev + 2 * n;
-    // cells a thread: what brings the grid down to kRateBlocks workgroups, up to 4
-    // (beyond, a workgroup makes several passes)
-    const int64_t per = (int64_t)kRateThreads * kRateBlocks;
-    const int K = (int)std::min<int64_t>(4, (n + per - 1) / per);
-    const int64_t pass = (int64_t)K * kRateThreads, upass = 256 * kUpdateCells;
+    // cells a thread: what brings the grid down to 1024 workgroups, up to 3 (four
+    // take 176 registers); beyond kMaxRateBlocks of them, passes of equal length
+    const int64_t per = (int64_t)kRateThreads * 1024;
+    const int K = (int)std::min<int64_t>(3, (n + per - 1) / per);
     auto blocks = [&](int64_t cells, int cap) {   // a multiple of 8 from 64 workgroups
-        const int64_t b = std::min<int64_t>(cap, (n + cells - 1) / cells);
+        const int64_t chunks = (n + cells - 1) / cells, passes = (chunks + cap - 1) / cap;
+        const int64_t b = (chunks + passes - 1) / passes;
         return (int)(b < 64 ? b : (b + 7) / 8 * 8);
     };
-    const int nb = blocks(pass, kRateBlocks), nu = blocks(upass, kUpdateBlocks);
+    const int nb = blocks((int64_t)K * kRateThreads, kMaxRateBlocks), nu = blocks(256 * kUpdateCells, kUpdateBlocks);
     const int64_t row = kRateThreads / grid->nx;
     const CellStep step{kRateThreads % grid->nx, (int)(row % grid->ny), (int)(row / grid->ny)};
-    const auto k_rate = K == 1 ? k_sat_rate<1> : (K == 2 ? k_sat_rate<2> : (K == 3 ? k_sat_rate<3> : k_sat_rate<4>));
+    const auto k_rate = K == 1 ? k_sat_rate<1> : (K == 2 ? k_sat_rate<2> : k_sat_rate<3>);
     hipLaunchKernelGGL(k_transport_begin, dim3(blocks_for(n, 8192)), dim3(256), 0, s, n, s_dev, fw, t_dev);
     for (int m = 0; m < substeps; ++m) {
         hipLaunchKernelGGL(k_rate, dim3(nb), dim3(kRateThreads), 0, s, grid->nx, grid->ny, grid->nz, grid->hx, grid->hy,

@@ -1,5 +1,5 @@
 """Saturation sub-steps at sizes on both sides of every cells-a-thread rule (1 up
-to 524288 cells, then 2, 3, 4, and several passes beyond 2 million), with
+to 524288 cells, then 2, 3, and several passes beyond 3.1 million), with
 extents below, at and beyond the 512 cells between a thread's own, against the
 oracle; S within 1e-12 absolute and the summed step within 1e-12 relative, the
 bars of the smaller cases.
@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("shape", [(2, 3, 511), (3, 512, 1), (513, 2, 3), (1, 70000, 1), (64, 64, 128), (64, 64, 129),
-                                   (85, 220, 60), (131, 111, 109), (128, 128, 129), (9, 701, 700)])
+                                   (85, 220, 60), (131, 111, 109), (128, 128, 129), (9, 701, 700),
+                                   (150, 151, 152)])
 def test_sizes(shape):
     import torch
     from paper_2403_19342_amd.specmg import transport
