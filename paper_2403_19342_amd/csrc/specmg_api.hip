@@ -350,7 +350,7 @@ int nvec_for(int target) {
 //   residual + restriction (A_l blocks, r, u, V in; r_up out)    diag + cpl + 2 dim + Vsz + dimup
 //   prolongation (u in and out, V, e_up)                         2 dim + Vsz + dimup
 //   residual + sweep (A_l, D^-1, couplings, r, u in; e out)      2 diag + 3 cpl + 3 dim
-// and each further sweep pair (nu_c = 2) twice the last line plus a copy.
+// and each further sweep pair (nu_c = 2) twice the last line.
 // The coarsest product reads the n_L x n_L inverse and three n_L vectors.
 static void coarse_traffic(specmg_ctx* c) {
     double words = 0.0;
@@ -380,7 +380,7 @@ static void coarse_traffic(specmg_ctx* c) {
             dimup += up.nkeep_h[E];
         }
         words += 4 * diag + 7 * cpl + 9 * dim + 2 * vsz + 2 * dimup;
-        words += (c->nu_c - 1) * 2.0 * (2 * diag + 3 * cpl + 5 * dim);
+        words += (c->nu_c - 1) * 2.0 * (2 * diag + 3 * cpl + 3 * dim);
     }
     double nl = 0.0;
     for (int k : c->lev.back().nkeep_h) nl += k;
