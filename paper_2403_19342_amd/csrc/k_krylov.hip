@@ -5,7 +5,7 @@
 // Arnoldi step orthogonalises w = A z_j by classical Gram-Schmidt applied
 // twice, h = V^T w and w -= V h, in three streaming passes over the basis: the
 // first subtraction forms the second one's products as it goes, and the second
-// the norm.  At 96 x 64 x 128 (7 MB a vector) a step's orthogonalisation took
+// the norm.  At 96 x 64 x 128 (6.3 MB a vector) a step's orthogonalisation took
 // 130 us in five passes, and 85 in these, the basis read at 3.7 to 4.8 TB/s.  The (restart+1) x restart Hessenberg problem lives in device memory
 // and is reduced by Givens rotations there, so the host reads back only the
 // convergence flag.
