@@ -815,6 +815,9 @@ __global__ __launch_bounds__(256) void k_galerkin2(FineGeom g, const double* __r
 // Face blocks of level l+1 from those of level l (Galerkin with V_E):
 //   D_up[E][d] = sum_{c on face d of E} V_c^T D[c][d] V_c
 //   Aoff_up[E][ax] = sum_{c on face +ax of E} V_c^T Aoff[c][ax] V'_{c+ax}
+// A workgroup per parent and block (blockIdx.y: the six D, the three Aoff): each is a
+// chain of agg^2 children, and a workgroup a parent ran nine of them in turn (268
+// -> 39 us for 64 parents of 64 x 9 rows, 0.36 ms for 512 of 64 x 11 before).
 __global__ __launch_bounds__(256) void k_galerkin_up(CoarseGeom lo, CoarseGeom up, const double* __restrict__ Dlo,
                                                      const double* __restrict__ Aofflo,
                                                      const double* __restrict__ V,
@@ -831,63 +834,59 @@ __global__ __launch_bounds__(256) void k_galerkin_up(CoarseGeom lo, CoarseGeom u
     const int Ec[3] = {Ex, Ey, Ez};
     const int ext[3] = {up.mx, up.my, up.mz};
     const int estride[3] = {1, up.mx, up.mx * up.my};
-    const int cstride[3] = {1, lo.mx, lo.mx * lo.my};
-    for (int blk = 0; blk < 9; ++blk) {
-        const bool isD = blk < 6;
-        const int d = isD ? blk : 2 * (blk - 6) + 1;
-        const int ax = d >> 1;
-        const bool plus = d & 1;
-        const bool has_nb = isD || (Ec[ax] + 1 < ext[ax]);
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        if (has_nb) {
-            for (int f = 0; f < agg * agg; ++f) {
-                const int u = f % agg, v = f / agg;
-                int q[3];
-                q[ax] = plus ? agg - 1 : 0;
-                q[(ax + 1) % 3] = u;
-                q[(ax + 2) % 3] = v;
-                const int p = q[0] + agg * (q[1] + agg * q[2]);
-                const int c = (Ex * agg + q[0]) + lo.mx * ((Ey * agg + q[1]) + lo.my * (Ez * agg + q[2]));
-                // stage B, V_c and (for couplings) V'_{c'}
-                for (int t = threadIdx.x; t < Lp * Lp; t += blockDim.x)
-                    sB[t] = isD ? Dlo[((size_t)c * 6 + d) * Lp * Lp + t] : Aofflo[((size_t)c * 3 + ax) * Lp * Lp + t];
-                for (int t = threadIdx.x; t < Lp * Lu; t += blockDim.x) {
-                    const int b = t / Lu, j = t % Lu;
-                    sV[t] = V[((size_t)E * Lu + j) * n + p * Lp + b];
-                    if (isD) {
-                        sW[t] = sV[t];
-                    } else {
-                        int qn[3] = {q[0], q[1], q[2]};
-                        qn[ax] = 0;
-                        const int pn = qn[0] + agg * (qn[1] + agg * qn[2]);
-                        const int En = E + estride[ax];
-                        sW[t] = V[((size_t)En * Lu + j) * n + pn * Lp + b];
-                    }
+    const int blk = blockIdx.y;
+    const bool isD = blk < 6;
+    const int d = isD ? blk : 2 * (blk - 6) + 1;
+    const int ax = d >> 1;
+    const bool plus = d & 1;
+    const bool has_nb = isD || (Ec[ax] + 1 < ext[ax]);
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    if (has_nb) {
+        for (int f = 0; f < agg * agg; ++f) {
+            const int u = f % agg, v = f / agg;
+            int q[3];
+            q[ax] = plus ? agg - 1 : 0;
+            q[(ax + 1) % 3] = u;
+            q[(ax + 2) % 3] = v;
+            const int p = q[0] + agg * (q[1] + agg * q[2]);
+            const int c = (Ex * agg + q[0]) + lo.mx * ((Ey * agg + q[1]) + lo.my * (Ez * agg + q[2]));
+            // stage B, V_c and (for couplings) V'_{c'}
+            for (int t = threadIdx.x; t < Lp * Lp; t += blockDim.x)
+                sB[t] = isD ? Dlo[((size_t)c * 6 + d) * Lp * Lp + t] : Aofflo[((size_t)c * 3 + ax) * Lp * Lp + t];
+            for (int t = threadIdx.x; t < Lp * Lu; t += blockDim.x) {
+                const int b = t / Lu, j = t % Lu;
+                sV[t] = V[((size_t)E * Lu + j) * n + p * Lp + b];
+                if (isD) {
+                    sW[t] = sV[t];
+                } else {
+                    int qn[3] = {q[0], q[1], q[2]};
+                    qn[ax] = 0;
+                    const int pn = qn[0] + agg * (qn[1] + agg * qn[2]);
+                    const int En = E + estride[ax];
+                    sW[t] = V[((size_t)En * Lu + j) * n + pn * Lp + b];
                 }
-                __syncthreads();
-                for (int t = threadIdx.x; t < Lp * Lu; t += blockDim.x) {
-                    const int a = t / Lu, j = t % Lu;
-                    double s = 0.0;
-                    for (int b = 0; b < Lp; ++b) s += sB[a * Lp + b] * sW[b * Lu + j];
-                    sBW[t] = s;
-                }
-                __syncthreads();
-                for (int t = threadIdx.x, k = 0; t < Lu * Lu; t += blockDim.x, ++k) {
-                    const int i = t / Lu, j = t % Lu;
-                    double s = 0.0;
-                    for (int a = 0; a < Lp; ++a) s += sV[a * Lu + i] * sBW[a * Lu + j];
-                    acc[k] += s;
-                }
-                __syncthreads();
-                (void)cstride;
             }
-        }
-        for (int t = threadIdx.x, k = 0; t < Lu * Lu; t += blockDim.x, ++k) {
-            if (isD) Dup[((size_t)E * 6 + d) * Lu * Lu + t] = acc[k];
-            else Aoffup[((size_t)E * 3 + ax) * Lu * Lu + t] = acc[k];
+            __syncthreads();
+            for (int t = threadIdx.x; t < Lp * Lu; t += blockDim.x) {
+                const int a = t / Lu, j = t % Lu;
+                double s = 0.0;
+                for (int b = 0; b < Lp; ++b) s += sB[a * Lp + b] * sW[b * Lu + j];
+                sBW[t] = s;
+            }
+            __syncthreads();
+            for (int t = threadIdx.x, k = 0; t < Lu * Lu; t += blockDim.x, ++k) {
+                const int i = t / Lu, j = t % Lu;
+                double s = 0.0;
+                for (int a = 0; a < Lp; ++a) s += sV[a * Lu + i] * sBW[a * Lu + j];
+                acc[k] += s;
+            }
+            __syncthreads();
         }
     }
-    (void)nkeep_up;
+    for (int t = threadIdx.x, k = 0; t < Lu * Lu; t += blockDim.x, ++k) {
+        if (isD) Dup[((size_t)E * 6 + d) * Lu * Lu + t] = acc[k];
+        else Aoffup[((size_t)E * 3 + ax) * Lu * Lu + t] = acc[k];
+    }
 }
 
 // Ad = Aint + sum_d D[e][d]
@@ -1384,7 +1383,7 @@ void launch_galerkin2(const FineGeom& g, const double* kt, const double* phi, co
 
 void launch_galerkin_up(const CoarseGeom& lo, const CoarseGeom& up, const double* Dlo, const double* Aofflo,
                         const double* V, const int* nkeep_up, double* Dup, double* Aoffup, hipStream_t s) {
-    hipLaunchKernelGGL(k_galerkin_up, dim3(up.m), dim3(256), 0, s, lo, up, Dlo, Aofflo, V, nkeep_up, Dup, Aoffup);
+    hipLaunchKernelGGL(k_galerkin_up, dim3(up.m, 9), dim3(256), 0, s, lo, up, Dlo, Aofflo, V, nkeep_up, Dup, Aoffup);
 }
 
 void launch_assemble_diag(const CoarseGeom& g, const double* Aint, const double* D, double* Ad, hipStream_t s) {
