@@ -258,7 +258,8 @@ void launch_pre_smooth(const FineGeom& g, const T* kt, const T* invd, double* r,
                        T* u, Scalars* sc, RedBuf rb, int mode, hipStream_t s);
 template <typename T, typename TB, typename C>
 void launch_resid_restrict(const FineGeom& g, const T* kt, const T* u, const double* r, const TB* phi,
-                           const int* nkeep, int L, C* r2, Scalars* sc, int check_done, hipStream_t s);
+                           const int* nkeep, int L, C* r2, Scalars* sc, RedBuf rb, int pre_mode, int check_done,
+                          hipStream_t s);   // pre_mode: the mode of the pre-smoother before it, whose ||r||^2 it may sum
 template <typename T, typename TB, typename C>
 void launch_prolong(const FineGeom& g, T* u, const TB* phi, const int* nkeep, int L, const C* e2,
                     Scalars* sc, int check_done, hipStream_t s);

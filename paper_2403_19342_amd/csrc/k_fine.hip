@@ -542,19 +542,128 @@ __device__ __forceinline__ void pencil_residual(const FineGeom& g, const T* __re
     pencil_apply<O, DY>(g, j, k, uc, kc, ky, kz, um, km, up, kp, xlo, xhi, ff, s);
 }
 
+// Sums the block partials of one reduction and applies the CG scalar update
+// of the reduction site.  Block b sums partials [b kFinSpan, (b + 1) kFinSpan);
+// with several blocks each publishes its sum, and the block that arrives last
+// (an agent-scope ticket, reset by that block) adds them in block order.  Every
+// sum runs in a fixed order, so the result does not depend on timing.  A chain
+// of memory latencies between two full-grid kernels, so everything that is read
+// is read at once, the flag and the scalars too (waited for together before
+// the flag is looked at), and a single block (up to 2048 partials, 128^3 and
+// below) goes straight on to the scalars: 4.3 -> 2.4 us at 32^3, 5.2 -> 3.6 at
+// 96^3, 5.4 -> 4.4 at 128^3.
+// ONE: called by the last block of another kernel, for at most kFinSpan partials.
+template <bool ONE>
+__device__ __forceinline__ void finalize_blocks(int site, int nb, Scalars* sc, RedBuf rb, double* out, int check_done) {
+    __shared__ double sred[2][kFinThreads / 64];
+    __shared__ int last;
+    const int nv = (site == RS_RZ || site == RS_GEN2) ? 2 : 1;
+    const int b0 = ONE ? 0 : blockIdx.x * kFinSpan, lim = min(kFinSpan, nb - b0);
+    double a[2][kFinPer];
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int u = 0; u < kFinPer; ++u) {
+            const int i = u * kFinThreads + threadIdx.x;
+            a[k][u] = k < nv && i < lim ? rb.partial[(size_t)k * kMaxRedBlocks + b0 + i] : 0.0;
+        }
+    Scalars in{};
+    if (sc) in = *sc;
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int u = 0; u < kFinPer; ++u) asm volatile("" : "+v"(a[k][u]));
+    if (check_done && in.done) return;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    auto sum2 = [&](double x, double y, double (&t)[2]) {
+        x = wave_sum(x);
+        y = wave_sum(y);
+        __syncthreads();
+        if (lane == 0) {
+            sred[0][w] = x;
+            sred[1][w] = y;
+        }
+        __syncthreads();
+        t[0] = t[1] = 0.0;
+#pragma unroll
+        for (int i = 0; i < kFinThreads / 64; ++i) {
+            t[0] += sred[0][i];
+            t[1] += sred[1][i];
+        }
+    };
+    double v[2] = {0.0, 0.0}, t[2];
+#pragma unroll
+    for (int u = 0; u < kFinPer; ++u) {
+        v[0] += a[0][u];
+        v[1] += a[1][u];
+    }
+    sum2(v[0], v[1], t);
+    if (!ONE && gridDim.x > 1) {
+        if (threadIdx.x == 0) {
+            for (int k = 0; k < nv; ++k)
+                __hip_atomic_store(rb.partial2 + k * kFinBlocks + blockIdx.x, t[k], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned prev = __hip_atomic_fetch_add(rb.ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+            last = prev == gridDim.x - 1;
+        }
+        __syncthreads();
+        if (!last) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        for (int k = 0; k < nv; ++k)
+            v[k] = threadIdx.x < gridDim.x ? atomic_load_relaxed(rb.partial2 + k * kFinBlocks + threadIdx.x) : 0.0;
+        sum2(v[0], nv > 1 ? v[1] : 0.0, t);
+        if (threadIdx.x == 0) __hip_atomic_store(rb.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (threadIdx.x != 0) return;
+    if (site == RS_PQ) {
+        sc->pq = t[0];
+        sc->iter = in.iter + 1;
+        if (!(t[0] > 0.0) || !isfinite(t[0])) {
+            sc->done = 2;
+            sc->alpha = 0.0;
+            sc->alpha_x = 0.0;
+        } else {
+            sc->alpha = in.rz / t[0];
+            sc->alpha_x = in.rz / t[0];
+        }
+    } else if (site == RS_RR) {
+        sc->rr = t[0];
+        if (t[0] <= in.thresh2) sc->done = 1;
+        else if (!isfinite(t[0])) sc->done = 2;
+    } else if (site == RS_RZ) {
+        const double old = in.rz;
+        double beta = 0.0;
+        if (old != 0.0) beta = in.flexible ? (-in.alpha * t[1] / old) : (t[0] / old);
+        sc->beta = beta;
+        sc->rz_new = t[0];
+        sc->zq = t[1];
+        sc->rz = t[0];
+    } else {
+        out[0] = t[0];
+        if (nv == 2) out[1] = t[1];
+    }
+}
+
 // T: stored word of kappa~ and u; TB: stored word of the basis; C: the
-// arithmetic and the word of the level-2 residual r2
+// arithmetic and the word of the level-2 residual r2.  rr_parts: one block more
+// than the elements need sums the pre-smoother's ||r||^2, whose outcome (the
+// converged flag) stops the kernels after this one: a launch of its own, 4.4 us
+// at 128^3, waited for nothing that this kernel does.
 template <typename T, typename TB, typename C, bool O>
 __global__ __launch_bounds__(256) void k_resid_restrict(FineGeom g, const T* __restrict__ kt,
                                                        const T* __restrict__ u, const double* __restrict__ r,
                                                        const TB* __restrict__ phi, const int* __restrict__ nkeep,
-                                                       int L, C* __restrict__ r2, const Scalars* sc,
-                                                       int check_done) {
+                                                       int L, C* __restrict__ r2, Scalars* sc, RedBuf rb,
+                                                       int rr_parts, int check_done) {
+    if (rr_parts && blockIdx.x == gridDim.x - 1) {
+        finalize_blocks<true>(RS_RR, rr_parts, sc, rb, nullptr, check_done);
+        return;
+    }
     if (check_done && sc->done) return;
     __shared__ C sff[4][512];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int m = g.mx * g.my * g.mz;
-    const int nb = gridDim.x;
+    const int nb = gridDim.x - (rr_parts ? 1 : 0);
     int b = blockIdx.x;
     if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
     const int e = b * 4 + (threadIdx.x >> 6);
@@ -906,105 +1015,9 @@ __global__ __launch_bounds__(256) void k_sum_abs(const double* __restrict__ a, i
     write_partials<2>(v, rb);
 }
 
-// Sums the block partials of one reduction and applies the CG scalar update
-// of the reduction site.  Block b sums partials [b kFinSpan, (b + 1) kFinSpan);
-// with several blocks each publishes its sum, and the block that arrives last
-// (an agent-scope ticket, reset by that block) adds them in block order.  Every
-// sum runs in a fixed order, so the result does not depend on timing.  A chain
-// of memory latencies between two full-grid kernels, so everything that is read
-// is read at once, the flag and the scalars too (waited for together before
-// the flag is looked at), and a single block (up to 2048 partials, 128^3 and
-// below) goes straight on to the scalars: 4.3 -> 2.4 us at 32^3, 5.2 -> 3.6 at
-// 96^3, 5.4 -> 4.4 at 128^3.
 __global__ __launch_bounds__(kFinThreads) void k_finalize(int site, int nb, Scalars* sc, RedBuf rb, double* out,
                                                           int check_done) {
-    __shared__ double sred[2][kFinThreads / 64];
-    __shared__ int last;
-    const int nv = (site == RS_RZ || site == RS_GEN2) ? 2 : 1;
-    const int b0 = blockIdx.x * kFinSpan, lim = min(kFinSpan, nb - b0);
-    double a[2][kFinPer];
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-        for (int u = 0; u < kFinPer; ++u) {
-            const int i = u * kFinThreads + threadIdx.x;
-            a[k][u] = k < nv && i < lim ? rb.partial[(size_t)k * kMaxRedBlocks + b0 + i] : 0.0;
-        }
-    Scalars in{};
-    if (sc) in = *sc;
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-#pragma unroll
-        for (int u = 0; u < kFinPer; ++u) asm volatile("" : "+v"(a[k][u]));
-    if (check_done && in.done) return;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    auto sum2 = [&](double x, double y, double (&t)[2]) {
-        x = wave_sum(x);
-        y = wave_sum(y);
-        __syncthreads();
-        if (lane == 0) {
-            sred[0][w] = x;
-            sred[1][w] = y;
-        }
-        __syncthreads();
-        t[0] = t[1] = 0.0;
-#pragma unroll
-        for (int i = 0; i < kFinThreads / 64; ++i) {
-            t[0] += sred[0][i];
-            t[1] += sred[1][i];
-        }
-    };
-    double v[2] = {0.0, 0.0}, t[2];
-#pragma unroll
-    for (int u = 0; u < kFinPer; ++u) {
-        v[0] += a[0][u];
-        v[1] += a[1][u];
-    }
-    sum2(v[0], v[1], t);
-    if (gridDim.x > 1) {
-        if (threadIdx.x == 0) {
-            for (int k = 0; k < nv; ++k)
-                __hip_atomic_store(rb.partial2 + k * kFinBlocks + blockIdx.x, t[k], __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            const unsigned prev = __hip_atomic_fetch_add(rb.ticket, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-            last = prev == gridDim.x - 1;
-        }
-        __syncthreads();
-        if (!last) return;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        for (int k = 0; k < nv; ++k)
-            v[k] = threadIdx.x < gridDim.x ? atomic_load_relaxed(rb.partial2 + k * kFinBlocks + threadIdx.x) : 0.0;
-        sum2(v[0], nv > 1 ? v[1] : 0.0, t);
-        if (threadIdx.x == 0) __hip_atomic_store(rb.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (threadIdx.x != 0) return;
-    if (site == RS_PQ) {
-        sc->pq = t[0];
-        sc->iter = in.iter + 1;
-        if (!(t[0] > 0.0) || !isfinite(t[0])) {
-            sc->done = 2;
-            sc->alpha = 0.0;
-            sc->alpha_x = 0.0;
-        } else {
-            sc->alpha = in.rz / t[0];
-            sc->alpha_x = in.rz / t[0];
-        }
-    } else if (site == RS_RR) {
-        sc->rr = t[0];
-        if (t[0] <= in.thresh2) sc->done = 1;
-        else if (!isfinite(t[0])) sc->done = 2;
-    } else if (site == RS_RZ) {
-        const double old = in.rz;
-        double beta = 0.0;
-        if (old != 0.0) beta = in.flexible ? (-in.alpha * t[1] / old) : (t[0] / old);
-        sc->beta = beta;
-        sc->rz_new = t[0];
-        sc->zq = t[1];
-        sc->rz = t[0];
-    } else {
-        out[0] = t[0];
-        if (nv == 2) out[1] = t[1];
-    }
+    finalize_blocks<false>(site, nb, sc, rb, out, check_done);
 }
 
 void launch_finalize(int site, int nblocks, Scalars* sc, RedBuf rb, double* out, int check_done,
@@ -1101,21 +1114,27 @@ static inline int grid_1d(int64_t n) {
         __VA_ARGS__;                                                                       \
     }
 
+// the sum of ||r||^2 rides in the residual's launch if one block can form it
+static bool rr_with_restrict(const FineGeom& g) { return g.ntiles <= kFinSpan; }
+
 template <typename T, typename C>
 void launch_pre_smooth(const FineGeom& g, const T* kt, const T* invd, double* r, const double* q, T* u,
                        Scalars* sc, RedBuf rb, int mode, hipStream_t s) {
     SPECMG_O_DISPATCH(T, SPECMG_EX_DISPATCH(g.ex, SPECMG_TIMED_LAUNCH((k_pre_smooth<EX, T, C, O>), dim3(g.ntiles),
                                                                       dim3(64 * EX), 0, s, g, kt, invd, r, q, u, sc,
                                                                       rb, mode)));
-    if (mode & 1) launch_finalize(RS_RR, g.ntiles, sc, rb, nullptr, (mode & 2) ? 1 : 0, s);
+    if ((mode & 1) && !rr_with_restrict(g)) launch_finalize(RS_RR, g.ntiles, sc, rb, nullptr, (mode & 2) ? 1 : 0, s);
 }
 
 template <typename T, typename TB, typename C>
 void launch_resid_restrict(const FineGeom& g, const T* kt, const T* u, const double* r, const TB* phi,
-                           const int* nkeep, int L, C* r2, Scalars* sc, int check_done, hipStream_t s) {
+                           const int* nkeep, int L, C* r2, Scalars* sc, RedBuf rb, int pre_mode, int check_done,
+                          hipStream_t s) {
     const int m = g.mx * g.my * g.mz;
-    SPECMG_O_DISPATCH(T, SPECMG_TIMED_LAUNCH((k_resid_restrict<T, TB, C, O>), dim3((m + 3) / 4), dim3(256), 0, s, g,
-                                             kt, u, r, phi, nkeep, L, r2, sc, check_done));
+    const int rr_parts = (pre_mode & 1) && rr_with_restrict(g) ? g.ntiles : 0;
+    SPECMG_O_DISPATCH(T, SPECMG_TIMED_LAUNCH((k_resid_restrict<T, TB, C, O>), dim3((m + 3) / 4 + (rr_parts ? 1 : 0)),
+                                             dim3(256), 0, s, g, kt, u, r, phi, nkeep, L, r2, sc, rb, rr_parts,
+                                             check_done));
 }
 
 template <typename T, typename TB, typename C>
@@ -1231,7 +1250,7 @@ void launch_pcg_init(Scalars* sc, double thresh2, int flexible, hipStream_t s) {
     template void launch_pre_smooth<T, C>(const FineGeom&, const T*, const T*, double*, const double*, T*,         \
                                           Scalars*, RedBuf, int, hipStream_t);                                     \
     template void launch_resid_restrict<T, TB, C>(const FineGeom&, const T*, const T*, const double*, const TB*,   \
-                                                  const int*, int, C*, Scalars*, int, hipStream_t);                \
+                                                  const int*, int, C*, Scalars*, RedBuf, int, int, hipStream_t);   \
     template void launch_prolong<T, TB, C>(const FineGeom&, T*, const TB*, const int*, int, const C*, Scalars*,    \
                                            int, hipStream_t);                                                      \
     template void launch_post_fused<T, C>(const FineGeom&, const T*, const T*, const T*, const double*,            \
@@ -1241,7 +1260,7 @@ SPECMG_FINE_INST(float, float, float)
 SPECMG_FINE_INST(float, float, double)
 template void launch_resid_restrict<double, float, double>(const FineGeom&, const double*, const double*,
                                                            const double*, const float*, const int*, int, double*,
-                                                           Scalars*, int, hipStream_t);
+                                                           Scalars*, RedBuf, int, int, hipStream_t);
 template void launch_prolong<double, float, double>(const FineGeom&, double*, const float*, const int*, int,
                                                     const double*, Scalars*, int, hipStream_t);
 #undef SPECMG_FINE_INST

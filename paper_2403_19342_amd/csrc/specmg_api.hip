@@ -296,7 +296,7 @@ void vcycle_fine(specmg_ctx* c, double* r, double* z, const double* q, int pre_m
     prof_end(c, ev, PC_PRE, s);
     for (int it = 1; it < c->nu; ++it) extra_fine_sweep<T, C>(c, r, z, check, s);
     ev = prof_begin(c, s);
-    launch_resid_restrict<T, TB, C>(c->fg, kt, u1, r, phi, l2.nkeep, l2.L, r2, c->sc, check, s);
+    launch_resid_restrict<T, TB, C>(c->fg, kt, u1, r, phi, l2.nkeep, l2.L, r2, c->sc, c->rb, pre_mode, check, s);
     prof_end(c, ev, PC_RESTRICT, s);
     ev = prof_begin_range(c, s);
     if constexpr (std::is_same<C, float>::value) {
