@@ -168,6 +168,12 @@ __device__ __forceinline__ void invert_block(gl_double* T, int m, int ld, lds_do
     }
 }
 
+// Cycles with the inverse filter: up to 10 were seen to suffice, all but one
+// of some 36,000 elements a field; what is left converges by the filter in
+// H_E, of kDampDeg applications.
+constexpr int kInverseCycles = 14;
+constexpr int kDampDeg = 40;
+
 template <int M, int NT>
 struct UpShared {
     double G[M * M];
@@ -630,6 +636,28 @@ struct UpProblem {
         }
     }
 
+    // The Chebyshev polynomial of H_E itself that damps [a, b], for blocks on
+    // which the inverses' rounding (their error times |H_E|) stays above the
+    // tolerance: Y <- T_deg((H_E - c) / e) Y
+    __device__ __forceinline__ void damp_inl(double a, double b, int deg) const {
+        const double c = 0.5 * (a + b), ie = 2.0 / (b - a);
+#pragma unroll 1
+        for (int d = 1; d <= deg; ++d) {
+            apply();
+            __syncthreads();
+            for (int t = threadIdx.x; t < n * PG; t += NT) {
+                const int i = t / PG, j = t % PG;
+                if (j >= M) continue;
+                const double y = Y[i * PT + j];
+                const double z = (AYg[t] - c * y) * ie;
+                const double v = d == 1 ? z : 2.0 * z - Xg[t];
+                Xg[t] = y;
+                Y[i * PT + j] = v;
+            }
+            __syncthreads();
+        }
+    }
+
     // The phases as calls of their own (inlined together they exceed the
     // registers and the instruction cache), each on a copy of the problem in scalar
     // registers.
@@ -659,6 +687,7 @@ struct UpProblem {
         return scalar().rayleigh_ritz_inl(rough, nval, pad);
     }
     __device__ __attribute__((noinline)) void factor(double sigma) const { scalar().factor_inl(sigma); }
+    __device__ __attribute__((noinline)) void damp(double a, double b) const { scalar().damp_inl(a, b, kDampDeg); }
     __device__ __attribute__((noinline)) void filter(double a, double sigma, int deg) const {
         scalar().filter_inl(a, sigma, (int)uniform32((unsigned)deg));
     }
@@ -835,6 +864,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_
                 const double a = sh.th[M - 1], want = fmax(0.1 * a, 1e-7 * bnd);
                 const int nk = cluster_cut_dev(sh.th, M, target, crtol, thr);
                 __syncthreads();
+                if (cyc >= kInverseCycles) {
+                    pr.damp(a, bnd);
+                    ++cyc;
+                    continue;
+                }
                 if (sigma < 0.0 || want < 0.7 * sigma || want > sigma) {
                     sigma = want;
                     pr.factor(sigma);
