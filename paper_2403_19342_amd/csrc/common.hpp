@@ -333,14 +333,14 @@ void launch_coarse_smooth(const CoarseGeom& g, const T* SM, T* r, int nparts, T*
 // the first kernel to read r_up adds them
 int coarse_restrict_parts(const CoarseGeom& g);
 template <typename T>
-void launch_coarse_resid_restrict(const CoarseGeom& g, const T* Ad, const T* Aoff, const T* r,
+void launch_coarse_resid_restrict(const CoarseGeom& g, const T* AdT, const T* Aoff, const T* r,
                                   const T* u, const T* V, const int* nkeep_up, int Lup, T* rup,
                                   const Scalars* sc, int check_done, hipStream_t s);
 template <typename T>
 void launch_coarse_prolong(const CoarseGeom& g, T* u, const T* V, const int* nkeep_up, int Lup,
                            const T* eup, const Scalars* sc, int check_done, hipStream_t s);
 template <typename T>
-void launch_coarse_resid_smooth(const CoarseGeom& g, const T* Ad, const T* Aoff, const T* SM, const T* r,
+void launch_coarse_resid_smooth(const CoarseGeom& g, const T* AdT, const T* Aoff, const T* SM, const T* r,
                                 const T* u, T* e, const Scalars* sc, int check_done, hipStream_t s);
 // words of the sweep's matrices SM (g.m elements of level l)
 size_t coarse_sweep_doubles(const CoarseGeom& g);
@@ -369,7 +369,7 @@ void launch_galerkin_up(const CoarseGeom& lo, const CoarseGeom& up, const double
 void launch_assemble_diag(const CoarseGeom& g, const double* Aint, const double* D, double* Ad,
                           hipStream_t s);
 void launch_blockic_setup(const CoarseGeom& g, const double* Ad, const double* Aoff, const int* nkeep,
-                          double* Dinv, double* SM, int* bad, hipStream_t s);
+                          double* Dinv, double* SM, double* AdT, int* bad, hipStream_t s);
 void launch_build_coarsest(const CoarseGeom& g, const double* Ad, const double* Aoff,
                            const int* cmap_inv, int np, double* dense, hipStream_t s);
 template <typename S, typename T>
@@ -395,10 +395,8 @@ void launch_cnn_backward(const void* packs, int k, int kp, const float* patches,
                          hipStream_t s);
 void launch_cnn_adam(float* theta, const float* grad, float* m1, float* m2, int64_t n, float lr, float b1, float b2,
                      float eps, float c1, float c2, uint16_t* theta16, hipStream_t s);
-// doubles of the workspace of launch_eig_up (free once the stream has passed it)
-size_t eig_up_work_doubles(const CoarseGeom& lo, const CoarseGeom& up, int nvec);
 void launch_eig_up(const CoarseGeom& lo, const CoarseGeom& up, const double* Aint_lo, const double* Dlo,
-                   const double* Aofflo, const int* nkeep_lo, const double* zlo, double* Hd_work, double* work,
+                   const double* Aofflo, const int* nkeep_lo, const double* zlo, double* Hd_work,
                    int target, int nvec, double tol, double crtol, double thr, double* V, double* lam, int* nkeep,
                    double* Aint, double* zup, int* status, hipStream_t s);
 

@@ -74,14 +74,18 @@ __device__ void build_planes(int agg, int* pos, int* off) {
 constexpr int kMaxLc = 23;   // padded widths up to target 20 + 3 (levels >= 3)
 constexpr int kNarrow = 13;  // widths up to target 10 + 3 get their own instantiations
 
-// y_c = (A_l u)_c for row a of child element c: the diagonal block (symmetric:
-// its column, which neighbouring rows read side by side), then both coupling
-// blocks of each axis (at the domain boundary from valid stand-in rows of the
-// element itself, whose sums a select then drops).  ALL: every load of the row
-// is in flight at once, one wait for memory, for launches that leave the chip
-// idle; otherwise one axis at a time, four waits but half the registers.
-template <typename T, int LP, bool ALL>
-__device__ __forceinline__ T block_row_apply(const CoarseGeom& g, const T* __restrict__ Ad,
+// y_c = (A_l u)_c for row a of child element c: the diagonal block (its row,
+// which neighbouring threads read side by side from the transposed copy AdT),
+// then both coupling blocks of each axis (at the domain boundary from valid
+// stand-in rows of the element itself, whose sums a select then drops).  The
+// order of the sums is part of the result (on media of contrast 1e6 the last bit
+// of a pressure shows in the face fluxes): in a sweep (SWEEP) the two sums of an
+// axis first; in a residual to be restricted one after the other, at widths above
+// 9 entry by entry onto the row's sum.  ALL: every load of the row is in flight at
+// once, one wait for memory, for launches that leave the chip idle; otherwise one
+// axis at a time, four waits but half the registers.
+template <typename T, int LP, bool ALL, bool SWEEP>
+__device__ __forceinline__ T block_row_apply(const CoarseGeom& g, const T* __restrict__ AdT,
                                              const T* __restrict__ Aoff, const T* __restrict__ u, int c,
                                              int a) {
     constexpr bool RT = LP == kMaxLc;   // the widest serves every width above kNarrow
@@ -89,7 +93,7 @@ __device__ __forceinline__ T block_row_apply(const CoarseGeom& g, const T* __res
     const int cx = c % g.mx, cy = (c / g.mx) % g.my, cz = c / (g.mx * g.my);
     T acc = T(0);
     {
-        const T* ad = Ad + (size_t)c * W * W + a;
+        const T* ad = AdT + (size_t)c * W * W + a;
         const T* uc = u + (size_t)c * W;
 #pragma unroll
         for (int b = 0; b < LP; ++b)
@@ -106,15 +110,34 @@ __device__ __forceinline__ T block_row_apply(const CoarseGeom& g, const T* __res
         const T* om = Aoff + ((size_t)cm * 3 + ax) * W * W + a;
         const T* up = u + (size_t)cp * W;
         const T* um = u + (size_t)cm * W;
-        T sp = T(0), sm = T(0);
+        if constexpr (SWEEP || LP <= 9) {
+            T sp = T(0), sm = T(0);
 #pragma unroll
-        for (int b = 0; b < LP; ++b) {
-            if (RT && b >= W) continue;
-            sp += op[b] * up[b];
-            sm += om[b * W] * um[b];
+            for (int b = 0; b < LP; ++b) {
+                if (RT && b >= W) continue;
+                sp += op[b] * up[b];
+                sm += om[b * W] * um[b];
+            }
+            sp = hp ? sp : T(0);
+            sm = hm ? sm : T(0);
+            if constexpr (SWEEP) {
+                acc += sp + sm;
+            } else {
+                acc += sp;
+                acc += sm;
+            }
+        } else {
+            T t = acc;
+#pragma unroll
+            for (int b = 0; b < LP; ++b)
+                if (!RT || b < W) t += op[b] * up[b];
+            acc = hp ? t : acc;
+            t = acc;
+#pragma unroll
+            for (int b = 0; b < LP; ++b)
+                if (!RT || b < W) t += om[b * W] * um[b];
+            acc = hm ? t : acc;
         }
-        acc += hp ? sp : T(0);
-        acc += hm ? sm : T(0);
     };
     if constexpr (ALL && !RT) {
 #pragma unroll
@@ -128,7 +151,7 @@ __device__ __forceinline__ T block_row_apply(const CoarseGeom& g, const T* __res
 
 constexpr int kCoarseThreads = 1024;   // upper bound; launches use agg^3 L rounded to waves
 constexpr int kMaxChildren = 64;   // agg <= 4
-constexpr int kRestrictParts4 = 4;   // parts of a parent's restricted residual (agg 4)
+constexpr int kMaxParts = 12;      // parts of a parent's restricted residual (agg 4: up to its width)
 constexpr int kMaxL = kMaxLc;      // set-up arrays of the levels >= 3
 constexpr int kMaxL2 = 16;         // level 2 (target <= 10)
 
@@ -178,9 +201,9 @@ struct ResidRow {
     __device__ static __forceinline__ Place place(const CoarseGeom& g, int c, int a, int k, int pos) {
         return {c, a, k, pos & 3, (pos >> 2) & 3, pos >> 4, c % g.mx, (c / g.mx) % g.my, c / (g.mx * g.my)};
     }
-    // A(c, c) is symmetric, so its column a, which neighbouring rows read side
-    // by side, stands for its row; A(c, c+e) = Aoff[c][ax], A(c, c-e) = Aoff[c-e][ax]^T,
-    // beyond the domain any block of the array, against zeros
+    // row a of A(c, c) from the transposed copy, where neighbouring rows lie side by
+    // side; A(c, c+e) = Aoff[c][ax], A(c, c-e) = Aoff[c-e][ax]^T, beyond the domain
+    // any block of the array, against zeros
     __device__ static __forceinline__ const T* above_row(const Place& p, const T* Aoff, int ax) {
         return Aoff + (((size_t)p.c * 3 + ax) * LP + p.a) * LP;
     }
@@ -197,10 +220,10 @@ struct ResidRow {
         const int i = ax == 0 ? p.qy : p.qx, j = ax == 2 ? p.qy : p.qz;
         return in ? kCP.rank4[up ? pos + st : pos - st] : 64 + ((2 * ax + (up ? 1 : 0)) << 4) + i + (j << 2);
     }
-    __device__ __forceinline__ void load(const CoarseGeom& g, const Place& p, const T* __restrict__ Ad,
+    __device__ __forceinline__ void load(const CoarseGeom& g, const Place& p, const T* __restrict__ AdT,
                                          const T* __restrict__ Aoff) {
 #pragma unroll
-        for (int b = 0; b < LP; ++b) ad[b] = Ad[((size_t)p.c * LP + b) * LP + p.a];
+        for (int b = 0; b < LP; ++b) ad[b] = AdT[((size_t)p.c * LP + b) * LP + p.a];
 #pragma unroll
         for (int ax = 0; ax < FIRST; ++ax) {
             const T* po = above_row(p, Aoff, ax);
@@ -248,6 +271,21 @@ struct ResidRow {
     }
 };
 
+// value of a level vector that arrives in nparts parts, pstride apart: all loaded
+// at once, added in order
+template <typename T>
+__device__ __forceinline__ T gather_parts(const T* r, int nparts, int64_t pstride) {
+    T v = r[0];
+    if (nparts > 1) {
+        T w[kMaxParts - 1];
+#pragma unroll
+        for (int i = 1; i < kMaxParts; ++i) w[i - 1] = r[(i < nparts ? i : 0) * pstride];
+#pragma unroll
+        for (int i = 1; i < kMaxParts; ++i) v = i < nparts ? v + w[i - 1] : v;
+    }
+    return v;
+}
+
 // parents of one sweep workgroup: with 2x aggregation as many as fill about 512
 // threads (a parent has 8 W rows), otherwise one
 constexpr int sweep_parents(int agg, int W) {
@@ -275,7 +313,7 @@ constexpr int sweep_parents(int agg, int W) {
 // 9.8 / 13.4 -> 9.1 / 13.2 (27 of 64 x 7).
 template <typename T, int LP, bool A2, int MODE>
 __global__ __launch_bounds__(A2 ? 512 : 64 * LP) void k_coarse_sweep(
-    CoarseGeom g, const T* __restrict__ Ad, const T* __restrict__ Aoff, const T* __restrict__ SM,
+    CoarseGeom g, const T* __restrict__ AdT, const T* __restrict__ Aoff, const T* __restrict__ SM,
     T* __restrict__ r, const T* u, T* out, const Scalars* sc, int check_done, int npar, int nparts) {
     if (check_done && sc->done) return;
     // row width: LP, except in the widest instantiation, which serves every
@@ -320,19 +358,19 @@ __global__ __launch_bounds__(A2 ? 512 : 64 * LP) void k_coarse_sweep(
     if (live) {
         tv = r[row];
         // the restriction's partial sums, in order; their sum is kept in r
-        for (int i = 1; MODE == 0 && i < nparts; ++i) tv += r[row + (size_t)i * g.m * W];
+        if (MODE == 0 && nparts > 1) tv = gather_parts(r + row, nparts, (int64_t)g.m * W);
     }
     if (MODE == 0 && nparts > 1 && live) r[row] = tv;
     if constexpr (MODE && A2) {
         if (live) {
             own = u[row];
-            tv -= block_row_apply<T, LP, false>(g, Ad, Aoff, u, c, a);
+            tv -= block_row_apply<T, LP, false, true>(g, AdT, Aoff, u, c, a);
         }
     } else if constexpr (MODE) {
         using Row = ResidRow<T, LP>;
         const auto at = Row::place(g, c, a, k, p);
         Row rr;
-        if (live) rr.load(g, at, Ad, Aoff);
+        if (live) rr.load(g, at, AdT, Aoff);
         stage_u<T, LP>(g, u, blockIdx.x, sU);
         __syncthreads();
         if (live) {
@@ -430,44 +468,49 @@ __global__ __launch_bounds__(A2 ? 512 : 64 * LP) void k_coarse_sweep(
 }
 
 // s = r - A_l u on the children of parent E, then r_up[E] = V_E^T s, one row a
-// thread.  With agg 4 a workgroup takes one z plane of a parent's children and
-// writes its part of the sum (part p at r_up + p M Lup; the kernel that reads
-// r_up next adds the parts in order): a parent is a small task for 16 W rows
-// of latency, and levels of 27 to 64 parents left most of the chip idle.
-template <typename T, int LP, int LU, bool A2>
-__global__ __launch_bounds__(((A2 ? 8 : 16) * LP + 63) / 64 * 64) __attribute__((amdgpu_waves_per_eu(A2 ? 4 : 2))) void k_coarse_resid_restrict(
-    CoarseGeom g, const T* __restrict__ Ad, const T* __restrict__ Aoff, const T* __restrict__ r,
+// thread, the wavefronts' sums added in wavefront order.  SPLIT (agg 4, few
+// parents): a workgroup is one of the W wavefronts of 64 rows that a parent has,
+// and writes its part of the sum (part p at r_up + p M Lup; the kernel that reads
+// r_up next adds the parts in order): a parent is a small task for 64 W rows of
+// latency, and levels of 27 to 64 parents left most of the chip idle.
+template <typename T, int LP, int LU, bool A2, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? 64 : ((A2 ? 8 : 64) * LP + 63) / 64 * 64) void k_coarse_resid_restrict(
+    CoarseGeom g, const T* __restrict__ AdT, const T* __restrict__ Aoff, const T* __restrict__ r,
     const T* __restrict__ u, const T* __restrict__ V, const int* __restrict__ nkeep_up, int Lup,
     T* __restrict__ rup, const Scalars* sc, int check_done) {
     if (check_done && sc->done) return;
     constexpr bool RT = LP == kMaxLc;
-    constexpr int PARTS = A2 ? 1 : kRestrictParts4, NC = A2 ? 8 : 64;
-    __shared__ double sacc[(16 * LP + 63) / 64][LU];
-    const int E = blockIdx.x / PARTS, part = blockIdx.x % PARTS;
-    const int W = RT ? g.L : LP, n = NC * W, rows = n / PARTS;
+    constexpr int NC = A2 ? 8 : 64;
+    __shared__ double sacc[SPLIT ? 1 : (NC * LP + 63) / 64][LU];
+    const int W = RT ? g.L : LP, n = NC * W;
+    const int E = SPLIT ? blockIdx.x / W : blockIdx.x, part = SPLIT ? blockIdx.x % W : 0;
     const int nk = nkeep_up[E];
-    const int t = threadIdx.x, tr = t < rows ? t : 0;
-    const int p = part * (NC / PARTS) + tr / W, a = tr % W;
+    const int t = 64 * part + threadIdx.x, tr = t < n ? t : 0;
+    const int p = tr / W, a = tr % W;
     const int c = child_of(g, E, p);
-    const bool live = t < rows && (g.nkeep == nullptr || a < g.nkeep[c]);   // zero rows beyond the kept slots
-    const T* v = V + (size_t)E * Lup * n + (size_t)p * W + a;
+    const bool live = t < n && (g.nkeep == nullptr || a < g.nkeep[c]);   // zero rows beyond the kept slots
+    const T* v = V + (size_t)E * Lup * n + tr;
     T vv[LU];
 #pragma unroll
     for (int j = 0; j < LU; ++j) vv[j] = live ? v[(size_t)(j < nk ? j : nk - 1) * n] : T(0);
     double sv = 0.0;
-    if (live) sv = (double)(r[(size_t)c * W + a] - block_row_apply<T, LP, !A2>(g, Ad, Aoff, u, c, a));
+    if (live) sv = (double)(r[(size_t)c * W + a] - block_row_apply<T, LP, SPLIT, false>(g, AdT, Aoff, u, c, a));
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    double mine = 0.0;
 #pragma unroll
     for (int j = 0; j < LU; ++j) {
-        const double x = wave_sum((double)vv[j] * sv);
-        if (lane == 0) sacc[w][j] = x;
+        // the product rounded by itself: left bare, it is contracted with the first step of the sum
+        const double x = wave_sum(fma((double)vv[j], sv, 0.0));
+        if (SPLIT) mine = lane == j ? x : mine;
+        else if (lane == 0) sacc[w][j] = x;
     }
-    __syncthreads();
-    if ((int)threadIdx.x < Lup) {
-        double x = 0.0;
-        for (int ww = 0; ww < (int)(blockDim.x >> 6); ++ww) x += sacc[ww][threadIdx.x];
-        rup[((size_t)part * g.M + E) * Lup + threadIdx.x] = (int)threadIdx.x < nk ? (T)x : T(0);
+    if constexpr (!SPLIT) {
+        __syncthreads();
+        if ((int)threadIdx.x < Lup)
+            for (int ww = 0; ww < (int)(blockDim.x >> 6); ++ww) mine += sacc[ww][threadIdx.x];
     }
+    if ((int)threadIdx.x < Lup)
+        rup[((size_t)part * g.M + E) * Lup + threadIdx.x] = (int)threadIdx.x < nk ? (T)mine : T(0);
 }
 
 // u += V_E e_up[E] on the children of E
@@ -503,20 +546,6 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_prolong(CoarseGeom g,
 // at a time (64 KB contiguous per row and chunk: concurrent streams of many
 // rows a full row apart share few HBM channels and ran at 2.2 TB/s).
 constexpr int kCoarsestRows = 16;
-
-// value of a level vector that arrives in nparts parts, pstride apart
-template <typename T>
-__device__ __forceinline__ T gather_parts(const T* r, int nparts, int64_t pstride) {
-    T v = r[0];
-    if (nparts == kRestrictParts4) {
-        T w[kRestrictParts4 - 1];
-#pragma unroll
-        for (int i = 1; i < kRestrictParts4; ++i) w[i - 1] = r[i * pstride];
-#pragma unroll
-        for (int i = 1; i < kRestrictParts4; ++i) v += w[i - 1];
-    }
-    return v;
-}
 
 template <typename T>
 __global__ void k_gather_compact(int n, const int* __restrict__ cmap, const T* __restrict__ r, int nparts, int64_t pstride,
@@ -583,7 +612,6 @@ __global__ __launch_bounds__(64 * NW) void k_coarsest(int n, int np, const doubl
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int i0 = blockIdx.x * NW * RW + w * RW;
     for (int j = threadIdx.x; j < n; j += blockDim.x) srz[j] = (double)gather_parts(r + cmap[j], nparts, pstride);
-    if ((n & 1) && threadIdx.x == 0) srz[n] = 0.0;
     __syncthreads();
     double acc[RW];
     const double* row[RW];
@@ -592,15 +620,12 @@ __global__ __launch_bounds__(64 * NW) void k_coarsest(int n, int np, const doubl
         acc[q] = 0.0;
         row[q] = Pinv + (size_t)min(i0 + q, n - 1) * np;
     }
-    // pairs of columns (np is a multiple of 32, so the last pair exists)
-#pragma unroll 4
-    for (int j = 2 * lane; j < n; j += 128) {
-        const double2 v = *reinterpret_cast<const double2*>(srz + j);
+    // lane l sums the columns l, l + 64, ... in turn
+#pragma unroll 8
+    for (int j = lane; j < n; j += 64) {
+        const double v = srz[j];
 #pragma unroll
-        for (int q = 0; q < RW; ++q) {
-            const double2 m = *reinterpret_cast<const double2*>(row[q] + j);
-            acc[q] += m.x * v.x + m.y * v.y;
-        }
+        for (int q = 0; q < RW; ++q) acc[q] += row[q][j] * v;
     }
 #pragma unroll
     for (int q = 0; q < RW; ++q) {
@@ -905,25 +930,27 @@ __global__ void k_assemble_diag(CoarseGeom g, const double* __restrict__ Aint, c
 // children of one hyperplane (at most 12, 3 with agg 2) are factored in
 // parallel, one wavefront each.  Entry t = lane + 64 u of an L x L block is
 // lane's u-th register, U of them; LDS passes blocks and pivot rows around
-// the wavefront.  The inverse is that of the Cholesky factor, A = L L^T,
-// W = L^{-1} by eliminating [A | I] row by row (column k of I takes the place
-// that column k of A leaves), then W^T W; padded slots (index >= nkeep) are
-// rows of the identity.
+// the wavefront.  The inverse solves C C^T X = I with the Cholesky factor C:
+// the factor and the forward substitution eliminate [A | I] row by row (column k
+// of I takes the place that column k of A leaves), the backward substitution
+// takes a lane a column.  Every entry sees its products in the order of the
+// textbook loops (k ascending, divisions by the pivot's root): the order is part
+// of the result, see block_row_apply.  Padded slots (index >= nkeep) are rows of
+// the identity.
 // A chain: per plane one memory round trip, three Schur updates, L pivots of
-// one LDS round trip each.  With lane 0 alone factoring and lane k solving for
-// column k, from LDS, and the couplings read where they are used, it took 433 us for
-// 64 parents of 64 x 9 (128^3), 2.2 ms for 512 of 64 x 11, 46 ms for the 32768 of
-// 8 x 9 and 4096 of 8 x 13 at 512^3; now 85 us, 0.20 ms and 1.2 ms.
+// one LDS round trip, a root and a division each, L steps back.
 constexpr int kMaxPlane = 12;   // children per hyperplane of a 4^3 parent
-template <int U>
+template <int LP>
 __global__ __launch_bounds__(64 * kMaxPlane) void k_blockic_setup(CoarseGeom g, const double* __restrict__ Ad,
                                                                    const double* __restrict__ Aoff,
                                                                    const int* __restrict__ nkeep, double* Dinv,
                                                                    int* bad) {
+    constexpr bool RT = LP == kMaxLc;   // the widest serves every width above kNarrow
+    constexpr int U = (LP * LP + 63) / 64;
     __shared__ int pos[kMaxChildren], off[12];
     extern __shared__ double work_lds[];   // [children of the widest plane][3][L * L]
     const int E = blockIdx.x;
-    const int L = g.L, agg = g.agg, LL = L * L;
+    const int L = RT ? g.L : LP, agg = g.agg, LL = L * L;
     build_planes(agg, pos, off);
     const int nplanes = 3 * (agg - 1) + 1;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1005,47 +1032,55 @@ __global__ __launch_bounds__(64 * kMaxPlane) void k_blockic_setup(CoarseGeom g, 
                 P[u] = 0.5 * (P[u] + sA[col[u] * L + row[u]]);
                 if (row[u] >= nk || col[u] >= nk) P[u] = row[u] == col[u] ? 1.0 : 0.0;
             }
-            // W, its rows scaled at the end by the root of their pivots
-            double piv[U];
+            // C (to sA) and C^-1
             bool ok = true;
-#pragma unroll
-            for (int u = 0; u < U; ++u) piv[u] = 1.0;
             for (int k = 0; k < L; ++k) {
+                // column k of what is left of A from row k on, row k of what has come of I before
 #pragma unroll
                 for (int u = 0; u < U; ++u)
-                    if (in[u] && row[u] == k) sR[col[u]] = P[u];
+                    if (in[u]) {
+                        if (col[u] == k && row[u] >= k) sR[row[u]] = P[u];
+                        if (row[u] == k && col[u] < k) sR[col[u]] = P[u];
+                    }
                 wave_sync();
                 double d = sR[k];
                 if (!(d > 0.0)) {
                     ok = false;
                     d = 1.0;
                 }
-                const double rd = 1.0 / d;
+                const double root = sqrt(d);
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const double l = sR[row[u]] * rd, f = sR[col[u]];
-                    if (row[u] > k) P[u] = col[u] == k ? -l : P[u] - l * f;
-                    if (row[u] == k) {
-                        piv[u] = d;
-                        if (col[u] == k) P[u] = 1.0;
+                    const double l = sR[row[u]] / root, f = (col[u] == k ? 1.0 : sR[col[u]]) / root;
+                    if (row[u] > k) {
+                        if (in[u] && col[u] == k) sA[row[u] * L + k] = l;
+                        P[u] = col[u] == k ? -(l * f) : P[u] - l * f;
+                    } else if (row[u] == k && col[u] <= k) {
+                        P[u] = f;
                     }
                 }
+                if (lane == 0) sA[k * L + k] = root;
                 wave_sync();
             }
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                if (in[u]) sA[lane + 64 * u] = col[u] <= row[u] ? P[u] / sqrt(piv[u]) : 0.0;
+                if (in[u]) sB[lane + 64 * u] = col[u] <= row[u] ? P[u] : 0.0;
             wave_sync();
+            if (lane < L) {
+                double x[LP];
 #pragma unroll
-            for (int u = 0; u < U; ++u) P[u] = 0.0;
-            for (int b = 0; b < L; ++b)
+                for (int i = LP - 1; i >= 0; --i) {
+                    if (RT && i >= L) continue;
+                    double v = sB[i * L + lane];
 #pragma unroll
-                for (int u = 0; u < U; ++u) P[u] += sA[b * L + row[u]] * sA[b * L + col[u]];
+                    for (int k = 0; k < LP; ++k)
+                        if (k > i && (!RT || k < L)) v -= sA[k * L + i] * x[k];
+                    x[i] = v / sA[i * L + i];
+                    Dinv[(size_t)c * LL + i * L + lane] = x[i];
+                }
+            }
             wave_sync();
             if (!ok && lane == 0) atomicOr(bad, 2);
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (in[u]) Dinv[(size_t)c * LL + lane + 64 * u] = P[u];
         }
         __syncthreads();   // the plane's pivots are read by this workgroup alone
     }
@@ -1053,8 +1088,10 @@ __global__ __launch_bounds__(64 * kMaxPlane) void k_blockic_setup(CoarseGeom g, 
 
 // the sweep's matrices: Dinv_c, and Dinv_c A(c, c -+ e_ax) for neighbours
 // inside the same parent (zero otherwise), in the layout of k_coarse_sweep
-__global__ __launch_bounds__(256) void k_blockic_couple(CoarseGeom g, const double* __restrict__ Aoff,
-                                                         const double* __restrict__ Dinv, double* __restrict__ SM) {
+__global__ __launch_bounds__(256) void k_blockic_couple(CoarseGeom g, const double* __restrict__ Ad,
+                                                         const double* __restrict__ Aoff,
+                                                         const double* __restrict__ Dinv, double* __restrict__ SM,
+                                                         double* __restrict__ AdT) {
     const int c = blockIdx.x;
     const int L = g.L, LL = L * L, agg = g.agg, nc = agg * agg * agg;
     const int cx = c % g.mx, cy = (c / g.mx) % g.my, cz = c / (g.mx * g.my);
@@ -1063,6 +1100,7 @@ __global__ __launch_bounds__(256) void k_blockic_couple(CoarseGeom g, const doub
     const int E = cx / agg + g.px * (cy / agg + g.py * (cz / agg)), pos = q[0] + agg * (q[1] + agg * q[2]);
     const int k = agg == 4 ? kCP.rank4[pos] : kCP.rank2[pos], nd = agg == 4 ? 7 : 4, rows = nc * L;
     const double* Di = Dinv + (size_t)c * LL;
+    for (int t = threadIdx.x; t < LL; t += blockDim.x) AdT[(size_t)c * LL + t % L * L + t / L] = Ad[(size_t)c * LL + t];
     for (int t = threadIdx.x; t < nd * LL; t += blockDim.x) {
         const int d = t / LL, b = (t % LL) / L, a = t % L;
         double v = 0.0;
@@ -1084,7 +1122,9 @@ __global__ __launch_bounds__(256) void k_blockic_couple(CoarseGeom g, const doub
     }
 }
 
-int coarse_restrict_parts(const CoarseGeom& g) { return g.agg == 4 ? kRestrictParts4 : 1; }
+// a part a wavefront where one workgroup a parent would leave more than half of
+// the CUs idle
+int coarse_restrict_parts(const CoarseGeom& g) { return g.agg == 4 && g.M <= 128 ? g.L : 1; }
 
 size_t coarse_sweep_doubles(const CoarseGeom& g) { return (size_t)g.m * (g.agg == 4 ? 7 : 4) * g.L * g.L; }
 
@@ -1182,7 +1222,7 @@ __global__ void k_convert(const S* __restrict__ src, T* __restrict__ dst, int64_
 // block barrier.
 template <typename T, int LP, int LU>
 __global__ __launch_bounds__(256) void k_coarse_resid_restrict_w(
-    CoarseGeom g, const T* __restrict__ Ad, const T* __restrict__ Aoff, const T* __restrict__ r,
+    CoarseGeom g, const T* __restrict__ AdT, const T* __restrict__ Aoff, const T* __restrict__ r,
     const T* __restrict__ u, const T* __restrict__ V, const int* __restrict__ nkeep_up, int Lup,
     T* __restrict__ rup, const Scalars* sc, int check_done) {
     if (check_done && sc->done) return;
@@ -1207,7 +1247,7 @@ __global__ __launch_bounds__(256) void k_coarse_resid_restrict_w(
             for (int q = 1; q < 8; ++q) p += qr >= pre[q] ? 1 : 0;
             const int a = qr - pre[p];
             const int c = child_of(g, E, p);
-            const double sv = (double)(r[(size_t)c * L + a] - block_row_apply<T, LP, false>(g, Ad, Aoff, u, c, a));
+            const double sv = (double)(r[(size_t)c * L + a] - block_row_apply<T, LP, false, false>(g, AdT, Aoff, u, c, a));
             const T* vc = V + (size_t)E * Lup * n + (size_t)p * L + a;
 #pragma unroll
             for (int j = 0; j < LU; ++j)
@@ -1224,42 +1264,47 @@ __global__ __launch_bounds__(256) void k_coarse_resid_restrict_w(
 }
 
 template <typename T>
-void launch_coarse_resid_restrict(const CoarseGeom& g0, const T* Ad, const T* Aoff, const T* r, const T* u,
+void launch_coarse_resid_restrict(const CoarseGeom& g0, const T* AdT, const T* Aoff, const T* r, const T* u,
                                   const T* V, const int* nkeep_up, int Lup, T* rup, const Scalars* sc,
                                   int check_done, hipStream_t s) {
     CoarseGeom g = g0;
-    if (g.agg == 4 && g.M * kRestrictParts4 <= 256) g.nkeep = nullptr;   // as the sweeps
-    const int parts = coarse_restrict_parts(g), rows = g.agg * g.agg * g.agg * g.L / parts;
-    const int th = (rows + 63) / 64 * 64;
-    if (g.L < 4 || g.L > kMaxLc) throw HipError{hipErrorInvalidValue, "coarse residual width"};
+    const bool split = coarse_restrict_parts(g) > 1;
+    if (split) g.nkeep = nullptr;   // as the sweeps
+    const int rows = g.agg * g.agg * g.agg * g.L;
+    const dim3 nb(g.M), th((rows + 63) / 64 * 64);
+    if (g.L < 4 || g.L > kMaxLc || (g.agg == 4 && g.L > kMaxParts))
+        throw HipError{hipErrorInvalidValue, "coarse residual width"};
     if (Lup > kMaxLc) throw HipError{hipErrorInvalidValue, "coarse residual upper width"};
     // wider blocks keep about 8 L > 64 rows per parent, two passes of the
     // wavefront: there the workgroup form is faster
     if (g.agg == 2 && g.L <= 9) {
-        const int nb = (g.M + 3) / 4;
+        const int nb4 = (g.M + 3) / 4;
         if (Lup <= kNarrow) {
-            SPECMG_LP_DISPATCH_NARROW(g.L, hipLaunchKernelGGL((k_coarse_resid_restrict_w<T, LP, kNarrow>), dim3(nb),
-                                                       dim3(256), 0, s, g, Ad, Aoff, r, u, V, nkeep_up, Lup, rup, sc,
+            SPECMG_LP_DISPATCH_NARROW(g.L, hipLaunchKernelGGL((k_coarse_resid_restrict_w<T, LP, kNarrow>), dim3(nb4),
+                                                       dim3(256), 0, s, g, AdT, Aoff, r, u, V, nkeep_up, Lup, rup, sc,
                                                        check_done));
         } else {
-            SPECMG_LP_DISPATCH_NARROW(g.L, hipLaunchKernelGGL((k_coarse_resid_restrict_w<T, LP, kMaxLc>), dim3(nb),
-                                                       dim3(256), 0, s, g, Ad, Aoff, r, u, V, nkeep_up, Lup, rup, sc,
+            SPECMG_LP_DISPATCH_NARROW(g.L, hipLaunchKernelGGL((k_coarse_resid_restrict_w<T, LP, kMaxLc>), dim3(nb4),
+                                                       dim3(256), 0, s, g, AdT, Aoff, r, u, V, nkeep_up, Lup, rup, sc,
                                                        check_done));
         }
-    } else if (g.agg == 2) {
-        SPECMG_LP_DISPATCH_WIDE(g.L, if (Lup <= kNarrow)
-            hipLaunchKernelGGL((k_coarse_resid_restrict<T, LP, kNarrow, true>), dim3(g.M), dim3(th), 0, s, g, Ad, Aoff, r,
-                               u, V, nkeep_up, Lup, rup, sc, check_done);
-            else hipLaunchKernelGGL((k_coarse_resid_restrict<T, LP, kMaxLc, true>), dim3(g.M), dim3(th), 0, s, g, Ad, Aoff,
-                                    r, u, V, nkeep_up, Lup, rup, sc, check_done));
-    } else {
-        const dim3 nb(g.M * parts);
-        SPECMG_LP_DISPATCH(g.L, if (Lup <= kNarrow)
-            hipLaunchKernelGGL((k_coarse_resid_restrict<T, LP, kNarrow, false>), nb, dim3(th), 0, s, g, Ad, Aoff, r, u, V,
-                               nkeep_up, Lup, rup, sc, check_done);
-            else hipLaunchKernelGGL((k_coarse_resid_restrict<T, LP, kMaxLc, false>), nb, dim3(th), 0, s, g, Ad, Aoff, r, u,
-                                    V, nkeep_up, Lup, rup, sc, check_done));
+        return;
     }
+#define SPECMG_RESTRICT(A2, SPLIT, NB, TH)                                                                            \
+    if (Lup <= kNarrow)                                                                                               \
+        hipLaunchKernelGGL((k_coarse_resid_restrict<T, LP, kNarrow, A2, SPLIT>), NB, TH, 0, s, g, AdT, Aoff, r, u, V,   \
+                           nkeep_up, Lup, rup, sc, check_done);                                                       \
+    else                                                                                                              \
+        hipLaunchKernelGGL((k_coarse_resid_restrict<T, LP, kMaxLc, A2, SPLIT>), NB, TH, 0, s, g, AdT, Aoff, r, u, V,    \
+                           nkeep_up, Lup, rup, sc, check_done)
+    if (g.agg == 2) {
+        SPECMG_LP_DISPATCH_WIDE(g.L, SPECMG_RESTRICT(true, false, nb, th));
+    } else if (split) {
+        SPECMG_LP_DISPATCH_SWEEP4(g.L, SPECMG_RESTRICT(false, true, dim3(g.M * g.L), dim3(64)));
+    } else {
+        SPECMG_LP_DISPATCH_SWEEP4(g.L, SPECMG_RESTRICT(false, false, nb, th));
+    }
+#undef SPECMG_RESTRICT
 }
 
 template <typename T>
@@ -1287,7 +1332,7 @@ static int sweep_blocks(const CoarseGeom& g) {
 }
 
 template <typename T, int MODE>
-static void launch_sweep(const CoarseGeom& g0, const T* Ad, const T* Aoff, const T* SM, T* r, const T* u, T* out,
+static void launch_sweep(const CoarseGeom& g0, const T* AdT, const T* Aoff, const T* SM, T* r, const T* u, T* out,
                          const Scalars* sc, int check_done, int nparts, hipStream_t s) {
     CoarseGeom g = g0;
     if (g.L < 4 || g.L > kMaxLc || sweep_threads(g) > 768) throw HipError{hipErrorInvalidValue, "coarse sweep shape"};
@@ -1298,10 +1343,10 @@ static void launch_sweep(const CoarseGeom& g0, const T* Ad, const T* Aoff, const
     // (27 parents of 64 x 7 rows: 9.8 -> 9.1 us; 64 of 64 x 9: no difference)
     if (sweep_blocks(g) <= 256) g.nkeep = nullptr;
     if (g.agg == 2) {
-        SPECMG_LP_DISPATCH(g.L, hipLaunchKernelGGL((k_coarse_sweep<T, LP, true, MODE>), nb, th, 0, s, g, Ad, Aoff, SM, r, u,
+        SPECMG_LP_DISPATCH(g.L, hipLaunchKernelGGL((k_coarse_sweep<T, LP, true, MODE>), nb, th, 0, s, g, AdT, Aoff, SM, r, u,
                                                    out, sc, check_done, npar, nparts));
     } else {
-        SPECMG_LP_DISPATCH_SWEEP4(g.L, hipLaunchKernelGGL((k_coarse_sweep<T, LP, false, MODE>), nb, th, 0, s, g, Ad, Aoff,
+        SPECMG_LP_DISPATCH_SWEEP4(g.L, hipLaunchKernelGGL((k_coarse_sweep<T, LP, false, MODE>), nb, th, 0, s, g, AdT, Aoff,
                                                           SM, r, u, out, sc, check_done, npar, nparts));
     }
 }
@@ -1315,9 +1360,9 @@ void launch_coarse_smooth(const CoarseGeom& g, const T* SM, T* r, int nparts, T*
 
 // e = u + M_l^{-1} (r - A_l u)
 template <typename T>
-void launch_coarse_resid_smooth(const CoarseGeom& g, const T* Ad, const T* Aoff, const T* SM, const T* r, const T* u, T* e,
+void launch_coarse_resid_smooth(const CoarseGeom& g, const T* AdT, const T* Aoff, const T* SM, const T* r, const T* u, T* e,
                                 const Scalars* sc, int check_done, hipStream_t s) {
-    launch_sweep<T, 1>(g, Ad, Aoff, SM, const_cast<T*>(r), u, e, sc, check_done, 1, s);
+    launch_sweep<T, 1>(g, AdT, Aoff, SM, const_cast<T*>(r), u, e, sc, check_done, 1, s);
 }
 
 int coarsest_sym_tile() { return kSymT; }
@@ -1358,7 +1403,7 @@ template <typename T>
 void launch_coarsest(int n, int np, const double* Pinv, const int* cmap, const T* r, int nparts, int64_t pstride, T* e,
                      double* rc,
                      const Scalars* sc, int check_done, hipStream_t s) {
-    const size_t lds = (size_t)(std::min(n, kCoarsestChunk) + 1) * sizeof(double);
+    const size_t lds = (size_t)std::min(n, kCoarsestChunk) * sizeof(double);
     if (n <= 1024) {
         SPECMG_TIMED_LAUNCH((k_coarsest<T, 1, 4>), dim3((n + 3) / 4), dim3(256), lds, s, n, np, Pinv, cmap, r, nparts,
                             pstride, e, sc, check_done);
@@ -1391,17 +1436,14 @@ void launch_assemble_diag(const CoarseGeom& g, const double* Aint, const double*
 }
 
 void launch_blockic_setup(const CoarseGeom& g, const double* Ad, const double* Aoff, const int* nkeep,
-                          double* Dinv, double* SM, int* bad, hipStream_t s) {
+                          double* Dinv, double* SM, double* AdT, int* bad, hipStream_t s) {
     // widest hyperplane of the parent's children: 3 (agg 2) or 12 (agg 4)
     const int wmax = g.agg == 2 ? 3 : kMaxPlane;
     const size_t shmem = (size_t)wmax * 3 * g.L * g.L * sizeof(double);
     if (g.L > kMaxL || shmem > 64 * 1024) throw HipError{hipErrorInvalidValue, "block-IC set-up shape"};
     const dim3 nb(g.M), th(64 * wmax);
-    const int entries = (g.L * g.L + 63) / 64;
-    if (entries <= 2) hipLaunchKernelGGL(k_blockic_setup<2>, nb, th, shmem, s, g, Ad, Aoff, nkeep, Dinv, bad);
-    else if (entries <= 4) hipLaunchKernelGGL(k_blockic_setup<4>, nb, th, shmem, s, g, Ad, Aoff, nkeep, Dinv, bad);
-    else hipLaunchKernelGGL(k_blockic_setup<9>, nb, th, shmem, s, g, Ad, Aoff, nkeep, Dinv, bad);
-    hipLaunchKernelGGL(k_blockic_couple, dim3(g.m), dim3(256), 0, s, g, Aoff, Dinv, SM);
+    SPECMG_LP_DISPATCH(g.L, hipLaunchKernelGGL(k_blockic_setup<LP>, nb, th, shmem, s, g, Ad, Aoff, nkeep, Dinv, bad));
+    hipLaunchKernelGGL(k_blockic_couple, dim3(g.m), dim3(256), 0, s, g, Ad, Aoff, Dinv, SM, AdT);
 }
 
 void launch_build_coarsest(const CoarseGeom& g, const double* Ad, const double* Aoff, const int* cinv, int np,

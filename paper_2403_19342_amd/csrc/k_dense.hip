@@ -3,9 +3,8 @@
 // matrix-vector product.
 //
 // Matrices are row-major np x np with np a multiple of 32 (padding rows and
-// columns carry an identity).  Up to kElimMax rows, which is every matrix that
-// is kept dense, k_elim_* eliminate by blocks of 64 (second half of this file).
-// Above, Cholesky A = L L^T is right-looking in panels of KB = 256 columns: inside a panel, 32 x 32 diagonal tiles in LDS, a panel
+// columns carry an identity).  Cholesky A = L L^T is right-looking in panels
+// of KB = 256 columns: inside a panel, 32 x 32 diagonal tiles in LDS, a panel
 // solve and rank-32 updates restricted to the panel; after the panel, one
 // rank-KB update of the trailing lower triangle.  W = L^{-1}: every KB x KB
 // diagonal block inverted at once, then halves joined bottom-up,
@@ -359,353 +358,9 @@ static void trtri_node(const double* Lm, double* W, double* P, int np, int b0, i
     launch_gemm<OPN, OPN, 0>(q, s);
 }
 
-// ---------------------------------------------------------------------------
-// Spaces of up to kElimMax unknowns: A = L L^T and W = L^{-1} in one forward
-// elimination of [A | I] by blocks of 64, two launches a block.
-//
-// The lower tiles of the working matrix V hold, at step k, the rows of
-// L^{-1} applied so far in the columns j <= k (I starts implicitly: column k
-// enters at step k) and the remaining A in the columns j > k.  Step k, with
-// W_kk = L_kk^{-1} already in V_kk:
-//   k_elim_panel   Y_i = A_ik W_kk^T for i > k (kept as Y^T, 64 x nw), and
-//                  row k: W_kj = W_kk V_kj for j < k
-//   k_elim_update  rows i > k: V_ij -= Y_i W_kj (j <= k, V_ik from zero),
-//                  V_ij -= Y_i Y_j^T (j > k); the workgroup of the next
-//                  diagonal tile goes on to factor and invert it, which the
-//                  other tiles hide
-// and at the end A^{-1} = W^T W (k_elim_wtw).  The arithmetic is that of
-// the factorisation by panels; what it saves is the serial part (there
-// 3 launches for 32 columns, 45 us at any size, and 0.46 to 0.66 ms for the
-// inverses of the diagonal blocks).  All products are wavefront tiles of 32 x
-// 32 on v_mfma_f64_16x16x4f64 whose operands are read from the caches in
-// operand order: rows of V and of Y^T, 16 consecutive columns a lane group,
-// so nothing is staged and nothing waits.  Measured, panels of 256 columns
-// against this: 0.066 / 0.031 ms at 32 rows, 1.23 / 0.164 at 384, 2.57 / 0.42
-// at 1024, 10.4 / 2.8 at 4096, 14.2 / 4.7 at 5120, 29.4 / 17.0 at 8192.  The
-// rank-64 updates read and write their whole range, np^3 / 12 bytes in all,
-// four times what panels of 256 do, and pass the caches by then: hence
-// kElimMax.  A step below 2000 rows is the launch of the panel (5 us) and the
-// 18 us of the update's diagonal tile.
-constexpr int EB = 64;
-constexpr int kElimMax = 8192;
-constexpr int ELD = EB + 2, EYD = 18;
-
-static int elim_ld(int np) { return (np + EB - 1) / EB * EB; }
-
-__device__ __forceinline__ double rcp_f64(double x) {
-    const double y = __builtin_amdgcn_rcp(x);
-    const double e = fma(-x, y, 1.0);
-    return fma(y, fma(e, e, e), y);
-}
-
-union F64Words {
-    double d;
-    unsigned w[2];
-};
-
-// lane l of x, for a compile-time l
-template <int LANE>
-__device__ __forceinline__ double lane_value(double x) {
-    F64Words u{x};
-    u.w[0] = __builtin_amdgcn_readlane(u.w[0], LANE);
-    u.w[1] = __builtin_amdgcn_readlane(u.w[1], LANE);
-    return u.d;
-}
-
-// lane J of every group of 16 lanes, to its group
-template <int J>
-__device__ __forceinline__ double group_lane(double x) {
-    F64Words u{x};
-#pragma unroll
-    for (int h = 0; h < 2; ++h) u.w[h] = __builtin_amdgcn_update_dpp(0, (int)u.w[h], 0x150 + J, 0xf, 0xf, true);
-    return u.d;
-}
-
-// group G of 16 lanes, to all four groups
-template <int G>
-__device__ __forceinline__ double group_bcast(double x) {
-    F64Words u{x};
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const auto y = __builtin_amdgcn_permlane32_swap(u.w[h], u.w[h], false, false);
-        const unsigned z = G < 2 ? y[0] : y[1];
-        const auto v = __builtin_amdgcn_permlane16_swap(z, z, false, false);
-        u.w[h] = G % 2 == 0 ? v[0] : v[1];
-    }
-    return u.d;
-}
-
-// pivot J of elim_diag16
-template <int J>
-__device__ __forceinline__ void elim_pivot(double (&a)[4], int g, int i, double& dsave, bool& ok) {
-    constexpr int G = J / 4, E = J % 4;
-    double d = lane_value<16 * G + J>(a[E]);
-    if (!(d > 0.0)) {
-        ok = false;
-        d = 1.0;
-    }
-    if (i == J) dsave = d;
-    const double q = group_bcast<G>(a[E]) * rcp_f64(d);
-    const double lf = i > J ? -q : 0.0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const double t = fma(lf, group_lane<J>(a[e]), a[e]);
-        a[e] = e == E && g == G ? (i == J ? 1.0 : lf) : t;
-    }
-    if constexpr (J < 15) elim_pivot<J + 1>(a, g, i, dsave, ok);
-}
-
-// The 16 x 16 tile of S at (r0, r0), symmetric, becomes the inverse of its
-// Cholesky factor: [A | I] eliminated pivot by pivot in one wavefront, lane
-// 16 g + i holding row i, columns 4 g to 4 g + 3; column j of I takes the
-// place that column j of A leaves.  Returns false if a pivot is not positive.
-__device__ __forceinline__ bool elim_diag16(double* S, int r0) {
-    const int i = threadIdx.x & 15, g = (threadIdx.x >> 4) & 3;
-    double* T = S + (r0 + i) * ELD + r0 + 4 * g;
-    double a[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) a[e] = T[e];
-    double dsave = 1.0;
-    bool ok = true;
-    elim_pivot<0>(a, g, i, dsave, ok);
-    const double rs = 1.0 / sqrt(dsave);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) T[e] = 4 * g + e <= i ? a[e] * rs : 0.0;
-    return ok;
-}
-
-// acc += sum over 16 values of k of A(i, k) B(k, j); A(i, k) at a[i * ai + k * ak]
-__device__ __forceinline__ dbl4 elim_mul16(const double* a, int ai, int ak, const double* b, int bk, int bj,
-                                           dbl4 acc) {
-    const int li = threadIdx.x & 15, lk = (threadIdx.x >> 4) & 3;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const double x = a[li * ai + (4 * q + lk) * ak], y = b[(4 * q + lk) * bk + li * bj];
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, acc, 0, 0, 0);
-    }
-    return acc;
-}
-
-// the 64 x 64 tile in S becomes the inverse of its Cholesky factor (lower; the
-// tiles above the diagonal are left as they are): the same elimination by
-// blocks of 16, one workgroup of four wavefronts.  About 13 us (23 with lane i
-// holding all of row i: 16 columns a lane, read lane by lane), a serial chain.
-__device__ bool elim_diag64(double* S, double* Y) {
-    const int w = threadIdx.x >> 6, li = threadIdx.x & 15, lk = (threadIdx.x >> 4) & 3;
-    bool ok = true;
-#pragma nounroll
-    for (int b = 0; b < 4; ++b) {
-        const int r0 = 16 * b;
-        if (w == 0) ok &= elim_diag16(S, r0);
-        __syncthreads();
-        if (w < 3) {
-            const int t = w < b ? w : w + 1;
-            const double* Wb = S + r0 * ELD + r0;
-            dbl4 c{0.0, 0.0, 0.0, 0.0};
-            if (t > b) {
-                c = elim_mul16(S + 16 * t * ELD + r0, ELD, 1, Wb, 1, ELD, c);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) Y[(16 * t + lk + 4 * r) * EYD + li] = c[r];
-            } else {
-                c = elim_mul16(Wb, ELD, 1, S + r0 * ELD + 16 * t, ELD, 1, c);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) S[(r0 + lk + 4 * r) * ELD + 16 * t + li] = c[r];
-            }
-        }
-        __syncthreads();
-        int e = w;
-        for (int i = b + 1; i < 4; ++i) {
-            for (; e <= i; e += 4) {
-                const int j = e;
-                double* C = S + 16 * i * ELD + 16 * j;
-                dbl4 old{0.0, 0.0, 0.0, 0.0}, c{0.0, 0.0, 0.0, 0.0};
-                if (j != b)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) old[r] = C[(lk + 4 * r) * ELD + li];
-                const bool w_row = j <= b;
-                const double* B = w_row ? S + r0 * ELD + 16 * j : Y + 16 * j * EYD;
-                c = elim_mul16(Y + 16 * i * EYD, EYD, 1, B, w_row ? ELD : 1, w_row ? 1 : EYD, c);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) C[(lk + 4 * r) * ELD + li] = old[r] - c[r];
-            }
-            e -= i + 1;
-        }
-        __syncthreads();
-    }
-    return ok;
-}
-
-// the tile in S to V_kk (zero above the diagonal), after elim_diag64
-__device__ __forceinline__ void elim_store_diag(double* S, double* Y, double* Vkk, int nw, int* bad) {
-    if (!elim_diag64(S, Y) && threadIdx.x == 0) atomicOr(bad, 4);
-    for (int t = threadIdx.x; t < EB * EB; t += 256) {
-        const int i = t / EB, j = t % EB;
-        Vkk[(size_t)i * nw + j] = j <= i ? S[i * ELD + j] : 0.0;
-    }
-}
-
-// V <- lower tiles of A (the identity beyond np), and the first diagonal tile
-__global__ __launch_bounds__(256) void k_elim_begin(const double* __restrict__ A, int np, double* V, int nw, int* bad) {
-    __shared__ double S[EB * ELD], Y[EB * EYD];
-    int ti, tj;
-    lower_tile(blockIdx.x, ti, tj);
-    for (int t = threadIdx.x; t < EB * EB; t += 256) {
-        const int i = EB * ti + t / EB, j = EB * tj + t % EB;
-        const int hi = max(i, j), lo = min(i, j);   // only the lower triangle of A is read
-        const double v = hi < np ? A[(size_t)hi * np + lo] : (i == j ? 1.0 : 0.0);
-        if (blockIdx.x == 0) S[(t / EB) * ELD + t % EB] = v;
-        else V[(size_t)i * nw + j] = v;
-    }
-    if (blockIdx.x == 0) {
-        __syncthreads();
-        elim_store_diag(S, Y, V, nw, bad);
-    }
-}
-
-// acc (32 x 32 of a wavefront) += sum over 64 values of k of A(i, k) B(k, j),
-// A(i, k) at a[k * ld + i], B(k, j) at b[k * ld + j]
-__device__ __forceinline__ void elim_mul64(const double* a, const double* b, size_t ld, dbl4 (&acc)[2][2]) {
-    const int li = threadIdx.x & 15, lk = (threadIdx.x >> 4) & 3;
-    a += lk * ld + li;
-    b += lk * ld + li;
-#pragma unroll 8
-    for (int q = 0; q < EB / 4; ++q) {
-        double x[2], y[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            x[u] = a[16 * u + 4 * q * ld];
-            y[u] = b[16 * u + 4 * q * ld];
-        }
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-#pragma unroll
-            for (int n = 0; n < 2; ++n) acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[m], y[n], acc[m][n], 0, 0, 0);
-    }
-}
-
-// both factors are staged: read from the caches in operand order, 32 bytes of
-// a row at a time, the same products take 10 us
-__global__ __launch_bounds__(512) void k_elim_panel(double* V, int nw, double* YT, int k) {
-    __shared__ double Ws[EB * ELD], Bs[EB * ELD];
-    const int j = (int)blockIdx.x < k ? blockIdx.x : blockIdx.x + 1;
-    const size_t ld = nw;
-    const double* Wkk = V + (size_t)EB * k * ld + EB * k;
-    const double* B = j < k ? V + (size_t)EB * k * ld + EB * j : V + (size_t)EB * j * ld + EB * k;
-    double wv[8], bv[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int r = (threadIdx.x >> 6) + 8 * u, c = threadIdx.x & 63;
-        wv[u] = Wkk[r * ld + c];
-        bv[u] = B[r * ld + c];
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const int r = (threadIdx.x >> 6) + 8 * u, c = threadIdx.x & 63;
-        Ws[r * ELD + c] = wv[u];
-        Bs[r * ELD + c] = bv[u];
-    }
-    __syncthreads();
-    // wavefront w: rows 32 (w / 4), columns 16 (w % 4)
-    const int w = threadIdx.x >> 6, li = threadIdx.x & 15, lk = (threadIdx.x >> 4) & 3;
-    const int wr = 32 * (w >> 2), wc = 16 * (w & 3);
-    const int bk = j < k ? ELD : 1, bj = j < k ? 1 : ELD;   // B(m, x), or its transpose
-    const double* a = Ws + (wr + li) * ELD + lk;
-    const double* b = Bs + lk * bk + (wc + li) * bj;
-    dbl4 acc[2] = {};
-#pragma unroll
-    for (int q = 0; q < EB / 4; ++q)
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-            acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[16 * m * ELD + 4 * q], b[4 * q * bk], acc[m], 0, 0, 0);
-    double* out = j < k ? V + (size_t)EB * k * ld + EB * j : YT + EB * j;
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) out[(size_t)(wr + 16 * m + lk + 4 * r) * ld + wc + li] = acc[m][r];
-}
-
-// block 0 is the tile (k + 1, k + 1)
-__global__ __launch_bounds__(256) void k_elim_update(double* V, int nw, const double* __restrict__ YT, int k, int* bad) {
-    __shared__ double S[EB * ELD], Y[EB * EYD];
-    const int w = threadIdx.x >> 6, li = threadIdx.x & 15, lk = (threadIdx.x >> 4) & 3;
-    const int wr = 32 * (w >> 1), wc = 32 * (w & 1);
-    int i, j;
-    lower_tile(blockIdx.x + (k + 1) * (k + 2) / 2, i, j);
-    j = i - j;
-    const size_t ld = nw;
-    double* C = V + ((size_t)EB * i + wr + lk) * ld + EB * j + wc + li;
-    dbl4 acc[2][2] = {}, old[2][2] = {};   // the sum is taken off at once: one rounding at the size of V_ij
-    if (j != k)
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-#pragma unroll
-            for (int n = 0; n < 2; ++n)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) old[m][n][r] = C[(size_t)(16 * m + 4 * r) * ld + 16 * n];
-    const double* Z = (j <= k ? V + (size_t)EB * k * ld : YT) + EB * j + wc;
-    elim_mul64(YT + EB * i + wr, Z, ld, acc);
-    if (blockIdx.x == 0) {
-#pragma unroll
-        for (int m = 0; m < 2; ++m)
-#pragma unroll
-            for (int n = 0; n < 2; ++n)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    S[(wr + 16 * m + lk + 4 * r) * ELD + wc + 16 * n + li] = old[m][n][r] - acc[m][n][r];
-        __syncthreads();
-        elim_store_diag(S, Y, V + (size_t)EB * i * ld + EB * j, nw, bad);
-        return;
-    }
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int n = 0; n < 2; ++n)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) C[(size_t)(16 * m + 4 * r) * ld + 16 * n] = old[m][n][r] - acc[m][n][r];
-}
-
-// A <- W^T W, lower tiles and their mirror images (W_kj = 0 for k < j)
-__global__ __launch_bounds__(256) void k_elim_wtw(const double* __restrict__ V, int nw, double* A, int np) {
-    const int w = threadIdx.x >> 6, li = threadIdx.x & 15, lk = (threadIdx.x >> 4) & 3;
-    const int wr = 32 * (w >> 1), wc = 32 * (w & 1);
-    int ti, tj;
-    lower_tile(blockIdx.x, ti, tj);
-    const size_t ld = nw;
-    dbl4 acc[2][2] = {};
-    for (int k = ti; k < nw / EB; ++k)
-        elim_mul64(V + (size_t)EB * k * ld + EB * ti + wr, V + (size_t)EB * k * ld + EB * tj + wc, ld, acc);
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int n = 0; n < 2; ++n)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = EB * ti + wr + 16 * m + lk + 4 * r, j = EB * tj + wc + 16 * n + li;
-                if (i >= np || j >= np) continue;
-                A[(size_t)i * np + j] = acc[m][n][r];
-                if (ti != tj) A[(size_t)j * np + i] = acc[m][n][r];
-            }
-}
-
-static int elim_inverse(double* a, int np, double* V, double* YT, int* bad, hipStream_t s) {
-    const int nw = elim_ld(np), nb = nw / EB, lower = nb * (nb + 1) / 2;
-    hipLaunchKernelGGL(k_elim_begin, dim3(lower), dim3(256), 0, s, a, np, V, nw, bad);
-    for (int k = 0; k < nb; ++k) {
-        if (nb > 1) hipLaunchKernelGGL(k_elim_panel, dim3(nb - 1), dim3(512), 0, s, V, nw, YT, k);
-        const int tiles = lower - (k + 1) * (k + 2) / 2;
-        if (tiles > 0) hipLaunchKernelGGL(k_elim_update, dim3(tiles), dim3(256), 0, s, V, nw, YT, k, bad);
-    }
-    hipLaunchKernelGGL(k_elim_wtw, dim3(lower), dim3(256), 0, s, V, nw, a, np);
-    return (int)hipGetLastError();
-}
-
-size_t dense_spd_inverse_work_doubles(int np) {
-    const size_t n = np <= kElimMax ? elim_ld(np) : np;
-    return n * n;
-}
+size_t dense_spd_inverse_work_doubles(int np) { return (size_t)np * np; }   // W
 
 size_t dense_spd_inverse_tbuf_doubles(int np) {
-    if (np <= kElimMax) return (size_t)EB * elim_ld(np);   // Y^T
     // P of the root node of trtri_node, the largest
     const int nb = (np + KB - 1) / KB;
     const size_t h = (size_t)KB * (nb / 2);
@@ -714,11 +369,6 @@ size_t dense_spd_inverse_tbuf_doubles(int np) {
 
 int dense_spd_inverse(double* a, int np, double* work, double* tbuf, int* bad, hipStream_t s) {
     if (np % NB) return (int)hipErrorInvalidValue;
-    if (np <= kElimMax) {
-        const int r = elim_inverse(a, np, work, tbuf, bad, s);
-        const hipError_t e = hipStreamSynchronize(s);
-        return r != 0 ? r : (int)e;
-    }
     // ---- Cholesky, panels of KB columns; the trailing update on the matrix cores
     for (int k0 = 0; k0 < np; k0 += KB) {
         const int kw = std::min(KB, np - k0);

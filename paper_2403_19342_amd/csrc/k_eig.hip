@@ -1,36 +1,817 @@
-// Local eigensolves of the levels >= 3 (Section 3, eq. spectral cc): on every
-// parent element E the restricted problem H_E v = lambda v with
-// H_E = B_E^T A_E B_E assembled from the level below (its Gram is the identity
-// for S-normalised bases), a block 7-point matrix over the kept slots of the
-// agg^3 children.
+// Batched local eigensolves of the set-up phase (Section 3).
 //
-// Method: subspace iteration with a Chebyshev filter in the shifted inverse.
-// The wanted eigenvalues lie at the bottom of a spectrum of several decades,
-// where a polynomial in H_E separates them by sqrt((a - lambda) / b) per degree
-// (300 to 700 applications per element at 128^3, contrast 1e6); a polynomial in
-// (H_E + sigma)^-1 separates them by sqrt((a - lambda) / (lambda + sigma)): about 22
-// solves and 3 factorisations per element, in 3 to 4 cycles.  sigma is a tenth of
-// the block's largest Ritz value (at least 1e-7 of the spectral bound), so the
-// inverse stays well conditioned and is applied explicitly.
+// Level 2 (eq. spepb): on every 8^3 element K, the smallest eigenpairs of
+//   A_K phi = lambda S_K phi,  S_K = diag(tr kappa~),
+// solved in the symmetric form A~ x = lambda x with A~ = S^-1/2 A_K S^-1/2,
+// phi = S^-1/2 x (so phi^T S phi = 1, the normalisation of Section 3).
+// Levels >= 3 (eq. spectral cc): on every parent element E the restricted
+// problem H_E v = lambda v with H_E = B_E^T A_E B_E assembled from the level
+// below (its Gram is the identity for S-normalised bases).
 //
-// The inverse is kept in block form over the planes of children in z
-// (agg = 4: four planes of up to 16 children; agg = 2: one block when its rows
-// fit, else two planes): T_p = S_p^-1 with S_p = D_p + sigma -
-// C_{p-1}^T T_{p-1} C_{p-1}, D_p the plane's block of H_E and C_p its couplings
-// to the next plane (one child each).  A solve is 2 P - 1 dense products
-// T_p (m x m) times (m x M) on the FP64 matrix cores.
-//
-// One workgroup per parent; the block (rows x M) lives in LDS, the planes'
-// inverses and the filter's second iterate in a workspace slot of the
-// workgroup (read through L2).  Rows are compact: kept slots only.
-#include <algorithm>
-
-#include "eig_common.hpp"
+// Method: Chebyshev-filtered subspace iteration.  One workgroup per element
+// holds a block of M vectors; each cycle applies a degree-DEG Chebyshev
+// polynomial that damps the unwanted interval [a, b] (b: Gershgorin bound,
+// a: largest Ritz value of the block), re-orthonormalises by Cholesky-QR
+// (twice) and performs Rayleigh-Ritz with a one-wavefront parallel cyclic
+// Jacobi eigensolver.  Only operator applications and M x M reductions are
+// needed, so the whole solve stays in registers and LDS.
+#include "common.hpp"
 
 namespace specmg {
 
-constexpr int kMaxLP = 23;        // lower-level widths up to target 20 + 3
-constexpr int kUpSingle = 112;    // rows up to which the children form one block (agg = 2)
+constexpr int kDeg = 20;          // Chebyshev degree per cycle of a relaxed, warm-started solve
+constexpr int kDegExact = 40;     // ... of an exact solve (fewer cycles, so fewer orthonormalisations
+                                  //     and Rayleigh-Ritz steps per filtered vector)
+constexpr int kMaxCycles = 300;
+constexpr int kMaxEigWaves = 12;   // workgroups of at most 768 threads
+constexpr int kWarmCycles = 4;     // cycles a learned start gets to reach the relaxed residual
+
+
+__device__ __forceinline__ double hash_noise(unsigned a, unsigned b, unsigned c) {
+    unsigned h = a * 0x9E3779B1u ^ (b + 0x7F4A7C15u) * 0x85EBCA77u ^ (c + 0x165667B1u) * 0xC2B2AE3Du;
+    h ^= h >> 15;
+    h *= 0x2C1B3C6Du;
+    h ^= h >> 12;
+    h *= 0x297A2D39u;
+    h ^= h >> 15;
+    return (double)(h & 0xFFFFFF) / 8388608.0 - 1.0;   // [-1, 1)
+}
+
+// low-frequency cosine modes (p, q, r) by increasing p^2+q^2+r^2
+__constant__ unsigned char kModes[16][3] = {
+    {0, 0, 0}, {1, 0, 0}, {0, 1, 0}, {0, 0, 1}, {1, 1, 0}, {1, 0, 1}, {0, 1, 1}, {1, 1, 1},
+    {2, 0, 0}, {0, 2, 0}, {0, 0, 2}, {2, 1, 0}, {1, 2, 0}, {2, 0, 1}, {0, 2, 1}, {1, 0, 2}};
+
+template <typename T>
+__device__ __forceinline__ T harm_e(T a, T b) {
+    const T s = a + b;
+    return s > T(0) ? (T(2) * a * b) / s : T(0);
+}
+
+// ---------------------------------------------------------------------------
+// small dense helpers on LDS, run by one thread or one wavefront
+
+// Circle-method round robin on M players (M even): in round r player M-1
+// meets player r and every other pair (i, j) has i + j = 2r modulo M-1.
+template <int M>
+__device__ __forceinline__ int jac_partner(int i, int r) {
+    constexpr int K = M - 1;
+    if (i == K) return r;
+    if (i == r) return K;
+    int j = 2 * r - i;
+    j = j < 0 ? j + K : (j >= K ? j - K : j);
+    return j;
+}
+
+// Rotation (c, s) that annihilates H[p][q] (p < q): the rotated rows are
+// p' = c p - s q and q' = s p + c q.
+__device__ __forceinline__ void jac_rot(const double* H, int M, int p, int q, double& c, double& s) {
+    const double hpp = H[p * M + p], hqq = H[q * M + q], hpq = H[p * M + q];
+    c = 1.0;
+    s = 0.0;
+    if (hpq != 0.0) {
+        const double tt = (hqq - hpp) / (2.0 * hpq);
+        const double t = (tt >= 0.0 ? 1.0 : -1.0) / (fabs(tt) + sqrt(tt * tt + 1.0));
+        c = 1.0 / sqrt(t * t + 1.0);
+        s = t * c;
+    }
+}
+
+// Symmetric eigendecomposition H = Q diag(th) Q^T, eigenvalues ascending,
+// by parallel cyclic Jacobi in wavefront 0: each round applies M/2 disjoint
+// rotations at once; lanes 0..M-1 derive the round's rotations (scr holds
+// the cosines and sines), then every lane applies them to its own elements:
+// a round is one rotation phase, one read phase and one write phase.  Stops
+// when the largest off-diagonal entry is below 1e-15 times the largest
+// diagonal entry.  H (M*M) is destroyed; Q (M*M)
+// receives the eigenvectors as columns.  Must be called by all threads.
+template <int M>
+__device__ __forceinline__ void jacobi_eig(double* H, double* Q, double* th, double* scr, int* iscr) {
+    static_assert(M % 2 == 0 && M <= 26, "Jacobi block size");
+    constexpr int MM = M * M;
+    constexpr int PER = (MM + 63) / 64;
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        int ei[PER], ej[PER];
+        bool ev[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int t = lane + 64 * u;
+            ev[u] = t < MM;
+            ei[u] = ev[u] ? t / M : 0;
+            ej[u] = ev[u] ? t % M : 0;
+            if (ev[u]) Q[t] = (ei[u] == ej[u]) ? 1.0 : 0.0;
+        }
+        wave_sync();
+#pragma unroll 1
+        for (int sweep = 0; sweep < 30; ++sweep) {
+            double off = 0.0, dg = 0.0;
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const double h = ev[u] ? fabs(H[ei[u] * M + ej[u]]) : 0.0;
+                if (ei[u] != ej[u]) off = fmax(off, h);
+                else dg = fmax(dg, h);
+            }
+            off = wave_max(off);
+            dg = wave_max(dg);
+            if (off <= 1e-15 * dg || off == 0.0) break;
+#pragma unroll 1
+            for (int r = 0; r < M - 1; ++r) {
+                // the round's M/2 rotations, once each: lane i < M stores the
+                // rotation of its pair (both members hold the same one)
+                if (lane < M) {
+                    const int pl = jac_partner<M>(lane, r);
+                    double cl, sl;
+                    jac_rot(H, M, lane < pl ? lane : pl, lane < pl ? pl : lane, cl, sl);
+                    scr[lane] = cl;
+                    scr[M + lane] = sl;
+                }
+                wave_sync();
+                double nh[PER], nq[PER];
+#pragma unroll
+                for (int u = 0; u < PER; ++u) {
+                    const int i = ei[u], j = ej[u];
+                    const int pi = jac_partner<M>(i, r), pj = jac_partner<M>(j, r);
+                    const int ai = i < pi ? i : pi, bi = i < pi ? pi : i;
+                    const int aj = j < pj ? j : pj, bj = j < pj ? pj : j;
+                    const double ci = scr[i], si = scr[M + i], cj = scr[j], sj = scr[M + j];
+                    const double wra = (i == ai) ? ci : si, wrb = (i == ai) ? -si : ci;
+                    const double wca = (j == aj) ? cj : sj, wcb = (j == aj) ? -sj : cj;
+                    nh[u] = wra * (wca * H[ai * M + aj] + wcb * H[ai * M + bj]) +
+                            wrb * (wca * H[bi * M + aj] + wcb * H[bi * M + bj]);
+                    // the annihilated entry of a rotated pair is zero exactly
+                    if (ai == aj && bi == bj && i != j) nh[u] = 0.0;
+                    nq[u] = wca * Q[i * M + aj] + wcb * Q[i * M + bj];
+                }
+                wave_sync();
+#pragma unroll
+                for (int u = 0; u < PER; ++u) {
+                    if (ev[u]) {
+                        H[ei[u] * M + ej[u]] = nh[u];
+                        Q[ei[u] * M + ej[u]] = nq[u];
+                    }
+                }
+                wave_sync();
+            }
+        }
+        // ascending order: lane k < M finds the rank of H[k][k]
+        if (lane < M) {
+            const double hk = H[lane * M + lane];
+            int rank = 0;
+#pragma unroll
+            for (int l = 0; l < M; ++l) {
+                const double hl = H[l * M + l];
+                rank += (hl < hk || (hl == hk && l < lane)) ? 1 : 0;
+            }
+            iscr[rank] = lane;
+            th[rank] = hk;
+        }
+        wave_sync();
+        double nq[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) nq[u] = ev[u] ? Q[ei[u] * M + iscr[ej[u]]] : 0.0;
+        wave_sync();
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (ev[u]) Q[ei[u] * M + ej[u]] = nq[u];
+    }
+    __syncthreads();
+}
+
+// Cholesky G = R^T R of the SPD M x M matrix G (R upper triangular, stored
+// in Rm; dinv[j] = 1 / R[j][j]) by wavefront 0, one column per step with a
+// lane-parallel trailing update.  G is left intact.  Returns false (in every
+// thread) when G is not numerically positive definite.
+template <int M>
+__device__ __forceinline__ bool chol_wave(const double* G, double* Rm, double* dinv, int* flag) {
+    constexpr int MM = M * M;
+    constexpr int PER = (MM + 63) / 64;
+    if (threadIdx.x < 64) {
+        const int lane = threadIdx.x;
+        int ei[PER], ej[PER];
+        bool ev[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int t = lane + 64 * u;
+            ev[u] = t < MM;
+            ei[u] = ev[u] ? t / M : 0;
+            ej[u] = ev[u] ? t % M : 0;
+            if (ev[u]) Rm[t] = ei[u] <= ej[u] ? G[t] : 0.0;
+        }
+        wave_sync();
+        int ok = 1;
+#pragma unroll 1
+        for (int j = 0; j < M; ++j) {
+            double d = Rm[j * M + j];
+            if (!(d > 0.0)) {
+                ok = 0;
+                d = 1.0;
+            }
+            const double inv_d = 1.0 / d;
+            // trailing update of the upper triangle with the unscaled row j
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int i = ei[u], l = ej[u];
+                if (ev[u] && i > j && l >= i) Rm[i * M + l] -= Rm[j * M + i] * Rm[j * M + l] * inv_d;
+            }
+            wave_sync();
+            const double rjj = sqrt(d), ir = 1.0 / rjj;
+            if (lane > j && lane < M) Rm[j * M + lane] *= ir;
+            if (lane == j) {
+                Rm[j * M + j] = rjj;
+                dinv[j] = ir;
+            }
+            wave_sync();
+        }
+        if (lane == 0) *flag = ok;
+    }
+    __syncthreads();
+    const bool ok = *flag != 0;
+    __syncthreads();
+    return ok;
+}
+
+// Cluster rule on ascending values th[0..n-1] (n >= target+4 or all values):
+// keep `target`, grow to the end of a cluster of equal values up to
+// target+3, or shrink before the cluster when it runs past that cap.
+__device__ int cluster_cut_dev(const double* th, int n, int target, double rtol, double thr) {
+    if (thr > 0.0) {
+        // threshold rule (strategy 2 of Section 5): the eigenvalues below
+        // thr, at least one and at most target, then the cluster rule
+        int below = 0;
+        for (int j = 0; j < n; ++j) below += th[j] < thr ? 1 : 0;
+        target = below < 1 ? 1 : (below < target ? below : target);
+    }
+    if (target >= n) return n;
+    auto same = [&](int k) { return th[k] - th[k - 1] <= rtol * fmax(fabs(th[k]), 1e-12); };
+    int k = target;
+    const int cap = target + 3 < n ? target + 3 : n;
+    while (k < cap && same(k)) ++k;
+    if (k == cap && k < n && same(k)) {
+        k = target;
+        while (k > 1 && same(k)) --k;
+    }
+    return k;
+}
+
+// Empty asm statements that take v as an operand: the arithmetic producing v
+// runs before them, and no memory access moves across pin().  Used after
+// every few columns of an operator apply, so that the compiler cannot hoist
+// all of its LDS loads ahead of the arithmetic (a register per loaded value,
+// which halves the waves per SIMD).
+__device__ __forceinline__ void pin(double& v) { asm volatile("" : "+v"(v)::"memory"); }
+__device__ __forceinline__ void pin_value(double& v) { asm volatile("" : "+v"(v)); }
+
+// ---------------------------------------------------------------------------
+// Block storage: the current block lives in LDS as Y[j * ld + row] (ld odd,
+// so column-strided reads spread over the banks); each thread owns rows
+// threadIdx.x + r * blockDim.x, r < R, and keeps at most three M-vectors of
+// them in registers.
+
+template <int M>
+struct EigShared {
+    double red[kMaxEigWaves * M * M];
+    double G[M * M];
+    double Q[M * M];
+    double Rm[M * M];
+    double scr[M * M];
+    double dinv[M];
+    double th[M];
+    double nrm[M];
+    double misc[kMaxEigWaves];
+    int iscr[2 * M];
+    int flag;
+};
+
+// G = sym(Y^T B) over all block rows: Y in LDS, B this thread's rows in
+// registers.  With B = the thread's own rows of Y this is the Gram matrix.
+// One wave reduction per entry; the M reductions of a row of G overlap.
+template <int M, int R>
+__device__ void gram_lds_reg(const double* Y, int ld, int n, const double (&B)[R][M], double* G,
+                             double* red) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+#pragma unroll 1
+    for (int i = 0; i < M; ++i) {
+        double yi[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int row = threadIdx.x + r * blockDim.x;
+            yi[r] = row < n ? Y[i * ld + row] : 0.0;
+        }
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            double v = 0.0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) v += yi[r] * B[r][j];
+            v = wave_sum(v);
+            if (lane == 0) red[w * M * M + i * M + j] = v;
+        }
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < M * M; t += blockDim.x) {
+        const int i = t / M, j = t % M;
+        if (i <= j) {
+            double x = 0.0, y = 0.0;
+            for (int ww = 0; ww < nw; ++ww) {
+                x += red[ww * M * M + i * M + j];
+                y += red[ww * M * M + j * M + i];
+            }
+            const double v = 0.5 * (x + y);
+            G[i * M + j] = v;
+            G[j * M + i] = v;
+        }
+    }
+    __syncthreads();
+}
+
+// column sums of squares of registers A into out[M]
+template <int M, int R>
+__device__ void colnorm2(const double (&A)[R][M], double* out, double* red) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+        double v = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) v += A[r][j] * A[r][j];
+        v = wave_sum(v);
+        if (lane == 0) red[w * M + j] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < M) {
+        double s = 0.0;
+        for (int ww = 0; ww < nw; ++ww) s += red[ww * M + threadIdx.x];
+        out[threadIdx.x] = s;
+    }
+    __syncthreads();
+}
+
+// registers A <- A C (C: M*M in LDS, read by every lane at the same address);
+// the row loop stays rolled and picks A[r][i] by selects, so no register
+// array is indexed dynamically
+template <int M, int R>
+__device__ __forceinline__ void rmul(double (&A)[R][M], const double* C) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        double t[M];
+#pragma unroll
+        for (int j = 0; j < M; ++j) t[j] = 0.0;
+#pragma unroll 1
+        for (int i = 0; i < M; ++i) {
+            double a = 0.0;
+#pragma unroll
+            for (int k = 0; k < M; ++k) a = (k == i) ? A[r][k] : a;
+#pragma unroll
+            for (int j = 0; j < M; ++j) t[j] += a * C[i * M + j];
+        }
+#pragma unroll
+        for (int j = 0; j < M; ++j) A[r][j] = t[j];
+    }
+}
+
+template <int M, int R>
+__device__ __forceinline__ void store_block(double* Y, int ld, int n, const double (&A)[R][M]) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int row = threadIdx.x + r * blockDim.x;
+        if (row < n) {
+#pragma unroll
+            for (int j = 0; j < M; ++j) Y[j * ld + row] = A[r][j];
+        }
+    }
+}
+
+template <int M, int R>
+__device__ __forceinline__ void load_block(const double* Y, int ld, int n, double (&A)[R][M]) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int row = threadIdx.x + r * blockDim.x;
+#pragma unroll
+        for (int j = 0; j < M; ++j) A[r][j] = row < n ? Y[j * ld + row] : 0.0;
+    }
+}
+
+// Inverse of the upper triangular factor (Rm, dinv from chol_wave) into
+// Ri, by wavefront 0: rows from the bottom up, lane l owning column l.
+template <int M>
+__device__ __forceinline__ void trtri_wave(const double* Rm, const double* dinv, double* Ri) {
+    if (threadIdx.x < 64) {
+        const int l = threadIdx.x;
+#pragma unroll 1
+        for (int i = M - 1; i >= 0; --i) {
+            if (l < M) {
+                double v = (l == i) ? 1.0 : 0.0;
+                for (int k = i + 1; k <= l; ++k) v -= Rm[i * M + k] * Ri[k * M + l];
+                Ri[i * M + l] = l >= i ? v * dinv[i] : 0.0;
+            }
+            wave_sync();
+        }
+    }
+    __syncthreads();
+}
+
+// Orthonormalise the LDS block (Cholesky-QR, twice): Y <- Y R^-1 with
+// Y^T Y = R^T R.
+template <int M, int R>
+__device__ __forceinline__ void orthonormalise(double* Y, int ld, int n, EigShared<M>& sh) {
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {
+        double A[R][M];
+        load_block<M, R>(Y, ld, n, A);
+        gram_lds_reg<M, R>(Y, ld, n, A, sh.G, sh.red);
+        if (!chol_wave<M>(sh.G, sh.Rm, sh.dinv, &sh.flag)) {
+            // rank-deficient block: a tiny diagonal shift keeps the factor
+            // finite; the next Chebyshev cycle restores the lost directions
+            if (threadIdx.x == 0) {
+                double mx = 0.0;
+                for (int i = 0; i < M; ++i) mx = fmax(mx, sh.G[i * M + i]);
+                for (int i = 0; i < M; ++i) sh.G[i * M + i] += 1e-12 * mx + 1e-300;
+            }
+            __syncthreads();
+            chol_wave<M>(sh.G, sh.Rm, sh.dinv, &sh.flag);
+        }
+        trtri_wave<M>(sh.Rm, sh.dinv, sh.scr);
+        rmul<M, R>(A, sh.scr);
+        store_block<M, R>(Y, ld, n, A);
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// operators: out = A * (block in LDS), rows of this thread
+
+// Level 2: A~ = S^-1/2 A_K S^-1/2 on one 8^3 element, thread = cell.
+struct Op2 {
+    double diag;
+    double off[6];
+    int nb[6];
+    template <int M>
+    __device__ __forceinline__ void apply(const double* Y, int ld, double (&out)[1][M]) const {
+        const int c = threadIdx.x;
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            double s = diag * Y[j * ld + c];
+#pragma unroll
+            for (int d = 0; d < 6; ++d) s -= off[d] * Y[j * ld + nb[d]];
+            out[0][j] = s;
+            if (j % 3 == 2) {
+                pin_value(out[0][j - 2]);
+                pin_value(out[0][j - 1]);
+                pin(out[0][j]);
+            }
+        }
+    }
+};
+
+// Levels >= 3: block 7-point H_E on the agg^3 children of E, lp slots per
+// child (the padded width of the lower level, at most kMaxLP); row =
+// p * lp + a (child position p, slot a), one row per thread.  The row's own
+// diagonal block stays in registers; the coupling rows of the six directions
+// are re-read (from L2) on every apply, the loads of a direction issued
+// together; a missing neighbour reads its own child with weight zero.
+constexpr int kMaxLP = 23;   // lower-level widths up to target 20 + 3
+
+// LPT > 0: the width is a compile-time constant; LPT = 0: run-time width lp
+// (arrays sized for kMaxLP, slots beyond lp masked)
+template <int LPT>
+struct OpUp {
+    static constexpr int kW = LPT > 0 ? LPT : kMaxLP;
+    const double* Aoff;   // [m_lo][3][lp][lp]
+    double hd[kW];        // H_d[c][a][0..lp-1], zero beyond lp
+    int lp_rt;
+    int c, a, p;          // child element, slot, child position in E
+    int qx, qy, qz;       // child coordinates inside E (scalars: an indexed
+    int sy, sz;           // array would live in scratch); element-index steps
+                          // of the lower grid in y and z (1 in x)
+    int agg;
+    bool valid;           // kept slot of an existing child row
+    __device__ __forceinline__ int lp() const { return LPT > 0 ? LPT : lp_rt; }
+    template <int M>
+    __device__ __forceinline__ void apply(const double* Y, int ld, double (&out)[1][M]) const {
+        const int w = lp();
+#pragma unroll
+        for (int j = 0; j < M; ++j) out[0][j] = 0.0;
+        if (!valid) return;
+        // row base recomputed on every apply: hoisted out of the solver's loops,
+        // one address per (column, slot) would stay live and spill
+        int pw = p * w;
+        asm volatile("" : "+v"(pw));
+        const double* ys = Y + pw;
+#pragma unroll
+        for (int b = 0; b < kW; ++b) {
+            if (b < w) {
+#pragma unroll
+                for (int j = 0; j < M; ++j) out[0][j] += hd[b] * ys[j * ld + b];
+            }
+        }
+#pragma unroll 1
+        for (int d = 0; d < 6; ++d) {
+            const int ax = d >> 1;
+            const int qa = ax == 0 ? qx : (ax == 1 ? qy : qz);
+            const int cs = ax == 0 ? 1 : (ax == 1 ? sy : sz);
+            const int ps = ax == 0 ? 1 : (ax == 1 ? agg : agg * agg);
+            const bool in = (d & 1) ? (qa < agg - 1) : (qa > 0);
+            const int cn = in ? ((d & 1) ? c + cs : c - cs) : c;
+            const int pn = in ? ((d & 1) ? p + ps : p - ps) : p;
+            const double msk = in ? 1.0 : 0.0;
+            // + direction: A(c, cn)[a][b] = Aoff[c][ax][a][b]; - direction: Aoff[cn][ax][b][a]
+            const size_t base = (d & 1) ? (((size_t)c * 3 + ax) * w + a) * w : (((size_t)cn * 3 + ax) * w) * w + a;
+            const int st = (d & 1) ? 1 : w;
+            double h[kW];
+#pragma unroll
+            for (int b = 0; b < kW; ++b) h[b] = b < w ? Aoff[base + (size_t)b * st] * msk : 0.0;
+#pragma unroll
+            for (int b = 0; b < kW; ++b) {
+                if (b < w) {
+#pragma unroll
+                    for (int j = 0; j < M; ++j) out[0][j] += h[b] * Y[j * ld + pn * w + b];
+                }
+            }
+        }
+    }
+};
+
+// Chebyshev filter of degree deg applied to X (registers); the filtered
+// block is left in LDS.  Wanted spectrum below a, damped interval [a, b],
+// a0 below the whole spectrum.
+template <int M, int R, class OP>
+__device__ void cheb_filter(const OP& op, double (&X)[R][M], double* Y, int ld, int n, double a, double b,
+                            double a0, int deg) {
+    const double e = 0.5 * (b - a), cc = 0.5 * (b + a);
+    double sigma = e / (a0 - cc);
+    const double tau = 2.0 / sigma;
+    double T[R][M];
+    store_block<M, R>(Y, ld, n, X);
+    __syncthreads();
+    op.template apply<M>(Y, ld, T);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int j = 0; j < M; ++j) T[r][j] = (T[r][j] - cc * X[r][j]) * (sigma / e);
+    __syncthreads();
+    store_block<M, R>(Y, ld, n, T);
+    __syncthreads();
+#pragma unroll 1
+    for (int it = 2; it <= deg; ++it) {
+        const double sn = 1.0 / (tau - sigma);
+        op.template apply<M>(Y, ld, T);
+        // own rows' base recomputed every step (hoisted, one address per
+        // column would stay live across the loop)
+        int tb = threadIdx.x;
+        asm volatile("" : "+v"(tb));
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int row = tb + r * blockDim.x;
+#pragma unroll
+            for (int j = 0; j < M; ++j) {
+                const double yc = row < n ? Y[j * ld + row] : 0.0;
+                T[r][j] = (T[r][j] - cc * yc) * (2.0 * sn / e) - (sigma * sn) * X[r][j];
+                X[r][j] = yc;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int row = tb + r * blockDim.x;
+            if (row < n) {
+#pragma unroll
+                for (int j = 0; j < M; ++j) Y[j * ld + row] = T[r][j];
+            }
+        }
+        __syncthreads();
+        sigma = sn;
+    }
+}
+
+// Rayleigh-Ritz on the orthonormal LDS block Y: X = Y Q (also left in
+// LDS), AX = A X, sh.th ascending.  A Y is dead while the small
+// eigenproblem runs; A X is formed afresh from X.
+// With nval < M the columns nval.. of Y are zero: their diagonal entries of
+// the projected matrix are set to pad (above the spectrum), so that they
+// sort last and their Ritz vectors stay zero.
+template <int M, int R, class OP>
+__device__ void rayleigh_ritz(const OP& op, double* Y, int ld, int n, double (&X)[R][M],
+                              double (&AX)[R][M], EigShared<M>& sh, int nval = M, double pad = 0.0) {
+    {
+        double AY[R][M];
+        op.template apply<M>(Y, ld, AY);
+        gram_lds_reg<M, R>(Y, ld, n, AY, sh.G, sh.red);
+    }
+    if (nval < M) {
+        if ((int)threadIdx.x < M && (int)threadIdx.x >= nval) sh.G[threadIdx.x * M + threadIdx.x] = pad;
+        __syncthreads();
+    }
+    jacobi_eig<M>(sh.G, sh.Q, sh.th, sh.scr, sh.iscr);
+    load_block<M, R>(Y, ld, n, X);
+    rmul<M, R>(X, sh.Q);
+    __syncthreads();
+    store_block<M, R>(Y, ld, n, X);
+    __syncthreads();
+    op.template apply<M>(Y, ld, AX);
+}
+
+// Full CheFSI loop.  X holds the start block on entry and the Ritz vectors
+// on exit, AX = A X.  Returns the number of cycles, or -1 when the residual
+// tolerance (relative to bnd) was not met within max_cycles.
+// Convergence: vectors that the cluster rule keeps need residual <= tol*bnd;
+// the remaining ones up to index need-1 only feed the cluster decision
+// through their eigenvalues (error <= residual^2 / gap), so sqrt(tol)*bnd,
+// unless their Ritz value already lies 5 % above the last kept one: then the
+// decision cannot change (a partner of a kept eigenvalue would have been
+// amplified like the kept vectors, which have converged; under the threshold
+// rule this needs at least one filter cycle).  Without that
+// exception a degenerate cluster straddling the block's end (the Laplace
+// ladder of a homogeneous element) is never resolved: the filter's cut sits
+// on the cluster.
+template <int M, int R, class OP>
+__device__ int chefsi(const OP& op, double* Y, int ld, int n, double (&X)[R][M], double (&AX)[R][M],
+                      double bnd, int need, double tol, int target, double crtol, double thr, EigShared<M>& sh,
+                      int max_cycles = kMaxCycles, int deg = kDegExact) {
+    store_block<M, R>(Y, ld, n, X);
+    __syncthreads();
+    orthonormalise<M, R>(Y, ld, n, sh);
+    for (int cyc = 0;; ++cyc) {
+        rayleigh_ritz<M, R>(op, Y, ld, n, X, AX, sh);
+        {
+            double Rs[R][M];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int j = 0; j < M; ++j) Rs[r][j] = AX[r][j] - sh.th[j] * X[r][j];
+            colnorm2<M, R>(Rs, sh.nrm, sh.red);
+        }
+        const int nk = cluster_cut_dev(sh.th, M, target, crtol, thr);
+        bool ok = true;
+        for (int j = 0; j < need; ++j) {
+            const double rj = sqrt(sh.nrm[j]);
+            // under the threshold rule the 5 % separation counts only after
+            // a filter cycle: an eigenvalue below the threshold that the start
+            // block misses has not been amplified yet and would change the count
+            const bool sep = (thr <= 0.0 || cyc > 0) && j >= nk && nk > 0 &&
+                             sh.th[j] - sh.th[nk - 1] > 0.05 * fabs(sh.th[j]);
+            ok = ok && (rj <= (j < nk ? tol : sqrt(tol)) * bnd || sep);
+        }
+        if (ok) return cyc;
+        if (cyc >= max_cycles) return -1;
+        const double a = fmin(sh.th[M - 1], 0.5 * bnd);
+        const double a0 = fmin(sh.th[0], 0.0) - 1e-3 * bnd;
+        __syncthreads();
+        cheb_filter<M, R>(op, X, Y, ld, n, a, bnd, a0, deg);
+        orthonormalise<M, R>(Y, ld, n, sh);
+    }
+}
+
+__device__ __forceinline__ double block_max(double v, double* sh) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    v = wave_max(v);
+    __syncthreads();
+    if (lane == 0) sh[w] = v;
+    __syncthreads();
+    double t = 0.0;
+    for (int i = 0; i < nw; ++i) t = fmax(t, sh[i]);
+    __syncthreads();
+    return t;
+}
+
+// Per-column sums over all rows of registers A, written (by threads < cnt) to
+// dst[j] (j < nk) and zero for nk <= j < cnt.
+template <int M, int R>
+__device__ void column_sums(const double (&A)[R][M], double* dst, int cnt, int nk, double* red) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+        double v = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) v += A[r][j];
+        v = wave_sum(v);
+        if (lane == 0) red[w * M + j] = v;
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < cnt) {
+        double s = 0.0;
+        for (int ww = 0; ww < nw; ++ww) s += red[ww * M + threadIdx.x];
+        dst[threadIdx.x] = ((int)threadIdx.x < nk) ? s : 0.0;
+    }
+    __syncthreads();
+}
+
+// ---------------------------------------------------------------------------
+// level 2 kernel: one 512-thread workgroup per 8^3 element
+// Learned start (warm != null): the first kw columns of the start block are
+// the predicted cell vectors warm[blockIdx.x][0..kw-1][512] (row pitch kp),
+// the rest the next cosine modes.  From that block the eigensolve runs to
+// the relaxed residual ws_tol (times the spectral bound) within
+// kWarmCycles cycles; an element that does not get there falls back to the
+// exact solve (tolerance tol) from the cold start, and ws_fb[e] = 1.
+// status[e] counts the cycles of both attempts.
+// At most 128 VGPRs (four waves per SIMD): with about 68 KB of LDS per
+// workgroup, two elements then share a CU, and one element's serial phases
+// (Jacobi, Cholesky) overlap the other's filter.
+template <int M>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_eig2(
+    FineGeom g, const double* __restrict__ kt, int target, int L, double tol, double crtol,
+    double* __restrict__ phi, double* __restrict__ lam, int* __restrict__ nkeep, double* __restrict__ Aint,
+    double* __restrict__ zc, int* __restrict__ status, int e0, const float* __restrict__ warm, int kp, int kw,
+    double ws_tol, int* __restrict__ ws_fb, double thr) {
+    constexpr int LD = 513;
+    __shared__ double sY[M * LD];
+    __shared__ EigShared<M> sh;
+    const int e = e0 + blockIdx.x;
+    const int ex = e % g.mx, ey = (e / g.mx) % g.my, ez = e / (g.mx * g.my);
+    const int c = threadIdx.x;
+    const int i = c & 7, j = (c >> 3) & 7, k = c >> 6;
+    auto gid = [&](int x, int y, int z) { return eidx(g, x, y, z); };
+    // kappa~ per face direction: one array (isotropic) or three (orthotropic)
+    const size_t N = g.ortho ? g.ncell() : 0;
+    const size_t gc = gid(ex * 8 + i, ey * 8 + j, ez * 8 + k);
+    const double kc[3] = {kt[gc], kt[N + gc], kt[2 * N + gc]};
+    // weight tr K~: kappa~ (1 + cy + cz) with the y and z faces carrying cy
+    // and cz, or the sum of the three components
+    const double wsum = 1.0 + g.cy + g.cz;
+    auto weight = [&](size_t q) { return g.ortho ? kt[q] + kt[N + q] + kt[2 * N + q] : wsum * kt[q]; };
+    const double S = weight(gc);
+    const double sq = sqrt(S);
+    Op2 op;
+    double diag = 0.0, rowsum = 0.0;
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+        const int ii = i + (d == 0 ? -1 : (d == 1 ? 1 : 0));
+        const int jj = j + (d == 2 ? -1 : (d == 3 ? 1 : 0));
+        const int kk = k + (d == 4 ? -1 : (d == 5 ? 1 : 0));
+        op.off[d] = 0.0;
+        op.nb[d] = c;
+        if (ii >= 0 && ii < 8 && jj >= 0 && jj < 8 && kk >= 0 && kk < 8) {
+            const int ax = d >> 1;
+            const size_t gn = gid(ex * 8 + ii, ey * 8 + jj, ez * 8 + kk);
+            const double T = harm_e(kc[ax], kt[ax * N + gn]) * (ax == 0 ? 1.0 : (ax == 1 ? g.cy : g.cz));
+            diag += T;
+            op.off[d] = T / (sq * sqrt(weight(gn)));
+            op.nb[d] = ii + 8 * (jj + 8 * kk);
+            rowsum += op.off[d];
+        }
+    }
+    op.diag = diag / S;
+    const double bnd = block_max(op.diag + rowsum, sh.misc);
+
+    double X[1][M], AX[1][M];
+    const double pi8 = 3.14159265358979323846 / 8.0;
+    const int nw = warm ? kw : 0;
+#pragma unroll
+    for (int jj = 0; jj < M; ++jj) {
+        const double md = cos(pi8 * kModes[jj][0] * (i + 0.5)) * cos(pi8 * kModes[jj][1] * (j + 0.5)) *
+                          cos(pi8 * kModes[jj][2] * (k + 0.5));
+        const double cold = sq * (md + 0.05 * hash_noise((unsigned)e, (unsigned)jj, (unsigned)c));
+        X[0][jj] = jj < nw ? sq * (double)warm[((size_t)blockIdx.x * kp + jj) * 512 + c] : cold;
+    }
+    const int need = (target + 4 < M - 2) ? target + 4 : M - 2;
+    int cyc = -1, spent = 0;
+    if (warm) {
+        cyc = chefsi<M, 1>(op, sY, LD, 512, X, AX, bnd, need, ws_tol, target, crtol, thr, sh, kWarmCycles, kDeg);
+        const bool fb = cyc < 0;
+        if (fb) {
+            spent = kWarmCycles + 1;
+#pragma unroll
+            for (int jj = 0; jj < M; ++jj) {
+                const double md = cos(pi8 * kModes[jj][0] * (i + 0.5)) * cos(pi8 * kModes[jj][1] * (j + 0.5)) *
+                                  cos(pi8 * kModes[jj][2] * (k + 0.5));
+                X[0][jj] = sq * (md + 0.05 * hash_noise((unsigned)e, (unsigned)jj, (unsigned)c));
+            }
+        }
+        if (c == 0) ws_fb[e] = fb ? 1 : 0;
+        __syncthreads();
+    }
+    if (cyc < 0) {
+        cyc = chefsi<M, 1>(op, sY, LD, 512, X, AX, bnd, need, tol, target, crtol, thr, sh);
+        if (cyc >= 0) cyc += spent;
+    }
+
+    if (threadIdx.x == 0) {
+        const int nk = cluster_cut_dev(sh.th, M, target, crtol, thr);
+        sh.flag = nk;
+        nkeep[e] = nk;
+        status[e] = cyc;
+        for (int a = 0; a < L; ++a) lam[(size_t)e * L + a] = sh.th[a];
+    }
+    __syncthreads();
+    const int nk = sh.flag;
+    __syncthreads();
+    // interior block X^T A~ X on the kept vectors (= Phi^T A_K Phi)
+    store_block<M, 1>(sY, LD, 512, X);
+    __syncthreads();
+    gram_lds_reg<M, 1>(sY, LD, 512, AX, sh.G, sh.red);
+    for (int t = threadIdx.x; t < L * L; t += blockDim.x) {
+        const int a = t / L, b = t % L;
+        Aint[(size_t)e * L * L + t] = (a < nk && b < nk) ? sh.G[a * M + b] : 0.0;
+    }
+    // coefficients of the constant function: Phi^T S 1 = X^T S^1/2 1
+    double zv[1][M];
+#pragma unroll
+    for (int jj = 0; jj < M; ++jj) zv[0][jj] = X[0][jj] * sq;
+    column_sums<M, 1>(zv, zc + (size_t)e * L, L, nk, sh.red);
+#pragma unroll
+    for (int jj = 0; jj < M; ++jj) {
+        if (jj < L) phi[((size_t)e * L + jj) * 512 + phi_pos(c)] = (jj < nk) ? X[0][jj] / sq : 0.0;
+    }
+}
 
 // Hd[c] = Aint[c] + sum of D[c][d] over the faces of c interior to its parent
 __global__ void k_build_hd(CoarseGeom lo, const double* __restrict__ Aint, const double* __restrict__ D,
@@ -51,906 +832,205 @@ __global__ void k_build_hd(CoarseGeom lo, const double* __restrict__ Aint, const
     }
 }
 
-typedef double v4d __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(1))) double gl_double;
-typedef __attribute__((address_space(3))) unsigned short lds_ushort;
-
-__device__ __forceinline__ unsigned uniform32(unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane((int)v); }
-__device__ __forceinline__ unsigned long long uniform64(unsigned long long v) {
-    return (unsigned long long)uniform32((unsigned)v) | ((unsigned long long)uniform32((unsigned)(v >> 32)) << 32);
-}
-
-__device__ __forceinline__ int ceil16(int m) { return (m + 15) & ~15; }
-
-// 1 / x: the hardware estimate and one third-order correction
-__device__ __forceinline__ double rcp_f64(double x) {
-    const double r = __builtin_amdgcn_rcp(x);
-    const double e = fma(-x, r, 1.0);
-    return fma(r, fma(e, e, e), r);
-}
-
-// In-place inverse of the symmetric positive definite m x m matrix at T (leading
-// dimension ld) by symmetric sweeps over pairs of pivots, the matrix in the
-// registers of the NT threads (thread (ty, tx) of a TY x TX grid owns elements
-// (ty + TY a, tx + TX b)).  A sweep publishes its two pivot rows (by symmetry
-// also the columns) through one of two LDS buffers in turn, so a pair costs one
-// barrier; the latency of that exchange and of the pivots' reciprocals is what
-// bounds it.  Entries beyond m come out zero.  rows: 4 x 192 doubles.
-constexpr int kSweepRow = 192;
-template <int NT, int A, int B>
-__device__ __attribute__((noinline)) void sweep_inverse(gl_double* Tv, int mv, int ldv, lds_double* rowsv) {
-    gl_double* const T = (gl_double*)uniform64((unsigned long long)Tv);
-    lds_double* const rows = (lds_double*)uniform32((unsigned)(size_t)rowsv);
-    const int m = (int)uniform32((unsigned)mv), ld = (int)uniform32((unsigned)ldv);
-    constexpr int TY = 16, TX = NT / TY;
-    static_assert(TX == TY || TX == 2 * TY, "pivot columns in a static register");
-    const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
-    double v[A][B];
+// level >= 3 kernel: one workgroup per parent element E, one thread per row
+// of H_E (blockDim = agg^3 * lo.L rounded up to whole wavefronts, <= 768).
+// thr > 0 selects the kept count by the threshold rule (see cluster_cut_dev).
+template <int M, int LPT>
+__global__ __launch_bounds__(768) void k_eig_up(CoarseGeom lo, CoarseGeom up, const double* __restrict__ Hd,
+                                                const double* __restrict__ Aoff,
+                                                const int* __restrict__ nkeep_lo,
+                                                const double* __restrict__ zlo, int target, double tol,
+                                                double crtol, double thr, double* __restrict__ V,
+                                                double* __restrict__ lam, int* __restrict__ nkeep,
+                                                double* __restrict__ Aint, double* __restrict__ zup,
+                                                int* __restrict__ status) {
+    extern __shared__ double dyn[];
+    __shared__ EigShared<M> sh;
+    const int E = blockIdx.x;
+    const int agg = lo.agg, Lu = up.L, LP = LPT > 0 ? LPT : lo.L;
+    const int n = agg * agg * agg * LP;
+    const int ld = n | 1;
+    const int Ex = E % up.mx, Ey = (E / up.mx) % up.my, Ez = E / (up.mx * up.my);
+    const int row = threadIdx.x;
+    OpUp<LPT> op;
+    op.Aoff = Aoff;
+    op.lp_rt = LP;
+    const int rr = row < n ? row : n - 1;
+    const int p = rr / LP, a = rr % LP;
+    const int qx = p % agg, qy = (p / agg) % agg, qz = p / (agg * agg);
+    const int c = (Ex * agg + qx) + lo.mx * ((Ey * agg + qy) + lo.my * (Ez * agg + qz));
+    op.c = c;
+    op.a = a;
+    op.p = p;
+    op.qx = qx;
+    op.qy = qy;
+    op.qz = qz;
+    op.sy = lo.mx;
+    op.sz = lo.mx * lo.my;
+    op.agg = agg;
+    op.valid = row < n && a < nkeep_lo[c];
 #pragma unroll
-    for (int a = 0; a < A; ++a)
+    for (int b = 0; b < OpUp<LPT>::kW; ++b) op.hd[b] = b < LP ? Hd[((size_t)c * LP + a) * LP + b] : 0.0;
+    // Gershgorin bound: absolute row sum of H_E
+    double rs = 0.0;
+    if (op.valid) {
 #pragma unroll
-        for (int b = 0; b < B; ++b) {
-            const int i = ty + TY * a, j = tx + TX * b;
-            v[a][b] = i < m && j < m ? T[(size_t)i * ld + j] : 0.0;
-        }
-#pragma unroll
-    for (int a = 0; a < A; ++a) {
-        constexpr int step = TX / TY;
-        const int bk = a / step;   // register column of the pivots
-#pragma unroll 1
-        for (int s = 0; s < TY; s += 2) {
-            const int k = TY * a + s;
-            if (k >= m) break;
-            lds_double* r0 = rows + 2 * kSweepRow * ((k >> 1) & 1);
-            lds_double* r1 = r0 + kSweepRow;
-            if ((ty & ~1) == s) {
-                lds_double* r = ty == s ? r0 : r1;
-#pragma unroll
-                for (int b = 0; b < B; ++b) r[tx + TX * b] = v[a][b];
-            }
-            __syncthreads();
-            // inverse of the pivot block; a row k + 1 beyond m is zero
-            const bool two = k + 1 < m;
-            const double a00 = r0[k], a01 = r0[k + 1], a11 = r1[k + 1];
-            const double i0 = rcp_f64(a00), l = a01 * i0;
-            const double i1 = rcp_f64(two ? a11 - l * a01 : 1.0);
-            const double p01 = -l * i1, p00 = i0 - l * p01, p11 = two ? i1 : 0.0;
-            double c0[B], c1[B], w0[A], w1[A];
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                const double x = r0[tx + TX * b], y = r1[tx + TX * b];
-                c0[b] = p00 * x + p01 * y;
-                c1[b] = p01 * x + p11 * y;
-            }
-#pragma unroll
-            for (int i = 0; i < A; ++i) {
-                w0[i] = r0[ty + TY * i];
-                w1[i] = r1[ty + TY * i];
-            }
-#pragma unroll
-            for (int i = 0; i < A; ++i)
-#pragma unroll
-                for (int b = 0; b < B; ++b) v[i][b] -= w0[i] * c0[b] + w1[i] * c1[b];
-            const bool row0 = ty == s, row1 = ty == s + 1, col0 = tx == k % TX, col1 = tx == k % TX + 1;
-            if (row0 || row1) {
-#pragma unroll
-                for (int b = 0; b < B; ++b) v[a][b] = row0 ? c0[b] : c1[b];
-            }
-            if (col0 || col1) {
-#pragma unroll
-                for (int i = 0; i < A; ++i) v[i][bk] = col0 ? p00 * w0[i] + p01 * w1[i] : p01 * w0[i] + p11 * w1[i];
-                if (row0) v[a][bk] = col0 ? -p00 : -p01;
-                if (row1) v[a][bk] = col0 ? -p01 : -p11;
-            }
+        for (int b = 0; b < OpUp<LPT>::kW; ++b) rs += fabs(op.hd[b]);
+        for (int d = 0; d < 6; ++d) {
+            const int ax = d >> 1;
+            const int qa = ax == 0 ? qx : (ax == 1 ? qy : qz);
+            const int cs = ax == 0 ? 1 : (ax == 1 ? lo.mx : lo.mx * lo.my);
+            const bool in = (d & 1) ? (qa < agg - 1) : (qa > 0);
+            if (!in) continue;
+            const int cn = (d & 1) ? c + cs : c - cs;
+            for (int b = 0; b < LP; ++b)
+                rs += fabs((d & 1) ? Aoff[(((size_t)c * 3 + ax) * LP + a) * LP + b]
+                                   : Aoff[(((size_t)cn * 3 + ax) * LP + b) * LP + a]);
         }
     }
+    const double bnd = block_max(rs, sh.misc);
+    // dimension of H_E (the kept slots of the children) and the compact
+    // index of this row among them
+    int nval = 0, ci = a;
+    for (int pp = 0; pp < agg * agg * agg; ++pp) {
+        const int c2 = (Ex * agg + pp % agg) + lo.mx * ((Ey * agg + (pp / agg) % agg) + lo.my * (Ez * agg + pp / (agg * agg)));
+        const int k2 = nkeep_lo[c2];
+        nval += k2;
+        if (pp < p) ci += k2;
+    }
+    const double zr = op.valid ? zlo[(size_t)c * LP + a] : 0.0;
+    double X[1][M], AX[1][M];
+    int cyc = 0;
+    if (nval <= M) {
+        // the block can hold the whole space: unit vectors and one
+        // Rayleigh-Ritz step give the exact eigenpairs
 #pragma unroll
-    for (int a = 0; a < A; ++a)
-#pragma unroll
-        for (int b = 0; b < B; ++b) {
-            const int i = ty + TY * a, j = tx + TX * b;
-            if (i < ld && j < ld) T[(size_t)i * ld + j] = -v[a][b];
-        }
-    __syncthreads();
-}
-
-template <int NT>
-__device__ __forceinline__ void invert_block(gl_double* T, int m, int ld, lds_double* rows) {
-    if constexpr (NT == 256) {
-        if (m <= 48) sweep_inverse<NT, 3, 3>(T, m, ld, rows);
-        else if (m <= 64) sweep_inverse<NT, 4, 4>(T, m, ld, rows);
-        else if (m <= 80) sweep_inverse<NT, 5, 5>(T, m, ld, rows);
-        else sweep_inverse<NT, 7, 7>(T, m, ld, rows);
+        for (int j = 0; j < M; ++j) X[0][j] = (op.valid && ci == j) ? 1.0 : 0.0;
+        store_block<M, 1>(dyn, ld, n, X);
+        __syncthreads();
+        rayleigh_ritz<M, 1>(op, dyn, ld, n, X, AX, sh, nval, 2.0 * bnd + 1.0);
     } else {
-        if (m <= 96) sweep_inverse<NT, 6, 3>(T, m, ld, rows);
-        else if (m <= 128) sweep_inverse<NT, 8, 4>(T, m, ld, rows);
-        else sweep_inverse<NT, 12, 6>(T, m, ld, rows);
-    }
-}
-
-// Cycles with the inverse filter: up to 10 were seen to suffice, all but one
-// of some 36,000 elements a field; what is left converges by the filter in
-// H_E, of kDampDeg applications.
-constexpr int kInverseCycles = 14;
-constexpr int kDampDeg = 40;
-
-template <int M, int NT>
-struct UpShared {
-    double G[M * M];
-    double H[M * M];
-    double Q[M * M];
-    double th[M], nrm[M], scr[M];
-    double red[NT];
-    double rows[4 * kSweepRow];
-    double misc[NT / 64];
-    double ct[3 * 4];
-    double low;
-    int iscr[M];
-    int koff[65];     // first compact row of child p (65: the number of rows)
-    int elem[64];     // lower-level element of child p
-};
-
-// the parent's operator and block, shared by the kernel's phases
-template <int M, int NT>
-struct UpProblem {
-    static constexpr int NW = NT / 64;
-    static constexpr int NCT = (M + 15) / 16;       // column tiles of the matrix cores
-    static constexpr int PT = M <= 16 ? 18 : M + 2;  // row pitch of the LDS blocks
-    static constexpr int PG = 16 * NCT;             // row pitch of the workspace blocks
-    // address spaces are spelled out: the phases are calls of their own, and
-    // through plain pointers their accesses would be flat ones
-    typedef __attribute__((address_space(3))) UpShared<M, NT> lds_shared;
-    lds_shared* sh;
-    lds_double* Y;         // rows x PT: the block (the solve's result while filtering)
-    lds_double* U;         // a plane's right-hand side
-    lds_ushort* row;       // child position << 8 | slot of a compact row
-    gl_double* T;          // workspace: the planes' inverses, mp^2 each
-    gl_double *Wk, *Yg, *Xg, *AYg;
-    const gl_double *Hd, *Aoff;
-    int LP, agg, n, planes, mpmax;
-    int w, lane;
-
-    __device__ __forceinline__ int plane_row(int p) const {
-        return (int)uniform32((unsigned)sh->koff[planes == 1 ? p * 64 : p * agg * agg]);
-    }
-    __device__ __forceinline__ int plane_end(int p) const {
-        return planes == 1 ? n : (int)uniform32((unsigned)sh->koff[(p + 1) * agg * agg]);
-    }
-
-    // entry (i, j) of H_E for rows of children that are equal or neighbours
-    // along axis ax (ax < 0: the same child); up: the child of j lies above
-    __device__ __forceinline__ double entry(int ci, int ai, int cj, int bj, int ax, bool up) const {
-        if (ax < 0) return Hd[((size_t)ci * LP + ai) * LP + bj];
-        return up ? Aoff[(((size_t)ci * 3 + ax) * LP + ai) * LP + bj] : Aoff[(((size_t)cj * 3 + ax) * LP + bj) * LP + ai];
-    }
-
-    // coordinates of child p (agg is 2 or 4: shifts)
-    __device__ __forceinline__ int lg() const { return agg == 4 ? 2 : 1; }
-    __device__ __forceinline__ int child_x(int p) const { return p & (agg - 1); }
-    __device__ __forceinline__ int child_y(int p) const { return (p >> lg()) & (agg - 1); }
-    __device__ __forceinline__ int child_z(int p) const { return p >> (2 * lg()); }
-
-    // sum_k c[k cs] x[k xs], k < kn (kn >= 1): eight of each in flight (beyond kn
-    // the last one again, with weight zero, so that no load is conditional)
-    template <class PC, class PX>
-    static __device__ __forceinline__ double coupled(PC c, int cs, PX x, int xs, int kn) {
-        double s = 0.0;
-#pragma unroll 1
-        for (int k0 = 0; k0 < kn; k0 += 8) {
-            double h[8], y[8];
+        // start block: the constant function, smooth weights of the
+        // children's constant modes, and noise on every kept slot.  The
+        // noise has one amplitude for the whole element: the constant
+        // function's coefficient zr vanishes on the children's non-constant
+        // slots, and noise scaled by it would leave the block without those
+        // directions, which a polynomial filter cannot restore
+        const double pa = 3.14159265358979323846 / agg;
+        const double az = block_max(op.valid ? fabs(zr) : 0.0, sh.misc) + 1e-300;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) h[u] = c[min(k0 + u, kn - 1) * cs];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) y[u] = x[min(k0 + u, kn - 1) * xs];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += (k0 + u < kn ? h[u] : 0.0) * y[u];
+        for (int j = 0; j < M; ++j) {
+            double v = 0.05 * az * hash_noise((unsigned)E + 77u, (unsigned)j, (unsigned)row);
+            if (j == 0) v = zr;
+            else if (a == 0)
+                v += zr * cos(pa * kModes[j & 15][0] * (qx + 0.5)) * cos(pa * kModes[j & 15][1] * (qy + 0.5)) *
+                     cos(pa * kModes[j & 15][2] * (qz + 0.5));
+            X[0][j] = op.valid ? v : 0.0;
         }
-        return s;
+        const int need = (target + 4 < M - 2) ? target + 4 : M - 2;
+        cyc = chefsi<M, 1>(op, dyn, ld, n, X, AX, bnd, need, tol, target, crtol, thr, sh);
     }
-
-    // AYg = H_E Y, one row per thread
-    __device__ __forceinline__ void apply() const {
-        const int a2 = agg * agg;
-#pragma unroll 1
-        for (int r = threadIdx.x; r < n; r += NT) {
-            const int p = row[r] >> 8, a = row[r] & 255;
-            const int qx = child_x(p), qy = child_y(p), qz = child_z(p);
-            const int c = sh->elem[p];
-            double acc[M];
-#pragma unroll
-            for (int j = 0; j < M; ++j) acc[j] = 0.0;
-#pragma unroll 1
-            for (int d = -1; d < 6; ++d) {
-                const int ax = d < 0 ? -1 : d >> 1;
-                const int q = ax <= 0 ? qx : (ax == 1 ? qy : qz);
-                const bool up = d & 1;
-                if (d >= 0 && (up ? q >= agg - 1 : q <= 0)) continue;
-                const int st = ax <= 0 ? 1 : (ax == 1 ? agg : a2);
-                const int pn = d < 0 ? p : (up ? p + st : p - st);
-                const int cn = sh->elem[pn], k0 = sh->koff[pn], kn = sh->koff[pn + 1] - k0;
-#pragma unroll 4
-                for (int b = 0; b < kn; ++b) {
-                    const double h = entry(c, a, cn, b, ax, up);
-                    const lds_double* y = Y + (k0 + b) * PT;
-#pragma unroll
-                    for (int j = 0; j < M; ++j) acc[j] += h * y[j];
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < M; ++j) AYg[(size_t)r * PG + j] = acc[j];
-        }
+    if (threadIdx.x == 0) {
+        const int nk = cluster_cut_dev(sh.th, nval < M ? nval : M, target, crtol, thr);
+        sh.flag = nk;
+        nkeep[E] = nk;
+        status[E] = cyc;
+        for (int b = 0; b < Lu; ++b) lam[(size_t)E * Lu + b] = b < nval ? sh.th[b] : 0.0;
     }
-
-    // sh->G = Y^T Y, sh->H = Y^T AYg on the matrix cores: the two operands of a
-    // Gram product are the same registers.  The wavefronts' sums are added in
-    // wavefront order.
-    __device__ __forceinline__ void grams() const {
-        v4d g[NCT][NCT], h[NCT][NCT];
-#pragma unroll
-        for (int a = 0; a < NCT; ++a)
-#pragma unroll
-            for (int b = 0; b < NCT; ++b) g[a][b] = h[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
-        const int li = lane & 15, lk = lane >> 4;
-#pragma unroll 2
-        for (int t = w; 4 * t < n; t += NW) {
-            const int r = 4 * t + lk;
-            double y[NCT], z[NCT];
-#pragma unroll
-            for (int a = 0; a < NCT; ++a) {
-                const int j = 16 * a + li;
-                const bool in = r < n && j < M;
-                y[a] = in ? Y[r * PT + j] : 0.0;
-                z[a] = in ? AYg[(size_t)r * PG + j] : 0.0;
-            }
-#pragma unroll
-            for (int a = 0; a < NCT; ++a)
-#pragma unroll
-                for (int b = 0; b < NCT; ++b) {
-                    g[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[a], y[b], g[a][b], 0, 0, 0);
-                    h[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[a], z[b], h[a][b], 0, 0, 0);
-                }
-        }
-#pragma unroll 1
-        for (int ww = 0; ww < NW; ++ww) {
-            if (w == ww) {
-#pragma unroll
-                for (int a = 0; a < NCT; ++a)
-#pragma unroll
-                    for (int b = 0; b < NCT; ++b)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const int i = 16 * a + lk + 4 * r, j = 16 * b + li;
-                            if (i < M && j < M) {
-                                sh->G[i * M + j] = (ww ? sh->G[i * M + j] : 0.0) + g[a][b][r];
-                                sh->H[i * M + j] = (ww ? sh->H[i * M + j] : 0.0) + h[a][b][r];
-                            }
-                        }
-            }
-            __syncthreads();
-        }
+    __syncthreads();
+    const int nk = sh.flag;
+    __syncthreads();
+    store_block<M, 1>(dyn, ld, n, X);
+    __syncthreads();
+    gram_lds_reg<M, 1>(dyn, ld, n, AX, sh.G, sh.red);
+    for (int t = threadIdx.x; t < Lu * Lu; t += blockDim.x) {
+        const int i = t / Lu, j = t % Lu;
+        Aint[(size_t)E * Lu * Lu + t] = (i < nk && j < nk) ? sh.G[i * M + j] : 0.0;
     }
-
-    // rows of X (pitch px) times the M x M matrix sh->Q, in place; a wavefront
-    // owns whole 16-row tiles
-    template <class P>
-    __device__ __forceinline__ void mul(P X, int px) const {
-        const int li = lane & 15, lk = lane >> 4;
-        double q[NCT][(M + 3) / 4];
+    double zv[1][M];
 #pragma unroll
-        for (int t = 0; t < (M + 3) / 4; ++t)
+    for (int jj = 0; jj < M; ++jj) zv[0][jj] = X[0][jj] * zr;
+    column_sums<M, 1>(zv, zup + (size_t)E * Lu, Lu, nk, sh.red);
+    if (row < n) {
 #pragma unroll
-            for (int b = 0; b < NCT; ++b) {
-                const int k = 4 * t + lk, j = 16 * b + li;
-                q[b][t] = k < M && j < M ? sh->Q[k * M + j] : 0.0;
-            }
-#pragma unroll 1
-        for (int r0 = 16 * w; r0 < n; r0 += 16 * NW) {
-            v4d acc[NCT];
-#pragma unroll
-            for (int b = 0; b < NCT; ++b) acc[b] = v4d{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int t = 0; t < (M + 3) / 4; ++t) {
-                const int k = 4 * t + lk;
-                const double x = k < M && r0 + li < n ? X[(size_t)(r0 + li) * px + k] : 0.0;
-#pragma unroll
-                for (int b = 0; b < NCT; ++b) acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, q[b][t], acc[b], 0, 0, 0);
-            }
-#pragma unroll
-            for (int b = 0; b < NCT; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = r0 + lk + 4 * r, j = 16 * b + li;
-                    if (i < n && j < M) X[(size_t)i * px + j] = acc[b][r];
-                }
-        }
-    }
-
-    // sums over all rows of f(row, column) into out[0..M-1]
-    template <class F>
-    __device__ __forceinline__ void column_sums(lds_double* out, F f) const {
-        const int j = threadIdx.x % PG;
-        double s = 0.0;
-        if (j < M)
-            for (int r = threadIdx.x / PG; r < n; r += NT / PG) s += f(r, j);
-        sh->red[threadIdx.x] = s;
-        __syncthreads();
-        if (threadIdx.x < M) {
-            double t = 0.0;
-            for (int k = 0; k < NT / PG; ++k) t += sh->red[k * PG + threadIdx.x];
-            out[threadIdx.x] = t;
-        }
-        __syncthreads();
-    }
-
-    // Rayleigh-Ritz of the LDS block: Y and AYg become the Ritz vectors and their
-    // images, sh->th the values, sh->nrm the squared residual norms; nval < M: only
-    // the first nval columns exist.  Returns the smallest scaled pivot.
-    __device__ __forceinline__ double rayleigh_ritz_inl(bool rough, int nval, double pad) const {
-        const double min_ritz = rough ? 1e-9 : 1e-5;
-        double low = 0.0;
-#pragma unroll 1
-        for (int pass = 0; pass < 4; ++pass) {
-            apply();
-            __syncthreads();
-            grams();
-            if (threadIdx.x < 64) {
-                const double lw = ritz_wave<M>(sh->G, sh->H, sh->Q, sh->scr, sh->th, sh->iscr,
-                                               pass < 3 ? min_ritz : 0.0, rough ? 1e-6 : 1e-15, nval, pad);
-                if (threadIdx.x == 0) sh->low = lw;
-            }
-            __syncthreads();
-            low = sh->low;
-            mul(Y, PT);
-            if (low >= min_ritz || pass == 3) break;
-            __syncthreads();
-        }
-        mul(AYg, PG);
-        __syncthreads();
-        column_sums(sh->nrm, [&](int r, int j) {
-            const double d = AYg[(size_t)r * PG + j] - sh->th[j] * Y[r * PT + j];
-            return d * d;
-        });
-        return low;
-    }
-
-    // T_p = (S_p)^-1 for every plane
-    __device__ __forceinline__ void factor_inl(double sigma) const {
-        const int a2 = agg * agg;
-#pragma unroll 1
-        for (int p = 0; p < planes; ++p) {
-            const int r0 = plane_row(p), m = plane_end(p) - r0, ld = ceil16(m);
-            gl_double* Tp = T + (size_t)p * mpmax * mpmax;
-            const int q0 = p ? plane_row(p - 1) : 0, mq = r0 - q0, ldq = ceil16(mq);
-            const gl_double* Tq = T + (size_t)(p - 1) * mpmax * mpmax;
-            const int c0 = planes == 1 ? 0 : p * a2, nch = planes == 1 ? a2 * agg : a2;
-            if (p) {
-                // Wk[j][i] = (T_{p-1} C_{p-1})[i][j]: a wavefront takes a child of this
-                // plane, a lane a row i of the plane below; the child's couplings are
-                // the same for every lane
-#pragma unroll 1
-                for (int q = w; q < nch; q += NW) {
-                    const int pj = (int)uniform32((unsigned)(c0 + q)), pb = pj - a2;
-                    const int kb = (int)uniform32((unsigned)sh->koff[pb]), kn = (int)uniform32((unsigned)sh->koff[pb + 1]) - kb;
-                    const int jb = (int)uniform32((unsigned)sh->koff[pj]), jn = (int)uniform32((unsigned)sh->koff[pj + 1]) - jb;
-                    const gl_double* C = Aoff + ((size_t)uniform32((unsigned)sh->elem[pb]) * 3 + 2) * LP * LP;
-                    for (int i = lane; i < mq; i += 64) {
-                        const gl_double* t = Tq + (size_t)(kb - q0) * ldq + i;
-#pragma unroll 1
-                        for (int k0 = 0; k0 < kn; k0 += 8) {
-                            double x[8];
-#pragma unroll
-                            for (int u = 0; u < 8; ++u) x[u] = t[min(k0 + u, kn - 1) * ldq];
-#pragma unroll
-                            for (int u = 0; u < 8; ++u) x[u] = k0 + u < kn ? x[u] : 0.0;
-#pragma unroll 2
-                            for (int b = 0; b < jn; ++b) {
-                                gl_double* o = Wk + (size_t)(jb - r0 + b) * mpmax + i;
-                                double v = k0 ? *o : 0.0;
-#pragma unroll
-                                for (int u = 0; u < 8; ++u) v += x[u] * C[min(k0 + u, kn - 1) * LP + b];
-                                *o = v;
-                            }
-                        }
-                    }
-                }
-                __syncthreads();
-            }
-            // S_p row by row of a child: a lane takes a column j
-#pragma unroll 1
-            for (int q = w; q < nch; q += NW) {
-                const int pi = (int)uniform32((unsigned)(c0 + q)), ci = (int)uniform32((unsigned)sh->elem[pi]);
-                const int ib = (int)uniform32((unsigned)sh->koff[pi]), in = (int)uniform32((unsigned)sh->koff[pi + 1]) - ib;
-                const int xi = child_x(pi), yi = child_y(pi), zi = child_z(pi);
-                const int pb = p ? pi - a2 : pi;
-                const int kb = (int)uniform32((unsigned)sh->koff[pb]), kn = p ? (int)uniform32((unsigned)sh->koff[pb + 1]) - kb : 0;
-                const gl_double* C = Aoff + ((size_t)uniform32((unsigned)sh->elem[pb]) * 3 + 2) * LP * LP;
-                for (int j = lane; j < m; j += 64) {
-                    const int pj = row[r0 + j] >> 8, bj = row[r0 + j] & 255, cj = sh->elem[pj];
-                    const int dx = child_x(pj) - xi, dy = child_y(pj) - yi, dz = child_z(pj) - zi;
-                    const int dist = abs(dx) + abs(dy) + abs(dz);
-                    const bool up = dx + dy + dz > 0;
-                    const int ax = dx ? 0 : (dy ? 1 : 2);
-                    // entries of the lane's column: e[a es]
-                    const gl_double* e = dist == 0 ? Hd + (size_t)ci * LP * LP + bj
-                                                   : Aoff + ((size_t)(up ? ci : cj) * 3 + ax) * LP * LP + (up ? bj : bj * LP);
-                    const int es = dist == 0 || up ? LP : 1;
-                    const double we = dist <= 1 ? 1.0 : 0.0;
-                    if (dist > 1) e = Hd;   // any valid entry, weight zero
-                    const gl_double* x0 = Wk + (size_t)j * mpmax + (p ? kb - q0 : 0);
-#pragma unroll 1
-                    for (int a0 = 0; a0 < in; a0 += 4) {
-                        double v[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) v[u] = e[dist <= 1 ? min(a0 + u, in - 1) * es : 0];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-                            v[u] = we * v[u] + (dist == 0 && a0 + u == bj ? sigma : 0.0);
-#pragma unroll 1
-                        for (int k0 = 0; k0 < kn; k0 += 8) {
-                            double x[8];
-#pragma unroll
-                            for (int k = 0; k < 8; ++k) x[k] = x0[min(k0 + k, kn - 1)];
-#pragma unroll
-                            for (int k = 0; k < 8; ++k) x[k] = k0 + k < kn ? x[k] : 0.0;
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                                for (int k = 0; k < 8; ++k)
-                                    v[u] -= C[min(k0 + k, kn - 1) * LP + min(a0 + u, in - 1)] * x[k];
-                        }
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-                            if (a0 + u < in) Tp[(size_t)(ib - r0 + a0 + u) * ld + j] = v[u];
-                    }
-                }
-            }
-            __syncthreads();
-            invert_block<NT>(Tp, m, ld, sh->rows);
-        }
-    }
-
-    // acc = T_p U on the rows of the plane: V rows = acc (sub: V -= acc).  The
-    // symmetric T_p is read by its columns, 128 contiguous bytes per 16 lanes,
-    // in groups of four k-steps, three groups in flight (the last group again
-    // past the end, so that no load is conditional); the first ones are
-    // loaded by the caller ahead of U's barrier.  Columns of U beyond M only reach
-    // columns of the result that are not stored.
-    struct Ahead {
-        double a[3][4];
-    };
-    __device__ __forceinline__ void load_group(const gl_double* tc, int ld, int g, double (&a)[4]) const {
-        const gl_double* t = tc + (size_t)(16 * min(g, ld / 16 - 1)) * ld;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) a[u] = t[(size_t)(4 * u) * ld];
-    }
-    __device__ __forceinline__ const gl_double* tile_column(int p, int ld, int t0) const {
-        return T + (size_t)p * mpmax * mpmax + (size_t)(lane >> 4) * ld + min(t0, ld - 16) + (lane & 15);
-    }
-    __device__ __forceinline__ void product_first(int p, Ahead& f) const {
-        const int ld = ceil16(plane_end(p) - plane_row(p));
-        const gl_double* tc = tile_column(p, ld, 16 * w);
-#pragma unroll
-        for (int g = 0; g < 3; ++g) load_group(tc, ld, g, f.a[g]);
-    }
-    __device__ __forceinline__ void product(int p, bool sub, Ahead& f) const {
-        const int r0 = plane_row(p), m = plane_end(p) - r0, ld = ceil16(m), ng = ld / 16;
-        const int li = lane & 15, lk = lane >> 4;
-#pragma unroll 1
-        for (int t0 = 16 * w; t0 < ld; t0 += 16 * NW) {
-            v4d acc[NCT];
-#pragma unroll
-            for (int b = 0; b < NCT; ++b) acc[b] = v4d{0.0, 0.0, 0.0, 0.0};
-            const gl_double* tc = tile_column(p, ld, t0);
-            if (t0 != 16 * w) {
-#pragma unroll
-                for (int g = 0; g < 3; ++g) load_group(tc, ld, g, f.a[g]);
-            }
-#pragma unroll 1
-            for (int g0 = 0; g0 < ng; g0 += 3) {
-#pragma unroll
-                for (int g = 0; g < 3; ++g) {
-                    if (g0 + g < ng) {
-                        double x[NCT][4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-#pragma unroll
-                            for (int b = 0; b < NCT; ++b)
-                                x[b][u] = U[(16 * (g0 + g) + 4 * u + lk) * PT + min(16 * b + li, PT - 1)];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-#pragma unroll
-                            for (int b = 0; b < NCT; ++b)
-                                acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[g][u], x[b][u], acc[b], 0, 0, 0);
-                        load_group(tc, ld, g0 + g + 3, f.a[g]);
-                    }
-                }
-            }
-#pragma unroll
-            for (int b = 0; b < NCT; ++b)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = t0 + lk + 4 * r, j = 16 * b + li;
-                    if (i < m && j < M) {
-                        lds_double* v = Y + (r0 + i) * PT + j;
-                        *v = sub ? *v - acc[b][r] : acc[b][r];
-                    }
-                }
-        }
-    }
-
-    // Y = (H_E + sigma)^-1 Yg by the planes' inverses
-    __device__ __forceinline__ void solve() const {
-        const int a2 = agg * agg;
-#pragma unroll 1
-        for (int s = 0; s < 2 * planes - 1; ++s) {
-            const bool back = s >= planes;
-            const int p = back ? 2 * planes - 2 - s : s;
-            const int r0 = plane_row(p), m = plane_end(p) - r0, ld = ceil16(m);
-            Ahead first;
-            product_first(p, first);
-            const int j = min((int)threadIdx.x % PG, M - 1);
-#pragma unroll 1
-            for (int i = threadIdx.x / PG; i < ld; i += NT / PG) {
-                const int r = r0 + min(i, m - 1);
-                double v = back ? 0.0 : Yg[(size_t)r * PG + j];
-                if (s) {
-                    // the coupled child: below on the way up, above on the way down
-                    const int pi = row[r] >> 8, ai = row[r] & 255;
-                    const int pn = back ? pi + a2 : pi - a2, k0 = sh->koff[pn], kn = sh->koff[pn + 1] - k0;
-                    const gl_double* h =
-                        Aoff + ((size_t)sh->elem[back ? pi : pn] * 3 + 2) * LP * LP + (back ? ai * LP : ai);
-                    const double q = coupled(h, back ? 1 : LP, Y + k0 * PT + j, PT, kn);
-                    v = back ? q : v - q;
-                }
-                if (threadIdx.x % PG < M) U[i * PT + j] = i < m ? v : 0.0;
-            }
-            __syncthreads();
-            product(p, back, first);
-            __syncthreads();
-        }
-    }
-
-    // T_deg of the inverse mapped from [0, 1 / (a + sigma)] to [-1, 1], applied
-    // to the block (left unscaled, see the level-2 filter)
-    __device__ __forceinline__ void filter_inl(double a, double sigma, int deg) const {
-        const double f = 2.0 * (a + sigma);
-        for (int t = threadIdx.x; t < n * PG; t += NT) {
-            const int i = t / PG, j = t % PG;
-            if (j < M) Yg[t] = Y[i * PT + j];
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int d = 1; d <= deg; ++d) {
-            solve();
-            for (int t = threadIdx.x; t < n * PG; t += NT) {
-                const int i = t / PG, j = t % PG;
-                if (j >= M) continue;
-                const double y = Yg[t];
-                const double z = f * Y[i * PT + j] - y;
-                const double v = d == 1 ? z : 2.0 * z - Xg[t];
-                Xg[t] = y;
-                Yg[t] = v;
-                if (d == deg) Y[i * PT + j] = v;
-            }
-            __syncthreads();
-        }
-    }
-
-    // The Chebyshev polynomial of H_E itself that damps [a, b], for blocks on
-    // which the inverses' rounding (their error times |H_E|) stays above the
-    // tolerance: Y <- T_deg((H_E - c) / e) Y
-    __device__ __forceinline__ void damp_inl(double a, double b, int deg) const {
-        const double c = 0.5 * (a + b), ie = 2.0 / (b - a);
-#pragma unroll 1
-        for (int d = 1; d <= deg; ++d) {
-            apply();
-            __syncthreads();
-            for (int t = threadIdx.x; t < n * PG; t += NT) {
-                const int i = t / PG, j = t % PG;
-                if (j >= M) continue;
-                const double y = Y[i * PT + j];
-                const double z = (AYg[t] - c * y) * ie;
-                const double v = d == 1 ? z : 2.0 * z - Xg[t];
-                Xg[t] = y;
-                Y[i * PT + j] = v;
-            }
-            __syncthreads();
-        }
-    }
-
-    // The phases as calls of their own (inlined together they exceed the
-    // registers and the instruction cache), each on a copy of the problem in scalar
-    // registers.
-    __device__ __forceinline__ UpProblem scalar() const {
-        UpProblem l = *this;
-        l.sh = (lds_shared*)uniform32((unsigned)(size_t)sh);
-        l.Y = (lds_double*)uniform32((unsigned)(size_t)Y);
-        l.U = (lds_double*)uniform32((unsigned)(size_t)U);
-        l.row = (lds_ushort*)uniform32((unsigned)(size_t)row);
-        l.T = (gl_double*)uniform64((unsigned long long)T);
-        l.Wk = (gl_double*)uniform64((unsigned long long)Wk);
-        l.Yg = (gl_double*)uniform64((unsigned long long)Yg);
-        l.Xg = (gl_double*)uniform64((unsigned long long)Xg);
-        l.AYg = (gl_double*)uniform64((unsigned long long)AYg);
-        l.Hd = (const gl_double*)uniform64((unsigned long long)Hd);
-        l.Aoff = (const gl_double*)uniform64((unsigned long long)Aoff);
-        l.LP = (int)uniform32((unsigned)LP);
-        l.agg = (int)uniform32((unsigned)agg);
-        l.n = (int)uniform32((unsigned)n);
-        l.planes = (int)uniform32((unsigned)planes);
-        l.mpmax = (int)uniform32((unsigned)mpmax);
-        l.w = (int)uniform32((unsigned)w);
-        l.lane = (int)(threadIdx.x & 63);
-        return l;
-    }
-    __device__ __attribute__((noinline)) double rayleigh_ritz(bool rough, int nval, double pad) const {
-        return scalar().rayleigh_ritz_inl(rough, nval, pad);
-    }
-    __device__ __attribute__((noinline)) void factor(double sigma) const { scalar().factor_inl(sigma); }
-    __device__ __attribute__((noinline)) void damp(double a, double b) const { scalar().damp_inl(a, b, kDampDeg); }
-    __device__ __attribute__((noinline)) void filter(double a, double sigma, int deg) const {
-        scalar().filter_inl(a, sigma, (int)uniform32((unsigned)deg));
-    }
-};
-
-// Degree of the next filter (see the level-2 solver's): the residual of the
-// slowest vector that still has to converge shrinks by exp(-acosh t) per degree,
-// t its image in the damped interval's coordinate.  At most 4 in the first
-// cycle (its cut is far too high), 8 in the next two (the block's columns
-// must stay independent), 20 later.
-__device__ __forceinline__ int inverse_degree(const double* th, const double* nrm, int lane, int need, double tol,
-                                              double bnd, int nk, double a, double sigma, int cyc) {
-    const int cap = cyc == 0 ? 4 : (cyc < 3 ? 8 : 20);
-    double d = 2.0;
-    if (lane < need) {
-        const double rho = sqrt(nrm[lane]) / ((lane < nk ? tol : sqrt(tol)) * bnd);
-        const bool sep = lane >= nk && nk > 0 && th[lane] - th[nk - 1] > 0.05 * fabs(th[lane]);
-        if (rho > 1.0 && !sep) {
-            const double t = 2.0 * (a + sigma) / (th[lane] + sigma) - 1.0;
-            d = t > 1.0001 ? fmin((double)cap, log(10.0 * rho) / log(t + sqrt(t * t - 1.0)) + 2.0) : (double)cap;
-        }
-    }
-    return (int)wave_max(fmax(d, 2.0));
-}
-
-__host__ __device__ inline int up_planes(int agg, int lp) { return agg * agg * agg * lp <= kUpSingle ? 1 : agg; }
-// rows of a plane, rounded up to whole tiles
-__host__ __device__ inline int up_plane_rows(int agg, int lp) {
-    const int m = (up_planes(agg, lp) == 1 ? agg * agg * agg : agg * agg) * lp;
-    return (m + 15) & ~15;
-}
-// doubles of one workspace slot: the planes' inverses and one product, three blocks
-static size_t up_slot_doubles(int agg, int lp, int M) {
-    const size_t mp = up_plane_rows(agg, lp), n = (size_t)agg * agg * agg * lp, pg = M <= 16 ? 16 : 32;
-    return (up_planes(agg, lp) + 1) * mp * mp + 3 * n * pg;
-}
-
-template <int M, int NT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_eig_up(CoarseGeom lo, CoarseGeom up, const double* __restrict__ Hd,
-                                               const double* __restrict__ Aoff, const int* __restrict__ nkeep_lo,
-                                               const double* __restrict__ zlo, int target, double tol, double crtol,
-                                               double thr, double* __restrict__ V, double* __restrict__ lam,
-                                               int* __restrict__ nkeep, double* __restrict__ Aint,
-                                               double* __restrict__ zup, int* __restrict__ status,
-                                               double* __restrict__ work, size_t slot) {
-    extern __shared__ __align__(16) double dyn[];
-    __shared__ UpShared<M, NT> sh;
-    typedef UpProblem<M, NT> UP;
-    constexpr int PT = UP::PT;
-    const int agg = lo.agg, Lu = up.L, LP = lo.L, nch = agg * agg * agg, npad = nch * LP;
-    const int planes = up_planes(agg, LP), mpmax = up_plane_rows(agg, LP);
-    const int lane = threadIdx.x & 63;
-    double* ws = work + (size_t)blockIdx.x * slot;
-    double* Ub = dyn + (size_t)npad * PT;
-    UP pr{(typename UP::lds_shared*)&sh, (lds_double*)dyn, (lds_double*)Ub, (lds_ushort*)(Ub + (size_t)mpmax * PT),
-          (gl_double*)ws, (gl_double*)(ws + (size_t)planes * mpmax * mpmax), nullptr, nullptr, nullptr,
-          (const gl_double*)Hd, (const gl_double*)Aoff, LP, agg, 0, planes, mpmax, (int)(threadIdx.x >> 6), lane};
-    pr.Yg = pr.Wk + (size_t)mpmax * mpmax;
-    pr.Xg = pr.Yg + (size_t)npad * UP::PG;
-    pr.AYg = pr.Xg + (size_t)npad * UP::PG;
-    // one-dimensional factors cos(pi p (q + 1/2) / agg) of the start modes
-    if (threadIdx.x < 12)
-        sh.ct[threadIdx.x] =
-            cos(3.14159265358979323846 / agg * (double)(threadIdx.x >> 2) * ((threadIdx.x & 3) + 0.5));
-#pragma unroll 1
-    for (int E = blockIdx.x; E < up.m; E += gridDim.x) {
-        const int Ex = E % up.mx, Ey = (E / up.mx) % up.my, Ez = E / (up.mx * up.my);
-        __syncthreads();
-        if (threadIdx.x < 64) {
-            // children and the prefix sums of their kept slots, one child per lane
-            int k = 0;
-            if (lane < nch) {
-                const int c = (Ex * agg + lane % agg) +
-                              lo.mx * ((Ey * agg + (lane / agg) % agg) + lo.my * (Ez * agg + lane / (agg * agg)));
-                sh.elem[lane] = c;
-                k = nkeep_lo[c];
-            }
-            int s = k;
-            for (int off = 1; off < 64; off <<= 1) {
-                const int o = __shfl_up(s, off, 64);
-                if (lane >= off) s += o;
-            }
-            if (lane < nch) sh.koff[lane] = s - k;
-            if (lane == 63) {
-                for (int p = nch; p <= 64; ++p) sh.koff[p] = s;
-            }
-        }
-        __syncthreads();
-        const int nval = sh.koff[nch];
-        pr.n = nval;
-        for (int t = threadIdx.x; t < npad; t += NT) {
-            const int p = t / LP, a = t % LP;
-            if (a < sh.koff[p + 1] - sh.koff[p]) pr.row[sh.koff[p] + a] = (unsigned short)(p << 8 | a);
-        }
-        __syncthreads();
-        // Gershgorin bound (absolute row sums) and the largest constant coefficient
-        double rs = 0.0, az = 0.0;
-        for (int r = threadIdx.x; r < nval; r += NT) {
-            const int p = pr.row[r] >> 8, a = pr.row[r] & 255, c = sh.elem[p];
-            const int q[3] = {pr.child_x(p), pr.child_y(p), pr.child_z(p)}, st[3] = {1, agg, agg * agg};
-            double s = 0.0;
-            for (int b = 0; b < sh.koff[p + 1] - sh.koff[p]; ++b) s += fabs(pr.entry(c, a, c, b, -1, false));
-#pragma unroll
-            for (int d = 0; d < 6; ++d) {
-                const bool in = (d & 1) ? q[d >> 1] < agg - 1 : q[d >> 1] > 0;
-                if (!in) continue;
-                const int pn = (d & 1) ? p + st[d >> 1] : p - st[d >> 1], cn = sh.elem[pn];
-                for (int b = 0; b < sh.koff[pn + 1] - sh.koff[pn]; ++b)
-                    s += fabs(pr.entry(c, a, cn, b, d >> 1, d & 1));
-            }
-            rs = fmax(rs, s);
-            az = fmax(az, fabs(zlo[(size_t)c * LP + a]));
-        }
-        auto block_max = [&](double v) {
-            v = wave_max(v);
-            __syncthreads();
-            if (lane == 0) sh.misc[threadIdx.x >> 6] = v;
-            __syncthreads();
-            double t = sh.misc[0];
-            for (int i = 1; i < NT / 64; ++i) t = fmax(t, sh.misc[i]);
-            return t;
-        };
-        const double bnd = block_max(rs);
-        az = block_max(az) + 1e-300;
-        // Start block: unit vectors when they span the whole space (one
-        // Rayleigh-Ritz step is then exact); else the constant function, smooth
-        // weights of the children's constant modes, and noise on every kept
-        // slot.  The noise has one amplitude for the whole element: the constant
-        // function's coefficient vanishes on the children's non-constant slots,
-        // and noise scaled by it would leave the block without those
-        // directions, which a filter cannot restore.
-        const bool whole = nval <= M;
-        for (int t = threadIdx.x; t < nval * M; t += NT) {
-            const int r = t / M, j = t % M;
-            const int p = pr.row[r] >> 8, a = pr.row[r] & 255;
-            double v;
-            if (whole) {
-                v = r == j ? 1.0 : 0.0;
-            } else {
-                const double z = zlo[(size_t)sh.elem[p] * LP + a];
-                v = 0.05 * az * hash_noise((unsigned)E + 77u, (unsigned)j, (unsigned)(p * LP + a));
-                if (j == 0) v = z;
-                else if (a == 0) {
-                    const unsigned char* md = kModes[j & 15];
-                    v += z * sh.ct[4 * md[0] + pr.child_x(p)] * sh.ct[4 * md[1] + pr.child_y(p)] *
-                         sh.ct[4 * md[2] + pr.child_z(p)];
-                }
-            }
-            pr.Y[r * PT + j] = v;
-        }
-        __syncthreads();
-        int cyc = 0;
-        if (whole) {
-            pr.rayleigh_ritz(false, nval, 2.0 * bnd + 1.0);
-        } else {
-            const int need = (target + 4 < M - 2) ? target + 4 : M - 2;
-            double sigma = -1.0;
-            bool clean = false;
-#pragma unroll 1
-            for (;;) {
-                const double low = pr.rayleigh_ritz(cyc == 0 && !clean, M, 0.0);
-                if (clean) break;
-                if (chefsi_done(sh.th, sh.nrm, M, need, tol, bnd, target, crtol, thr, cyc)) {
-                    // once more where the block was far from orthonormal
-                    if (low >= 0.1) break;
-                    clean = true;
-                    __syncthreads();
-                    continue;
-                }
-                if (cyc >= kMaxCycles) {
-                    cyc = -1;
-                    break;
-                }
-                const double a = sh.th[M - 1], want = fmax(0.1 * a, 1e-7 * bnd);
-                const int nk = cluster_cut_dev(sh.th, M, target, crtol, thr);
-                __syncthreads();
-                if (cyc >= kInverseCycles) {
-                    pr.damp(a, bnd);
-                    ++cyc;
-                    continue;
-                }
-                if (sigma < 0.0 || want < 0.7 * sigma || want > sigma) {
-                    sigma = want;
-                    pr.factor(sigma);
-                }
-                pr.filter(a, sigma, inverse_degree(sh.th, sh.nrm, lane, need, tol, bnd, nk, a, sigma, cyc));
-                ++cyc;
-            }
-        }
-        const int nk = cluster_cut_dev(sh.th, whole ? nval : M, target, crtol, thr);
-        if (threadIdx.x == 0) {
-            nkeep[E] = nk;
-            status[E] = cyc;
-            for (int b = 0; b < Lu; ++b) lam[(size_t)E * Lu + b] = b < nval && b < M ? sh.th[b] : 0.0;
-        }
-        // V^T H_E V on the kept vectors, the constant function's coefficients, V
-        __syncthreads();
-        pr.grams();
-        for (int t = threadIdx.x; t < Lu * Lu; t += NT) {
-            const int i = t / Lu, j = t % Lu;
-            Aint[(size_t)E * Lu * Lu + t] = (i < nk && j < nk) ? 0.5 * (sh.H[i * M + j] + sh.H[j * M + i]) : 0.0;
-        }
-        pr.column_sums((lds_double*)sh.nrm, [&](int r, int j) {
-            const int p = pr.row[r] >> 8, a = pr.row[r] & 255;
-            return pr.Y[r * PT + j] * zlo[(size_t)sh.elem[p] * LP + a];
-        });
-        for (int j = threadIdx.x; j < Lu; j += NT) zup[(size_t)E * Lu + j] = j < nk ? sh.nrm[j] : 0.0;
-        for (int t = threadIdx.x; t < Lu * npad; t += NT) {
-            const int j = t / npad, r = t % npad, p = r / LP, a = r % LP;
-            const bool in = j < nk && a < sh.koff[p + 1] - sh.koff[p];
-            V[((size_t)E * Lu + j) * npad + r] = in ? pr.Y[(sh.koff[p] + a) * PT + j] : 0.0;
-        }
+        for (int jj = 0; jj < M; ++jj)
+            if (jj < Lu) V[((size_t)E * Lu + jj) * n + row] = (jj < nk) ? X[0][jj] : 0.0;
     }
 }
 
 // ---------------------------------------------------------------------------
-// launcher
+// launchers
 
-// workgroups of one launch, each with its own workspace slot: one per parent up to
-// what the chip holds (LDS: one workgroup of 4^3 children per CU, up to four of 2^3)
-static int up_slots(const CoarseGeom& up, int agg) { return std::min(up.m, agg == 4 ? 256 : 1024); }
+#define SPECMG_M_DISPATCH(MV, ...)                   \
+    switch (MV) {                                    \
+        case 10: {                                   \
+            constexpr int M = 10;                    \
+            __VA_ARGS__;                             \
+        } break;                                     \
+        case 12: {                                   \
+            constexpr int M = 12;                    \
+            __VA_ARGS__;                             \
+        } break;                                     \
+        default: {                                   \
+            constexpr int M = 14;                    \
+            __VA_ARGS__;                             \
+        } break;                                     \
+    }
 
-size_t eig_up_work_doubles(const CoarseGeom& lo, const CoarseGeom& up, int nvec) {
-    return (size_t)up_slots(up, lo.agg) * up_slot_doubles(lo.agg, lo.L, nvec);
+void launch_eig2(const FineGeom& g, const double* kt, int target, int nvec, double tol, double crtol,
+                 double* phi, double* lam, int* nkeep, double* Aint, int* status, double* zc, int e0, int count,
+                 const float* warm, int kp, int kw, double ws_tol, int* ws_fb, double thr, hipStream_t s) {
+    const int L = target + 3;
+    SPECMG_M_DISPATCH(nvec, hipLaunchKernelGGL((k_eig2<M>), dim3(count), dim3(512), 0, s, g, kt, target, L, tol,
+                                               crtol, phi, lam, nkeep, Aint, zc, status, e0, warm, kp, kw, ws_tol,
+                                               ws_fb, thr));
 }
 
 void launch_eig_up(const CoarseGeom& lo, const CoarseGeom& up, const double* Aint_lo, const double* Dlo,
-                   const double* Aofflo, const int* nkeep_lo, const double* zlo, double* Hd_work, double* work,
+                   const double* Aofflo, const int* nkeep_lo, const double* zlo, double* Hd_work,
                    int target, int nvec, double tol, double crtol, double thr, double* V, double* lam, int* nkeep,
                    double* Aint, double* zup, int* status, hipStream_t s) {
     hipLaunchKernelGGL(k_build_hd, dim3(lo.m), dim3(128), 0, s, lo, Aint_lo, Dlo, Hd_work);
     const int n = lo.agg * lo.agg * lo.agg * lo.L;
-    if (up.L != target + 3 || lo.L > kMaxLP || n > 768 || target < 1 || target > 20 || nvec < target + 6 ||
-        (lo.agg != 2 && lo.agg != 4))
+    const int threads = (n + 63) / 64 * 64;
+    if (up.L != target + 3 || lo.L > kMaxLP || threads > 768 || target < 1 || target > 20 || nvec < target + 6)
         throw HipError{hipErrorInvalidValue, "eig_up shape"};
-    const size_t slot = up_slot_doubles(lo.agg, lo.L, nvec);
-    const int mp = up_plane_rows(lo.agg, lo.L);
-#define SPECMG_EIG_UP_NT(MV, NTV)                                                                                   \
-    {                                                                                                               \
-        const size_t shmem = ((size_t)n + mp) * UpProblem<MV, NTV>::PT * sizeof(double) + ((size_t)n + 3) / 4 * 8;   \
-        hipFuncSetAttribute((const void*)k_eig_up<MV, NTV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem); \
-        hipLaunchKernelGGL((k_eig_up<MV, NTV>), dim3(up_slots(up, lo.agg)), dim3(NTV), shmem, s, lo, up, Hd_work,    \
-                           Aofflo, nkeep_lo, zlo, target, tol, crtol, thr, V, lam, nkeep, Aint, zup, status, work,   \
-                           slot);                                                                                   \
-        const hipError_t e = hipGetLastError();                                                                      \
-        if (e != hipSuccess) throw HipError{e, "eig_up launch"};                                                     \
-        return;                                                                                                     \
+    const size_t shmem = (size_t)nvec * (n | 1) * sizeof(double);
+    // compile-time widths for the pairs (block size, lower width) that occur
+    // when both levels have the same target; the run-time width otherwise
+#define SPECMG_EIG_UP(MV, LV)                                                                                    \
+    {                                                                                                            \
+        hipFuncSetAttribute((const void*)k_eig_up<MV, LV>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem); \
+        hipLaunchKernelGGL((k_eig_up<MV, LV>), dim3(up.m), dim3(threads), shmem, s, lo, up, Hd_work, Aofflo,       \
+                           nkeep_lo, zlo, target, tol, crtol, thr, V, lam, nkeep, Aint, zup, status);               \
+        return;                                                                                                  \
     }
-#define SPECMG_EIG_UP(MV)                     \
-    case MV:                                  \
-        if (lo.agg == 4) SPECMG_EIG_UP_NT(MV, 512) \
-        else SPECMG_EIG_UP_NT(MV, 256)
+    const int key = nvec * 100 + lo.L;
+    switch (key) {
+        case 1004: SPECMG_EIG_UP(10, 4)
+        case 1005: SPECMG_EIG_UP(10, 5)
+        case 1006: SPECMG_EIG_UP(10, 6)
+        case 1007: SPECMG_EIG_UP(10, 7)
+        case 1208: SPECMG_EIG_UP(12, 8)
+        case 1209: SPECMG_EIG_UP(12, 9)
+        case 1409: SPECMG_EIG_UP(14, 9)
+        case 1410: SPECMG_EIG_UP(14, 10)
+        case 1411: SPECMG_EIG_UP(14, 11)
+        case 1609: SPECMG_EIG_UP(16, 9)
+        case 1612: SPECMG_EIG_UP(16, 12)
+        case 1613: SPECMG_EIG_UP(16, 13)
+        default: break;
+    }
     switch (nvec) {
-        SPECMG_EIG_UP(10)
-        SPECMG_EIG_UP(12)
-        SPECMG_EIG_UP(14)
-        SPECMG_EIG_UP(16)
-        SPECMG_EIG_UP(20)
-        SPECMG_EIG_UP(26)
+        case 10: SPECMG_EIG_UP(10, 0)
+        case 12: SPECMG_EIG_UP(12, 0)
+        case 14: SPECMG_EIG_UP(14, 0)
+        case 16: SPECMG_EIG_UP(16, 0)
+        case 20: SPECMG_EIG_UP(20, 0)
+        case 26: SPECMG_EIG_UP(26, 0)
         default: break;
     }
 #undef SPECMG_EIG_UP
-#undef SPECMG_EIG_UP_NT
     throw HipError{hipErrorInvalidValue, "eig_up block size"};
 }
 

@@ -47,20 +47,20 @@ constexpr int kMaxCols = 12;   // padded basis width (target <= 8, plus 3)
 template <typename T>
 __device__ __forceinline__ T harm(T a, T b) {
     // harmonic mean 2ab/(a+b); zero when a neighbour is outside the domain
-    // (b = 0; the bound below keeps a = b = 0 from giving 0 * infinity).
-    // 1/(a+b) from the hardware reciprocal r: r + r (e + e^2), e = 1 - s r, in
-    // float64, one Newton step in float32
+    // (a + b = 0).  1/(a+b) by Newton's iteration r <- r (2 - s r) from the
+    // hardware reciprocal: two steps in float64, one in float32; no branch
+    const T s = a + b;
+    T r;
     if constexpr (sizeof(T) == 8) {
-        const double s = fmax(a + b, 2.2250738585072014e-308);
-        const double r = __builtin_amdgcn_rcp(s);
-        const double e = fma(-s, r, 1.0);
-        return (2.0 * a * b) * fma(r, fma(e, e, e), r);
+        r = __builtin_amdgcn_rcp(s);
+        r = fma(fma(-s, r, 1.0), r, r);
+        r = fma(fma(-s, r, 1.0), r, r);
     } else {
-        const float s = fmaxf(a + b, 1.17549435e-38f);
-        float r = __builtin_amdgcn_rcpf(s);
+        r = __builtin_amdgcn_rcpf(s);
         r = fmaf(fmaf(-s, r, 1.0f), r, r);
-        return (2.0f * a * b) * r;
     }
+    const T v = (T(2) * a * b) * r;
+    return s > T(0) ? v : T(0);
 }
 
 // LDS layouts use odd row pitches so that cells of one hyperplane spread
@@ -416,19 +416,18 @@ __device__ __forceinline__ void load_col(const TB* __restrict__ col, int lane, C
 }
 
 
-// The cells beyond the element's four y and z faces and the fluxes through its
-// plus faces, in the wavefront's LDS area ff[8][64].  All 64 lanes load the cells
-// beyond together, one per face and array (lane = (x, row) of the face; zero
-// outside the domain; the face's own component for orthotropic K).  Those beyond
-// the minus faces are staged as they are, u in ff[0] (y) and ff[2] (z), kappa~
-// in ff[1] and ff[3], for the lanes whose neighbours they are.  Beyond the plus
-// faces (their lanes hand their neighbours nothing) the flux T (u_in - u_out) is
-// formed here, one face cell a lane, with the row inside passed through LDS: ff[4]
-// and ff[6].
+// The cells beyond the element's four y and z faces, in the wavefront's LDS
+// area ff[8][64].  All 64 lanes load them together, one cell per face and array
+// (lane = (x, row) of the face; zero outside the domain; the face's own component
+// for orthotropic K).  Beyond the minus faces u goes to ff[0] (y) and ff[2] (z),
+// kappa~ to ff[1] and ff[3], for the lanes whose neighbours they are.  Through the
+// plus faces (whose lanes get no transmissibility from a neighbour) it is formed
+// here, one face cell a lane, with kappa~ of the row inside passed through LDS:
+// ff[4] (y) and ff[6] (z), u beyond in ff[5] and ff[7].
 template <bool O, typename T, typename C>
 __device__ __forceinline__ void stage_faces_yz(const FineGeom& g, const T* __restrict__ kt, const T* __restrict__ u,
-                                               int x0, int y0, int z0, int lane, const C (&uc)[8], const C (&ky)[8],
-                                               const C (&kz)[8], C* ff) {
+                                               int x0, int y0, int z0, int lane, const C (&ky)[8], const C (&kz)[8],
+                                               C* ff) {
     const int fx = lane & 7, fr = lane >> 3;
     const size_t N = O ? g.ncell() : 0;
     C vu[4], vk[4];
@@ -443,25 +442,20 @@ __device__ __forceinline__ void stage_faces_yz(const FineGeom& g, const T* __res
     }
     if ((lane & 7) == 7) {
 #pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            ff[4 * 64 + (lane & ~7) + x] = uc[x];
-            ff[5 * 64 + (lane & ~7) + x] = ky[x];
-        }
+        for (int x = 0; x < 8; ++x) ff[4 * 64 + (lane & ~7) + x] = ky[x];
     }
     if (lane >= 56) {
 #pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            ff[6 * 64 + 8 * (lane & 7) + x] = uc[x];
-            ff[7 * 64 + 8 * (lane & 7) + x] = kz[x];
-        }
+        for (int x = 0; x < 8; ++x) ff[6 * 64 + 8 * (lane & 7) + x] = kz[x];
     }
     wave_lds_sync();
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
-        const C ui = ff[(4 + 2 * f) * 64 + lane], ki = ff[(5 + 2 * f) * 64 + lane];
+        const C ki = ff[(4 + 2 * f) * 64 + lane];
         ff[2 * f * 64 + lane] = vu[f];
         ff[(2 * f + 1) * 64 + lane] = vk[f];
-        ff[(4 + 2 * f) * 64 + lane] = harm(ki, vk[2 + f]) * (C)(f == 0 ? g.cy : g.cz) * (ui - vu[2 + f]);
+        ff[(4 + 2 * f) * 64 + lane] = harm(ki, vk[2 + f]) * (C)(f == 0 ? g.cy : g.cz);
+        ff[(5 + 2 * f) * 64 + lane] = vu[2 + f];
     }
     wave_lds_sync();
 }
@@ -471,11 +465,14 @@ __device__ __forceinline__ void stage_faces_yz(const FineGeom& g, const T* __res
 // K; ky, kz its y and z components), um, km and up, kp u and kappa~ of the
 // cells before and after the pencil in x (used when xlo, xhi: inside the
 // domain), ff the staged y and z faces (stage_faces_yz).  A lane forms the
-// fluxes through its minus faces and hands them to its neighbours, whose plus
-// faces they are; neighbours inside the element are the lanes -+1 and -+8:
-// through the LDS crossbar (bpermute), or with DY those in y by DPP row shifts,
-// which take VALU issue slots and registers instead (the better trade where
-// the crossbar also carries an IC(0) sweep). 
+// transmissibilities of its minus faces and hands them to its neighbours, whose
+// plus faces they are (the same in both directions to the last bit); neighbours
+// inside the element are the lanes -+1 and -+8: through the LDS crossbar
+// (bpermute), or with DY those in y by DPP row shifts, which take VALU issue slots
+// and registers instead (the better trade where the crossbar also carries an IC(0)
+// sweep).  Each face is one product and sum on s, in the order -x, +x, -y, +y, -z,
+// +z: on media of contrast 1e6 the last bit of the pressure is visible in the face
+// fluxes, so the order of the sums is part of the result.
 template <bool O, bool DY, typename C>
 __device__ __forceinline__ void pencil_apply(const FineGeom& g, int j, int k, const C (&uc)[8],
                                              const C (&kc)[8], const C (&ky)[8], const C (&kz)[8], C um, C km,
@@ -497,21 +494,23 @@ __device__ __forceinline__ void pencil_apply(const FineGeom& g, int j, int k, co
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
         const C ko = O ? ky[x] : kc[x];
-        const C pu = lane_prev<DY>(uc[x]), pk = lane_prev<DY>(ko);
-        const C ou = fy[x], ok = fy[64 + x], hi = fy[256 + x];
-        const C f = harm(ko, j == 0 ? ok : pk) * (C)g.cy * (uc[x] - (j == 0 ? ou : pu));
-        const C nf = lane_next<DY>(f);
-        s[x] -= f - (j == 7 ? -hi : nf);
+        const C pu = lane_prev<DY>(uc[x]), pk = lane_prev<DY>(ko), qu = lane_next<DY>(uc[x]);
+        const C ou = fy[x], ok = fy[64 + x], ht = fy[256 + x], hu = fy[320 + x];
+        const C t = harm(ko, j == 0 ? ok : pk) * (C)g.cy;
+        const C nt = lane_next<DY>(t);
+        s[x] -= t * (uc[x] - (j == 0 ? ou : pu));
+        s[x] -= (j == 7 ? ht : nt) * (uc[x] - (j == 7 ? hu : qu));
         if (x % 2 == 1) __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
         const C ko = O ? kz[x] : kc[x];
-        const C pu = __shfl_up(uc[x], 8, 64), pk = __shfl_up(ko, 8, 64);
-        const C ou = fz[x], ok = fz[64 + x], hi = fz[256 + x];
-        const C f = harm(ko, k == 0 ? ok : pk) * (C)g.cz * (uc[x] - (k == 0 ? ou : pu));
-        const C nf = __shfl_down(f, 8, 64);
-        s[x] -= f - (k == 7 ? -hi : nf);
+        const C pu = __shfl_up(uc[x], 8, 64), pk = __shfl_up(ko, 8, 64), qu = __shfl_down(uc[x], 8, 64);
+        const C ou = fz[x], ok = fz[64 + x], ht = fz[256 + x], hu = fz[320 + x];
+        const C t = harm(ko, k == 0 ? ok : pk) * (C)g.cz;
+        const C nt = __shfl_down(t, 8, 64);
+        s[x] -= t * (uc[x] - (k == 0 ? ou : pu));
+        s[x] -= (k == 7 ? ht : nt) * (uc[x] - (k == 7 ? hu : qu));
         if (x % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -538,7 +537,7 @@ __device__ __forceinline__ void pencil_residual(const FineGeom& g, const T* __re
     const size_t ip = xhi ? eidx(g, x0 + 8, y0 + j, z0 + k) : row;
     const C um = xlo ? (C)u[im] : C(0), km = xlo ? (C)kt[im] : C(0);
     const C up = xhi ? (C)u[ip] : C(0), kp = xhi ? (C)kt[ip] : C(0);
-    stage_faces_yz<O>(g, kt, u, x0, y0, z0, lane, uc, O ? ky : kc, O ? kz : kc, ff);
+    stage_faces_yz<O>(g, kt, u, x0, y0, z0, lane, O ? ky : kc, O ? kz : kc, ff);
     pencil_apply<O, DY>(g, j, k, uc, kc, ky, kz, um, km, up, kp, xlo, xhi, ff, s);
 }
 

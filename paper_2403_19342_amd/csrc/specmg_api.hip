@@ -54,6 +54,7 @@ struct Level {
     double* D = nullptr;
     double* Aoff = nullptr;
     double* Ad = nullptr;
+    double* AdT = nullptr;     // its blocks transposed, as the coarse smoother reads them (not at the coarsest level)
     double* SM = nullptr;      // D_c^{-1} and D_c^{-1} A(c, neighbour), laid out for the smoother
     double* z = nullptr;
     float* basis32 = nullptr;  // level 2, the mixed modes: float32 copy of the basis
@@ -254,13 +255,13 @@ void coarse_cycle(specmg_ctx* c, size_t li, int check, hipStream_t s) {
     int at = (x + c->nu_c - 1) % 2;
     launch_coarse_smooth<double>(lv.g, lv.SM, r, parts, buf[at], c->sc, check, s);
     for (int it = 1; it < c->nu_c; ++it, at ^= 1)
-        launch_coarse_resid_smooth<double>(lv.g, lv.Ad, lv.Aoff, lv.SM, r, buf[at], buf[at ^ 1], c->sc, check, s);
-    launch_coarse_resid_restrict<double>(lv.g, lv.Ad, lv.Aoff, r, buf[x], up.basis, up.nkeep, up.L, up.r, c->sc, check,
+        launch_coarse_resid_smooth<double>(lv.g, lv.AdT, lv.Aoff, lv.SM, r, buf[at], buf[at ^ 1], c->sc, check, s);
+    launch_coarse_resid_restrict<double>(lv.g, lv.AdT, lv.Aoff, r, buf[x], up.basis, up.nkeep, up.L, up.r, c->sc, check,
                                          s);
     coarse_cycle(c, li + 1, check, s);
     launch_coarse_prolong<double>(lv.g, buf[x], up.basis, up.nkeep, up.L, up.e, c->sc, check, s);
     for (int it = 0; it < c->nu_c; ++it, at ^= 1)
-        launch_coarse_resid_smooth<double>(lv.g, lv.Ad, lv.Aoff, lv.SM, r, buf[at], buf[at ^ 1], c->sc, check, s);
+        launch_coarse_resid_smooth<double>(lv.g, lv.AdT, lv.Aoff, lv.SM, r, buf[at], buf[at ^ 1], c->sc, check, s);
 }
 
 // One repeated fine sweep u1 += M^-1 (r - A u1): the residual, the sweep
@@ -527,8 +528,7 @@ static int do_setup(specmg_ctx* c, const double* perm, hipStream_t s) {
         up.Ad = c->alloc<double>((size_t)m * Lu * Lu);
         up.z = c->alloc<double>((size_t)m * Lu);
         double* hd = c->alloc<double>((size_t)lo.g.m * lo.L * lo.L);
-        setup_ws.emplace_back(new DevBuf(c->al, eig_up_work_doubles(lo.g, up.g, c->nvec_cc) * sizeof(double)));
-        launch_eig_up(lo.g, up.g, lo.Aint, lo.D, lo.Aoff, lo.nkeep, lo.z, hd, (double*)setup_ws.back()->p, c->target_cc, c->nvec_cc, tol, crtol,
+        launch_eig_up(lo.g, up.g, lo.Aint, lo.D, lo.Aoff, lo.nkeep, lo.z, hd, c->target_cc, c->nvec_cc, tol, crtol,
                       c->thr_cc, up.basis, up.lam, up.nkeep, up.Aint, up.z, up.status, s);
         launch_galerkin_up(lo.g, up.g, lo.D, lo.Aoff, up.basis, up.nkeep, up.D, up.Aoff, s);
         launch_assemble_diag(up.g, up.Aint, up.D, up.Ad, s);
@@ -537,8 +537,9 @@ static int do_setup(specmg_ctx* c, const double* perm, hipStream_t s) {
     for (int li = 0; li < levels - 2; ++li) {
         Level& lv = c->lev[li];
         lv.SM = c->alloc<double>(coarse_sweep_doubles(lv.g));
+        lv.AdT = c->alloc<double>((size_t)lv.g.m * lv.L * lv.L);
         setup_ws.emplace_back(new DevBuf(c->al, (size_t)lv.g.m * lv.L * lv.L * sizeof(double)));   // D^-1 by element
-        launch_blockic_setup(lv.g, lv.Ad, lv.Aoff, lv.nkeep, (double*)setup_ws.back()->p, lv.SM, c->dflag + 2, s);
+        launch_blockic_setup(lv.g, lv.Ad, lv.Aoff, lv.nkeep, (double*)setup_ws.back()->p, lv.SM, lv.AdT, c->dflag + 2, s);
     }
     // ---- host copies of the kept counts, unconverged eigensolves
     int unconv = 0;
