@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libspecmg.so")
-SOURCES = ["k_fine.hip", "k_coarse.hip", "k_eig.hip", "k_dense.hip", "k_cnn.hip", "k_krylov.hip", "k_flux.hip",
+SOURCES = ["k_fine.hip", "k_coarse.hip", "k_eig2.hip", "k_eig.hip", "k_dense.hip", "k_cnn.hip", "k_krylov.hip", "k_flux.hip",
            "k_transport.hip", "specmg_api.hip", "cnn_api.hip"]
 ARCH = os.environ.get("SPECMG_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

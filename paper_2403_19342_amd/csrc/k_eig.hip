@@ -694,125 +694,6 @@ __device__ void column_sums(const double (&A)[R][M], double* dst, int cnt, int n
     __syncthreads();
 }
 
-// ---------------------------------------------------------------------------
-// level 2 kernel: one 512-thread workgroup per 8^3 element
-// Learned start (warm != null): the first kw columns of the start block are
-// the predicted cell vectors warm[blockIdx.x][0..kw-1][512] (row pitch kp),
-// the rest the next cosine modes.  From that block the eigensolve runs to
-// the relaxed residual ws_tol (times the spectral bound) within
-// kWarmCycles cycles; an element that does not get there falls back to the
-// exact solve (tolerance tol) from the cold start, and ws_fb[e] = 1.
-// status[e] counts the cycles of both attempts.
-// At most 128 VGPRs (four waves per SIMD): with about 68 KB of LDS per
-// workgroup, two elements then share a CU, and one element's serial phases
-// (Jacobi, Cholesky) overlap the other's filter.
-template <int M>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_eig2(
-    FineGeom g, const double* __restrict__ kt, int target, int L, double tol, double crtol,
-    double* __restrict__ phi, double* __restrict__ lam, int* __restrict__ nkeep, double* __restrict__ Aint,
-    double* __restrict__ zc, int* __restrict__ status, int e0, const float* __restrict__ warm, int kp, int kw,
-    double ws_tol, int* __restrict__ ws_fb, double thr) {
-    constexpr int LD = 513;
-    __shared__ double sY[M * LD];
-    __shared__ EigShared<M> sh;
-    const int e = e0 + blockIdx.x;
-    const int ex = e % g.mx, ey = (e / g.mx) % g.my, ez = e / (g.mx * g.my);
-    const int c = threadIdx.x;
-    const int i = c & 7, j = (c >> 3) & 7, k = c >> 6;
-    auto gid = [&](int x, int y, int z) { return eidx(g, x, y, z); };
-    // kappa~ per face direction: one array (isotropic) or three (orthotropic)
-    const size_t N = g.ortho ? g.ncell() : 0;
-    const size_t gc = gid(ex * 8 + i, ey * 8 + j, ez * 8 + k);
-    const double kc[3] = {kt[gc], kt[N + gc], kt[2 * N + gc]};
-    // weight tr K~: kappa~ (1 + cy + cz) with the y and z faces carrying cy
-    // and cz, or the sum of the three components
-    const double wsum = 1.0 + g.cy + g.cz;
-    auto weight = [&](size_t q) { return g.ortho ? kt[q] + kt[N + q] + kt[2 * N + q] : wsum * kt[q]; };
-    const double S = weight(gc);
-    const double sq = sqrt(S);
-    Op2 op;
-    double diag = 0.0, rowsum = 0.0;
-#pragma unroll
-    for (int d = 0; d < 6; ++d) {
-        const int ii = i + (d == 0 ? -1 : (d == 1 ? 1 : 0));
-        const int jj = j + (d == 2 ? -1 : (d == 3 ? 1 : 0));
-        const int kk = k + (d == 4 ? -1 : (d == 5 ? 1 : 0));
-        op.off[d] = 0.0;
-        op.nb[d] = c;
-        if (ii >= 0 && ii < 8 && jj >= 0 && jj < 8 && kk >= 0 && kk < 8) {
-            const int ax = d >> 1;
-            const size_t gn = gid(ex * 8 + ii, ey * 8 + jj, ez * 8 + kk);
-            const double T = harm_e(kc[ax], kt[ax * N + gn]) * (ax == 0 ? 1.0 : (ax == 1 ? g.cy : g.cz));
-            diag += T;
-            op.off[d] = T / (sq * sqrt(weight(gn)));
-            op.nb[d] = ii + 8 * (jj + 8 * kk);
-            rowsum += op.off[d];
-        }
-    }
-    op.diag = diag / S;
-    const double bnd = block_max(op.diag + rowsum, sh.misc);
-
-    double X[1][M], AX[1][M];
-    const double pi8 = 3.14159265358979323846 / 8.0;
-    const int nw = warm ? kw : 0;
-#pragma unroll
-    for (int jj = 0; jj < M; ++jj) {
-        const double md = cos(pi8 * kModes[jj][0] * (i + 0.5)) * cos(pi8 * kModes[jj][1] * (j + 0.5)) *
-                          cos(pi8 * kModes[jj][2] * (k + 0.5));
-        const double cold = sq * (md + 0.05 * hash_noise((unsigned)e, (unsigned)jj, (unsigned)c));
-        X[0][jj] = jj < nw ? sq * (double)warm[((size_t)blockIdx.x * kp + jj) * 512 + c] : cold;
-    }
-    const int need = (target + 4 < M - 2) ? target + 4 : M - 2;
-    int cyc = -1, spent = 0;
-    if (warm) {
-        cyc = chefsi<M, 1>(op, sY, LD, 512, X, AX, bnd, need, ws_tol, target, crtol, thr, sh, kWarmCycles, kDeg);
-        const bool fb = cyc < 0;
-        if (fb) {
-            spent = kWarmCycles + 1;
-#pragma unroll
-            for (int jj = 0; jj < M; ++jj) {
-                const double md = cos(pi8 * kModes[jj][0] * (i + 0.5)) * cos(pi8 * kModes[jj][1] * (j + 0.5)) *
-                                  cos(pi8 * kModes[jj][2] * (k + 0.5));
-                X[0][jj] = sq * (md + 0.05 * hash_noise((unsigned)e, (unsigned)jj, (unsigned)c));
-            }
-        }
-        if (c == 0) ws_fb[e] = fb ? 1 : 0;
-        __syncthreads();
-    }
-    if (cyc < 0) {
-        cyc = chefsi<M, 1>(op, sY, LD, 512, X, AX, bnd, need, tol, target, crtol, thr, sh);
-        if (cyc >= 0) cyc += spent;
-    }
-
-    if (threadIdx.x == 0) {
-        const int nk = cluster_cut_dev(sh.th, M, target, crtol, thr);
-        sh.flag = nk;
-        nkeep[e] = nk;
-        status[e] = cyc;
-        for (int a = 0; a < L; ++a) lam[(size_t)e * L + a] = sh.th[a];
-    }
-    __syncthreads();
-    const int nk = sh.flag;
-    __syncthreads();
-    // interior block X^T A~ X on the kept vectors (= Phi^T A_K Phi)
-    store_block<M, 1>(sY, LD, 512, X);
-    __syncthreads();
-    gram_lds_reg<M, 1>(sY, LD, 512, AX, sh.G, sh.red);
-    for (int t = threadIdx.x; t < L * L; t += blockDim.x) {
-        const int a = t / L, b = t % L;
-        Aint[(size_t)e * L * L + t] = (a < nk && b < nk) ? sh.G[a * M + b] : 0.0;
-    }
-    // coefficients of the constant function: Phi^T S 1 = X^T S^1/2 1
-    double zv[1][M];
-#pragma unroll
-    for (int jj = 0; jj < M; ++jj) zv[0][jj] = X[0][jj] * sq;
-    column_sums<M, 1>(zv, zc + (size_t)e * L, L, nk, sh.red);
-#pragma unroll
-    for (int jj = 0; jj < M; ++jj) {
-        if (jj < L) phi[((size_t)e * L + jj) * 512 + phi_pos(c)] = (jj < nk) ? X[0][jj] / sq : 0.0;
-    }
-}
-
 // Hd[c] = Aint[c] + sum of D[c][d] over the faces of c interior to its parent
 __global__ void k_build_hd(CoarseGeom lo, const double* __restrict__ Aint, const double* __restrict__ D,
                            double* __restrict__ Hd) {
@@ -960,31 +841,6 @@ __global__ __launch_bounds__(768) void k_eig_up(CoarseGeom lo, CoarseGeom up, co
 
 // ---------------------------------------------------------------------------
 // launchers
-
-#define SPECMG_M_DISPATCH(MV, ...)                   \
-    switch (MV) {                                    \
-        case 10: {                                   \
-            constexpr int M = 10;                    \
-            __VA_ARGS__;                             \
-        } break;                                     \
-        case 12: {                                   \
-            constexpr int M = 12;                    \
-            __VA_ARGS__;                             \
-        } break;                                     \
-        default: {                                   \
-            constexpr int M = 14;                    \
-            __VA_ARGS__;                             \
-        } break;                                     \
-    }
-
-void launch_eig2(const FineGeom& g, const double* kt, int target, int nvec, double tol, double crtol,
-                 double* phi, double* lam, int* nkeep, double* Aint, int* status, double* zc, int e0, int count,
-                 const float* warm, int kp, int kw, double ws_tol, int* ws_fb, double thr, hipStream_t s) {
-    const int L = target + 3;
-    SPECMG_M_DISPATCH(nvec, hipLaunchKernelGGL((k_eig2<M>), dim3(count), dim3(512), 0, s, g, kt, target, L, tol,
-                                               crtol, phi, lam, nkeep, Aint, zc, status, e0, warm, kp, kw, ws_tol,
-                                               ws_fb, thr));
-}
 
 void launch_eig_up(const CoarseGeom& lo, const CoarseGeom& up, const double* Aint_lo, const double* Dlo,
                    const double* Aofflo, const int* nkeep_lo, const double* zlo, double* Hd_work,
