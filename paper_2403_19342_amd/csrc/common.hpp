@@ -395,8 +395,10 @@ void launch_cnn_backward(const void* packs, int k, int kp, const float* patches,
                          hipStream_t s);
 void launch_cnn_adam(float* theta, const float* grad, float* m1, float* m2, int64_t n, float lr, float b1, float b2,
                      float eps, float c1, float c2, uint16_t* theta16, hipStream_t s);
+// doubles of the workspace of launch_eig_up (free once the stream has passed it)
+size_t eig_up_work_doubles(const CoarseGeom& lo, const CoarseGeom& up, int nvec);
 void launch_eig_up(const CoarseGeom& lo, const CoarseGeom& up, const double* Aint_lo, const double* Dlo,
-                   const double* Aofflo, const int* nkeep_lo, const double* zlo, double* Hd_work,
+                   const double* Aofflo, const int* nkeep_lo, const double* zlo, double* Hd_work, double* work,
                    int target, int nvec, double tol, double crtol, double thr, double* V, double* lam, int* nkeep,
                    double* Aint, double* zup, int* status, hipStream_t s);
 

@@ -528,7 +528,9 @@ static int do_setup(specmg_ctx* c, const double* perm, hipStream_t s) {
         up.Ad = c->alloc<double>((size_t)m * Lu * Lu);
         up.z = c->alloc<double>((size_t)m * Lu);
         double* hd = c->alloc<double>((size_t)lo.g.m * lo.L * lo.L);
-        launch_eig_up(lo.g, up.g, lo.Aint, lo.D, lo.Aoff, lo.nkeep, lo.z, hd, c->target_cc, c->nvec_cc, tol, crtol,
+        setup_ws.emplace_back(new DevBuf(c->al, eig_up_work_doubles(lo.g, up.g, c->nvec_cc) * sizeof(double)));
+        launch_eig_up(lo.g, up.g, lo.Aint, lo.D, lo.Aoff, lo.nkeep, lo.z, hd, (double*)setup_ws.back()->p, c->target_cc,
+                      c->nvec_cc, tol, crtol,
                       c->thr_cc, up.basis, up.lam, up.nkeep, up.Aint, up.z, up.status, s);
         launch_galerkin_up(lo.g, up.g, lo.D, lo.Aoff, up.basis, up.nkeep, up.D, up.Aoff, s);
         launch_assemble_diag(up.g, up.Aint, up.D, up.Ad, s);
