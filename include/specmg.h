@@ -113,7 +113,11 @@ typedef struct {
                                 within 4 Chebyshev cycles falls back to the
                                 exact solve (eig_tol) from the cold start */
     int32_t eigs_coarse;     /* L_cc, 0..20; 0 = eigs_per_subdomain.  With
-                                agg 4 and four or more levels at most 9.
+                                agg 4 and four or more levels at most 9;
+                                with agg 4 and three levels 11..14 needs
+                                eigs_per_subdomain <= 7 and 15..20 at most 2
+                                (the eigensolver's block must fit one CU's
+                                LDS; SPECMG_EINVAL otherwise).
                                 Above 10 the coarse-coarse eigensolves use a
                                 block of 20 or 26 vectors, and a level of
                                 width L_cc + 3 > 13 runs the wide (spilling)

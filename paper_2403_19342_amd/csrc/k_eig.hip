@@ -26,8 +26,6 @@
 
 namespace specmg {
 
-constexpr int kMaxLP = 23;        // lower-level widths up to target 20 + 3
-
 // Hd[c] = Aint[c] + sum of D[c][d] over the faces of c interior to its parent
 __global__ void k_build_hd(CoarseGeom lo, const double* __restrict__ Aint, const double* __restrict__ D,
                            double* __restrict__ Hd) {
@@ -590,19 +588,28 @@ size_t eig_up_work_doubles(const CoarseGeom& lo, const CoarseGeom& up, int nvec)
 }
 
 // bytes of dynamic LDS: the block, the tiles' sums, the terms' rows
-static size_t up_lds(int agg, int lp, int M) {
+constexpr size_t up_lds(int agg, int lp, int M) {
     const size_t n = (size_t)agg * agg * agg * lp, tiles = (n + 63) / 64;
     return (n * (M + 1) + tiles * (M * (M + 1) / 2)) * sizeof(double) + (size_t)up_terms(agg, lp) * 2;
 }
+
+// the widest lower levels that set-up lets through, block by block, fit a CU's 160 KB
+template <int M, int NT, int AGG, int RT>
+constexpr bool up_fits(int lp) {
+    return up_lds(AGG, lp, M) + sizeof(typename UpProblem<M, NT, AGG, RT>::Shared) <= 163840;
+}
+static_assert(up_fits<10, 512, 4, 1>(eig_up_widest(4, 10)) && up_fits<12, 512, 4, 1>(eig_up_widest(4, 12)) &&
+              up_fits<14, 512, 4, 1>(eig_up_widest(4, 14)) && up_fits<16, 512, 4, 1>(eig_up_widest(4, 16)) &&
+              up_fits<20, 512, 4, 1>(eig_up_widest(4, 20)) && up_fits<26, 512, 4, 1>(eig_up_widest(4, 26)) &&
+              up_fits<26, 256, 2, 2>(eig_up_widest(2, 26)), "LDS of the upper levels' eigensolver");
 
 void launch_eig_up(const CoarseGeom& lo, const CoarseGeom& up, const double* Aint_lo, const double* Dlo,
                    const double* Aofflo, const int* nkeep_lo, const double* zlo, double* Hd_work, double* work,
                    int target, int nvec, double tol, double crtol, double thr, double* V, double* lam, int* nkeep,
                    double* Aint, double* zup, int* status, hipStream_t s) {
     hipLaunchKernelGGL(k_build_hd, dim3(lo.m), dim3(128), 0, s, lo, Aint_lo, Dlo, Hd_work);
-    const int n = lo.agg * lo.agg * lo.agg * lo.L;
-    if (up.L != target + 3 || lo.L > (lo.agg == 4 ? 12 : kMaxLP) || n > 768 || target < 1 || target > 20 ||
-        nvec < target + 6 || (lo.agg != 2 && lo.agg != 4))
+    if (up.L != target + 3 || (lo.agg != 2 && lo.agg != 4) || lo.L > eig_up_widest(lo.agg, nvec) || target < 1 ||
+        target > 20 || nvec < target + 6)
         throw HipError{hipErrorInvalidValue, "eig_up shape"};
     const size_t slot = up_slot_doubles(lo.agg, lo.L, nvec), shmem = up_lds(lo.agg, lo.L, nvec);
 #define SPECMG_EIG_UP_AS(MV, NTV, AGGV, RTV)                                                                      \

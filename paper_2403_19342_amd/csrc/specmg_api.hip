@@ -748,6 +748,9 @@ extern "C" int specmg_setup_alloc(const double* perm_dev, int32_t perm_component
     if (opts->eigs_coarse < 0 || tcc > 20) return fail(SPECMG_EINVAL, "eigs_coarse must be in [0, 20]");
     if (G.agg == 4 && opts->levels >= 4 && tcc > 9)
         return fail(SPECMG_EINVAL, "agg 4 with four or more levels needs eigs_coarse <= 9");
+    // (of four and more levels, all have at most 9 + 3 kept slots and a block of 16)
+    if (opts->levels >= 3 && opts->eigs_per_subdomain + 3 > eig_up_widest(G.agg, nvec_for(tcc)))
+        return fail(SPECMG_EINVAL, "agg 4: eigs_coarse 11..14 needs eigs_per_subdomain <= 7, 15..20 at most 2");
     if (!(opts->eig_threshold_coarse >= 0.0) || !std::isfinite(opts->eig_threshold_coarse))
         return fail(SPECMG_EINVAL, "eig_threshold_coarse must be finite and >= 0");
     if (!(opts->eig_threshold >= 0.0) || !std::isfinite(opts->eig_threshold))
