@@ -107,7 +107,8 @@ struct CellStep {
 
 // K cells a thread and pass, kRateThreads apart.  Whether a neighbour is
 // upstream is known only from the velocities, so its f_w is loaded in any case
-// (from the cell itself at the boundary): all 15 values of all K cells are
+// (from the cell itself at the boundary, and in place of the boundary's velocity,
+// whose array need not reach that far): all 15 values of all K cells are
 // then in flight at once, one wait for memory, where loads behind the tests
 // took two and a cell at a time as many again: 20.0 -> 14.8 us for 1.12 million
 // cells (54 MB in, 9 MB out), three cells a thread.  Both passes of a sub-step,
@@ -148,8 +149,8 @@ __global__ __launch_bounds__(kRateThreads) void k_sat_rate(int nx, int ny, int n
                 const int64_t st = d == 0 ? 1 : (d == 1 ? sy : sz);
                 const double* v = d == 0 ? vx : (d == 1 ? vy : vz);
                 const int64_t cu = up[k][d] ? c + st : c, cd = dn[k][d] ? c - st : c;
-                vp[k][d] = v[c];
-                vm[k][d] = v[cd];
+                vp[k][d] = (up[k][d] ? v : fw)[c];   // the boundary's velocities are not read
+                vm[k][d] = (dn[k][d] ? v : fw)[cd];
                 fp[k][d] = fw[cu];
                 fm[k][d] = fw[cd];
             }
