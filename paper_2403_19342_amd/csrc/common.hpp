@@ -192,8 +192,9 @@ __device__ __forceinline__ double atomic_load_relaxed(const double* p) {
 
 // Grid-wide reductions: every block writes its NV block sums to
 // partial[k * kMaxRedBlocks + block] (no floating-point atomics); the
-// finalize kernel launched right after sums them in a fixed order (ranges
-// of partials, then the range sums), so results are reproducible.
+// next launch, the finalize kernel or the restriction behind a pre-smoother, sums
+// them in a fixed order (ranges of partials, then the range sums), so results
+// are reproducible.
 template <int NV>
 __device__ __forceinline__ void write_partials(const double (&v)[NV], RedBuf rb) {
     if (threadIdx.x == 0) {
@@ -255,11 +256,16 @@ struct CoarseGeom {
 // float, double) float32 storage with float64 arithmetic.
 template <typename T, typename C>
 void launch_pre_smooth(const FineGeom& g, const T* kt, const T* invd, double* r, const double* q,
-                       T* u, Scalars* sc, RedBuf rb, int mode, hipStream_t s);
+                       T* u, Scalars* sc, RedBuf rb, int mode, bool rr_rides, hipStream_t s);
 template <typename T, typename TB, typename C>
 void launch_resid_restrict(const FineGeom& g, const T* kt, const T* u, const double* r, const TB* phi,
-                           const int* nkeep, int L, C* r2, Scalars* sc, RedBuf rb, int pre_mode, int check_done,
-                          hipStream_t s);   // pre_mode: the mode of the pre-smoother before it, whose ||r||^2 it may sum
+                           const int* nkeep, int L, C* r2, Scalars* sc, RedBuf rb, bool rr_rides, int check_done,
+                          hipStream_t s);
+// rr_rides: the pre-smoother leaves its ||r||^2 partials to the restriction's launch,
+// which sums them and sets the converged flag.  Allowed on grids that rr_with_restrict
+// says, and only with no launch between the two: one that writes partials would
+// destroy them, one that the flag gates would run once more.
+bool rr_with_restrict(const FineGeom& g);
 template <typename T, typename TB, typename C>
 void launch_prolong(const FineGeom& g, T* u, const TB* phi, const int* nkeep, int L, const C* e2,
                     Scalars* sc, int check_done, hipStream_t s);

@@ -1114,23 +1114,23 @@ static inline int grid_1d(int64_t n) {
     }
 
 // the sum of ||r||^2 rides in the residual's launch if one block can form it
-static bool rr_with_restrict(const FineGeom& g) { return g.ntiles <= kFinSpan; }
+bool rr_with_restrict(const FineGeom& g) { return g.ntiles <= kFinSpan; }
 
 template <typename T, typename C>
 void launch_pre_smooth(const FineGeom& g, const T* kt, const T* invd, double* r, const double* q, T* u,
-                       Scalars* sc, RedBuf rb, int mode, hipStream_t s) {
+                       Scalars* sc, RedBuf rb, int mode, bool rr_rides, hipStream_t s) {
     SPECMG_O_DISPATCH(T, SPECMG_EX_DISPATCH(g.ex, SPECMG_TIMED_LAUNCH((k_pre_smooth<EX, T, C, O>), dim3(g.ntiles),
                                                                       dim3(64 * EX), 0, s, g, kt, invd, r, q, u, sc,
                                                                       rb, mode)));
-    if ((mode & 1) && !rr_with_restrict(g)) launch_finalize(RS_RR, g.ntiles, sc, rb, nullptr, (mode & 2) ? 1 : 0, s);
+    if ((mode & 1) && !rr_rides) launch_finalize(RS_RR, g.ntiles, sc, rb, nullptr, (mode & 2) ? 1 : 0, s);
 }
 
 template <typename T, typename TB, typename C>
 void launch_resid_restrict(const FineGeom& g, const T* kt, const T* u, const double* r, const TB* phi,
-                           const int* nkeep, int L, C* r2, Scalars* sc, RedBuf rb, int pre_mode, int check_done,
+                           const int* nkeep, int L, C* r2, Scalars* sc, RedBuf rb, bool rr_rides, int check_done,
                           hipStream_t s) {
     const int m = g.mx * g.my * g.mz;
-    const int rr_parts = (pre_mode & 1) && rr_with_restrict(g) ? g.ntiles : 0;
+    const int rr_parts = rr_rides ? g.ntiles : 0;
     SPECMG_O_DISPATCH(T, SPECMG_TIMED_LAUNCH((k_resid_restrict<T, TB, C, O>), dim3((m + 3) / 4 + (rr_parts ? 1 : 0)),
                                              dim3(256), 0, s, g, kt, u, r, phi, nkeep, L, r2, sc, rb, rr_parts,
                                              check_done));
@@ -1247,9 +1247,9 @@ void launch_pcg_init(Scalars* sc, double thresh2, int flexible, hipStream_t s) {
 // (float, double) float32 storage with float64 arithmetic
 #define SPECMG_FINE_INST(T, TB, C)                                                                                 \
     template void launch_pre_smooth<T, C>(const FineGeom&, const T*, const T*, double*, const double*, T*,         \
-                                          Scalars*, RedBuf, int, hipStream_t);                                     \
+                                          Scalars*, RedBuf, int, bool, hipStream_t);                               \
     template void launch_resid_restrict<T, TB, C>(const FineGeom&, const T*, const T*, const double*, const TB*,   \
-                                                  const int*, int, C*, Scalars*, RedBuf, int, int, hipStream_t);   \
+                                                  const int*, int, C*, Scalars*, RedBuf, bool, int, hipStream_t);  \
     template void launch_prolong<T, TB, C>(const FineGeom&, T*, const TB*, const int*, int, const C*, Scalars*,    \
                                            int, hipStream_t);                                                      \
     template void launch_post_fused<T, C>(const FineGeom&, const T*, const T*, const T*, const double*,            \
@@ -1259,7 +1259,7 @@ SPECMG_FINE_INST(float, float, float)
 SPECMG_FINE_INST(float, float, double)
 template void launch_resid_restrict<double, float, double>(const FineGeom&, const double*, const double*,
                                                            const double*, const float*, const int*, int, double*,
-                                                           Scalars*, RedBuf, int, int, hipStream_t);
+                                                           Scalars*, RedBuf, bool, int, hipStream_t);
 template void launch_prolong<double, float, double>(const FineGeom&, double*, const float*, const int*, int,
                                                     const double*, Scalars*, int, hipStream_t);
 #undef SPECMG_FINE_INST

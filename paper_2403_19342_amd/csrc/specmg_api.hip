@@ -292,12 +292,13 @@ void vcycle_fine(specmg_ctx* c, double* r, double* z, const double* q, int pre_m
     const TB* phi = pick<TB>(l2.basis, l2.basis32);
     C* r2 = pick<C>(l2.r, l2.r32);
     C* e2 = pick<C>(l2.e, l2.e32);
+    const bool rr_rides = (pre_mode & 1) && c->nu == 1 && rr_with_restrict(c->fg);
     size_t ev = prof_begin(c, s);
-    launch_pre_smooth<T, C>(c->fg, kt, invd, r, q, u1, c->sc, c->rb, pre_mode, s);
+    launch_pre_smooth<T, C>(c->fg, kt, invd, r, q, u1, c->sc, c->rb, pre_mode, rr_rides, s);
     prof_end(c, ev, PC_PRE, s);
     for (int it = 1; it < c->nu; ++it) extra_fine_sweep<T, C>(c, r, z, check, s);
     ev = prof_begin(c, s);
-    launch_resid_restrict<T, TB, C>(c->fg, kt, u1, r, phi, l2.nkeep, l2.L, r2, c->sc, c->rb, pre_mode, check, s);
+    launch_resid_restrict<T, TB, C>(c->fg, kt, u1, r, phi, l2.nkeep, l2.L, r2, c->sc, c->rb, rr_rides, check, s);
     prof_end(c, ev, PC_RESTRICT, s);
     ev = prof_begin_range(c, s);
     if constexpr (std::is_same<C, float>::value) {
