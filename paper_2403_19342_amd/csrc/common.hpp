@@ -321,9 +321,10 @@ void launch_mdot(const double* V, int64_t pitch, int cnt, const double* w, int64
 void launch_maxpy(const double* V, int64_t pitch, int cnt, const double* coef, double sign, double* w, int64_t n,
                   hipStream_t s);
 void launch_scale_dev(double* dst, const double* src, const double* factor, int64_t n, hipStream_t s);
-void launch_gmres_begin(GmresState* st, double thr, hipStream_t s);
-void launch_gmres_orthogonalise(const double* V, int64_t n, int j, double* w, double* part, GmresState* st, double thr,
-                                hipStream_t s);
+// both set sc->done, which gates the V-cycle
+void launch_gmres_begin(GmresState* st, Scalars* sc, double thr, hipStream_t s);
+void launch_gmres_orthogonalise(const double* V, int64_t n, int j, double* w, double* part, GmresState* st, Scalars* sc,
+                                double thr, hipStream_t s);
 void launch_gmres_lsq(GmresState* st, int k, hipStream_t s);
 // copy / convert a vector; with sc non-null nothing is done once the solve
 // has converged (sc->done), as in the V-cycle kernels

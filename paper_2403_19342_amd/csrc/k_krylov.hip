@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kKryThreads) void k_scale_dev(double* __restrict__ 
 }
 
 // (re)start: beta = ||r|| from nrm2, g = beta e_1, inv = 1 / beta
-__global__ void k_gmres_begin(GmresState* st, double thr) {
+__global__ void k_gmres_begin(GmresState* st, Scalars* sc, double thr) {
     const double beta = sqrt(st->nrm2);
     st->tail.beta = beta;
     for (int i = 0; i <= kMaxRestart; ++i) st->g[i] = 0.0;
@@ -138,6 +138,7 @@ __global__ void k_gmres_begin(GmresState* st, double thr) {
     st->inv = beta > 0.0 ? 1.0 / beta : 0.0;
     st->tail.res = beta;
     st->tail.done = beta <= thr ? 1 : 0;
+    sc->done = st->tail.done;
 }
 
 // Arnoldi step j: ||w||^2 from its block sums; column j of H from the two
@@ -145,7 +146,7 @@ __global__ void k_gmres_begin(GmresState* st, double thr) {
 // when |g_{j+1}| <= thr or w vanished (the Krylov space is invariant: the
 // iterate is exact).  One block: all that is read comes in at once, the
 // rotations run on LDS.
-__global__ __launch_bounds__(kKryThreads) void k_gmres_step(GmresState* st, int j, double thr,
+__global__ __launch_bounds__(kKryThreads) void k_gmres_step(GmresState* st, Scalars* sc, int j, double thr,
                                                             const double* __restrict__ part, int nb) {
     constexpr int ld = kMaxRestart + 1;
     __shared__ double red[kKryThreads / 64], col[kMaxRestart + 2], cs[kMaxRestart], sn[kMaxRestart];
@@ -184,7 +185,9 @@ __global__ __launch_bounds__(kKryThreads) void k_gmres_step(GmresState* st, int 
         st->inv = hn > 0.0 ? 1.0 / hn : 0.0;
         st->tail.res = res;
         // 2: singular Hessenberg column, breakdown
-        st->tail.done = !(d > 0.0) ? 2 : ((res <= thr || !(hn > 0.0)) ? 1 : 0);
+        const int done = !(d > 0.0) ? 2 : ((res <= thr || !(hn > 0.0)) ? 1 : 0);
+        st->tail.done = done;
+        sc->done = done;   // the V-cycle queued next returns at once
     }
     __syncthreads();
     if (t <= j + 1) st->H[(size_t)j * ld + t] = col[t];
@@ -243,8 +246,8 @@ void launch_maxpy(const double* V, int64_t pitch, int cnt, const double* coef, d
 }
 
 // w -= V h, h2 = V^T w (new w), w -= V h2, ||w||^2 and Arnoldi step j, h given
-void launch_gmres_orthogonalise(const double* V, int64_t n, int j, double* w, double* part, GmresState* st, double thr,
-                                hipStream_t s) {
+void launch_gmres_orthogonalise(const double* V, int64_t n, int j, double* w, double* part, GmresState* st, Scalars* sc,
+                                double thr, hipStream_t s) {
     const int cnt = j + 1, nb = kry_blocks(n);
     if (cnt <= kDotChunk) {
         hipLaunchKernelGGL(k_project_dot<kDotChunk>, dim3(nb), dim3(kKryThreads), 0, s, V, n, cnt, st->h, w, n, part);
@@ -257,15 +260,15 @@ void launch_gmres_orthogonalise(const double* V, int64_t n, int j, double* w, do
         launch_mdot(V, n, cnt, w, n, part, st->h2, s);
     }
     hipLaunchKernelGGL(k_maxpy<true>, dim3(nb), dim3(kKryThreads), 0, s, V, n, cnt, st->h2, -1.0, w, n, part);
-    hipLaunchKernelGGL(k_gmres_step, dim3(1), dim3(kKryThreads), 0, s, st, j, thr, part, nb);
+    hipLaunchKernelGGL(k_gmres_step, dim3(1), dim3(kKryThreads), 0, s, st, sc, j, thr, part, nb);
 }
 
 void launch_scale_dev(double* dst, const double* src, const double* factor, int64_t n, hipStream_t s) {
     hipLaunchKernelGGL(k_scale_dev, dim3(kry_blocks(n)), dim3(kKryThreads), 0, s, dst, src, factor, n);
 }
 
-void launch_gmres_begin(GmresState* st, double thr, hipStream_t s) {
-    hipLaunchKernelGGL(k_gmres_begin, dim3(1), dim3(1), 0, s, st, thr);
+void launch_gmres_begin(GmresState* st, Scalars* sc, double thr, hipStream_t s) {
+    hipLaunchKernelGGL(k_gmres_begin, dim3(1), dim3(1), 0, s, st, sc, thr);
 }
 
 void launch_gmres_lsq(GmresState* st, int k, hipStream_t s) {

@@ -1054,7 +1054,7 @@ static int do_gmres(specmg_ctx* c, const double* b_nat, double* x_nat, int use_x
         launch_copy(V, b, n, s);
     }
     launch_mdot(V, n, 1, V, n, part, &st->nrm2, s);
-    launch_gmres_begin(st, thr, s);
+    launch_gmres_begin(st, c->sc, thr, s);
     read_state();
     bool converged = hs.done != 0;
     int rc = SPECMG_OK;
@@ -1064,20 +1064,21 @@ static int do_gmres(specmg_ctx* c, const double* b_nat, double* x_nat, int use_x
         int k = 0;
         // z_j = P^{-1} v_j, w = A z_j
         auto directions = [&](int j) {
-            run_vcycle(c, V + (size_t)j * n, Z + (size_t)j * n, nullptr, 0, 0, 0, s);
+            run_vcycle(c, V + (size_t)j * n, Z + (size_t)j * n, nullptr, 2, 2, 1, s);
             launch_apply_A(c->fg, c->kt, Z + (size_t)j * n, nullptr, w, 0, s);
         };
         directions(0);
         while (true) {
             launch_mdot(V, n, k + 1, w, n, part, st->h, s);
-            launch_gmres_orthogonalise(V, n, k, w, part, st, thr, s);
+            launch_gmres_orthogonalise(V, n, k, w, part, st, c->sc, thr, s);
             launch_scale_dev(V + (size_t)(k + 1) * n, w, &st->inv, n, s);
             HIPCHK(hipMemcpyAsync(c->gm_tail, &st->tail, sizeof(GmresTail), hipMemcpyDeviceToHost, s));
             HIPCHK(hipEventRecord(read.e, s));
             ++it;
             ++k;
             // the next direction is on its way while the host reads the flag
-            // (unused, and harmless, after the step that converges)
+            // (after the step that converges its V-cycle does nothing, and its
+            // product is unused)
             const bool more = k < restart && it < max_iter;
             if (more) directions(k);
             HIPCHK(hipEventSynchronize(read.e));
@@ -1092,7 +1093,7 @@ static int do_gmres(specmg_ctx* c, const double* b_nat, double* x_nat, int use_x
         launch_maxpy(Z, n, k, st->y, 1.0, x, n, s);
         launch_apply_A(c->fg, c->kt, x, b, V, 1, s);
         launch_mdot(V, n, 1, V, n, part, &st->nrm2, s);
-        launch_gmres_begin(st, thr, s);
+        launch_gmres_begin(st, c->sc, thr, s);
         read_state();
         converged = hs.done != 0;
         if (!converged && it < max_iter) si.replacements += 1;
