@@ -353,9 +353,9 @@ void launch_coarse_resid_smooth(const CoarseGeom& g, const T* AdT, const T* Aoff
 size_t coarse_sweep_doubles(const CoarseGeom& g);
 template <typename T>
 void launch_coarsest(int n, int np, const double* Pinv, const int* cmap, const T* r, int nparts, int64_t pstride, T* e,
-                     double* rc, const Scalars* sc, int check_done, hipStream_t s);
-// values of the coarsest right-hand side staged in LDS at a time; wider
-// coarsest spaces use the symmetric product below
+                     const Scalars* sc, int check_done, hipStream_t s);
+// unknowns of the widest coarsest space whose right-hand side k_coarsest stages in
+// LDS; wider ones use the symmetric product below
 constexpr int kCoarsestChunk = 8192;
 // coarsest product over the packed lower tiles of the symmetric inverse
 // (spaces wider than one LDS chunk); np a multiple of coarsest_sym_tile()

@@ -539,14 +539,8 @@ __global__ __launch_bounds__(kCoarseThreads) void k_coarse_prolong(CoarseGeom g,
 
 // e = B r at the coarsest level, B the dense inverse of the regularised
 // coarsest matrix, over the compact unknowns (cmap: compact index -> padded
-// index).  r is first gathered into a compact FP64 vector rc, staged through
-// LDS in chunks of kCoarsestChunk values (any size fits the 160 KB of LDS).
-// Spaces within one chunk give each wavefront one row; larger ones give each
-// block kCoarsestRows consecutive rows that the whole block streams one row
-// at a time (64 KB contiguous per row and chunk: concurrent streams of many
-// rows a full row apart share few HBM channels and ran at 2.2 TB/s).
-constexpr int kCoarsestRows = 16;
-
+// index), r in LDS.  Spaces beyond kCoarsestChunk unknowns use the packed
+// triangle (k_coarsest_sym), with r gathered into a compact vector first.
 template <typename T>
 __global__ void k_gather_compact(int n, const int* __restrict__ cmap, const T* __restrict__ r, int nparts, int64_t pstride,
                                  double* __restrict__ rc, const Scalars* sc, int check_done) {
@@ -555,48 +549,7 @@ __global__ void k_gather_compact(int n, const int* __restrict__ cmap, const T* _
         rc[i] = (double)gather_parts(r + cmap[i], nparts, pstride);
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_coarsest_rows(int n, int np, const double* __restrict__ Pinv,
-                                                        const int* __restrict__ cmap,
-                                                        const double* __restrict__ rc, T* __restrict__ e,
-                                                        const Scalars* sc, int check_done) {
-    if (check_done && sc->done) return;
-    extern __shared__ double srz[];
-    __shared__ double red[4][kCoarsestRows];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int i0 = blockIdx.x * kCoarsestRows;
-    double acc[kCoarsestRows];
-#pragma unroll
-    for (int r = 0; r < kCoarsestRows; ++r) acc[r] = 0.0;
-    for (int c0 = 0; c0 < n; c0 += kCoarsestChunk) {
-        const int cn = min(kCoarsestChunk, n - c0);
-        if (c0) __syncthreads();
-        for (int j = t; j < cn; j += 256) srz[j] = rc[c0 + j];
-        __syncthreads();
-#pragma unroll
-        for (int r = 0; r < kCoarsestRows; ++r) {
-            if (i0 + r < n) {
-                const double* row = Pinv + (size_t)(i0 + r) * np + c0;
-                double a0 = 0.0, a1 = 0.0;
-#pragma unroll 8
-                for (int j = t; j < cn; j += 512) {
-                    a0 += row[j] * srz[j];
-                    if (j + 256 < cn) a1 += row[j + 256] * srz[j + 256];
-                }
-                acc[r] += a0 + a1;
-            }
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < kCoarsestRows; ++r) {
-        const double s = wave_sum(acc[r]);
-        if (lane == 0) red[w][r] = s;
-    }
-    __syncthreads();
-    if (t < kCoarsestRows && i0 + t < n) e[cmap[i0 + t]] = (T)((red[0][t] + red[1][t]) + (red[2][t] + red[3][t]));
-}
-
-// Spaces of one LDS chunk: each block gathers the compact right-hand side
+// Each block gathers the compact right-hand side
 // itself from the level vector r through cmap, so no separate gather launch; a
 // wavefront takes RW rows, as many as leave a block a CU, since what a block
 // stages (n values, with their indices) is then a small part of what its rows
@@ -1401,23 +1354,18 @@ void launch_coarsest_sym(int n, int np, const double* packed, const int2* chunks
 
 template <typename T>
 void launch_coarsest(int n, int np, const double* Pinv, const int* cmap, const T* r, int nparts, int64_t pstride, T* e,
-                     double* rc,
                      const Scalars* sc, int check_done, hipStream_t s) {
-    const size_t lds = (size_t)std::min(n, kCoarsestChunk) * sizeof(double);
+    if (n > kCoarsestChunk) throw HipError{hipErrorInvalidValue, "coarsest product size"};
+    const size_t lds = (size_t)n * sizeof(double);
     if (n <= 1024) {
         SPECMG_TIMED_LAUNCH((k_coarsest<T, 1, 4>), dim3((n + 3) / 4), dim3(256), lds, s, n, np, Pinv, cmap, r, nparts,
                             pstride, e, sc, check_done);
     } else if (n <= 2048) {
         SPECMG_TIMED_LAUNCH((k_coarsest<T, 1, 8>), dim3((n + 7) / 8), dim3(512), lds, s, n, np, Pinv, cmap, r, nparts,
                             pstride, e, sc, check_done);
-    } else if (n <= kCoarsestChunk) {
+    } else {
         SPECMG_TIMED_LAUNCH((k_coarsest<T, 2, 8>), dim3((n + 15) / 16), dim3(512), lds, s, n, np, Pinv, cmap, r, nparts,
                             pstride, e, sc, check_done);
-    } else {
-        hipLaunchKernelGGL((k_gather_compact<T>), dim3(std::min((n + 255) / 256, 1024)), dim3(256), 0, s, n, cmap, r,
-                           nparts, pstride, rc, sc, check_done);
-        SPECMG_TIMED_LAUNCH((k_coarsest_rows<T>), dim3((n + kCoarsestRows - 1) / kCoarsestRows), dim3(256), lds, s,
-                            n, np, Pinv, cmap, rc, e, sc, check_done);
     }
 }
 
@@ -1460,25 +1408,15 @@ void launch_convert(const S* src, T* dst, int64_t n, hipStream_t s, const Scalar
 }
 
 template void launch_coarse_smooth<double>(const CoarseGeom&, const double*, double*, int, double*, const Scalars*, int, hipStream_t);
-template void launch_coarse_smooth<float>(const CoarseGeom&, const float*, float*, int, float*, const Scalars*, int, hipStream_t);
 template void launch_coarse_resid_restrict<double>(const CoarseGeom&, const double*, const double*, const double*,
                                                    const double*, const double*, const int*, int, double*,
                                                    const Scalars*, int, hipStream_t);
-template void launch_coarse_resid_restrict<float>(const CoarseGeom&, const float*, const float*, const float*,
-                                                  const float*, const float*, const int*, int, float*,
-                                                  const Scalars*, int, hipStream_t);
 template void launch_coarse_prolong<double>(const CoarseGeom&, double*, const double*, const int*, int,
                                             const double*, const Scalars*, int, hipStream_t);
-template void launch_coarse_prolong<float>(const CoarseGeom&, float*, const float*, const int*, int, const float*,
-                                           const Scalars*, int, hipStream_t);
 template void launch_coarse_resid_smooth<double>(const CoarseGeom&, const double*, const double*, const double*, const double*,
                                                  const double*, double*, const Scalars*, int, hipStream_t);
-template void launch_coarse_resid_smooth<float>(const CoarseGeom&, const float*, const float*, const float*, const float*,
-                                                 const float*, float*, const Scalars*, int, hipStream_t);
-template void launch_coarsest<double>(int, int, const double*, const int*, const double*, int, int64_t, double*, double*,
+template void launch_coarsest<double>(int, int, const double*, const int*, const double*, int, int64_t, double*,
                                       const Scalars*, int, hipStream_t);
-template void launch_coarsest<float>(int, int, const double*, const int*, const float*, int, int64_t, float*, double*,
-                                     const Scalars*, int, hipStream_t);
 template void launch_convert<double, float>(const double*, float*, int64_t, hipStream_t, const Scalars*);
 template void launch_convert<float, double>(const float*, double*, int64_t, hipStream_t, const Scalars*);
 

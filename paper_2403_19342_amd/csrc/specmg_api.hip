@@ -242,7 +242,7 @@ void coarse_cycle(specmg_ctx* c, size_t li, int check, hipStream_t s) {
             launch_coarsest_sym(c->nL, c->npL, c->Psym, c->sym_chunks, c->sym_nchunks, c->sym_maxc, c->cmap, r, parts, pstride, e,
                                 c->rc, c->sym_P, c->sym_Q, c->sc, check, s);
         else
-            launch_coarsest<double>(c->nL, c->npL, c->Pinv, c->cmap, r, parts, pstride, e, c->rc, c->sc, check, s);
+            launch_coarsest<double>(c->nL, c->npL, c->Pinv, c->cmap, r, parts, pstride, e, c->sc, check, s);
         prof_end(c, ev, PC_COARSEST, s);
         return;
     }
