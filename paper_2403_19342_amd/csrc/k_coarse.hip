@@ -893,11 +893,14 @@ __global__ void k_assemble_diag(CoarseGeom g, const double* __restrict__ Aint, c
 // A chain: per plane one memory round trip, three Schur updates, L pivots of
 // one LDS round trip, a root and a division each, L steps back.
 constexpr int kMaxPlane = 12;   // children per hyperplane of a 4^3 parent
+// Widths beyond 13 occur with agg 2 only (three wavefronts, so that all the registers
+// of the widest are there).
+constexpr int plane_waves(int width) { return width > 13 ? 3 : kMaxPlane; }
 template <int LP>
-__global__ __launch_bounds__(64 * kMaxPlane) void k_blockic_setup(CoarseGeom g, const double* __restrict__ Ad,
-                                                                   const double* __restrict__ Aoff,
-                                                                   const int* __restrict__ nkeep, double* Dinv,
-                                                                   int* bad) {
+__global__ __launch_bounds__(64 * plane_waves(LP)) void k_blockic_setup(CoarseGeom g, const double* __restrict__ Ad,
+                                                                        const double* __restrict__ Aoff,
+                                                                        const int* __restrict__ nkeep, double* Dinv,
+                                                                        int* bad) {
     constexpr bool RT = LP == kMaxLc;   // the widest serves every width above kNarrow
     constexpr int U = (LP * LP + 63) / 64;
     __shared__ int pos[kMaxChildren], off[12];
@@ -1388,7 +1391,8 @@ void launch_blockic_setup(const CoarseGeom& g, const double* Ad, const double* A
     // widest hyperplane of the parent's children: 3 (agg 2) or 12 (agg 4)
     const int wmax = g.agg == 2 ? 3 : kMaxPlane;
     const size_t shmem = (size_t)wmax * 3 * g.L * g.L * sizeof(double);
-    if (g.L > kMaxL || shmem > 64 * 1024) throw HipError{hipErrorInvalidValue, "block-IC set-up shape"};
+    if (g.L > kMaxL || wmax > plane_waves(g.L) || shmem > 64 * 1024)
+        throw HipError{hipErrorInvalidValue, "block-IC set-up shape"};
     const dim3 nb(g.M), th(64 * wmax);
     SPECMG_LP_DISPATCH(g.L, hipLaunchKernelGGL(k_blockic_setup<LP>, nb, th, shmem, s, g, Ad, Aoff, nkeep, Dinv, bad));
     hipLaunchKernelGGL(k_blockic_couple, dim3(g.m), dim3(256), 0, s, g, Ad, Aoff, Dinv, SM, AdT);
