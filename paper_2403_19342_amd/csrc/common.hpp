@@ -404,9 +404,11 @@ void launch_cnn_adam(float* theta, const float* grad, float* m1, float* m2, int6
                      float eps, float c1, float c2, uint16_t* theta16, hipStream_t s);
 // The widest lower level that launch_eig_up takes for a block of nvec vectors (the
 // target 20 + 3 at most).  With 64 children the block must share a CU's 160 KB of LDS
-// with the small matrices, and a child has three result registers (12 rows).
+// with the small matrices, and a child has three result registers (12 rows); with 8, a
+// child has one tile of rows or, for the wide blocks that wide levels come with, two.
 constexpr int eig_up_widest(int agg, int nvec) {
-    return agg == 2 ? 23 : (nvec <= 16 ? 12 : (nvec <= 20 ? 10 : 5));
+    if (agg == 2) return nvec <= 16 ? 16 : 23;
+    return nvec <= 16 ? 12 : (nvec <= 20 ? 10 : 5);
 }
 // doubles of the workspace of launch_eig_up (free once the stream has passed it)
 size_t eig_up_work_doubles(const CoarseGeom& lo, const CoarseGeom& up, int nvec);

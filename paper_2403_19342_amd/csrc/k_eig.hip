@@ -629,7 +629,7 @@ void launch_eig_up(const CoarseGeom& lo, const CoarseGeom& up, const double* Ain
     case MV:                                                                         \
         if (lo.agg == 4) SPECMG_EIG_UP_AS(MV, 512, 4, 1)                             \
         else if (lo.L <= 16) SPECMG_EIG_UP_AS(MV, (MV <= 16 ? 128 : 256), 2, 1)      \
-        else SPECMG_EIG_UP_AS(MV, 256, 2, 2)
+        else SPECMG_EIG_UP_AS((MV <= 16 ? 20 : MV), 256, 2, 2)   /* (blocks up to 16: refused above) */
     switch (nvec) {
         SPECMG_EIG_UP(10)
         SPECMG_EIG_UP(12)
