@@ -472,7 +472,10 @@ __device__ __forceinline__ void stage_faces_yz(const FineGeom& g, const T* __res
 // and registers instead (the better trade where the crossbar also carries an IC(0)
 // sweep).  Each face is one product and sum on s, in the order -x, +x, -y, +y, -z,
 // +z: on media of contrast 1e6 the last bit of the pressure is visible in the face
-// fluxes, so the order of the sums is part of the result.
+// fluxes, so the order of the sums is part of the result.  The barriers bound the
+// values in flight; one z cell at a time keeps the isotropic post-smoother (DY) at 167
+// registers, three wavefronts a SIMD, where four at a time took 171: 34.6 -> 32.9 us
+// at 128^3, 195 -> 170 at 256^3, 1.58 -> 1.40 ms at 512^3.
 template <bool O, bool DY, typename C>
 __device__ __forceinline__ void pencil_apply(const FineGeom& g, int j, int k, const C (&uc)[8],
                                              const C (&kc)[8], const C (&ky)[8], const C (&kz)[8], C um, C km,
@@ -511,7 +514,7 @@ __device__ __forceinline__ void pencil_apply(const FineGeom& g, int j, int k, co
         const C nt = __shfl_down(t, 8, 64);
         s[x] -= t * (uc[x] - (k == 0 ? ou : pu));
         s[x] -= (k == 7 ? ht : nt) * (uc[x] - (k == 7 ? hu : qu));
-        if (x % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        if ((DY && !O) || x % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
 }
 
