@@ -309,8 +309,8 @@ constexpr int sweep_parents(int agg, int W) {
 // rows the rows' arrival (0.3 MB a CU at 20 to 30 bytes a clock) takes 14k
 // clocks of 32k, the 20 plane steps 11.5k (LDS reads), in mode 1 the residual
 // 15k more.  With rows read from row-major blocks, one axis at a time, mode 0
-// took 16.2 us and mode 1 19.1; now 12.9 and 17.7 (64 parents of 64 x 9) and
-// 9.8 / 13.4 -> 9.1 / 13.2 (27 of 64 x 7).
+// took 16.2 us and mode 1 19.1; now 13.0 and 17.6 (64 parents of 64 x 9); the two
+// together 23.2 us before and after with 27 of 64 x 7, 111 and 112 with 512 of 64 x 11.
 template <typename T, int LP, bool A2, int MODE>
 __global__ __launch_bounds__(A2 ? 512 : 64 * LP) void k_coarse_sweep(
     CoarseGeom g, const T* __restrict__ AdT, const T* __restrict__ Aoff, const T* __restrict__ SM,
@@ -472,7 +472,9 @@ __global__ __launch_bounds__(A2 ? 512 : 64 * LP) void k_coarse_sweep(
 // parents): a workgroup is one of the W wavefronts of 64 rows that a parent has,
 // and writes its part of the sum (part p at r_up + p M Lup; the kernel that reads
 // r_up next adds the parts in order): a parent is a small task for 64 W rows of
-// latency, and levels of 27 to 64 parents left most of the chip idle.
+// latency, and levels of 27 to 64 parents left most of the chip idle (19.4 -> 8.4 us
+// for 64 parents of 64 x 9 rows, 12.5 -> 5.7 for 27 of 64 x 7).  The columns of V
+// come in together with the rows: 53 -> 39 us for 512 parents of 64 x 11.
 template <typename T, int LP, int LU, bool A2, bool SPLIT>
 __global__ __launch_bounds__(SPLIT ? 64 : ((A2 ? 8 : 64) * LP + 63) / 64 * 64) void k_coarse_resid_restrict(
     CoarseGeom g, const T* __restrict__ AdT, const T* __restrict__ Aoff, const T* __restrict__ r,
@@ -549,12 +551,12 @@ __global__ void k_gather_compact(int n, const int* __restrict__ cmap, const T* _
         rc[i] = (double)gather_parts(r + cmap[i], nparts, pstride);
 }
 
-// Each block gathers the compact right-hand side
-// itself from the level vector r through cmap, so no separate gather launch; a
-// wavefront takes RW rows, as many as leave a block a CU, since what a block
-// stages (n values, with their indices) is then a small part of what its rows
-// read.  One row a wavefront, the only form before, took 46 us at n = 4096
-// (2.7 TB/s) and 104 at 5120; eight wavefronts of two rows take 34 and 46.
+// Each block gathers the compact right-hand side itself from the level vector r
+// through cmap, so no separate gather launch; a wavefront takes RW rows, as many
+// as leave a block a CU, since what a block stages (n values, with their indices)
+// is then a small part of what its rows read.  One row a wavefront, the only form
+// before, took 46 us at n = 4096 (2.7 TB/s) and 104 at 5120; eight wavefronts of two
+// rows take 31 and 49.
 template <typename T, int RW, int NW>
 __global__ __launch_bounds__(64 * NW) void k_coarsest(int n, int np, const double* __restrict__ Pinv,
                                                    const int* __restrict__ cmap, const T* __restrict__ r, int nparts,
@@ -717,8 +719,9 @@ __global__ __launch_bounds__(kSymT * kSymRedGroups) void k_coarsest_sym_reduce(
 // (the terms of eq. discrete varia for faces between elements)
 // Bound by the basis: the face cells of a column lie in every one of its lines,
 // so the whole of it is fetched, and half of it again for the neighbours.  One sum of 64
-// products a thread, from LDS, took 1.90 ms at 256^3 with 11 columns; nine 16 x 16 products of depth 64 on the matrix cores,
-// all rows loaded at once, take 0.52 (0.20 -> 0.067 ms at 128^3).
+// products a thread, from LDS, took 1.90 ms at 256^3 with 11 columns; nine 16 x 16
+// products of depth 64 on the matrix cores (which add in the same order), all rows
+// loaded at once, take 0.52 (0.20 -> 0.065 ms at 128^3).
 __global__ __launch_bounds__(256) void k_galerkin2(FineGeom g, const double* __restrict__ kt,
                                                    const double* __restrict__ phi, const int* __restrict__ nkeep,
                                                    int L, double* __restrict__ D, double* __restrict__ Aoff) {
@@ -891,7 +894,9 @@ __global__ void k_assemble_diag(CoarseGeom g, const double* __restrict__ Aint, c
 // of the result, see block_row_apply.  Padded slots (index >= nkeep) are rows of
 // the identity.
 // A chain: per plane one memory round trip, three Schur updates, L pivots of
-// one LDS round trip, a root and a division each, L steps back.
+// one LDS round trip, a root and a division each, L steps back.  433 -> 114 us for 64
+// parents of 64 x 9 rows, 2.2 ms -> 262 us for 512 of 64 x 11, 6.0 ms -> 258 us for
+// 4,096 of 8 x 9 and then 512 of 8 x 13, against a form with the blocks in LDS.
 constexpr int kMaxPlane = 12;   // children per hyperplane of a 4^3 parent
 // Widths beyond 13 occur with agg 2 only (three wavefronts, so that all the registers
 // of the widest are there).

@@ -349,7 +349,7 @@ __device__ __forceinline__ void load_faces(const FineGeom& g, const T* __restric
 // T: stored word of kappa~, 1/d and u; C: arithmetic (T, or float64 with
 // float32 storage); O: three kappa~ arrays (orthotropic K)
 // Held to 128 registers (130 otherwise): the 4096 wavefronts of 128^3 are then
-// all resident, 25.5 -> 23.6 us; 256^3 145 us either way.
+// all resident, 26.0 -> 23.9 us; 256^3 139 -> 137 us.
 template <int EX, typename T, typename C, bool O>
 __global__ __launch_bounds__(64 * EX) __attribute__((amdgpu_waves_per_eu(O ? 1 : 4))) void k_pre_smooth(FineGeom g, const T* __restrict__ kt,
                                                         const T* __restrict__ invd, double* r,
@@ -552,8 +552,8 @@ __device__ __forceinline__ void pencil_residual(const FineGeom& g, const T* __re
 // of memory latencies between two full-grid kernels, so everything that is read
 // is read at once, the flag and the scalars too (waited for together before
 // the flag is looked at), and a single block (up to 2048 partials, 128^3 and
-// below) goes straight on to the scalars: 4.3 -> 2.4 us at 32^3, 5.2 -> 3.6 at
-// 96^3, 5.4 -> 4.4 at 128^3.
+// below) goes straight on to the scalars: 4.3 -> 2.8 us at 32^3, 4.8 -> 3.7 at
+// 96^3, 5.3 -> 4.7 at 128^3.
 // ONE: called by the last block of another kernel, for at most kFinSpan partials.
 template <bool ONE>
 __device__ __forceinline__ void finalize_blocks(int site, int nb, Scalars* sc, RedBuf rb, double* out, int check_done) {
@@ -649,7 +649,7 @@ __device__ __forceinline__ void finalize_blocks(int site, int nb, Scalars* sc, R
 // T: stored word of kappa~ and u; TB: stored word of the basis; C: the
 // arithmetic and the word of the level-2 residual r2.  rr_parts: one block more
 // than the elements need sums the pre-smoother's ||r||^2, whose outcome (the
-// converged flag) stops the kernels after this one: a launch of its own, 4.4 us
+// converged flag) stops the kernels after this one: a launch of its own, 4.7 us
 // at 128^3, waited for nothing that this kernel does.
 template <typename T, typename TB, typename C, bool O>
 __global__ __launch_bounds__(256) void k_resid_restrict(FineGeom g, const T* __restrict__ kt,
