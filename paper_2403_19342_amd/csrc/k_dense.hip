@@ -17,67 +17,88 @@ namespace specmg {
 constexpr int NB = 32;
 constexpr int KB = 256;   // panel width of the Cholesky factorisation, leaf of the triangular inverse
 
-__global__ __launch_bounds__(256) void k_potrf_diag(double* A, int np, int k0, int* bad) {
-    __shared__ double T[NB][NB + 1];
-    for (int t = threadIdx.x; t < NB * NB; t += blockDim.x) {
-        const int i = t / NB, j = t % NB;
-        T[i][j] = A[(size_t)(k0 + i) * np + k0 + j];
-    }
-    __syncthreads();
-    for (int j = 0; j < NB; ++j) {
-        if (threadIdx.x == 0) {
-            double d = T[j][j];
-            if (!(d > 0.0)) {
-                atomicOr(bad, 4);
-                d = 1.0;
-            }
-            T[j][j] = sqrt(d);
+// the value of one lane (the same for all), by scalar registers
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)b, lane);
+    const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Cholesky factor of one 32 x 32 tile by a wavefront: row i of the lower part in
+// lane i's registers, the current column first, so that the loop needs no run-time
+// register index; l: two columns in LDS.  A column is one root, one division a row and
+// the products that the textbook's right-looking loops subtract, in their order
+// (the order of every sum here is part of the result: the last bit of the pressure
+// shows in the fluxes of media of contrast 1e6).  A chain of 32 roots, divisions and
+// LDS round trips: 12.5 us (23 with 256 threads on a tile in LDS), of which 9 remain
+// where k_syrk_panel goes on to the next tile by itself.
+template <int W>
+__device__ __forceinline__ void factor_columns(double (&x)[NB], double* A, int np, int k0, int j0, int lane,
+                                               double (*l)[2 * NB], int* bad) {
+#pragma unroll 1
+    for (int j = j0; j < j0 + W / 2; ++j) {
+        double d = lane_value(x[0], j);
+        if (!(d > 0.0)) {
+            if (lane == 0) atomicOr(bad, 4);
+            d = 1.0;
         }
-        __syncthreads();
-        const double ljj = T[j][j];
-        for (int i = j + 1 + threadIdx.x; i < NB; i += blockDim.x) T[i][j] /= ljj;
-        __syncthreads();
-        for (int t = threadIdx.x; t < NB * NB; t += blockDim.x) {
-            const int i = t / NB, c = t % NB;
-            if (c > j && i >= c) T[i][c] -= T[i][j] * T[c][j];
-        }
-        __syncthreads();
+        const double root = sqrt(d), v = x[0] / root;
+        double* col = l[j & 1];
+        col[lane] = v;
+        if (lane < NB) A[(size_t)(k0 + lane) * np + k0 + j] = lane > j ? v : (lane == j ? root : 0.0);
+        wave_sync();
+#pragma unroll
+        for (int q = 0; q + 1 < W; ++q) x[q] = fma(-v, col[j + 1 + q], x[q + 1]);
     }
-    for (int t = threadIdx.x; t < NB * NB; t += blockDim.x) {
-        const int i = t / NB, j = t % NB;
-        A[(size_t)(k0 + i) * np + k0 + j] = (j <= i) ? T[i][j] : 0.0;
-    }
+}
+__device__ __forceinline__ void factor_tile(double (&x)[NB], double* A, int np, int k0, int lane, double (*l)[2 * NB],
+                                            int* bad) {
+    factor_columns<NB>(x, A, np, k0, 0, lane, l, bad);
+    factor_columns<NB / 2>(x, A, np, k0, NB / 2, lane, l, bad);
+    factor_columns<NB / 4>(x, A, np, k0, NB / 4 * 3, lane, l, bad);
+    factor_columns<NB / 8>(x, A, np, k0, NB / 8 * 7, lane, l, bad);
+    factor_columns<NB / 16>(x, A, np, k0, NB / 16 * 15, lane, l, bad);
+    factor_columns<NB / 16>(x, A, np, k0, NB - 1, lane, l, bad);
+}
+
+__global__ __launch_bounds__(64) void k_potrf_diag(double* A, int np, int k0, int* bad) {
+    __shared__ double l[2][2 * NB];
+    const int lane = threadIdx.x;
+    double x[NB];
+    const double* row = A + (size_t)(k0 + (lane & (NB - 1))) * np + k0;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) x[j] = row[j];
+    factor_tile(x, A, np, k0, lane, l, bad);
 }
 
 // rows i >= k0+NB: A[i, k0:k0+NB] <- A[i, k0:k0+NB] L_kk^{-T}
 __global__ __launch_bounds__(64) void k_trsm_panel(double* A, int np, int k0) {
     __shared__ double Lk[NB][NB + 1];
-    for (int t = threadIdx.x; t < NB * NB; t += blockDim.x) {
-        const int i = t / NB, j = t % NB;
-        Lk[i][j] = A[(size_t)(k0 + i) * np + k0 + j];
-    }
-    __syncthreads();
     const int i = k0 + NB + blockIdx.x * 64 + threadIdx.x;
-    if (i >= np) return;
+    double* row = A + (size_t)(i < np ? i : k0) * np + k0;
     double x[NB];
-    double* row = A + (size_t)i * np + k0;
 #pragma unroll
     for (int j = 0; j < NB; ++j) x[j] = row[j];
+    for (int t = threadIdx.x; t < NB * NB; t += 64) Lk[t % NB][t / NB] = A[(size_t)(k0 + t / NB) * np + k0 + t % NB];
+    __syncthreads();
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-        double v = x[j];
+        x[j] /= Lk[j][j];
 #pragma unroll
-        for (int k = 0; k < j; ++k) v -= x[k] * Lk[j][k];
-        x[j] = v / Lk[j][j];
+        for (int k = j + 1; k < NB; ++k) x[k] = fma(-x[j], Lk[j][k], x[k]);
     }
+    if (i >= np) return;
 #pragma unroll
     for (int j = 0; j < NB; ++j) row[j] = x[j];
 }
 
 // inside a panel: A[i][j] -= sum_{k < 32} A[i][kk+k] A[j][kk+k] for the lower
-// 32 x 32 tiles (ti >= tj) of rows >= kk+32 whose column tile tj < ntc
-__global__ __launch_bounds__(256) void k_syrk_panel(double* A, int np, int kk, int T) {
+// 32 x 32 tiles (ti >= tj) of rows >= kk+32 whose column tile tj < ntc; the
+// workgroup of the first of them, the next diagonal tile, factors it
+__global__ __launch_bounds__(256) void k_syrk_panel(double* A, int np, int kk, int T, int* bad) {
     __shared__ double Pi[NB][NB + 1], Pj[NB][NB + 1];
+    __shared__ double l[2][2 * NB];
     int b = blockIdx.x, tj = 0;
     while (b >= T - tj) {
         b -= T - tj;
@@ -86,20 +107,35 @@ __global__ __launch_bounds__(256) void k_syrk_panel(double* A, int np, int kk, i
     const int ti = tj + b;
     const int base = kk + NB;
     const int r0 = base + ti * NB, c0 = base + tj * NB;
-    for (int t = threadIdx.x; t < NB * NB; t += blockDim.x) {
-        const int i = t / NB, k = t % NB;
+    double a[NB * NB / 256];
+#pragma unroll
+    for (int u = 0; u < NB * NB / 256; ++u) {
+        const int t = threadIdx.x + 256 * u, i = t / NB, k = t % NB;
         Pi[i][k] = A[(size_t)(r0 + i) * np + kk + k];
         Pj[i][k] = A[(size_t)(c0 + i) * np + kk + k];
+        a[u] = A[(size_t)(r0 + i) * np + c0 + k];
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < NB * NB; t += blockDim.x) {
-        const int i = t / NB, j = t % NB;
-        if (ti == tj && j > i) continue;
+#pragma unroll
+    for (int u = 0; u < NB * NB / 256; ++u) {
+        const int t = threadIdx.x + 256 * u, i = t / NB, j = t % NB;
         double s = 0.0;
 #pragma unroll 8
         for (int k = 0; k < NB; ++k) s += Pi[i][k] * Pj[j][k];
-        A[(size_t)(r0 + i) * np + c0 + j] -= s;
+        a[u] -= s;
+        if (blockIdx.x && (ti != tj || j <= i)) A[(size_t)(r0 + i) * np + c0 + j] = a[u];
     }
+    if (blockIdx.x) return;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NB * NB / 256; ++u) Pi[(threadIdx.x + 256 * u) / NB][threadIdx.x % NB] = a[u];
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const int lane = threadIdx.x;
+    double x[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) x[j] = Pi[lane & (NB - 1)][j];
+    factor_tile(x, A, np, base, lane, l, bad);
 }
 
 enum { OPN = 0, OPT = 1 };
@@ -114,42 +150,74 @@ __device__ __forceinline__ void lower_tile(int b, int& ti, int& tj) {
     tj = b - i * (i + 1) / 2;
 }
 
-// W_JJ = L_JJ^{-1} for every KB x KB diagonal block (blockIdx.y; the last
-// one may be narrower): one workgroup per 32-column strip of the block, rows
-// marched downwards
-__global__ __launch_bounds__(256) void k_trtri_diag(const double* __restrict__ Lm, double* W, int np) {
-    __shared__ double Lii[NB][NB + 1];
-    __shared__ double R[NB][NB + 1];
-    const int o = blockIdx.y * KB;
-    const int nbk = min(KB, np - o) / NB;
-    const int J = blockIdx.x;
-    if (J >= nbk) return;   // whole workgroup
-    const int j0 = o + J * NB;
-    for (int I = J; I < nbk; ++I) {
-        const int i0 = o + I * NB;
-        for (int t = threadIdx.x; t < NB * NB; t += blockDim.x) {
-            const int i = t / NB, j = t % NB;
-            Lii[i][j] = Lm[(size_t)(i0 + i) * np + i0 + j];
-            double s = (I == J && i == j) ? 1.0 : 0.0;
-            for (int k = j0; k < i0; ++k) s -= Lm[(size_t)(i0 + i) * np + k] * W[(size_t)k * np + j0 + j];
-            R[i][j] = s;
+// W_JJ = L_JJ^{-1} for every KB x KB diagonal block (blockIdx.y; the last one may be
+// narrower), 16 columns a workgroup, two a wavefront, the rows in the lanes' registers
+// (row lane + 64 m): a column is a chain of KB divisions, each with the products of its
+// row on all rows below, which come in the order k of the forward substitution.  The
+// factor passes through LDS, 16 columns at a time, the next ones on their way.  A
+// column a thread, the rows in turn, took 551 us for 256 rows and more; now 77.
+constexpr int kTriCols = 16;
+__global__ __launch_bounds__(512) void k_trtri_diag(const double* __restrict__ Lm, double* W, int np) {
+    constexpr int M = KB / 64, U = KB * kTriCols / 512;
+    __shared__ double tile[KB][kTriCols + 1];
+    const int o = blockIdx.y * KB, n = min(KB, np - o);
+    const int j0 = blockIdx.x * kTriCols;
+    if (j0 >= n) return;   // whole workgroup
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int sc = threadIdx.x % kTriCols, sr = threadIdx.x / kTriCols;   // staged: column sc, rows sr + 32 u
+    double v[2][M];
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) v[c][m] = lane + 64 * m == j0 + 2 * w + c ? 1.0 : 0.0;
+    double next[U];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = sr + 32 * u;
+            next[u] = r >= k0 && r < n ? Lm[(size_t)(o + r) * np + o + k0 + sc] : 0.0;
         }
-        __syncthreads();
-        if (threadIdx.x < NB) {
-            const int j = threadIdx.x;
-            for (int i = 0; i < NB; ++i) {
-                double v = R[i][j];
-                for (int k = 0; k < i; ++k) v -= Lii[i][k] * R[k][j];
-                R[i][j] = v / Lii[i][i];
+    };
+    fetch(j0);
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+#pragma unroll 1
+        for (int k0 = max(j0, 64 * m); k0 < min(n, 64 * (m + 1)); k0 += kTriCols) {
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < U; ++u) tile[sr + 32 * u][sc] = next[u];
+            __syncthreads();
+            if (k0 + kTriCols < n) fetch(k0 + kTriCols);
+#pragma unroll 1
+            for (int kk = 0; kk < kTriCols; ++kk) {
+                const int k = k0 + kk;
+                const double d = tile[k][kk];
+                double q[2];
+#pragma unroll
+                for (int c = 0; c < 2; ++c) q[c] = lane_value(v[c][m], k & 63) / d;
+#pragma unroll
+                for (int mm = m; mm < M; ++mm) {
+                    const int r = lane + 64 * mm;
+                    const double l = tile[r][kk];
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const double t = fma(-l, q[c], v[c][mm]);
+                        v[c][mm] = r > k ? t : (r == k ? q[c] : v[c][mm]);
+                    }
+                }
             }
         }
-        __syncthreads();
-        for (int t = threadIdx.x; t < NB * NB; t += blockDim.x) {
-            const int i = t / NB, j = t % NB;
-            W[(size_t)(i0 + i) * np + j0 + j] = R[i][j];
-        }
-        __threadfence_block();
-        __syncthreads();
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) tile[lane + 64 * m][2 * w + c] = v[c][m];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int r = sr + 32 * u;
+        if (r >= j0 && r < n) W[(size_t)(o + r) * np + o + j0 + sc] = tile[r][sc];
     }
 }
 
@@ -373,13 +441,14 @@ int dense_spd_inverse(double* a, int np, double* work, double* tbuf, int* bad, h
     for (int k0 = 0; k0 < np; k0 += KB) {
         const int kw = std::min(KB, np - k0);
         for (int kk = k0; kk < k0 + kw; kk += NB) {
-            hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, s, a, np, kk, bad);
+            // (the panel's later diagonal tiles: by k_syrk_panel)
+            if (kk == k0) hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(64), 0, s, a, np, kk, bad);
             const int rest = np - kk - NB;
             if (rest > 0) {
                 hipLaunchKernelGGL(k_trsm_panel, dim3((rest + 63) / 64), dim3(64), 0, s, a, np, kk);
                 const int T = rest / NB, ntc = (k0 + kw - kk - NB) / NB;
                 const int blocks = ntc * T - ntc * (ntc - 1) / 2;
-                if (blocks > 0) hipLaunchKernelGGL(k_syrk_panel, dim3(blocks), dim3(256), 0, s, a, np, kk, T);
+                if (blocks > 0) hipLaunchKernelGGL(k_syrk_panel, dim3(blocks), dim3(256), 0, s, a, np, kk, T, bad);
             }
         }
         const int j0 = k0 + kw;
@@ -403,7 +472,7 @@ int dense_spd_inverse(double* a, int np, double* work, double* tbuf, int* bad, h
     hipError_t e = hipMemsetAsync(work, 0, (size_t)np * np * sizeof(double), s);
     if (e != hipSuccess) return (int)e;
     const int nb = (np + KB - 1) / KB;
-    hipLaunchKernelGGL(k_trtri_diag, dim3(KB / NB, nb), dim3(256), 0, s, a, work, np);
+    hipLaunchKernelGGL(k_trtri_diag, dim3(KB / kTriCols, nb), dim3(512), 0, s, a, work, np);
     trtri_node(a, work, tbuf, np, 0, nb, s);
     // ---- A^{-1} = W^T W (lower tiles, mirrored; W[k][i] = 0 for k < i)
     {
