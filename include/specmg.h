@@ -120,8 +120,8 @@ typedef struct {
                                 LDS; SPECMG_EINVAL otherwise).
                                 Above 10 the coarse-coarse eigensolves use a
                                 block of 20 or 26 vectors, and a level of
-                                width L_cc + 3 > 13 runs the wide (spilling)
-                                form of the coarse smoother */
+                                width L_cc + 3 > 13 runs the wide form of
+                                the coarse smoother (run-time width) */
     double eig_threshold_coarse; /* B_cc >= 0; 0 = fixed count eigs_coarse.
                                 Eigenvalues are those of eq. spectral cc with
                                 S-normalised bases (dimensionless) */
